@@ -138,9 +138,10 @@ extern "C" size_t kan_workspace_bytes(const kan_layer_desc *desc, int64_t B, int
 }
 
 // Forward pass with the scratch space given explicitly; shared by kan_forward and kan_forward_static.
+// keep_table: the caller may hand the workspace to kan_backward_saved, so the folded table must be in it.
 static int forward_impl(const kan_layer_desc *desc, int64_t B, const float *x, const float *coef,
                         const float *w_s, const float *w_b, float *y, void *ws, size_t ws_bytes,
-                        void *stream)
+                        void *stream, bool keep_table)
 {
     int rc = check_desc(desc);
     if (rc != KAN_OK) return rc;
@@ -155,7 +156,10 @@ static int forward_impl(const kan_layer_desc *desc, int64_t B, const float *x, c
     SplineGeom g = geom_of(desc);
     float *cf = (float *)ws;
     if (high_degree(desc))
-        return highk_forward(highk_of(desc), x, coef, w_s, w_b, cf, y, B, st) == hipSuccess ? KAN_OK : KAN_ERR_HIP;
+        return highk_forward(highk_of(desc), x, coef, w_s, w_b, cf, y, B, keep_table, st) == hipSuccess ? KAN_OK : KAN_ERR_HIP;
+    if (forward_direct_plan(g, B))
+        return launch_forward_direct(g, x, coef, w_s, w_b, keep_table ? cf : nullptr, y, B, st) == hipSuccess ? KAN_OK
+                                                                                                             : KAN_ERR_HIP;
     if (launch_fold_scale(coef, w_s, g.base_act ? w_b : nullptr, cf, g.n_in, g.rows, g.n_out, st) != hipSuccess) return KAN_ERR_HIP;
     hipError_t e = narrow_applicable(g)    ? launch_forward_narrow(g, x, cf, w_b, y, B, st)
                    : (g.n_out <= 64 && forward_lds_rows_plan(g, B)) ? launch_forward_lds_rows(g, x, cf, y, B, st)
@@ -170,7 +174,7 @@ extern "C" int kan_forward(const kan_layer_desc *desc, int64_t B, const float *x
                            const float *w_s, const float *w_b, float *y, void *ws, size_t ws_bytes,
                            void *stream)
 {
-    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, ws_bytes, stream);
+    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, ws_bytes, stream, true);
 }
 
 // ---- forward pass for callers that cannot allocate -------------------------------------------
@@ -212,7 +216,7 @@ extern "C" int kan_forward_static(const kan_layer_desc *desc, int64_t B, const f
     if (kan_workspace_bytes(desc, B, KAN_PASS_FORWARD) > (size_t)KAN_STATIC_SCRATCH_BYTES) return KAN_ERR_WORKSPACE;
     void *ws = static_scratch();
     if (!ws) return KAN_ERR_HIP;
-    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, KAN_STATIC_SCRATCH_BYTES, stream);
+    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, KAN_STATIC_SCRATCH_BYTES, stream, false);
 }
 
 // Backward pass; `folded` (may be null) is the scale-folded table a forward pass left in its workspace.

@@ -1,0 +1,199 @@
+// Forward kernel for small batches: one launch from the parameters as they are.
+//
+// The large-batch kernels give a workgroup 64 .. 512 samples and let it walk over all the inputs, so a
+// request of a few dozen samples occupies one or two of the 256 CUs and its time is that serial walk
+// (64 -> 64, G = 10, B = 16: 48 us behind a 6 us fold of the scale into the table).  What bounds such a
+// call is latency alone: the launches, and the chain x -> cell -> coefficient rows -> sum.  Here
+//   - a workgroup owns NS = 1 or 4 samples and one output tile, and its waves split the INPUTS between
+//     them: lane groups of LPS lanes (LPS * T outputs) take every NGRP-th input, so all the row loads of a
+//     sample are in flight at once; the groups' partial sums meet in LDS and are added in group order;
+//   - the scale is applied as the rows are read (one multiplication, rounded as the fold rounds it), so
+//     the sums need no table; the table that the backward pass wants is written by extra workgroups of
+//     the same launch (none of them when the caller keeps no table).
+// Same shape: 54 -> 10 us per call, most of what is left being the launch.
+#include "kan_device.hpp"
+#include "kan_launch.hpp"
+
+namespace KAN_NS {
+
+namespace {
+
+// per pair: kMaxK weights, base value, first row of the window (8 floats: two quads)
+constexpr int kDirectPairFloats = 8;
+constexpr int kFoldPerThread = 8;        // table elements a thread of a fold workgroup writes
+
+template <int T>
+__device__ __forceinline__ void direct_load(const float *p, float (&v)[T])
+{
+    if constexpr (T == 2) {
+        const float2 t = *reinterpret_cast<const float2 *>(p);
+        v[0] = t.x; v[1] = t.y;
+    } else {
+        static_assert(T == 1, "one or two outputs per lane");
+        v[0] = *p;
+    }
+}
+
+}  // namespace
+
+// grid: n_tiles * ceil(B / NS) workgroups of NW waves, then (cf != nullptr) fold workgroups.
+// Any rows >= 1, n_in, n_out (a multiple of T); tables are coef[n_in][rows][n_out].  w_s == nullptr: coef is scaled
+// already (a generated table); cf must then be null.
+template <int LPS, int T, int NS, int NW>
+__global__ __launch_bounds__(64 * NW) void forward_direct_kernel(SplineGeom g, const float *__restrict__ x,
+                                                                 const float *__restrict__ coef,
+                                                                 const float *__restrict__ w_s,
+                                                                 const float *__restrict__ w_b,
+                                                                 float *__restrict__ cf, float *__restrict__ y,
+                                                                 int64_t B, int n_tiles, int64_t n_main)
+{
+    constexpr int NT = 64 * NW, NGRP = NT / LPS, TJ = LPS * T, IPR = NT / NS;
+    static_assert(kMaxK <= 6, "a pair record is two quads");
+    __shared__ float4 pairs[NT * (kDirectPairFloats / 4)];
+    __shared__ float sums[NGRP * NS * TJ];
+    const int tid = threadIdx.x;
+
+    if ((int64_t)blockIdx.x >= n_main) {
+        // fold: cf[i][m][j] = w_s[i][j] * coef[i][m][j], last row w_b (as fold_scale_kernel)
+        const int64_t per_in = (int64_t)(g.rows + 1) * g.n_out, total = (int64_t)g.n_in * per_in;
+        const int64_t p0 = ((int64_t)blockIdx.x - n_main) * (NT * kFoldPerThread);
+        for (int u = 0; u < kFoldPerThread; ++u) {
+            const int64_t p = p0 + u * NT + tid;
+            if (p >= total) return;
+            const int64_t i = p / per_in, rem = p - i * per_in;
+            const int64_t m = rem / g.n_out, j = rem - m * g.n_out;
+            float v;
+            if (m < g.rows) v = coef[(i * g.rows + m) * g.n_out + j] * w_s[i * g.n_out + j];
+            else v = g.base_act ? w_b[i * g.n_out + j] : 0.0f;
+            cf[p] = v;
+        }
+        return;
+    }
+
+    const int tile = (int)(blockIdx.x % n_tiles);
+    const int64_t b0 = (int64_t)(blockIdx.x / n_tiles) * NS;
+    const int grp = tid / LPS, lj = tid % LPS;
+    const int j = tile * TJ + lj * T;
+    const int jc = j < g.n_out ? j : 0;              // lanes past the last output compute output 0 and drop it
+
+    float acc[NS][T];
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int r = 0; r < T; ++r) acc[s][r] = 0.0f;
+
+    for (int i0 = 0; i0 < g.n_in; i0 += IPR) {
+        const int n_ii = g.n_in - i0 < IPR ? g.n_in - i0 : IPR;
+        {
+            const int ii = tid / NS, s = tid % NS;
+            if (ii < n_ii) {
+                const int64_t b = b0 + s < B ? b0 + s : B - 1;
+                const Pair p = pair_eval<false>(x[b * g.n_in + i0 + ii], g, i0 + ii);
+                float rest[4];
+                if constexpr (kMaxK == 4) {
+                    rest[0] = p.base; rest[1] = __int_as_float(p.cell); rest[2] = 0.0f; rest[3] = 0.0f;
+                } else {
+                    rest[0] = p.base; rest[1] = __int_as_float(p.cell); rest[2] = p.w[kMaxK - 2]; rest[3] = p.w[kMaxK - 1];
+                }
+                pairs[tid * 2] = make_float4(p.w[0], p.w[1], p.w[2], p.w[3]);
+                pairs[tid * 2 + 1] = make_float4(rest[0], rest[1], rest[2], rest[3]);
+            }
+        }
+        __syncthreads();
+        for (int ii = grp; ii < n_ii; ii += NGRP) {
+            const int i = i0 + ii;
+            const float *slab = coef + (int64_t)i * g.rows * g.n_out + jc;
+            float sc[T], wb[T];
+#pragma unroll
+            for (int r = 0; r < T; ++r) sc[r] = 1.0f;
+            if (w_s) direct_load<T>(w_s + (int64_t)i * g.n_out + jc, sc);
+#pragma unroll
+            for (int r = 0; r < T; ++r) wb[r] = 0.0f;
+            if (g.base_act) direct_load<T>(w_b + (int64_t)i * g.n_out + jc, wb);
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const float4 a = pairs[(ii * NS + s) * 2], c = pairs[(ii * NS + s) * 2 + 1];
+                float w[kMaxK];
+                w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w;
+                if constexpr (kMaxK == 6) { w[kMaxK - 2] = c.z; w[kMaxK - 1] = c.w; }
+                const int cell = __float_as_int(c.y);
+                // rows outside the table have zero weight and are clamped into it: no branch, every load in flight
+                float v[kMaxK][T];
+#pragma unroll
+                for (int q = 0; q < kMaxK; ++q)
+                    direct_load<T>(slab + (int64_t)clampi(cell + q, 0, g.rows - 1) * g.n_out, v[q]);
+#pragma unroll
+                for (int q = 0; q < kMaxK; ++q)
+#pragma unroll
+                    for (int r = 0; r < T; ++r) acc[s][r] = fmaf(w[q], v[q][r] * sc[r], acc[s][r]);
+#pragma unroll
+                for (int r = 0; r < T; ++r) acc[s][r] = fmaf(c.x, wb[r], acc[s][r]);
+            }
+        }
+        __syncthreads();
+    }
+
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int r = 0; r < T; ++r) sums[(grp * NS + s) * TJ + lj * T + r] = acc[s][r];
+    __syncthreads();
+    for (int e = tid; e < NS * TJ; e += NT) {
+        const int s = e / TJ, jj = tile * TJ + e % TJ;
+        float v = 0.0f;
+#pragma unroll 8
+        for (int q = 0; q < NGRP; ++q) v += sums[q * NS * TJ + e];
+        if (b0 + s < B && jj < g.n_out) y[(b0 + s) * g.n_out + jj] = v;
+    }
+}
+
+template <int LPS, int T, int NS, int NW>
+static hipError_t direct_launch(const SplineGeom &g, const float *x, const float *coef, const float *w_s,
+                                const float *w_b, float *cf, float *y, int64_t B, hipStream_t st)
+{
+    const int n_tiles = (g.n_out + LPS * T - 1) / (LPS * T);
+    const int64_t n_main = (B + NS - 1) / NS * n_tiles;
+    const int64_t total = (int64_t)g.n_in * (g.rows + 1) * g.n_out, per = 64 * NW * kFoldPerThread;
+    const int64_t n_fold = cf ? (total + per - 1) / per : 0;
+    if (n_main + n_fold > 0x7fffffffll) return hipErrorInvalidConfiguration;
+    prof::Timed tm("forward_direct", st);
+    forward_direct_kernel<LPS, T, NS, NW><<<(unsigned)(n_main + n_fold), 64 * NW, 0, st>>>(g, x, coef, w_s, w_b, cf, y, B,
+                                                                                        n_tiles, n_main);
+    return hipGetLastError();
+}
+
+template <int LPS, int T>
+static hipError_t direct_by_size(const SplineGeom &g, const float *x, const float *coef, const float *w_s,
+                                 const float *w_b, float *cf, float *y, int64_t B, hipStream_t st)
+{
+    const int64_t tiles = (g.n_out + LPS * T - 1) / (LPS * T);
+    // four samples per workgroup (a row of scales and base weights serves four) once that leaves two workgroups per CU
+    if (B * tiles >= 2048)
+        return g.n_in >= 32 ? direct_launch<LPS, T, 4, 16>(g, x, coef, w_s, w_b, cf, y, B, st)
+                            : direct_launch<LPS, T, 4, 4>(g, x, coef, w_s, w_b, cf, y, B, st);
+    return g.n_in >= 32 ? direct_launch<LPS, T, 1, 16>(g, x, coef, w_s, w_b, cf, y, B, st)
+                        : direct_launch<LPS, T, 1, 4>(g, x, coef, w_s, w_b, cf, y, B, st);
+}
+
+// The direct kernel gathers every window row from L2 once per sample: its time is B * n_in * n_out edges at about
+// 1.0e12 edges/s.  The large-batch kernels walk the inputs one after the other and cost 0.85 us (64 outputs) to
+// 2.6 us (256 outputs) an input however small the batch.  So the line is one on B * n_out.  Measured, direct against
+// large-batch kernels: 64 -> 64, G = 10: B = 2048 27 / 56 us, 4096 47 / 57, 8192 86 / 58; 256 -> 256, G = 10: B = 1024
+// 75 / 661, 4096 281 / 666, 8192 555 / 662; 256 -> 256, G = 200: 2048 184 / 237, 4096 325 / 261; 512 -> 512, G = 200:
+// 1024 467 / 623, 2048 752 / 655; 128 -> 37: 4096 55 / 87.  Tiles of fewer than 16 outputs cost as much as 16.
+int forward_direct_plan(const SplineGeom &g, int64_t B)
+{
+    const int64_t w = g.n_out < 16 ? 16 : g.n_out;
+    return B * w <= (g.n_out >= 256 ? 1 << 19 : 1 << 18) ? 1 : 0;
+}
+
+hipError_t launch_forward_direct(const SplineGeom &g, const float *x, const float *coef, const float *w_s,
+                                 const float *w_b, float *cf, float *y, int64_t B, hipStream_t st)
+{
+    if (g.n_out <= 16) return direct_by_size<16, 1>(g, x, coef, w_s, w_b, cf, y, B, st);
+    if (g.n_out <= 32) return direct_by_size<32, 1>(g, x, coef, w_s, w_b, cf, y, B, st);
+    if (g.n_out % 2 == 0 && B * ((g.n_out + 127) / 128) >= 2048) return direct_by_size<64, 2>(g, x, coef, w_s, w_b, cf, y, B, st);
+    return direct_by_size<64, 1>(g, x, coef, w_s, w_b, cf, y, B, st);
+}
+
+}  // namespace KAN_NS

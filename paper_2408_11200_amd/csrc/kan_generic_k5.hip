@@ -5,6 +5,7 @@
 #define KAN_NS kan_k5
 #include "kan_generic.hip"
 #include "kan_rows.hip"
+#include "kan_direct.hip"
 #include "kan_highk.hpp"
 
 namespace kan {
@@ -22,7 +23,10 @@ kan_k5::SplineGeom geom_of(const HighKLayer &l)
 hipError_t highk_table_forward(const HighKLayer &l, const float *x, const float *table, const float *w_b, float *y,
                                int64_t B, hipStream_t st)
 {
-    return kan_k5::launch_forward_generic(geom_of(l), x, table, w_b, y, B, st);
+    const kan_k5::SplineGeom g = geom_of(l);
+    if (kan_k5::forward_direct_plan(g, B))
+        return kan_k5::launch_forward_direct(g, x, table, nullptr, w_b, nullptr, y, B, st);
+    return kan_k5::launch_forward_generic(g, x, table, w_b, y, B, st);
 }
 
 hipError_t highk_table_dx(const HighKLayer &l, const float *x, const float *table, const float *w_b, const float *gy,
@@ -40,9 +44,11 @@ hipError_t highk_table_dparam(const HighKLayer &l, const float *x, const float *
 int highk_row_blocks(int rows) { return kan_k5::dparam_generic_row_blocks(rows); }
 
 hipError_t highk_forward(const HighKLayer &l, const float *x, const float *coef, const float *w_s, const float *w_b,
-                         float *cf, float *y, int64_t B, hipStream_t st)
+                         float *cf, float *y, int64_t B, bool keep_table, hipStream_t st)
 {
     const kan_k5::SplineGeom g = geom_of(l);
+    if (kan_k5::forward_direct_plan(g, B))
+        return kan_k5::launch_forward_direct(g, x, coef, w_s, w_b, keep_table ? cf : nullptr, y, B, st);
     hipError_t e = kan_k5::launch_fold_scale(coef, w_s, g.base_act ? w_b : nullptr, cf, g.n_in, g.rows, g.n_out, st);
     if (e != hipSuccess) return e;
     if (kan_k5::forward_rows_plan(g)) return kan_k5::launch_forward_rows(g, x, cf, y, B, st);

@@ -17,9 +17,9 @@ struct HighKLayer {
 };
 
 int highk_row_blocks(int rows);     // base-term partial slices per chunk
-// y = layer(x); cf: scratch for the scale-folded table ((rows + 1) rows per input)
+// y = layer(x); cf: scratch for the scale-folded table ((rows + 1) rows per input); keep_table: it must be filled
 hipError_t highk_forward(const HighKLayer &l, const float *x, const float *coef, const float *w_s, const float *w_b,
-                         float *cf, float *y, int64_t B, hipStream_t st);
+                         float *cf, float *y, int64_t B, bool keep_table, hipStream_t st);
 // any of gx / (gcoef, gw_s, gw_b) may be null; part_c: n_chunks tables of rows rows, part_b: n_chunks *
 // highk_row_blocks(rows) edge slices
 hipError_t highk_backward(const HighKLayer &l, const float *x, const float *coef, const float *w_s, const float *w_b,

@@ -48,6 +48,13 @@ hipError_t launch_interval_index(const float *x, int32_t *idx, int64_t n, float 
 hipError_t launch_fold_scale(const float *coef, const float *w_s, const float *w_b, float *cf, int n_in, int rows,
                              int n_out, hipStream_t st);
 
+// small batches: one launch straight from the parameters.  The plan returns 0 when the large-batch kernels are the
+// better choice; cf (may be null) receives the scale-folded table in the same launch; w_s may be null when coef is a
+// scaled table (cf null too)
+int forward_direct_plan(const SplineGeom &g, int64_t B);
+hipError_t launch_forward_direct(const SplineGeom &g, const float *x, const float *coef, const float *w_s,
+                                 const float *w_b, float *cf, float *y, int64_t B, hipStream_t st);
+
 // generic (any shape) kernels
 hipError_t launch_forward_generic(const SplineGeom &g, const float *x, const float *cf, const float *w_b,
                                   float *y, int64_t B, hipStream_t st);

@@ -264,6 +264,7 @@ int forward_impl(const ukan_layer_desc *desc, int64_t B, const float *x, const u
     if (rc != KAN_OK) return rc;
     if (span) *span = pr.n_g;
     hipError_t e = high_degree(desc)                  ? highk_table_forward(highk_of(pr.g), x, pr.cf, p->w_b, y, B, st)
+                   : forward_direct_plan(pr.g, B)   ? launch_forward_direct(pr.g, x, pr.cf, nullptr, p->w_b, nullptr, y, B, st)
                    : narrow_applicable(pr.g)        ? launch_forward_narrow(pr.g, x, pr.cf, p->w_b, y, B, st)
                    : forward_lds_rows_plan(pr.g, B) ? launch_forward_lds_rows(pr.g, x, pr.cf, y, B, st)
                                                     : launch_forward_generic(pr.g, x, pr.cf, p->w_b, y, B, st);
