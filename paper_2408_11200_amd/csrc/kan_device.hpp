@@ -158,6 +158,26 @@ __device__ __forceinline__ void window_of(const Pair &p, int rows, int &row0, fl
     base = GRAD ? p.dbase : p.base;
 }
 
+// Vector accesses of rows that need not start on a 16-byte boundary (n_out not a multiple of 4): global memory
+// takes 8- and 16-byte accesses at any 4-byte address, so the instructions are those of the aligned types.
+struct __attribute__((packed, aligned(4))) Float4U { float x, y, z, w; };
+struct __attribute__((packed, aligned(4))) Float2U { float x, y; };
+__device__ __forceinline__ float4 load4u(const float *p)
+{
+    const Float4U t = *reinterpret_cast<const Float4U *>(p);
+    return make_float4(t.x, t.y, t.z, t.w);
+}
+__device__ __forceinline__ float2 load2u(const float *p)
+{
+    const Float2U t = *reinterpret_cast<const Float2U *>(p);
+    return make_float2(t.x, t.y);
+}
+__device__ __forceinline__ void store4u(float *p, float4 v)
+{
+    *reinterpret_cast<Float4U *>(p) = Float4U{v.x, v.y, v.z, v.w};
+}
+__device__ __forceinline__ void store2u(float *p, float2 v) { *reinterpret_cast<Float2U *>(p) = Float2U{v.x, v.y}; }
+
 // value of lane `src` (wave-uniform index) as a scalar
 __device__ __forceinline__ float lane_f(float v, int src)
 {

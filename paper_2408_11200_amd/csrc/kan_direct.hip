@@ -1,4 +1,4 @@
-// Forward kernel for small batches: one launch from the parameters as they are.
+// Forward kernel for small batches, and for narrow and ragged layers: one launch from the parameters as they are.
 //
 // The large-batch kernels give a workgroup 64 .. 512 samples and let it walk over all the inputs, so a
 // request of a few dozen samples occupies one or two of the 256 CUs and its time is that serial walk
@@ -10,7 +10,8 @@
 //   - the scale is applied as the rows are read (one multiplication, rounded as the fold rounds it), so
 //     the sums need no table; the table that the backward pass wants is written by extra workgroups of
 //     the same launch (none of them when the caller keeps no table).
-// Same shape: 54 -> 10 us per call, most of what is left being the launch.
+// Same shape: 54 -> 9.2 us per call, most of what is left being the launch.
+// Large batches run the same kernel with 16-byte row reads (T = 4) and four samples a workgroup, at the L2 gather rate.
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
 
@@ -25,11 +26,11 @@ constexpr int kFoldPerThread = 8;        // table elements a thread of a fold wo
 template <int T>
 __device__ __forceinline__ void direct_load(const float *p, float (&v)[T])
 {
-    if constexpr (T == 2) {
-        const float2 t = *reinterpret_cast<const float2 *>(p);
-        v[0] = t.x; v[1] = t.y;
+    if constexpr (T == 4) {
+        const float4 t = load4u(p);
+        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     } else {
-        static_assert(T == 1, "one or two outputs per lane");
+        static_assert(T == 1, "one or four outputs per lane");
         v[0] = *p;
     }
 }
@@ -37,7 +38,7 @@ __device__ __forceinline__ void direct_load(const float *p, float (&v)[T])
 }  // namespace
 
 // grid: n_tiles * ceil(B / NS) workgroups of NW waves, then (cf != nullptr) fold workgroups.
-// Any rows >= 1, n_in, n_out (a multiple of T); tables are coef[n_in][rows][n_out].  w_s == nullptr: coef is scaled
+// Any rows >= 1, n_in, n_out >= T (the lane of the last outputs is moved back inside the row); tables are coef[n_in][rows][n_out].  w_s == nullptr: coef is scaled
 // already (a generated table); cf must then be null.
 template <int LPS, int T, int NS, int NW>
 __global__ __launch_bounds__(64 * NW) void forward_direct_kernel(SplineGeom g, const float *__restrict__ x,
@@ -74,15 +75,24 @@ __global__ __launch_bounds__(64 * NW) void forward_direct_kernel(SplineGeom g, c
     const int64_t b0 = (int64_t)(blockIdx.x / n_tiles) * NS;
     const int grp = tid / LPS, lj = tid % LPS;
     const int j = tile * TJ + lj * T;
-    const int jc = j < g.n_out ? j : 0;              // lanes past the last output compute output 0 and drop it
+    // lanes past the last output compute outputs 0 .. and drop them; a lane that straddles it starts at n_out - T
+    const int jc = j >= g.n_out ? 0 : (j + T > g.n_out ? g.n_out - T : j);
 
-    float acc[NS][T];
+    // two-level sum over the inputs: a lane group's running sums are folded after about 32 of its inputs
+    constexpr int kFoldRounds = 32 * NS > LPS ? 32 * NS / LPS : 1;
+    float acc[NS][T], tot[NS][T];
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int r = 0; r < T; ++r) acc[s][r] = 0.0f;
+        for (int r = 0; r < T; ++r) { acc[s][r] = 0.0f; tot[s][r] = 0.0f; }
 
     for (int i0 = 0; i0 < g.n_in; i0 += IPR) {
+        if (i0 > 0 && (i0 / IPR) % kFoldRounds == 0) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int r = 0; r < T; ++r) { tot[s][r] += acc[s][r]; acc[s][r] = 0.0f; }
+        }
         const int n_ii = g.n_in - i0 < IPR ? g.n_in - i0 : IPR;
         {
             const int ii = tid / NS, s = tid % NS;
@@ -136,7 +146,8 @@ __global__ __launch_bounds__(64 * NW) void forward_direct_kernel(SplineGeom g, c
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int r = 0; r < T; ++r) sums[(grp * NS + s) * TJ + lj * T + r] = acc[s][r];
+        for (int r = 0; r < T; ++r)
+            if (j < g.n_out) sums[(grp * NS + s) * TJ + (jc - tile * TJ) + r] = tot[s][r] + acc[s][r];
     __syncthreads();
     for (int e = tid; e < NS * TJ; e += NT) {
         const int s = e / TJ, jj = tile * TJ + e % TJ;
@@ -162,38 +173,61 @@ static hipError_t direct_launch(const SplineGeom &g, const float *x, const float
     return hipGetLastError();
 }
 
-template <int LPS, int T>
-static hipError_t direct_by_size(const SplineGeom &g, const float *x, const float *coef, const float *w_s,
+// one sample per workgroup, one output per lane: the most workgroups and the shortest chain
+template <int LPS>
+static hipError_t direct_latency(const SplineGeom &g, const float *x, const float *coef, const float *w_s,
                                  const float *w_b, float *cf, float *y, int64_t B, hipStream_t st)
 {
-    const int64_t tiles = (g.n_out + LPS * T - 1) / (LPS * T);
-    // four samples per workgroup (a row of scales and base weights serves four) once that leaves two workgroups per CU
-    if (B * tiles >= 2048)
-        return g.n_in >= 32 ? direct_launch<LPS, T, 4, 16>(g, x, coef, w_s, w_b, cf, y, B, st)
-                            : direct_launch<LPS, T, 4, 4>(g, x, coef, w_s, w_b, cf, y, B, st);
-    return g.n_in >= 32 ? direct_launch<LPS, T, 1, 16>(g, x, coef, w_s, w_b, cf, y, B, st)
-                        : direct_launch<LPS, T, 1, 4>(g, x, coef, w_s, w_b, cf, y, B, st);
+    return g.n_in >= 32 ? direct_launch<LPS, 1, 1, 16>(g, x, coef, w_s, w_b, cf, y, B, st)
+                        : direct_launch<LPS, 1, 1, 4>(g, x, coef, w_s, w_b, cf, y, B, st);
 }
 
-// The direct kernel gathers every window row from L2 once per sample: its time is B * n_in * n_out edges at about
-// 1.0e12 edges/s.  The large-batch kernels walk the inputs one after the other and cost 0.85 us (64 outputs) to
-// 2.6 us (256 outputs) an input however small the batch.  So the line is one on B * n_out.  Measured, direct against
-// large-batch kernels: 64 -> 64, G = 10: B = 2048 27 / 56 us, 4096 47 / 57, 8192 86 / 58; 256 -> 256, G = 10: B = 1024
-// 75 / 661, 4096 281 / 666, 8192 555 / 662; 256 -> 256, G = 200: 2048 184 / 237, 4096 325 / 261; 512 -> 512, G = 200:
-// 1024 467 / 623, 2048 752 / 655; 128 -> 37: 4096 55 / 87.  Tiles of fewer than 16 outputs cost as much as 16.
+// Where the line lies.  The direct kernel gathers every window row from L2 once per sample: its time is the edges of the
+// padded width at about 1.8e12 edges/s while the table stays in L2.  The LDS-staged kernels walk the inputs one after the
+// other and, until their workgroups fill the chip, cost a fixed time an input however small the batch (2.6 us for 256-wide
+// tiles of 128 samples, 1.6 us for 512-wide ones, 0.85 us up to 64 outputs and for long tables), so against them the line
+// is one on B * n_out.  Against the kernels that gather from L2 themselves it wins outright on narrow and ragged widths.
+// Measured, other kernel / direct, us:
+//   64 -> 64, G = 10      B = 4096 57 / 14, 16384 59 / 44, 32768 62 / 88       (long-table kernel)
+//   256 -> 256, G = 10    B = 8192 661 / 302, 16384 663 / 594, 32768 666 / 1186       (LDS-staged, 256-wide)
+//   75 -> 130, G = 10     B = 6001 195 / 64, 16384 195 / 159
+//   512 -> 512, G = 10    B = 4096 832 / 600, 8192 836 / 1190                  (LDS-staged, 512-wide)
+//   256 -> 256, G = 200   B = 2048 236 / 152, 4096 260 / 283                   (generic, 256-wide tiles)
+//   32 -> 32, G = 1024    B = 8192 70 / 14, 131072 164 / 114                   (row-stream kernel)
+//   64 -> 64, G = 1024    B = 8192 133 / 63, 65536 273 / 436                   (row-stream kernel; the table is 17 MB)
+//   128 -> 37, G = 200    B = 32768 406 / 167; 100 -> 200, G = 300, B = 16384 413 / 537        (generic)
 int forward_direct_plan(const SplineGeom &g, int64_t B)
 {
-    const int64_t w = g.n_out < 16 ? 16 : g.n_out;
-    return B * w <= (g.n_out >= 256 ? 1 << 19 : 1 << 18) ? 1 : 0;
+    const int64_t w = g.n_out <= 16 ? 16 : (g.n_out <= 32 ? 32 : (g.n_out + 63) / 64 * 64);
+    const int64_t load = B * w * kMaxK / 4;
+    const bool in_l2 = (int64_t)g.n_in * g.slab_rows * g.n_out * 4 <= 8ll << 20;
+    if (g.n_out < 4) return B <= (g.n_in >= 32 ? 8192 : 2048) ? 1 : 0;        // one output per lane at any batch
+#if KAN_MAXK == 4
+    if (narrow_applicable(g)) return load <= (g.n_in >= 32 ? 1 << 20 : 1 << 17) ? 1 : 0;
+    if ((g.n_out <= 64 || !forward_lds_plan(g)) && forward_lds_rows_plan(g, B)) return load <= 1 << 20 ? 1 : 0;
+#endif
+    if (g.n_out <= 32) return 1;
+    if (g.n_out <= 64) return in_l2 || load <= 1 << 20 ? 1 : 0;
+    switch (forward_lds_plan(g)) {
+    case 4: return load <= (g.n_in >= 32 ? 7 << 19 : 1 << 21) ? 1 : 0;
+    case 8: return load <= 5 << 19 ? 1 : 0;
+    default: return (in_l2 && (g.n_out < 256 || g.n_out % 4 != 0)) || load <= 3 << 18 ? 1 : 0;
+    }
 }
 
 hipError_t launch_forward_direct(const SplineGeom &g, const float *x, const float *coef, const float *w_s,
                                  const float *w_b, float *cf, float *y, int64_t B, hipStream_t st)
 {
-    if (g.n_out <= 16) return direct_by_size<16, 1>(g, x, coef, w_s, w_b, cf, y, B, st);
-    if (g.n_out <= 32) return direct_by_size<32, 1>(g, x, coef, w_s, w_b, cf, y, B, st);
-    if (g.n_out % 2 == 0 && B * ((g.n_out + 127) / 128) >= 2048) return direct_by_size<64, 2>(g, x, coef, w_s, w_b, cf, y, B, st);
-    return direct_by_size<64, 1>(g, x, coef, w_s, w_b, cf, y, B, st);
+    // once workgroups of one sample fill the chip twice over: four samples per workgroup (they share the row of scales
+    // and base weights) and 16-byte row reads
+    if (B * ((g.n_out + 63) / 64) >= 2048 && g.n_out >= 4) {
+        if (g.n_out <= 16) return direct_launch<4, 4, 4, 4>(g, x, coef, w_s, w_b, cf, y, B, st);
+        if (g.n_out <= 32) return direct_launch<8, 4, 4, 4>(g, x, coef, w_s, w_b, cf, y, B, st);
+        return direct_launch<16, 4, 4, 4>(g, x, coef, w_s, w_b, cf, y, B, st);
+    }
+    if (g.n_out <= 16) return direct_latency<16>(g, x, coef, w_s, w_b, cf, y, B, st);
+    if (g.n_out <= 32) return direct_latency<32>(g, x, coef, w_s, w_b, cf, y, B, st);
+    return direct_latency<64>(g, x, coef, w_s, w_b, cf, y, B, st);
 }
 
 }  // namespace KAN_NS

@@ -48,7 +48,7 @@ hipError_t launch_interval_index(const float *x, int32_t *idx, int64_t n, float 
 hipError_t launch_fold_scale(const float *coef, const float *w_s, const float *w_b, float *cf, int n_in, int rows,
                              int n_out, hipStream_t st);
 
-// small batches: one launch straight from the parameters.  The plan returns 0 when the large-batch kernels are the
+// small batches, narrow and ragged layers: one launch straight from the parameters.  The plan returns 0 when the large-batch kernels are the
 // better choice; cf (may be null) receives the scale-folded table in the same launch; w_s may be null when coef is a
 // scaled table (cf null too)
 int forward_direct_plan(const SplineGeom &g, int64_t B);
@@ -77,7 +77,7 @@ hipError_t launch_forward_narrow(const SplineGeom &g, const float *x, const floa
 hipError_t launch_dx_narrow(const SplineGeom &g, const float *x, const float *cf, const float *w_b, const float *gy,
                             float *gx, int64_t B, hipStream_t st);
 
-// layers of 17 .. 64 outputs: four samples per wave, one per DPP row (0: not applicable)
+// layers of 33 .. 64 outputs: four samples per wave, one per DPP row (0: not applicable)
 int forward_rows_plan(const SplineGeom &g);
 hipError_t launch_forward_rows(const SplineGeom &g, const float *x, const float *cf, float *y, int64_t B,
                                hipStream_t st);

@@ -53,6 +53,8 @@ __device__ __forceinline__ void lds_row(const float *row, int lane, float (&v)[R
 // element offsets do not depend on the input, so they are computed once (SlabMap); per input the
 // copy is NQ loads off a scalar base.  Quads outside the slab or the layer load element 0 and are
 // zeroed on the way to LDS (MASK); the LDS slab is padded to NQ*NT quads so stores need no guard.
+// When n_out is no multiple of 4 the quad that holds a row's last outputs is the four outputs n_out - 4 ..
+// n_out - 1: the lane that reads it computes and stores those, some of them a second time with the same bits.
 template <int NQ>
 struct SlabMap {
     int off[NQ];          // float offset inside one input's block
@@ -70,7 +72,7 @@ __device__ __forceinline__ SlabMap<NQ> slab_map(const SplineGeom &g, int j0, int
         const int e = tid + c * NT;
         const int row = e / quads_per_row, j = j0 + (e % quads_per_row) * 4;
         const bool ok = row < g.slab_rows && j < g.n_out;
-        m.off[c] = ok ? row * g.n_out + j : 0;
+        m.off[c] = ok ? row * g.n_out + (j + 4 > g.n_out ? g.n_out - 4 : j) : 0;
         m.ok |= ok ? (1u << c) : 0u;
     }
     return m;
@@ -80,7 +82,7 @@ template <int NQ>
 __device__ __forceinline__ void slab_fetch(float4 (&q)[NQ], const SlabMap<NQ> &m, const float *__restrict__ block)
 {
 #pragma unroll
-    for (int c = 0; c < NQ; ++c) q[c] = *reinterpret_cast<const float4 *>(block + m.off[c]);
+    for (int c = 0; c < NQ; ++c) q[c] = load4u(block + m.off[c]);
 }
 
 template <int NT, int NQ, bool MASK>
@@ -203,7 +205,7 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_kernel(SplineGeom g, cons
                 const int j = j0 + h * 256 + lane * 4;
                 if (j < g.n_out) {
                     float4 o = make_float4(acc[t][4 * h], acc[t][4 * h + 1], acc[t][4 * h + 2], acc[t][4 * h + 3]);
-                    *reinterpret_cast<float4 *>(y + (b0 + t) * g.n_out + j) = o;
+                    store4u(y + (b0 + t) * g.n_out + (j + 4 > g.n_out ? g.n_out - 4 : j), o);
                 }
             }
         }
@@ -318,7 +320,7 @@ __global__ __launch_bounds__(64 * NW) void forward_pairs_kernel(SplineGeom g, co
                 const int j = j0 + h * 256 + lane * 4;
                 if (j < g.n_out) {
                     float4 o = make_float4(acc[t][4 * h], acc[t][4 * h + 1], acc[t][4 * h + 2], acc[t][4 * h + 3]);
-                    *reinterpret_cast<float4 *>(y + (b0 + t) * g.n_out + j) = o;
+                    store4u(y + (b0 + t) * g.n_out + (j + 4 > g.n_out ? g.n_out - 4 : j), o);
                 }
             }
         }
@@ -346,7 +348,7 @@ size_t lds_bytes(int rows, int R, int NW) { return 2ull * (size_t)quads_needed(r
 // 0 = not applicable, otherwise the outputs-per-lane the launcher will use
 int forward_lds_plan(const SplineGeom &g)
 {
-    if (g.rows < kMaxK || g.n_out % 4 != 0 || g.slab_rows != g.rows + 1) return 0;
+    if (g.rows < kMaxK || g.slab_rows != g.rows + 1) return 0;
     // eight outputs per lane: two slabs and the waves' pair areas (32 KB) must fit, the slab in at most 4 quads per thread
     if (g.n_out > 256 && quads_needed(g.rows, 8, 16) && quads_needed(g.rows, 8, 16) <= 4 &&
         lds_bytes(g.rows, 8, 16) + 16 * 64 * 8 * sizeof(float) <= kLdsBudget)

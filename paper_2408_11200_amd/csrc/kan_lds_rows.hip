@@ -33,7 +33,7 @@ struct TileMap {
 
 }  // namespace
 
-// grid (ceil(B / (NW * SPW * S)), ceil(n_out / TJ)), NW waves.  Needs rows >= kMaxK, n_out % 4 == 0.
+// grid (ceil(B / (NW * SPW * S)), ceil(n_out / TJ)), NW waves.  Needs rows >= kMaxK, n_out >= 4.
 // The table has slab_rows rows per input; with slab_rows == rows + 1 the last one is the w_b row.
 template <int LPS, int S, int NW, int NQ>
 __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g, const float *__restrict__ x,
@@ -77,14 +77,14 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
         const int e = tid + c * NT;
         const int row = e / LPS, jj = j0 + (e % LPS) * 4;
         const bool ok = row < g.slab_rows && jj < g.n_out;
-        map.off[c] = ok ? row * g.n_out + jj : 0;
+        map.off[c] = ok ? row * g.n_out + (jj + 4 > g.n_out ? g.n_out - 4 : jj) : 0;     // a row's last quad: n_out - 4 ..
         map.ok |= ok ? (1u << c) : 0u;
     }
     const int64_t block_floats = (int64_t)g.slab_rows * g.n_out;
     float4 qd[NQ];
     auto fetch = [&](const float *__restrict__ block) {
 #pragma unroll
-        for (int c = 0; c < NQ; ++c) qd[c] = *reinterpret_cast<const float4 *>(block + map.off[c]);
+        for (int c = 0; c < NQ; ++c) qd[c] = load4u(block + map.off[c]);
     };
     auto stage = [&](float *slab) {
 #pragma unroll
@@ -161,8 +161,8 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
         for (int q = 0; q < S; ++q) {
             const int64_t b = b0 + grp * S + q;
             if (b < B)
-                *reinterpret_cast<float4 *>(y + b * g.n_out + j) =
-                    make_float4(tot[q][0] + acc[q][0], tot[q][1] + acc[q][1], tot[q][2] + acc[q][2], tot[q][3] + acc[q][3]);
+                store4u(y + b * g.n_out + (j + 4 > g.n_out ? g.n_out - 4 : j),
+                        make_float4(tot[q][0] + acc[q][0], tot[q][1] + acc[q][1], tot[q][2] + acc[q][2], tot[q][3] + acc[q][3]));
         }
     }
 }
@@ -178,12 +178,12 @@ struct RowsPlan { int lps, nw, nq; };
 RowsPlan plan_of(const SplineGeom &g, int64_t B)
 {
     RowsPlan none = {0, 0, 0};
-    if (g.rows < kMaxK || g.n_out % 4 != 0 || g.n_out < 32) return none;
+    if (g.rows < kMaxK || g.n_out < 32) return none;
     if (g.slab_rows != g.rows + 1 && (g.slab_rows != g.rows || g.base_act != 0)) return none;
     const int lps_opts[] = {16, 8};
     for (int lps : lps_opts) {
         const int tj = lps * 4, spw = 64 / lps;
-        if (g.n_out < tj) continue;
+        if (lps == 16 && g.n_out <= 32) continue;
         const int64_t tiles = (g.n_out + tj - 1) / tj;
         // 16 waves when that still leaves about a workgroup per CU, else 8
         const int nw_opts[] = {16, 8};

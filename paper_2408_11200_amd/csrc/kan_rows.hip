@@ -1,12 +1,12 @@
-// Forward kernel for layers of 17 .. 64 outputs (the paper's own 32 -> 32 benchmark shape, 64 -> 64).
+// Forward kernel for layers of 33 .. 64 outputs whose tables do not fit an XCD's L2.
 //
-// With lanes <-> outputs and one sample at a time such a layer fills a quarter to a half of a wave,
-// and every coefficient load moves 128-256 bytes, so the texture path spends its time on load
+// With lanes <-> outputs and one sample at a time such a layer fills half of a wave or a
+// little more, and every coefficient load moves 132-256 bytes, so the texture path spends its time on load
 // instructions rather than on bytes.  Here a wave works on FOUR samples at once, one per DPP row of
-// 16 lanes; a lane holds T = 2 or 4 outputs of its row's sample.  Lane l of a row evaluates the pair
+// 16 lanes; a lane holds T = 4 outputs of its row's sample.  Lane l of a row evaluates the pair
 // (row's sample, input i0 + l); the window weights and the window row of input i0 + ii are then read
 // from lane ii of the same row with row_newbcast, so the four rows proceed in lockstep on
-// different samples with no scalar state.  One 8- or 16-byte load per lane fetches a table row for all
+// different samples with no scalar state.  One 16-byte load per lane fetches a table row for all
 // four samples.
 #include <type_traits>
 #include "kan_device.hpp"
@@ -36,22 +36,11 @@ __device__ __forceinline__ void static_for(F &&f)
     }
 }
 
-template <int T>
+constexpr int T = 4;                   // outputs per lane
 __device__ __forceinline__ void load_t(const float *p, float (&v)[T])
 {
-    if constexpr (T == 4) {
-        const float4 t = *reinterpret_cast<const float4 *>(p);
-        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-    } else {
-        const float2 t = *reinterpret_cast<const float2 *>(p);
-        v[0] = t.x; v[1] = t.y;
-    }
-}
-template <int T>
-__device__ __forceinline__ void store_t(float *p, const float (&v)[T])
-{
-    if constexpr (T == 4) *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
-    else *reinterpret_cast<float2 *>(p) = make_float2(v[0], v[1]);
+    const float4 t = load4u(p);
+    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
 }
 
 constexpr int kSamplesPerRow = 8;      // samples a DPP row handles one after the other
@@ -59,16 +48,17 @@ constexpr int kSamplesPerRow = 8;      // samples a DPP row handles one after th
 }  // namespace
 
 // grid: ceil(B / (4 waves * 4 rows * kSamplesPerRow)), 256 threads.  Needs rows >= kMaxK, a table with
-// the w_b row appended (slab_rows == rows + 1) and n_out % T == 0, n_out <= 16 * T.
-template <int T>
+// the w_b row appended (slab_rows == rows + 1) and T <= n_out <= 16 * T.
 __global__ __launch_bounds__(256) void forward_rows_kernel(SplineGeom g, const float *__restrict__ x,
                                                            const float *__restrict__ cf, float *__restrict__ y,
                                                            int64_t B)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int row = lane >> 4, l16 = lane & 15;
-    const int j = l16 * T;
-    const bool jok = j < g.n_out;
+    // the lane of a row's last outputs is moved back inside the row when n_out is no multiple of T: what it shares with
+    // its neighbour is computed twice from the same operands
+    const bool jok = l16 * T < g.n_out;
+    const int j = jok && l16 * T + T > g.n_out ? g.n_out - T : l16 * T;
     const int jc = jok ? j : 0;
     const int64_t first = (((int64_t)blockIdx.x * 4 + wave) * 4 + row) * kSamplesPerRow;
     const int64_t slab_floats = (int64_t)g.slab_rows * g.n_out;
@@ -104,8 +94,8 @@ __global__ __launch_bounds__(256) void forward_rows_kernel(SplineGeom g, const f
                 const int o = row_bcast<N>(off) + jc;
                 float c[kMaxK][T], wb[T];
 #pragma unroll
-                for (int s = 0; s < kMaxK; ++s) load_t<T>(slab + s * g.n_out + o, c[s]);
-                load_t<T>(slab + g.rows * g.n_out + jc, wb);
+                for (int s = 0; s < kMaxK; ++s) load_t(slab + s * g.n_out + o, c[s]);
+                load_t(slab + g.rows * g.n_out + jc, wb);
                 float ws[kMaxK];
 #pragma unroll
                 for (int s = 0; s < kMaxK; ++s) ws[s] = row_bcast<N>(w[s]);
@@ -124,17 +114,14 @@ __global__ __launch_bounds__(256) void forward_rows_kernel(SplineGeom g, const f
         }
 #pragma unroll
         for (int r = 0; r < T; ++r) tot[r] += acc[r];
-        if (jok && b < B) store_t<T>(y + b * g.n_out + j, tot);
+        if (jok && b < B) store4u(y + b * g.n_out + j, make_float4(tot[0], tot[1], tot[2], tot[3]));
     }
 }
 
-// 0: not applicable, else outputs per lane
+// 0: not applicable
 int forward_rows_plan(const SplineGeom &g)
 {
-    if (g.rows < kMaxK || g.slab_rows != g.rows + 1 || g.n_out <= 16 || g.n_out > 64) return 0;
-    if (g.n_out <= 32 && g.n_out % 2 == 0) return 2;
-    if (g.n_out % 4 == 0) return 4;
-    return 0;
+    return g.rows >= kMaxK && g.slab_rows == g.rows + 1 && g.n_out > 32 && g.n_out <= 64 ? 1 : 0;
 }
 
 hipError_t launch_forward_rows(const SplineGeom &g, const float *x, const float *cf, float *y, int64_t B,
@@ -142,11 +129,7 @@ hipError_t launch_forward_rows(const SplineGeom &g, const float *x, const float 
 {
     const unsigned blocks = (unsigned)((B + 16 * kSamplesPerRow - 1) / (16 * kSamplesPerRow));
     prof::Timed tm("forward_rows", st);
-    switch (forward_rows_plan(g)) {
-    case 2: forward_rows_kernel<2><<<blocks, 256, 0, st>>>(g, x, cf, y, B); break;
-    case 4: forward_rows_kernel<4><<<blocks, 256, 0, st>>>(g, x, cf, y, B); break;
-    default: return hipErrorInvalidValue;
-    }
+    forward_rows_kernel<<<blocks, 256, 0, st>>>(g, x, cf, y, B);
     return hipGetLastError();
 }
 

@@ -243,20 +243,22 @@ WalkPlan plan_walk(const SplineGeom &g, int64_t B, bool allow_shared, bool high_
     WalkPlan p = {};
     if (g.rows < kMaxK || g.rows > kRtRowMask || B < 1) return p;
     if (high_degree && g.rows < 6) return p;          // a six-row window must fit the table
-    if (g.n_out % 8 == 0 && g.n_out > 256) {
+    // every width has a variant (widths that are no multiple of T run its ragged build)
+    if (g.n_out > 256) {
         p.T = 8;            // one tile covers 512 outputs: the per-record work is shared by twice as many
         p.streams = 1;
-    } else if (g.n_out % 2 == 0 && g.n_out > 16 && g.n_out <= 32) {
+    } else if (g.n_out > 32) {
+        p.T = 4;
+        p.streams = g.n_out > 128 ? 1 : (g.n_out > 64 ? 2 : 4);
+    } else if (g.n_out > 16) {
         p.T = 2;            // 16 lanes x 2 outputs cover the layer: no idle lanes in a stream
         p.streams = 4;
     } else if (g.n_out % 4 == 0) {
         p.T = 4;
-        p.streams = g.n_out > 128 ? 1 : (g.n_out > 64 ? 2 : 4);
-    } else if (g.n_out <= 16) {
-        p.T = 1;
         p.streams = 4;
     } else {
-        return p;
+        p.T = 1;
+        p.streams = 4;
     }
     const int tile = (64 / p.streams) * p.T;
     p.n_jt = (g.n_out + tile - 1) / tile;
@@ -318,6 +320,12 @@ KAN_WALK_VARIANT(walk_launch_s2t4);
 KAN_WALK_VARIANT(walk_launch_s4t4);
 KAN_WALK_VARIANT(walk_launch_s4t2);
 KAN_WALK_VARIANT(walk_launch_s4t1);
+// n_out not a multiple of the outputs per lane
+KAN_WALK_VARIANT(walk_launch_s1t8_ragged);
+KAN_WALK_VARIANT(walk_launch_s1t4_ragged);
+KAN_WALK_VARIANT(walk_launch_s2t4_ragged);
+KAN_WALK_VARIANT(walk_launch_s4t4_ragged);
+KAN_WALK_VARIANT(walk_launch_s4t2_ragged);
 #undef KAN_WALK_VARIANT
 
 namespace {
@@ -430,20 +438,14 @@ hipError_t launch_backward_walk(const SplineGeom &g, const WalkPlan &p, const fl
         const int here = p.n_chunks - chunk0 < per_launch ? p.n_chunks - chunk0 : per_launch;
         {
             prof::Timed tm(dx ? "backward_walk" : "dparam_walk", st);
-            if (p.T == 8 && p.streams == 1)
-                walk_launch_s1t8(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx_out, B, p, bpc, m, prezeroed, carry, chunk0, here);
-            else if (p.T == 4 && p.streams == 1)
-                walk_launch_s1t4(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx_out, B, p, bpc, m, prezeroed, carry, chunk0, here);
-            else if (p.T == 4 && p.streams == 2)
-                walk_launch_s2t4(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx_out, B, p, bpc, m, prezeroed, carry, chunk0, here);
-            else if (p.T == 4 && p.streams == 4)
-                walk_launch_s4t4(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx_out, B, p, bpc, m, prezeroed, carry, chunk0, here);
-            else if (p.T == 2 && p.streams == 4)
-                walk_launch_s4t2(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx_out, B, p, bpc, m, prezeroed, carry, chunk0, here);
-            else if (p.T == 1 && p.streams == 4)
-                walk_launch_s4t1(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx_out, B, p, bpc, m, prezeroed, carry, chunk0, here);
-            else
-                return hipErrorInvalidValue;
+            const bool ragged = g.n_out % p.T != 0;
+            auto launch = p.T == 8 ? (ragged ? walk_launch_s1t8_ragged : walk_launch_s1t8)
+                          : p.T == 2 ? (ragged ? walk_launch_s4t2_ragged : walk_launch_s4t2)
+                          : p.T == 1 ? walk_launch_s4t1
+                          : p.streams == 1 ? (ragged ? walk_launch_s1t4_ragged : walk_launch_s1t4)
+                          : p.streams == 2 ? (ragged ? walk_launch_s2t4_ragged : walk_launch_s2t4)
+                                           : (ragged ? walk_launch_s4t4_ragged : walk_launch_s4t4);
+            launch(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx_out, B, p, bpc, m, prezeroed, carry, chunk0, here);
         }
         if (part_c != nullptr && p.n_seg > 1) {
             const int64_t nn = (int64_t)here * g.n_in * g.n_out;

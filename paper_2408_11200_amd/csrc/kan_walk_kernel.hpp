@@ -82,13 +82,13 @@ template <int T>
 __device__ __forceinline__ void load_vec(const float *p, float (&v)[T])
 {
     if constexpr (T == 8) {
-        const float4 t = *reinterpret_cast<const float4 *>(p), u = *reinterpret_cast<const float4 *>(p + 4);
+        const float4 t = load4u(p), u = load4u(p + 4);
         v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w; v[4] = u.x; v[5] = u.y; v[6] = u.z; v[7] = u.w;
     } else if constexpr (T == 4) {
-        const float4 t = *reinterpret_cast<const float4 *>(p);
+        const float4 t = load4u(p);
         v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     } else if constexpr (T == 2) {
-        const float2 t = *reinterpret_cast<const float2 *>(p);
+        const float2 t = load2u(p);
         v[0] = t.x; v[1] = t.y;
     } else {
         static_assert(T == 1, "one, two, four or eight outputs per lane");
@@ -99,12 +99,12 @@ template <int T>
 __device__ __forceinline__ void store_vec(float *p, const float (&v)[T])
 {
     if constexpr (T == 8) {
-        *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
-        *reinterpret_cast<float4 *>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
+        store4u(p, make_float4(v[0], v[1], v[2], v[3]));
+        store4u(p + 4, make_float4(v[4], v[5], v[6], v[7]));
     } else if constexpr (T == 4) {
-        *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
+        store4u(p, make_float4(v[0], v[1], v[2], v[3]));
     } else if constexpr (T == 2) {
-        *reinterpret_cast<float2 *>(p) = make_float2(v[0], v[1]);
+        store2u(p, make_float2(v[0], v[1]));
     } else {
         p[0] = v[0];
     }
@@ -132,7 +132,11 @@ __device__ __forceinline__ void rank1_update(f32x4 &acc, float a_quads, float b)
     acc = __builtin_amdgcn_mfma_f32_4x4x1f32(a_quads, b, acc, CBSZ, ABID, 0);
 }
 
-template <int STREAMS, int T, bool DX, bool FOLD>
+//
+// RAGGED: n_out is not a multiple of T.  The lane that holds the last outputs is moved back to n_out - T, so its
+// loads and stores stay inside the rows; the outputs it then shares with its neighbour are computed twice from the
+// same operands (both store the same bits), and count once in dL/dx (`own`) and in the shared slabs' additions.
+template <int STREAMS, int T, bool DX, bool FOLD, bool RAGGED>
 __global__ __launch_bounds__(256) void backward_walk_kernel(SplineGeom g, WalkRecords rec,
                                                             const float *__restrict__ gy,
                                                             const float *__restrict__ cf,
@@ -165,9 +169,11 @@ __global__ __launch_bounds__(256) void backward_walk_kernel(SplineGeom g, WalkRe
     const int seg = ws / (g.n_in * n_jt);
     // L entries per sorted list: S, or 2 S with two records per pair (hk); seg_len is a multiple of 16
     const int seg_len = L / n_seg;
-    const int j = (jt * LPS + q) * T;
-    const bool jok = j < g.n_out;
+    const int jl = (jt * LPS + q) * T;
+    const bool jok = jl < g.n_out;
+    const int j = RAGGED && jl + T > g.n_out ? g.n_out - T : jl;
     const int jc = jok ? j : 0;
+    const int shared_with_neighbour = RAGGED ? jl - j : 0;      // first outputs of the lane that are the neighbour's too
     const int64_t b0 = (int64_t)c * S;
     const int n_c = (int)((B - b0) < S ? (B - b0) : S);
     const int64_t list0 = ((int64_t)c * g.n_in + i) * L;
@@ -208,11 +214,20 @@ __global__ __launch_bounds__(256) void backward_walk_kernel(SplineGeom g, WalkRe
 
     // dL/dx: table rows cur .. cur+K-1 and the w_b row, zero in lanes past the last output
     float cw[kMaxK][T], wb[T];
-    const float jmask = jok ? 1.0f : 0.0f;
+    float own[RAGGED ? T : 1];
+#pragma unroll
+    for (int r = 0; r < (RAGGED ? T : 1); ++r) own[r] = jok && r >= shared_with_neighbour ? 1.0f : 0.0f;
+    if constexpr (!RAGGED) own[0] = jok ? 1.0f : 0.0f;
     if constexpr (DX) {
 #pragma unroll
         for (int r = 0; r < T; ++r) wb[r] = 0.0f;
-        if (jok && w_b != nullptr && g.base_act != 0) load_vec<T>(w_b + (int64_t)i * g.n_out + j, wb);
+        if (jok && w_b != nullptr && g.base_act != 0) {
+            load_vec<T>(w_b + (int64_t)i * g.n_out + j, wb);
+            if constexpr (RAGGED) {
+#pragma unroll
+                for (int r = 0; r < T; ++r) wb[r] = r >= shared_with_neighbour ? wb[r] : 0.0f;
+            }
+        }
     }
 
     // The window rows live in a ring: row m of the table is component m mod K of a[r] / hi[r] (and of
@@ -238,7 +253,8 @@ __global__ __launch_bounds__(256) void backward_walk_kernel(SplineGeom g, WalkRe
                 // only writer of the row and launches follow each other on the stream, so the sum is the
                 // same every run; the hardware add is used because it does not wait for the old value.
 #pragma unroll
-                for (int r = 0; r < T; ++r) unsafeAtomicAdd(dst + r, gone[r]);
+                for (int r = 0; r < T; ++r)
+                    if (!RAGGED || r >= shared_with_neighbour) unsafeAtomicAdd(dst + r, gone[r]);
             } else {
                 store_vec<T>(dst, gone);
             }
@@ -247,7 +263,7 @@ __global__ __launch_bounds__(256) void backward_walk_kernel(SplineGeom g, WalkRe
             const int enter = cur + kMaxK < g.rows ? cur + kMaxK : g.rows - 1;     // clamped: unused past the end
             load_vec<T>(cfi + (int64_t)enter * g.n_out, cw[SL]);
 #pragma unroll
-            for (int r = 0; r < T; ++r) cw[SL][r] *= jmask;
+            for (int r = 0; r < T; ++r) cw[SL][r] *= own[RAGGED ? r : 0];
         }
     };
     auto retire = [&](bool store, bool enter_next) {
@@ -267,7 +283,7 @@ __global__ __launch_bounds__(256) void backward_walk_kernel(SplineGeom g, WalkRe
                 const int row = cur + ((s - cur) & (kMaxK - 1));
                 load_vec<T>(cfi + (int64_t)row * g.n_out, cw[s]);
 #pragma unroll
-                for (int r = 0; r < T; ++r) cw[s][r] *= jmask;
+                for (int r = 0; r < T; ++r) cw[s][r] *= own[RAGGED ? r : 0];
             }
         }
     };
@@ -444,14 +460,14 @@ __global__ __launch_bounds__(256) void backward_walk_kernel(SplineGeom g, WalkRe
     }
 }
 
-template <int STREAMS, int T>
+template <int STREAMS, int T, bool RAGGED>
 void walk_launch(bool dx, unsigned blocks, hipStream_t st, const SplineGeom &g, const WalkRecords &rec,
                         const float *gy, const float *cf, const float *w_b, float *part_c, float *part_b, float *gx,
                         int64_t B, const WalkPlan &p, int bpc, int m, int prezeroed, float *carry, int chunk0,
                         int n_chunks)
 {
-    auto kern = dx ? (p.S > 1024 ? backward_walk_kernel<STREAMS, T, true, true> : backward_walk_kernel<STREAMS, T, true, false>)
-                   : (p.S > 1024 ? backward_walk_kernel<STREAMS, T, false, true> : backward_walk_kernel<STREAMS, T, false, false>);
+    auto kern = dx ? (p.S > 1024 ? backward_walk_kernel<STREAMS, T, true, true, RAGGED> : backward_walk_kernel<STREAMS, T, true, false, RAGGED>)
+                   : (p.S > 1024 ? backward_walk_kernel<STREAMS, T, false, true, RAGGED> : backward_walk_kernel<STREAMS, T, false, false, RAGGED>);
     // the first round of a shared run finds its slabs zero and stores like an unshared run
     kern<<<blocks, 256, 0, st>>>(g, rec, gy, cf, w_b, part_c, part_b, gx, B, p.S, n_chunks, p.n_jt, bpc, m, prezeroed,
                                  p.n_seg, carry, chunk0, (p.shared && chunk0 > 0) ? 1 : 0, p.L, p.hk);

@@ -8,7 +8,7 @@ void walk_launch_s4t2(bool dx, unsigned blocks, hipStream_t st, const SplineGeom
                       int64_t B, const WalkPlan &p, int bpc, int m, int prezeroed, float *carry, int chunk0,
                       int n_chunks)
 {
-    walk_launch<4, 2>(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx, B, p, bpc, m, prezeroed, carry, chunk0,
+    walk_launch<4, 2, false>(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx, B, p, bpc, m, prezeroed, carry, chunk0,
                       n_chunks);
 }
 

@@ -13,10 +13,12 @@ pytestmark = pytest.mark.gpu
     (5, 31, 16, 3, 3),                 # four waves, exactly one 16-lane tile
     (3, 33, 17, 10, 2),                # sixteen waves, ragged 32-lane tile
     (2, 1100, 33, 4, 3),               # more inputs than one round of pair evaluations, ragged 64-lane tile
-    (2049, 40, 65, 6, 3),              # four samples per workgroup, ragged batch, two tiles of one output per lane
-    (2050, 35, 126, 6, 3),             # two outputs per lane
-    (9, 70, 130, 12, 5), (2047, 20, 64, 5, 4),      # window of six rows
-    (4096, 10, 64, 8, 3), (4097, 10, 64, 8, 3),     # the last batch of the direct kernel and the first past it
+    (2049, 40, 65, 6, 3),              # four samples per workgroup, ragged batch, the last lane moved back
+    (2050, 600, 5, 6, 3),              # narrowest tile of four outputs per lane, running sums folded
+    (2048, 3, 3, 6, 3),                # fewer outputs than a lane takes
+    (4099, 35, 30, 40, 3), (2050, 35, 126, 6, 1),
+    (9, 70, 130, 12, 5), (2047, 20, 64, 5, 4), (5001, 20, 31, 5, 5),      # window of six rows
+    (16384, 5, 64, 8, 3), (16385, 5, 64, 8, 3),     # the last batch of the direct kernel and the first past it
 ])
 def test_small_batch_forward(B, n_in, n_out, G, k):
     w = workloads.random_kan_layer(B + n_in, B, n_in, n_out, G, k, outside_frac=0.2)
@@ -29,3 +31,32 @@ def test_small_batch_forward(B, n_in, n_out, G, k):
     binding.kan_forward(s, x, coef, w_s, w_b, ws=ws)
     table = torch.cat([coef * w_s[:, None, :], w_b[:, None, :]], dim=1)
     assert torch.equal(ws[:table.numel() * 4].view(torch.float32), table.flatten())
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (700, 5, 17, 9, 3), (700, 5, 31, 300, 3),       # two outputs per lane, the last lane moved back; sparse walk
+    (1100, 4, 33, 9, 3), (900, 4, 63, 12, 2),       # four per lane, four streams
+    (900, 3, 65, 9, 3), (2100, 3, 127, 40, 1),      # two streams
+    (900, 3, 130, 9, 3), (700, 3, 255, 10, 3),      # one stream
+    (600, 2, 257, 9, 3), (600, 2, 300, 9, 3), (500, 2, 515, 9, 3),      # eight per lane, one tile and two
+    (700, 4, 35, 10, 5),                            # two records per pair
+])
+def test_widths_that_are_no_multiple_of_the_lanes(B, n_in, n_out, G, k):
+    run_layer_parity(workloads.random_kan_layer(n_out, B, n_in, n_out, G, k, outside_frac=0.2))
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (32800, 7, 30, 20, 3), (16400, 5, 37, 20, 3),                   # long-table kernel, one tile
+    (16400, 70, 63, 700, 3),                                        # row-stream kernel
+    (16400, 40, 9, 20, 3), (65540, 34, 9, 20, 3),                   # narrow kernel past the direct one
+    (8200, 20, 127, 600, 3), (4200, 10, 260, 400, 3),               # long-table kernel with several tiles, generic
+    (11000, 9, 130, 15, 3), (5200, 5, 259, 15, 3),                  # LDS-staged kernels
+    (16400, 8, 50, 700, 5), (7300, 4, 131, 12, 4),                  # window of six rows
+])
+def test_large_batches_of_ragged_widths(B, n_in, n_out, G, k):
+    run_layer_parity(workloads.random_kan_layer(n_out + 1, B, n_in, n_out, G, k, outside_frac=0.1))
+
+
+def test_ragged_width_on_shared_partial_tables():
+    """Several rounds of chunks on one partial table: outputs two lanes share are added once."""
+    run_layer_parity(workloads.random_kan_layer(5, 220000, 3, 35, 400000, 3, outside_frac=0.0), gx_in_grid_units=True)
