@@ -85,7 +85,7 @@ struct BackwardPlan {
     size_t rec_bytes;       // transposed x + sorted records of the walk (0 for the generic kernel)
     int b_slices_per_chunk; // base-term partial slices each chunk writes
     int n_slabs;            // partial slabs of the table gradient (one per chunk, or one shared by all)
-    size_t tail_bytes;      // scratch behind a single shared slab for the row-slice sums of gw_s
+    size_t tail_bytes;      // scratch of the reduction over the chunks (row slices of gw_s)
 };
 
 BackwardPlan backward_plan(const kan_layer_desc *d, int64_t B)
@@ -95,10 +95,9 @@ BackwardPlan backward_plan(const kan_layer_desc *d, int64_t B)
     // degrees 4 and 5 walk two four-row records per pair
     bp.wp = plan_walk(g, B, true, high_degree(d));
     bp.walk = bp.wp.ok != 0;
-    bp.tail_bytes = 0;
+    bp.tail_bytes = align_up(reduce_scratch_bytes(g.n_in, g.rows, g.n_out));
     if (bp.walk) {
         bp.n_slabs = bp.wp.n_slabs;
-        if (bp.wp.shared) bp.tail_bytes = align_up(dparam_reduce_tail_bytes(g.n_in, g.n_out));
         bp.cp.n_chunks = bp.wp.n_chunks;
         bp.cp.chunk_len = bp.wp.S;
         bp.rec_bytes = align_up(walk_scratch_bytes(bp.wp, B, g.n_in, g.n_out));
@@ -271,16 +270,15 @@ static int backward_impl(const kan_layer_desc *desc, int64_t B, const float *x, 
         float *part_c = (float *)at;
         float *part_b = (float *)((char *)part_c + (size_t)bp.n_slabs * folded_bytes(desc) + bp.tail_bytes);
         // partial slabs are laid out back to back with the unpadded slab size
+        CarryRows cr = {nullptr, nullptr, 1};
         hipError_t e = bp.walk ? launch_backward_walk(g, bp.wp, x, gy, table, w_b, walk_scratch, fused_dx ? gx : nullptr,
-                                                      want_params ? part_c : nullptr, want_b ? part_b : nullptr, B, st)
+                                                      want_params ? part_c : nullptr, want_b ? part_b : nullptr, B, &cr, st)
                                : launch_dparam_generic(g, x, gy, part_c, want_b ? part_b : nullptr, B, cp.n_chunks,
                                                        cp.chunk_len, st);
         if (e != hipSuccess) return KAN_ERR_HIP;
         if (want_params &&
-            launch_dparam_reduce(part_c, want_b ? part_b : nullptr, coef, w_s, gcoef, gw_s, gw_b, g.n_in, g.rows,
-                                 g.n_out, bp.n_slabs, cp.n_chunks * bp.b_slices_per_chunk, st,
-                                 // a shared slab is followed by the folded table's spare row and the tail scratch
-                                 bp.tail_bytes ? bp.tail_bytes + (folded_bytes(desc) - (size_t)g.n_in * g.rows * g.n_out * sizeof(float)) : 0) != hipSuccess)
+            launch_dparam_reduce(part_c, want_b ? part_b : nullptr, cr, coef, w_s, gcoef, gw_s, gw_b, g.n_in, g.rows, g.n_out,
+                                 bp.n_slabs, cp.n_chunks * bp.b_slices_per_chunk, (char *)part_b - bp.tail_bytes, st) != hipSuccess)
             return KAN_ERR_HIP;
     }
     return KAN_OK;

@@ -366,122 +366,7 @@ __global__ __launch_bounds__(64) void dparam_generic_kernel(SplineGeom g, const 
     }
 }
 
-// Stage 2.  Sum the partial sums (n_chunks slabs for the coefficient rows, n_slices_b slices for the
-// base term) in order with an fp64 accumulator, so that the long batch sum costs no accuracy, and
-// turn them into the three gradients:
-//   gcoef = w_s * acc,   gw_s = sum_m coef * acc,   gw_b = base sums.
-// 2a: one thread per table element (input, row, output): the chunk sum, gcoef, and the summed
-//     acc written back over chunk 0 of part_c for 2b.
-__global__ __launch_bounds__(256) void dparam_reduce_rows_kernel(float *__restrict__ part_c,
-                                                                 const float *__restrict__ w_s,
-                                                                 float *__restrict__ gcoef, int n_in, int rows,
-                                                                 int n_out, int n_chunks, int keep_sum)
-{
-    const int64_t slab = (int64_t)n_in * rows * n_out;
-    const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (at >= slab) return;
-    double a = 0.0;
-    for (int c = 0; c < n_chunks; ++c) a += (double)part_c[c * slab + at];
-    const int j = (int)(at % n_out);
-    const int i = (int)(at / ((int64_t)rows * n_out));
-    if (gcoef) gcoef[at] = (float)((double)w_s[(int64_t)i * n_out + j] * a);
-    if (keep_sum) part_c[at] = (float)a;
-}
-
-// 2a for n_out % 4 == 0: four consecutive outputs per thread, 16-byte accesses.
-__global__ __launch_bounds__(256) void dparam_reduce_rows4_kernel(float *__restrict__ part_c,
-                                                                  const float *__restrict__ w_s,
-                                                                  float *__restrict__ gcoef, int n_in, int rows,
-                                                                  int n_out, int n_chunks, int keep_sum)
-{
-    const int64_t slab = (int64_t)n_in * rows * n_out;
-    const int64_t at = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-    if (at >= slab) return;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    int c = 0;
-    for (; c + 4 <= n_chunks; c += 4) {          // four loads in flight, summed in chunk order
-        float4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4 *>(part_c + (c + u) * slab + at);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) { a0 += (double)v[u].x; a1 += (double)v[u].y; a2 += (double)v[u].z; a3 += (double)v[u].w; }
-    }
-    for (; c < n_chunks; ++c) {
-        const float4 v = *reinterpret_cast<const float4 *>(part_c + c * slab + at);
-        a0 += (double)v.x; a1 += (double)v.y; a2 += (double)v.z; a3 += (double)v.w;
-    }
-    const int j = (int)(at % n_out);
-    const int i = (int)(at / ((int64_t)rows * n_out));
-    if (gcoef) {
-        const float4 w = *reinterpret_cast<const float4 *>(w_s + (int64_t)i * n_out + j);
-        *reinterpret_cast<float4 *>(gcoef + at) = make_float4((float)((double)w.x * a0), (float)((double)w.y * a1),
-                                                              (float)((double)w.z * a2), (float)((double)w.w * a3));
-    }
-    if (keep_sum) *reinterpret_cast<float4 *>(part_c + at) = make_float4((float)a0, (float)a1, (float)a2, (float)a3);
-}
-
-// 2b: gw_s from the summed acc, gw_b from the base slices.  grid (n_in, ceil(n_out / 64), n_rs), 256
-// threads: lane <-> output, the four waves split the rows (or slices) of the block's row slice
-// between them and their fp64 partial sums are added in wave order.  With n_rs > 1 row slices the
-// block sums go to slice_sums[rs][i][j] (fp64) and dparam_reduce_edges_final_kernel adds them up in
-// slice order; with one slice the result is written directly.
-__global__ __launch_bounds__(256) void dparam_reduce_edges_kernel(const float *__restrict__ acc_sum,
-                                                                  const float *__restrict__ part_b,
-                                                                  const float *__restrict__ coef,
-                                                                  float *__restrict__ gw_s, float *__restrict__ gw_b,
-                                                                  double *__restrict__ slice_sums, int n_in, int rows,
-                                                                  int n_out, int n_slices_b)
-{
-    __shared__ double part[2][4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i = blockIdx.x, j = blockIdx.y * 64 + lane;
-    const int n_rs = gridDim.z, rs = blockIdx.z;
-    const int per = (rows + n_rs - 1) / n_rs;
-    const int m_lo = rs * per, m_hi = (m_lo + per < rows) ? m_lo + per : rows;
-    const bool ok = j < n_out;
-    const int jc = ok ? j : 0;
-    double s = 0.0, a = 0.0;
-    if (gw_s) {
-        const float *cp = coef + (int64_t)i * rows * n_out + jc, *ap = acc_sum + (int64_t)i * rows * n_out + jc;
-        int m = m_lo + wave;
-        for (; m + 12 < m_hi; m += 16) {        // four rows of this wave in flight
-            float cv[4], av[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { cv[u] = cp[(int64_t)(m + 4 * u) * n_out]; av[u] = ap[(int64_t)(m + 4 * u) * n_out]; }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) s += (double)cv[u] * (double)av[u];
-        }
-        for (; m < m_hi; m += 4) s += (double)cp[(int64_t)m * n_out] * (double)ap[(int64_t)m * n_out];
-    }
-    if (gw_b && part_b && rs == 0) {
-        const float *bp = part_b + (int64_t)i * n_out + jc;
-        for (int c = wave; c < n_slices_b; c += 4) a += (double)bp[(int64_t)c * n_in * n_out];
-    }
-    part[0][wave][lane] = s;
-    part[1][wave][lane] = a;
-    __syncthreads();
-    if (wave == 0 && ok) {
-        const int64_t e = (int64_t)i * n_out + j;
-        const double ss = ((part[0][0][lane] + part[0][1][lane]) + part[0][2][lane]) + part[0][3][lane];
-        if (gw_s) {
-            if (n_rs > 1) slice_sums[(int64_t)rs * n_in * n_out + e] = ss;
-            else gw_s[e] = (float)ss;
-        }
-        // no base term: the gradient is identically zero
-        if (gw_b && rs == 0) gw_b[e] = (float)(((part[1][0][lane] + part[1][1][lane]) + part[1][2][lane]) + part[1][3][lane]);
-    }
-}
-
-__global__ __launch_bounds__(256) void dparam_reduce_edges_final_kernel(const double *__restrict__ slice_sums,
-                                                                        float *__restrict__ gw_s, int64_t edges,
-                                                                        int n_rs)
-{
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= edges) return;
-    double s = 0.0;
-    for (int r = 0; r < n_rs; ++r) s += slice_sums[(int64_t)r * edges + e];
-    gw_s[e] = (float)s;
-}
+// Stage 2, the sum over the chunks, is kan_reduce.hip.
 
 // ---- launchers -------------------------------------------------------------
 
@@ -585,44 +470,6 @@ hipError_t launch_dparam_generic(const SplineGeom &g, const float *x, const floa
     case 4: dparam_generic_kernel<4><<<grid, 64, 0, st>>>(g, x, gy, part_c, part_b, B, chunk_len, n_jt); break;
     case 2: dparam_generic_kernel<2><<<grid, 64, 0, st>>>(g, x, gy, part_c, part_b, B, chunk_len, n_jt); break;
     default: dparam_generic_kernel<1><<<grid, 64, 0, st>>>(g, x, gy, part_c, part_b, B, chunk_len, n_jt); break;
-    }
-    return hipGetLastError();
-}
-
-size_t dparam_reduce_tail_bytes(int n_in, int n_out) { return 64 * (size_t)n_in * n_out * sizeof(double) + 8; }
-
-hipError_t launch_dparam_reduce(float *part_c, const float *part_b, const float *coef, const float *w_s,
-                                float *gcoef, float *gw_s, float *gw_b, int n_in, int rows, int n_out,
-                                int n_chunks, int n_slices_b, hipStream_t st, size_t tail_scratch)
-{
-    const int64_t slab = (int64_t)n_in * rows * n_out, edges = (int64_t)n_in * n_out;
-    const bool vec4 = n_out % 4 == 0 && ((uintptr_t)part_c % 16) == 0 && (!gcoef || ((uintptr_t)gcoef % 16) == 0) &&
-                      ((uintptr_t)w_s % 16) == 0;
-    if (gcoef || gw_s) {
-        prof::Timed tm("dparam_reduce", st);
-        if (vec4)
-            dparam_reduce_rows4_kernel<<<(unsigned)((slab / 4 + 255) / 256), 256, 0, st>>>(part_c, w_s, gcoef, n_in, rows,
-                                                                                     n_out, n_chunks, gw_s ? 1 : 0);
-        else
-            dparam_reduce_rows_kernel<<<(unsigned)((slab + 255) / 256), 256, 0, st>>>(part_c, w_s, gcoef, n_in, rows,
-                                                                                    n_out, n_chunks, gw_s ? 1 : 0);
-    }
-    if (gw_s || gw_b) {
-        // Long tables: the row sum behind gw_s is cut into row slices.  Their fp64 block sums live in
-        // the second chunk's partial slab, which is dead once the chunks have been summed (or in the
-        // scratch the caller left behind a single slab).
-        int n_rs = 1;
-        double *slice_sums = nullptr;
-        if (gw_s && (n_chunks >= 2 || tail_scratch >= dparam_reduce_tail_bytes(n_in, n_out)) && rows >= 512) {
-            n_rs = rows / 256 < 64 ? rows / 256 : 64;
-            slice_sums = (double *)(((uintptr_t)(part_c + slab) + 7) & ~(uintptr_t)7);
-        }
-        prof::Timed te("dparam_reduce_edges", st);
-        dparam_reduce_edges_kernel<<<dim3((unsigned)n_in, (unsigned)((n_out + 63) / 64), (unsigned)n_rs), 256, 0, st>>>(
-            part_c, part_b, coef, gw_s, gw_b, slice_sums, n_in, rows, n_out, n_slices_b);
-        if (n_rs > 1)
-            dparam_reduce_edges_final_kernel<<<(unsigned)((edges + 255) / 256), 256, 0, st>>>(slice_sums, gw_s, edges,
-                                                                                            n_rs);
     }
     return hipGetLastError();
 }

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "kan_device.hpp"
+#include "kan_reduce.hpp"
 
 // Launch observer (kan_set_launch_observer in kan.h).  A Timed object calls the installed hooks on
 // the host right before and right after one kernel launch is enqueued, and does nothing when none
@@ -63,12 +64,6 @@ hipError_t launch_dx_generic(const SplineGeom &g, const float *x, const float *c
 int dparam_generic_row_blocks(int rows);     // base-term partial slices per chunk
 hipError_t launch_dparam_generic(const SplineGeom &g, const float *x, const float *gy, float *part_c,
                                  float *part_b, int64_t B, int n_chunks, int64_t chunk_len, hipStream_t st);
-// tail_scratch: bytes of scratch that follow the first partial slab when there is only one (with two
-// or more, the second slab serves); 0 = none
-size_t dparam_reduce_tail_bytes(int n_in, int n_out);
-hipError_t launch_dparam_reduce(float *part_c, const float *part_b, const float *coef, const float *w_s,
-                                float *gcoef, float *gw_s, float *gw_b, int n_in, int rows, int n_out,
-                                int n_chunks, int n_slices_b, hipStream_t st, size_t tail_scratch = 0);
 
 // narrow layers (n_out <= 16)
 int narrow_applicable(const SplineGeom &g);
@@ -131,9 +126,10 @@ struct WalkPlan {
 // chunks taking turns on the slabs that fit (ok stays 0 for them otherwise).
 WalkPlan plan_walk(const SplineGeom &g, int64_t B, bool allow_shared = false, bool high_degree = false);
 size_t walk_scratch_bytes(const WalkPlan &p, int64_t B, int n_in, int n_out);
+// carry_rows: what the reduction of part_c has to add (kan_reduce.hpp)
 hipError_t launch_backward_walk(const SplineGeom &g, const WalkPlan &p, const float *x, const float *gy,
                                 const float *cf, const float *w_b, void *scratch, float *gx, float *part_c,
-                                float *part_b, int64_t B, hipStream_t st);
+                                float *part_b, int64_t B, ::kan::CarryRows *carry_rows, hipStream_t st);
 
 // How the batch is cut into chunks for the parameter-gradient reduction: chunks of about 1024
 // samples, at most 64 of them, and no more than fit a 512 MiB budget of partial sums.

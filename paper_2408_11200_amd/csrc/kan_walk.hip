@@ -19,8 +19,8 @@
 //                            arrays: window row | sample, base value, the K weights)
 //   3. backward_walk_kernel  the walk; partial sums per chunk, reduced by dparam_reduce (fp64,
 //                            fixed order), so results are bit-reproducible
-//   4. walk_carry_kernel     when a list is cut into several segments (one stream each): adds what a
-//                            segment's window held past its last own row to the next segment's rows
+// When a list is cut into several segments (one stream each), what a segment's window holds past its last own row goes to
+// four carry rows, which the reduction over the chunks adds to the next segment's rows.
 //
 // Lanes <-> outputs.  A wave holds 64 / LPS streams of LPS lanes each (LPS = 16, 32 or 64), so that
 // narrow layers still fill the wave.  Records are loaded 16 at a time, one per lane of each DPP row
@@ -189,21 +189,20 @@ __global__ __launch_bounds__(64 * NW) void cell_sort_kernel(SplineGeom g, const 
     }
 }
 
-// Adds the carry rows of segments 1 .. n_seg-1 to the partial slabs, in segment order.  One thread
-// per (chunk, input, output).
-__global__ __launch_bounds__(256) void walk_carry_kernel(SplineGeom g, const int *__restrict__ rt,
+// Shared slabs: adds the carry rows of segments 1 .. n_seg-1 to the slabs, in segment order, after each round of chunks.
+// One thread per (chunk, input, output).  (Slabs of their own: the reduction over the chunks adds the carry rows.)
+__global__ __launch_bounds__(256) void walk_carry_kernel(SplineGeom g, const int *__restrict__ seg_row,
                                                          const float *__restrict__ carry, float *__restrict__ part_c,
-                                                         int L, int n_chunks, int n_seg, int chunk0, int shared)
+                                                         int n_chunks, int n_seg, int chunk0)
 {
-    // n_chunks chunks starting at chunk0 of the batch; shared: the launch's chunk number l adds to slab l
+    // n_chunks chunks starting at chunk0 of the batch; the launch's chunk number l adds to slab l
     const int64_t at = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (at >= (int64_t)n_chunks * g.n_in * g.n_out) return;
     const int j = (int)(at % g.n_out);
     const int64_t ci = (int64_t)chunk0 * g.n_in + at / g.n_out;               // chunk * n_in + input
-    const int seg_len = L / n_seg;              // L: entries per sorted list
-    float *slab = part_c + (shared ? at / g.n_out : ci) * g.rows * g.n_out + j;
+    float *slab = part_c + at / g.n_out * g.rows * g.n_out + j;
     for (int k = 1; k < n_seg; ++k) {
-        const int rf = rt[ci * L + (int64_t)k * seg_len] & kRtRowMask;
+        const int rf = seg_row[ci * n_seg + k];
         const float *cr = carry + ((ci * n_seg + k) * kMaxK) * g.n_out + j;
         for (int s = 0; s < kMaxK; ++s)
             if (rf + s < g.rows) slab[(int64_t)(rf + s) * g.n_out] += cr[(int64_t)s * g.n_out];
@@ -262,18 +261,24 @@ WalkPlan plan_walk(const SplineGeom &g, int64_t B, bool allow_shared, bool high_
     }
     const int tile = (64 / p.streams) * p.T;
     p.n_jt = (g.n_out + tile - 1) / tile;
-    // chunk length: a power of two between 256 and 8192 samples, the smaller of
-    //   - what keeps the gy rows of one chunk inside an XCD's L2 (4 MiB),
-    //   - an eighth of the batch (one chunk per XCD at least),
-    // then raised until the partial sums fit 2 GiB.  Few, long chunks keep the partial sums small;
-    // the parallelism comes from cutting each sorted list into segments (below).
+    // chunk length: a power of two between 256 and 8192 samples.  Every chunk writes a partial table that the reduction
+    // reads back, so few long chunks are better, as long as
+    //   - the gy rows of a chunk stay in cache (at most 8 MiB: twice an XCD's L2, the rest served by the memory-side
+    //     cache.  128 -> 256 -> 256 -> 1 with tables of 360 rows, B = 32768, walk + sort + reduction: 4 MiB 2.73 ms, 8 MiB
+    //     2.64 ms),
+    //   - there is an eighth of the batch in a chunk at most (one chunk per XCD) or two workgroups per CU left to sort
+    //     (256 -> 256, G = 200, B = 8192: eight chunks 538 us, four 422 us, two 368 us).
+    // Raised further until the partial sums fit 2 GiB.  The parallelism of the walk comes from cutting each sorted list
+    // into segments (below).
     // (two records per pair for degrees 4 and 5: the sort holds 2 S keys and a record has 12 bits for the sample)
     const int s_max = high_degree ? 4096 : 8192;
     auto pow2_floor = [s_max](int64_t v) { int64_t q = 256; while (q * 2 <= v && q < s_max) q *= 2; return (int)q; };
-    int S = pow2_floor((4ll << 20) / ((int64_t)g.n_out * 4));
+    int S = pow2_floor((8ll << 20) / ((int64_t)g.n_out * 4));
     if (p.T == 8 && S > 1024) S = 1024;      // eight outputs per lane: stay with single-level sums (registers)
-    const int s_b8 = pow2_floor(B / 8);
-    S = S < s_b8 ? S : s_b8;
+    int64_t share = B * g.n_in / 512 < B ? B * g.n_in / 512 : B;
+    if (share < B / 8) share = B / 8;
+    const int s_par = pow2_floor(share);
+    S = S < s_par ? S : s_par;
     const int64_t slab = (int64_t)g.n_in * g.rows * g.n_out * (int64_t)sizeof(float);
     while (S < s_max && ((B + S - 1) / S) * slab > (2ll << 30)) S *= 2;
     p.S = S;
@@ -313,7 +318,7 @@ WalkPlan plan_walk(const SplineGeom &g, int64_t B, bool allow_shared, bool high_
 #define KAN_WALK_VARIANT(name)                                                                                      \
     void name(bool dx, unsigned blocks, hipStream_t st, const SplineGeom &g, const WalkRecords &rec, const float *gy, \
               const float *cf, const float *w_b, float *part_c, float *part_b, float *gx, int64_t B,              \
-              const WalkPlan &p, int bpc, int m, int prezeroed, float *carry, int chunk0, int n_chunks)
+              const WalkPlan &p, int bpc, int m, int prezeroed, float *carry, int *seg_row, int chunk0, int n_chunks)
 KAN_WALK_VARIANT(walk_launch_s1t8);
 KAN_WALK_VARIANT(walk_launch_s1t4);
 KAN_WALK_VARIANT(walk_launch_s2t4);
@@ -333,11 +338,12 @@ size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 }
 
 // transposed x | records (row|sample, base, weights, derivative base, derivative weights) |
-// per-tile partial gx (layers wider than one tile) | carry rows of the list segments
+// per-tile partial gx (layers wider than one tile) | carry rows of the list segments | first row of every segment
 static size_t walk_carry_bytes(const WalkPlan &p, int n_in, int n_out)
 {
     return up256((size_t)p.n_chunks * n_in * (p.n_seg + 1) * kMaxK * n_out * sizeof(float));
 }
+static size_t walk_seg_row_bytes(const WalkPlan &p, int n_in) { return up256((size_t)p.n_chunks * n_in * p.n_seg * sizeof(int)); }
 
 size_t walk_scratch_bytes(const WalkPlan &p, int64_t B, int n_in, int n_out)
 {
@@ -345,7 +351,7 @@ size_t walk_scratch_bytes(const WalkPlan &p, int64_t B, int n_in, int n_out)
     const int n_part = p.n_jt * (p.hk ? 2 : 1);       // partial dL/dx results per (sample, input)
     const size_t gxp = n_part > 1 ? up256((size_t)n_part * B * n_in * sizeof(float)) : 0;
     return up256((size_t)B * n_in * sizeof(float)) + 3 * up256(n * 4) + 2 * up256(n * 16) + gxp +
-           walk_carry_bytes(p, n_in, n_out);
+           walk_carry_bytes(p, n_in, n_out) + walk_seg_row_bytes(p, n_in);
 }
 
 // x -> xT, then per (chunk of S samples, input) the records in sorted order.  S: a power of two >= 256.
@@ -383,7 +389,7 @@ hipError_t launch_sorted_records(const SplineGeom &g, const float *x, float *xT,
 // table ([n_in][slab_rows][n_out]); w_b may be null when the layer has no base term.
 hipError_t launch_backward_walk(const SplineGeom &g, const WalkPlan &p, const float *x, const float *gy,
                                 const float *cf, const float *w_b, void *scratch, float *gx, float *part_c,
-                                float *part_b, int64_t B, hipStream_t st)
+                                float *part_b, int64_t B, CarryRows *carry_rows, hipStream_t st)
 {
     const size_t n = (size_t)p.n_chunks * g.n_in * p.L;
     const int n_part = p.n_jt * (p.hk ? 2 : 1);
@@ -397,7 +403,10 @@ hipError_t launch_backward_walk(const SplineGeom &g, const WalkPlan &p, const fl
     rec.dbase = dx ? (float *)at : nullptr; at += up256(n * 4);
     rec.dw4 = dx ? (float *)at : nullptr;   at += up256(n * 16);
     float *gx_part = (float *)at;       at += n_part > 1 ? up256((size_t)n_part * B * g.n_in * sizeof(float)) : 0;
-    float *carry = (float *)at;
+    float *carry = (float *)at;         at += walk_carry_bytes(p, g.n_in, g.n_out);
+    int *seg_row = (int *)at;
+    // the chunks' carry rows are added by the reduction over the chunks; shared slabs take theirs below
+    *carry_rows = CarryRows{seg_row, carry, p.shared ? 1 : p.n_seg};
     if (p.hk) {
         // degrees 4 and 5: the records come from the kernel built for a window of six rows
         {
@@ -445,13 +454,12 @@ hipError_t launch_backward_walk(const SplineGeom &g, const WalkPlan &p, const fl
                           : p.streams == 1 ? (ragged ? walk_launch_s1t4_ragged : walk_launch_s1t4)
                           : p.streams == 2 ? (ragged ? walk_launch_s2t4_ragged : walk_launch_s2t4)
                                            : (ragged ? walk_launch_s4t4_ragged : walk_launch_s4t4);
-            launch(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx_out, B, p, bpc, m, prezeroed, carry, chunk0, here);
+            launch(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx_out, B, p, bpc, m, prezeroed, carry, seg_row, chunk0, here);
         }
-        if (part_c != nullptr && p.n_seg > 1) {
+        if (part_c != nullptr && p.n_seg > 1 && p.shared) {
             const int64_t nn = (int64_t)here * g.n_in * g.n_out;
             prof::Timed tm("walk_carry", st);
-            walk_carry_kernel<<<(unsigned)((nn + 255) / 256), 256, 0, st>>>(g, rec.rt, carry, part_c, p.L, here,
-                                                                           p.n_seg, chunk0, p.shared);
+            walk_carry_kernel<<<(unsigned)((nn + 255) / 256), 256, 0, st>>>(g, seg_row, carry, part_c, here, p.n_seg, chunk0);
         }
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }

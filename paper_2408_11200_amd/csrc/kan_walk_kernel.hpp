@@ -144,7 +144,7 @@ __global__ __launch_bounds__(256) void backward_walk_kernel(SplineGeom g, WalkRe
                                                             float *__restrict__ part_c, float *__restrict__ part_b,
                                                             float *__restrict__ gx, int64_t B, int S, int n_chunks,
                                                             int n_jt, int blocks_per_chunk, int xcd_groups, int prezeroed, int n_seg,
-                                                            float *__restrict__ carry, int chunk0, int shared, int L, int hk)
+                                                            float *__restrict__ carry, int *__restrict__ seg_row, int chunk0, int shared, int L, int hk)
 {
     constexpr int LPS = 64 / STREAMS;
     constexpr int RPW = LPS / 4;                    // records whose weights fit one register of a stream
@@ -209,6 +209,7 @@ __global__ __launch_bounds__(256) void backward_walk_kernel(SplineGeom g, WalkRe
     }
 
     int cur = rec.rt[list] & kRtRowMask;     // first row of the window the accumulators stand on
+    if (part_c != nullptr && n_seg > 1 && jt == 0 && q == 0) seg_row[((int64_t)c * g.n_in + i) * n_seg + seg] = cur;
     if (store_c && !prezeroed && seg == 0)
         for (int m = 0; m < cur; ++m) store_vec<T>(out + (int64_t)m * g.n_out, zero);
 
@@ -463,14 +464,14 @@ __global__ __launch_bounds__(256) void backward_walk_kernel(SplineGeom g, WalkRe
 template <int STREAMS, int T, bool RAGGED>
 void walk_launch(bool dx, unsigned blocks, hipStream_t st, const SplineGeom &g, const WalkRecords &rec,
                         const float *gy, const float *cf, const float *w_b, float *part_c, float *part_b, float *gx,
-                        int64_t B, const WalkPlan &p, int bpc, int m, int prezeroed, float *carry, int chunk0,
-                        int n_chunks)
+                        int64_t B, const WalkPlan &p, int bpc, int m, int prezeroed, float *carry,
+                        int *seg_row, int chunk0, int n_chunks)
 {
     auto kern = dx ? (p.S > 1024 ? backward_walk_kernel<STREAMS, T, true, true, RAGGED> : backward_walk_kernel<STREAMS, T, true, false, RAGGED>)
                    : (p.S > 1024 ? backward_walk_kernel<STREAMS, T, false, true, RAGGED> : backward_walk_kernel<STREAMS, T, false, false, RAGGED>);
     // the first round of a shared run finds its slabs zero and stores like an unshared run
     kern<<<blocks, 256, 0, st>>>(g, rec, gy, cf, w_b, part_c, part_b, gx, B, p.S, n_chunks, p.n_jt, bpc, m, prezeroed,
-                                 p.n_seg, carry, chunk0, (p.shared && chunk0 > 0) ? 1 : 0, p.L, p.hk);
+                                 p.n_seg, carry, seg_row, chunk0, (p.shared && chunk0 > 0) ? 1 : 0, p.L, p.hk);
 }
 
 }  // namespace

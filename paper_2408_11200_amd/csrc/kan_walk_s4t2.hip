@@ -5,10 +5,10 @@ namespace kan {
 
 void walk_launch_s4t2(bool dx, unsigned blocks, hipStream_t st, const SplineGeom &g, const WalkRecords &rec,
                       const float *gy, const float *cf, const float *w_b, float *part_c, float *part_b, float *gx,
-                      int64_t B, const WalkPlan &p, int bpc, int m, int prezeroed, float *carry, int chunk0,
+                      int64_t B, const WalkPlan &p, int bpc, int m, int prezeroed, float *carry, int *seg_row, int chunk0,
                       int n_chunks)
 {
-    walk_launch<4, 2, false>(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx, B, p, bpc, m, prezeroed, carry, chunk0,
+    walk_launch<4, 2, false>(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx, B, p, bpc, m, prezeroed, carry, seg_row, chunk0,
                       n_chunks);
 }
 

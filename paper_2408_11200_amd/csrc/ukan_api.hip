@@ -80,7 +80,7 @@ ChunkPlan chunks_for(const ukan_layer_desc *d, int64_t B, int32_t max_groups)
 struct Layout {
     size_t cmin, cmax, g_first, n_groups, cell_base, summary;
     size_t hid, cf;                                   // forward
-    size_t z, pre, raw, rec, part_c, part_b, gout, gpre, split;   // backward only
+    size_t z, pre, raw, rec, part_c, part_b, slices, gout, gpre, split;   // backward only
     size_t total;
 };
 
@@ -99,7 +99,7 @@ Layout make_layout(const ukan_layer_desc *d, int64_t B, int64_t n_g, int n_chunk
     L.n_groups = take(n_in * 4); L.cell_base = take(n_in * 4); L.summary = take(256);
     L.hid = take(rows * dh * 4);
     L.cf = take(table);
-    L.z = L.pre = L.raw = L.rec = L.part_c = L.part_b = L.gout = L.gpre = L.split = 0;
+    L.z = L.pre = L.raw = L.rec = L.part_c = L.part_b = L.slices = L.gout = L.gpre = L.split = 0;
     if (pass == KAN_PASS_BACKWARD) {
         L.z = take(rows * dz * 4);
         L.pre = take(rows * dh * 4);
@@ -107,6 +107,7 @@ Layout make_layout(const ukan_layer_desc *d, int64_t B, int64_t n_g, int n_chunk
         L.rec = take(rec_bytes);
         L.part_c = take((size_t)n_chunks * table);
         L.part_b = take((size_t)n_chunks * b_slices * n_in * n_out * 4);
+        L.slices = take(reduce_scratch_bytes(d->n_in, (int)(n_g * (int64_t)K), d->n_out));
         L.gout = take(table);
         L.gpre = take(rows * dh * 4);
         size_t s1 = (size_t)split_slices((int64_t)rows) * dh * n_o * 4;      // gW2 partials
@@ -392,9 +393,10 @@ int backward_body(const ukan_layer_desc *desc, int64_t B, const float *x, const 
     float *part_c = (float *)(w + L.part_c), *part_b = (float *)(w + L.part_b);
     float *gout = (float *)(w + L.gout);
     int b_slices;
+    CarryRows cr = {nullptr, nullptr, 1};
     if (wp.ok) {
         if (launch_backward_walk(pr.g, wp, x, gy, pr.cf, p->w_b, w + L.rec, fused_dx ? gx : nullptr,
-                                 want_params ? part_c : nullptr, want_b ? part_b : nullptr, B, st) != hipSuccess)
+                                 want_params ? part_c : nullptr, want_b ? part_b : nullptr, B, &cr, st) != hipSuccess)
             return KAN_ERR_HIP;
         b_slices = pr.cp.n_chunks * wp.n_seg;
     } else {
@@ -407,9 +409,8 @@ int backward_body(const ukan_layer_desc *desc, int64_t B, const float *x, const 
         b_slices = pr.cp.n_chunks * row_blocks_for(desc, pr.g.rows);
     }
     if (!want_params) return KAN_OK;
-    if (launch_dparam_reduce(part_c, want_b ? part_b : nullptr, pr.raw, p->scale,
-                             cg_grads ? gout : nullptr, g->gscale, g->gw_b, desc->n_in, pr.g.rows, desc->n_out,
-                             pr.cp.n_chunks, b_slices, st) != hipSuccess)
+    if (launch_dparam_reduce(part_c, want_b ? part_b : nullptr, cr, pr.raw, p->scale, cg_grads ? gout : nullptr, g->gscale,
+                             g->gw_b, desc->n_in, pr.g.rows, desc->n_out, pr.cp.n_chunks, b_slices, w + L.slices, st) != hipSuccess)
         return KAN_ERR_HIP;
     if (!cg_grads) return KAN_OK;
 

@@ -60,3 +60,13 @@ def test_large_batches_of_ragged_widths(B, n_in, n_out, G, k):
 def test_ragged_width_on_shared_partial_tables():
     """Several rounds of chunks on one partial table: outputs two lanes share are added once."""
     run_layer_parity(workloads.random_kan_layer(5, 220000, 3, 35, 400000, 3, outside_frac=0.0), gx_in_grid_units=True)
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (8192, 2, 3, 5, 3), (9000, 3, 4, 700, 3),       # one output per lane; row slices added by a second kernel
+    (70000, 2, 18, 9, 3), (33000, 3, 34, 3, 2),     # many segments of few rows, ragged tiles
+    (2500, 40, 520, 6, 3),                          # small workgroups (more than 512 of them), two tiles
+    (40000, 3, 20, 1030, 5),                        # two records per pair, long table
+])
+def test_reduction_over_the_chunks(B, n_in, n_out, G, k):
+    run_layer_parity(workloads.random_kan_layer(n_out + 7, B, n_in, n_out, G, k, outside_frac=0.1))
