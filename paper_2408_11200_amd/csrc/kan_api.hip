@@ -80,6 +80,7 @@ size_t edge_bytes(const kan_layer_desc *d)
 // which kernel takes the parameter gradients and how its scratch is cut
 struct BackwardPlan {
     bool walk;
+    DensePlan dense;        // ok: takes the whole pass instead
     WalkPlan wp;
     ChunkPlan cp;
     size_t rec_bytes;       // transposed x + sorted records of the walk (0 for the generic kernel)
@@ -92,6 +93,16 @@ BackwardPlan backward_plan(const kan_layer_desc *d, int64_t B)
 {
     SplineGeom g = geom_of(d);
     BackwardPlan bp;
+    bp.dense = plan_dense(g, B);
+    if (bp.dense.ok) {
+        bp.walk = false;
+        bp.cp.n_chunks = bp.n_slabs = bp.dense.n_chunks;
+        bp.cp.chunk_len = bp.dense.chunk_len;
+        bp.rec_bytes = 0;
+        bp.b_slices_per_chunk = 1;
+        bp.tail_bytes = align_up(reduce_scratch_bytes(g.n_in, g.rows, g.n_out));
+        return bp;
+    }
     // degrees 4 and 5 walk two four-row records per pair
     bp.wp = plan_walk(g, B, true, high_degree(d));
     bp.walk = bp.wp.ok != 0;
@@ -251,7 +262,7 @@ static int backward_impl(const kan_layer_desc *desc, int64_t B, const float *x, 
     // the chunk-sorted walk takes dL/dx together with the parameter gradients (one pass over gy)
     const bool fused_dx = gx && bp.walk;
     const float *table = folded ? folded : cf;        // the table dL/dx reads
-    if (gx) {
+    if (gx && !bp.dense.ok) {
         if (!folded &&
             launch_fold_scale(coef, w_s, g.base_act ? w_b : nullptr, cf, g.n_in, g.rows, g.n_out, st) != hipSuccess)
             return KAN_ERR_HIP;
@@ -262,7 +273,7 @@ static int backward_impl(const kan_layer_desc *desc, int64_t B, const float *x, 
         }
     }
     const bool want_b = gw_b && desc->base_act != KAN_BASE_NONE;
-    if (want_params || fused_dx) {
+    if (want_params || fused_dx || bp.dense.ok) {
         const ChunkPlan cp = bp.cp;
         char *at = (char *)ws + folded_bytes(desc);
         void *walk_scratch = at;
@@ -271,7 +282,9 @@ static int backward_impl(const kan_layer_desc *desc, int64_t B, const float *x, 
         float *part_b = (float *)((char *)part_c + (size_t)bp.n_slabs * folded_bytes(desc) + bp.tail_bytes);
         // partial slabs are laid out back to back with the unpadded slab size
         CarryRows cr = {nullptr, nullptr, 1};
-        hipError_t e = bp.walk ? launch_backward_walk(g, bp.wp, x, gy, table, w_b, walk_scratch, fused_dx ? gx : nullptr,
+        hipError_t e = bp.dense.ok ? launch_backward_dense(g, bp.dense, x, gy, coef, w_s, w_b, want_params ? part_c : nullptr,
+                                                           want_b ? part_b : nullptr, gx, B, st)
+                       : bp.walk ? launch_backward_walk(g, bp.wp, x, gy, table, w_b, walk_scratch, fused_dx ? gx : nullptr,
                                                       want_params ? part_c : nullptr, want_b ? part_b : nullptr, B, &cr, st)
                                : launch_dparam_generic(g, x, gy, part_c, want_b ? part_b : nullptr, B, cp.n_chunks,
                                                        cp.chunk_len, st);

@@ -131,6 +131,15 @@ hipError_t launch_backward_walk(const SplineGeom &g, const WalkPlan &p, const fl
                                 const float *cf, const float *w_b, void *scratch, float *gx, float *part_c,
                                 float *part_b, int64_t B, ::kan::CarryRows *carry_rows, hipStream_t st);
 
+// Layers of few rows and outputs: dense basis rows on the matrix cores (kan_dense.hip).  ok == 0: not covered.
+struct DensePlan { int ok; int n_chunks; int64_t chunk_len; };
+DensePlan plan_dense(const SplineGeom &g, int64_t B);
+// coef[n_in][rows][n_out]; w_s null: scaled already.  part_c[n_chunks][n_in][rows][n_out], part_b[n_chunks][n_in][n_out] and gx
+// may be null
+hipError_t launch_backward_dense(const SplineGeom &g, const DensePlan &p, const float *x, const float *gy, const float *coef,
+                                 const float *w_s, const float *w_b, float *part_c, float *part_b, float *gx, int64_t B,
+                                 hipStream_t st);
+
 // How the batch is cut into chunks for the parameter-gradient reduction: chunks of about 1024
 // samples, at most 64 of them, and no more than fit a 512 MiB budget of partial sums.
 struct ChunkPlan { int n_chunks; int64_t chunk_len; };

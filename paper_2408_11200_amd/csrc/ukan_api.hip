@@ -76,11 +76,21 @@ ChunkPlan chunks_for(const ukan_layer_desc *d, int64_t B, int32_t max_groups)
     return plan_chunks(B, d->n_in, max_groups * (d->k + 1), d->n_out);
 }
 
+// Partial sums of the dense-basis backward kernel, for the longest table it takes: which kernel runs depends on the span
+// found, and must fit the workspace planned for max_groups.
+size_t dense_part_bytes(const ukan_layer_desc *d, int64_t B)
+{
+    SplineGeom g = {};
+    g.n_in = d->n_in; g.n_out = d->n_out; g.rows = 1; g.slab_rows = 1; g.k = d->k;
+    const DensePlan p = plan_dense(g, B);
+    return p.ok ? (size_t)p.n_chunks * d->n_in * 64 * d->n_out * sizeof(float) : 0;
+}
+
 // Offsets (bytes) of every scratch region for `n_g` generator rows per input.
 struct Layout {
     size_t cmin, cmax, g_first, n_groups, cell_base, summary;
     size_t hid, cf;                                   // forward
-    size_t z, pre, raw, rec, part_c, part_b, slices, gout, gpre, split;   // backward only
+    size_t z, pre, raw, rec, part_c, part_b, slices, dense, gout, gpre, split;   // backward only
     size_t total;
 };
 
@@ -99,7 +109,7 @@ Layout make_layout(const ukan_layer_desc *d, int64_t B, int64_t n_g, int n_chunk
     L.n_groups = take(n_in * 4); L.cell_base = take(n_in * 4); L.summary = take(256);
     L.hid = take(rows * dh * 4);
     L.cf = take(table);
-    L.z = L.pre = L.raw = L.rec = L.part_c = L.part_b = L.slices = L.gout = L.gpre = L.split = 0;
+    L.z = L.pre = L.raw = L.rec = L.part_c = L.part_b = L.slices = L.dense = L.gout = L.gpre = L.split = 0;
     if (pass == KAN_PASS_BACKWARD) {
         L.z = take(rows * dz * 4);
         L.pre = take(rows * dh * 4);
@@ -108,6 +118,7 @@ Layout make_layout(const ukan_layer_desc *d, int64_t B, int64_t n_g, int n_chunk
         L.part_c = take((size_t)n_chunks * table);
         L.part_b = take((size_t)n_chunks * b_slices * n_in * n_out * 4);
         L.slices = take(reduce_scratch_bytes(d->n_in, (int)(n_g * (int64_t)K), d->n_out));
+        L.dense = take(dense_part_bytes(d, B));
         L.gout = take(table);
         L.gpre = take(rows * dh * 4);
         size_t s1 = (size_t)split_slices((int64_t)rows) * dh * n_o * 4;      // gW2 partials
@@ -376,7 +387,8 @@ int backward_body(const ukan_layer_desc *desc, int64_t B, const float *x, const 
 
     const bool narrow = narrow_applicable(pr.g) != 0;
     const WalkPlan wp = walk_for(desc, B, max_groups);
-    const bool fused_dx = gx && wp.ok;      // dL/dx rides along with the table gradient
+    const DensePlan dp = plan_dense(pr.g, B);
+    const bool fused_dx = gx && (wp.ok || dp.ok);      // dL/dx rides along with the table gradient
     if (gx && !fused_dx) {
         hipError_t e = high_degree(desc) ? highk_table_dx(highk_of(pr.g), x, pr.cf, p->w_b, gy, gx, B, st)
                        : narrow          ? launch_dx_narrow(pr.g, x, pr.cf, p->w_b, gy, gx, B, st)
@@ -394,7 +406,15 @@ int backward_body(const ukan_layer_desc *desc, int64_t B, const float *x, const 
     float *gout = (float *)(w + L.gout);
     int b_slices;
     CarryRows cr = {nullptr, nullptr, 1};
-    if (wp.ok) {
+    int n_chunks = pr.cp.n_chunks;
+    if (dp.ok) {
+        part_c = (float *)(w + L.dense);
+        part_b = part_c + (size_t)dp.n_chunks * desc->n_in * pr.g.rows * desc->n_out;
+        if (launch_backward_dense(pr.g, dp, x, gy, pr.cf, nullptr, p->w_b, want_params ? part_c : nullptr,
+                                  want_b ? part_b : nullptr, gx, B, st) != hipSuccess)
+            return KAN_ERR_HIP;
+        n_chunks = b_slices = dp.n_chunks;
+    } else if (wp.ok) {
         if (launch_backward_walk(pr.g, wp, x, gy, pr.cf, p->w_b, w + L.rec, fused_dx ? gx : nullptr,
                                  want_params ? part_c : nullptr, want_b ? part_b : nullptr, B, &cr, st) != hipSuccess)
             return KAN_ERR_HIP;
@@ -410,7 +430,7 @@ int backward_body(const ukan_layer_desc *desc, int64_t B, const float *x, const 
     }
     if (!want_params) return KAN_OK;
     if (launch_dparam_reduce(part_c, want_b ? part_b : nullptr, cr, pr.raw, p->scale, cg_grads ? gout : nullptr, g->gscale,
-                             g->gw_b, desc->n_in, pr.g.rows, desc->n_out, pr.cp.n_chunks, b_slices, w + L.slices, st) != hipSuccess)
+                             g->gw_b, desc->n_in, pr.g.rows, desc->n_out, n_chunks, b_slices, w + L.slices, st) != hipSuccess)
         return KAN_ERR_HIP;
     if (!cg_grads) return KAN_OK;
 

@@ -70,3 +70,29 @@ def test_ragged_width_on_shared_partial_tables():
 ])
 def test_reduction_over_the_chunks(B, n_in, n_out, G, k):
     run_layer_parity(workloads.random_kan_layer(n_out + 7, B, n_in, n_out, G, k, outside_frac=0.1))
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (1, 2, 1, 1, 1), (255, 3, 5, 12, 3), (257, 2, 16, 12, 3),       # one tile of 16 rows (12 + 3 + the base row) and outputs
+    (1000, 2, 17, 13, 3), (700, 3, 32, 28, 3),                      # just past a tile; the last of two tiles
+    (600, 2, 33, 29, 3), (513, 2, 64, 60, 3), (513, 2, 64, 61, 3),  # four tiles; the first length left to the walk
+    (65536, 16, 5, 9, 2), (65537, 16, 5, 9, 2),                     # sixteen sub-chunks a chunk; the first batch left to the walk
+])
+def test_dense_basis_backward(B, n_in, n_out, G, k):
+    run_layer_parity(workloads.random_kan_layer(n_out + 11, B, n_in, n_out, G, k, outside_frac=0.2))
+
+
+def test_dense_basis_backward_keeps_a_non_finite_gradient_to_its_rows():
+    w = workloads.random_kan_layer(3, 500, 2, 5, 10, 3, outside_frac=0.1)
+    s, p = w.layers[0], w.params[0]
+    x, coef, w_s, w_b, gy = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"], w.gy))
+    bad = gy.clone()
+    bad[300, 2] = float("inf")
+    good, got = (binding.kan_backward(s, x, coef, w_s, w_b, t) for t in (gy, bad))
+    idx = binding.kan_interval_index(s, x)[300].tolist()
+    for i, cell in enumerate(idx):
+        for m in range(s.G + s.k):
+            touched = cell <= m <= cell + s.k
+            assert bool(torch.isfinite(got["gcoef"][i, m, 2])) == (not touched), (i, m, cell)
+    keep = [0, 1, 3, 4]
+    assert torch.allclose(got["gcoef"][:, :, keep], good["gcoef"][:, :, keep], rtol=1e-5, atol=1e-6)
