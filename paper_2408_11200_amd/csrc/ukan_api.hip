@@ -88,7 +88,7 @@ size_t dense_part_bytes(const ukan_layer_desc *d, int64_t B)
 
 // Offsets (bytes) of every scratch region for `n_g` generator rows per input.
 struct Layout {
-    size_t cmin, cmax, g_first, n_groups, cell_base, summary;
+    size_t range, g_first, cell_base, summary;
     size_t hid, cf;                                   // forward
     size_t z, pre, raw, rec, part_c, part_b, slices, dense, gout, gpre, split;   // backward only
     size_t total;
@@ -105,8 +105,8 @@ Layout make_layout(const ukan_layer_desc *d, int64_t B, int64_t n_g, int n_chunk
     Layout L;
     size_t at = 0;
     auto take = [&](size_t bytes) { size_t here = at; at += align_up(bytes); return here; };
-    L.cmin = take(n_in * 4); L.cmax = take(n_in * 4); L.g_first = take(n_in * 4);
-    L.n_groups = take(n_in * 4); L.cell_base = take(n_in * 4); L.summary = take(256);
+    L.range = take(2 * (size_t)range_strips(B) * n_in * 4);
+    L.g_first = take(n_in * 4); L.cell_base = take(n_in * 4); L.summary = take(256);
     L.hid = take(rows * dh * 4);
     L.cf = take(table);
     L.z = L.pre = L.raw = L.rec = L.part_c = L.part_b = L.slices = L.dense = L.gout = L.gpre = L.split = 0;
@@ -121,11 +121,9 @@ Layout make_layout(const ukan_layer_desc *d, int64_t B, int64_t n_g, int n_chunk
         L.dense = take(dense_part_bytes(d, B));
         L.gout = take(table);
         L.gpre = take(rows * dh * 4);
-        size_t s1 = (size_t)split_slices((int64_t)rows) * dh * n_o * 4;      // gW2 partials
-        size_t s2 = (size_t)split_slices((int64_t)rows) * dz * dh * 4;       // gW1 partials
-        size_t s3 = (size_t)colsum_slices((int64_t)rows) * (n_o > dh ? n_o : dh) * 4;
-        size_t s = s1 > s2 ? s1 : s2;
-        L.split = take(s > s3 ? s : s3);
+        size_t s1 = (size_t)split_slices((int64_t)rows) * (dh + 1) * n_o * 4;      // gW2 and gb2 partials
+        size_t s2 = (size_t)split_slices((int64_t)rows) * (dz + 1) * dh * 4;       // gW1 and gb1 partials
+        L.split = take(s1 > s2 ? s1 : s2);
     }
     L.total = at;
     return L;
@@ -182,18 +180,16 @@ int prepare(const ukan_layer_desc *d, int64_t B, const float *x, const ukan_para
     const float inv_h = 1.0f / d->h;
     out->cp = chunks_for(d, B, max_groups);
     Layout L0 = make_layout(d, B, max_groups, out->cp.n_chunks, record_bytes_for(d, B, max_groups), b_slices_for(d, B, max_groups), pass);     // meta offsets do not depend on n_g
-    int32_t *cmin = (int32_t *)(ws + L0.cmin), *cmax = (int32_t *)(ws + L0.cmax);
-    int32_t *n_groups = (int32_t *)(ws + L0.n_groups), *summary = (int32_t *)(ws + L0.summary);
+    int32_t *range = (int32_t *)(ws + L0.range), *summary = (int32_t *)(ws + L0.summary);
     // the saved layout starts with g_first and cell_base at offsets that do not depend on the span
     const SavedLayout S0 = saved_layout(d, max_groups);
     int32_t *g_first = (int32_t *)(saved ? saved + S0.g_first : ws + L0.g_first);
     int32_t *cell_base = (int32_t *)(saved ? saved + S0.cell_base : ws + L0.cell_base);
-    if (launch_range(x, B, d->n_in, inv_h, K, cmin, cmax, g_first, n_groups, cell_base, summary, st) != hipSuccess)
+    if (launch_range(x, B, d->n_in, inv_h, K, range, g_first, cell_base, summary, provided_span,
+                     provided_span > 0 ? overflow : nullptr, st) != hipSuccess)
         return KAN_ERR_HIP;
     int32_t span = provided_span;
-    if (provided_span > 0) {
-        if (launch_span_check(summary, provided_span, overflow, st) != hipSuccess) return KAN_ERR_HIP;
-    } else {
+    if (provided_span <= 0) {
         if (hipMemcpyAsync(&span, summary, sizeof(span), hipMemcpyDeviceToHost, st) != hipSuccess) return KAN_ERR_HIP;
         if (hipStreamSynchronize(st) != hipSuccess) return KAN_ERR_HIP;
     }
@@ -441,16 +437,15 @@ int backward_body(const ukan_layer_desc *desc, int64_t B, const float *x, const 
     int64_t k_slice = (rows + slices - 1) / slices;
     k_slice = (k_slice + 15) / 16 * 16;
 
-    if (g->gb2 && launch_colsum(gout, split, g->gb2, rows, (int)n_o, st) != hipSuccess) return KAN_ERR_HIP;
-    if (g->gW2) {       // gW2[c][o] = sum_rows hid[row][c] * gout[row][o]
+    if (g->gW2 || g->gb2) {       // gW2[c][o] = sum_rows hid[row][c] * gout[row][o], gb2[o] = sum_rows gout[row][o]
         GemmArgs a = {};
         a.A = hid; a.a_rs = 1; a.a_cs = dh;
         a.B = gout; a.b_rs = n_o; a.b_cs = 1;
         a.C = split; a.ldc = n_o; a.M = dh; a.N = n_o; a.K = rows;
-        a.k_slice = k_slice; a.c_slice = (int64_t)dh * n_o;
+        a.k_slice = k_slice; a.c_slice = (int64_t)(dh + 1) * n_o; a.colsum = 1;
         const int used = (int)((rows + k_slice - 1) / k_slice);
         if (launch_gemm(a, EPI_PLAIN, used, "cg_gW2_gemm", st) != hipSuccess) return KAN_ERR_HIP;
-        if (launch_slice_sum(split, g->gW2, (int64_t)dh * n_o, used, st) != hipSuccess) return KAN_ERR_HIP;
+        if (launch_slice_sum(split, g->gW2, (int64_t)dh * n_o, g->gb2, n_o, used, st) != hipSuccess) return KAN_ERR_HIP;
     }
     if (g->gE || g->gW1 || g->gb1) {
         GemmArgs a = {};    // gpre[row][c] = (sum_o gout[row][o] * W2[c][o]) * silu'(pre[row][c])
@@ -460,16 +455,15 @@ int backward_body(const ukan_layer_desc *desc, int64_t B, const float *x, const 
         a.k_slice = n_o; a.c_slice = 0;
         a.aux = pr.pre;
         if (launch_gemm(a, EPI_SILU_GRAD, 1, "cg_ghid_gemm", st) != hipSuccess) return KAN_ERR_HIP;
-        if (g->gb1 && launch_colsum(gpre, split, g->gb1, rows, dh, st) != hipSuccess) return KAN_ERR_HIP;
-        if (g->gW1) {   // gW1[p][c] = sum_rows z[row][p] * gpre[row][c]
+        if (g->gW1 || g->gb1) {   // gW1[p][c] = sum_rows z[row][p] * gpre[row][c], gb1[c] = sum_rows gpre[row][c]
             GemmArgs b = {};
             b.A = pr.z; b.a_rs = 1; b.a_cs = dz;
             b.B = gpre; b.b_rs = dh; b.b_cs = 1;
             b.C = split; b.ldc = dh; b.M = dz; b.N = dh; b.K = rows;
-            b.k_slice = k_slice; b.c_slice = (int64_t)dz * dh;
+            b.k_slice = k_slice; b.c_slice = (int64_t)(dz + 1) * dh; b.colsum = 1;
             const int used = (int)((rows + k_slice - 1) / k_slice);
             if (launch_gemm(b, EPI_PLAIN, used, "cg_gW1_gemm", st) != hipSuccess) return KAN_ERR_HIP;
-            if (launch_slice_sum(split, g->gW1, (int64_t)dz * dh, used, st) != hipSuccess) return KAN_ERR_HIP;
+            if (launch_slice_sum(split, g->gW1, (int64_t)dz * dh, g->gb1, dh, used, st) != hipSuccess) return KAN_ERR_HIP;
         }
         if (g->gE && desc->d_feat > 0 &&
             launch_embed_grad(p->W1, gpre, g->gE, desc->n_in, pr.n_g, desc->d_feat, dh, st) != hipSuccess)

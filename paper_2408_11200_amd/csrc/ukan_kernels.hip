@@ -30,113 +30,192 @@ __global__ void group_index_kernel(const float *__restrict__ x, int32_t *__restr
 }
 
 // ---- per-input range of cells -------------------------------------------------
-__global__ void range_init_kernel(int32_t *__restrict__ cmin, int32_t *__restrict__ cmax, int n_in)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_in) { cmin[i] = INT_MAX; cmax[i] = INT_MIN; }
-}
+// Two kernels: strips of the batch write their partial minima and maxima, one workgroup combines them.  (Atomics on one
+// pair per input needed a third kernel to set them up and kept a thread to one column: 28 -> 18 us at 33 MB, 256 inputs.)
+constexpr int kRangeThreads = 1024;
 
-// lanes <-> inputs (coalesced rows of x); blockIdx.y strides over the batch.  Integer
-// min/max atomics: order-independent, so the result is deterministic.
-__global__ __launch_bounds__(256) void range_kernel(const float *__restrict__ x, int32_t *__restrict__ cmin,
-                                                    int32_t *__restrict__ cmax, int64_t B, int n_in, float inv_h)
+// grid (strips, input tiles).  LR lanes x V inputs cover a tile of a row, the other threads take other rows of the strip.
+template <int V>
+__global__ __launch_bounds__(kRangeThreads) void range_kernel(const float *__restrict__ x, int32_t *__restrict__ part,
+                                                              int64_t B, int n_in, float inv_h, int LR, int64_t strip)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_in) return;
-    int lo = INT_MAX, hi = INT_MIN;
-    int64_t b = blockIdx.y;
-    // four rows in flight per thread (the scan is bound by load latency otherwise)
-    for (; b + 3 * (int64_t)gridDim.y < B; b += 4 * (int64_t)gridDim.y) {
-        float v[4];
+    __shared__ int lo_s[kRangeThreads * V], hi_s[kRangeThreads * V];
+    const int tid = threadIdx.x, col = tid % LR, rg = tid / LR, RP = kRangeThreads / LR;
+    const int i = ((int)blockIdx.y * LR + col) * V;
+    const int64_t b1 = ((int64_t)blockIdx.x + 1) * strip < B ? ((int64_t)blockIdx.x + 1) * strip : B;
+    int lo[V], hi[V];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = x[(b + u * (int64_t)gridDim.y) * n_in + i];
+    for (int v = 0; v < V; ++v) { lo[v] = INT_MAX; hi[v] = INT_MIN; }
+    if (i < n_in) {                                  // V divides n_in
+        auto take = [&](const float (&q)[V]) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            float t, d;
-            const int c = interval_index(v[u], 0.0f, inv_h, &t, &d);
-            lo = c < lo ? c : lo;
-            hi = c > hi ? c : hi;
+            for (int v = 0; v < V; ++v) {
+                float t, d;
+                const int c = interval_index(q[v], 0.0f, inv_h, &t, &d);
+                lo[v] = c < lo[v] ? c : lo[v];
+                hi[v] = c > hi[v] ? c : hi[v];
+            }
+        };
+        auto load = [&](int64_t b, float (&q)[V]) {
+            if constexpr (V == 4) {
+                const float4 t = *reinterpret_cast<const float4 *>(x + b * n_in + i);
+                q[0] = t.x; q[1] = t.y; q[2] = t.z; q[3] = t.w;
+            } else {
+                q[0] = x[b * n_in + i];
+            }
+        };
+        int64_t b = (int64_t)blockIdx.x * strip + rg;
+        for (; b + 3 * RP < b1; b += 4 * RP) {       // four rows in flight
+            float q[4][V];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) load(b + u * RP, q[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) take(q[u]);
+        }
+        for (; b < b1; b += RP) {
+            float q[V];
+            load(b, q);
+            take(q);
         }
     }
-    for (; b < B; b += gridDim.y) {
-        float t, d;
-        int c = interval_index(x[b * n_in + i], 0.0f, inv_h, &t, &d);
-        lo = c < lo ? c : lo;
-        hi = c > hi ? c : hi;
-    }
-    if (lo <= hi) { atomicMin(&cmin[i], lo); atomicMax(&cmax[i], hi); }
-}
-
-// cells -> first group held, group count, relative-cell base; the widest span goes to summary[0]
-__global__ __launch_bounds__(256) void range_finalize_kernel(const int32_t *__restrict__ cmin,
-                                                             const int32_t *__restrict__ cmax,
-                                                             int32_t *__restrict__ g_first,
-                                                             int32_t *__restrict__ n_groups,
-                                                             int32_t *__restrict__ cell_base,
-                                                             int32_t *__restrict__ summary, int n_in, int K)
-{
-    __shared__ long long widest[256];
-    long long w = 0;
-    for (int i = threadIdx.x; i < n_in; i += blockDim.x) {
-        int gmin = floordiv(cmin[i], K), gmax = floordiv(cmax[i], K);
-        long long n = (long long)gmax - (long long)gmin + 2;      // groups gmin-1 .. gmax
-        g_first[i] = gmin - 1;
-        n_groups[i] = n > INT_MAX ? INT_MAX : (int)n;
-        cell_base[i] = gmin * K;        // cell c reads table rows c - gmin*K .. + K-1
-        w = n > w ? n : w;
-    }
-    widest[threadIdx.x] = w;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s && widest[threadIdx.x + s] > widest[threadIdx.x]) widest[threadIdx.x] = widest[threadIdx.x + s];
+    // rows of the workgroup, halving; columns stay
+#pragma unroll
+    for (int v = 0; v < V; ++v) { lo_s[tid * V + v] = lo[v]; hi_s[tid * V + v] = hi[v]; }
+    for (int s = RP / 2; s > 0; s >>= 1) {
         __syncthreads();
+        if (rg < s) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const int o = (tid + s * LR) * V + v, m = tid * V + v;
+                if (lo_s[o] < lo_s[m]) lo_s[m] = lo_s[o];
+                if (hi_s[o] > hi_s[m]) hi_s[m] = hi_s[o];
+            }
+        }
     }
-    if (threadIdx.x == 0) summary[0] = widest[0] > INT_MAX ? INT_MAX : (int)widest[0];
+    if (rg == 0 && i < n_in) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            part[((int64_t)blockIdx.x * 2) * n_in + i + v] = lo_s[tid * V + v];
+            part[((int64_t)blockIdx.x * 2 + 1) * n_in + i + v] = hi_s[tid * V + v];
+        }
+    }
 }
 
-// overflow[0] = 1 when the widest span found exceeds what the caller provided for, else 0
-__global__ void span_check_kernel(const int32_t *__restrict__ summary, int provided, int32_t *__restrict__ overflow)
+// partial ranges -> first group held, relative-cell base; the widest span goes to summary[0].  overflow (may be null)
+// receives 1 when the widest span exceeds `provided`, else 0.  One workgroup: LC lanes take the inputs of a tile, the
+// other threads other strips of them.
+__global__ __launch_bounds__(kRangeThreads) void range_finalize_kernel(const int32_t *__restrict__ part, int strips,
+                                                                       int32_t *__restrict__ g_first,
+                                                                       int32_t *__restrict__ cell_base,
+                                                                       int32_t *__restrict__ summary, int n_in, int K,
+                                                                       int LC, int provided, int32_t *__restrict__ overflow)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) overflow[0] = summary[0] > provided ? 1 : 0;
+    __shared__ int lo_s[kRangeThreads], hi_s[kRangeThreads];
+    const int tid = threadIdx.x, col = tid % LC, sg = tid / LC, SG = kRangeThreads / LC;
+    int widest = 0;
+    for (int i0 = 0; i0 < n_in; i0 += LC) {
+        const int i = i0 + col;
+        int lo = INT_MAX, hi = INT_MIN;
+        if (i < n_in)
+#pragma unroll 8
+            for (int s = sg; s < strips; s += SG) {
+                const int a = part[(int64_t)s * 2 * n_in + i], b = part[((int64_t)s * 2 + 1) * n_in + i];
+                lo = a < lo ? a : lo;
+                hi = b > hi ? b : hi;
+            }
+        __syncthreads();
+        lo_s[tid] = lo; hi_s[tid] = hi;
+        for (int s = SG / 2; s > 0; s >>= 1) {
+            __syncthreads();
+            if (sg < s) {
+                const int o = tid + s * LC;
+                if (lo_s[o] < lo_s[tid]) lo_s[tid] = lo_s[o];
+                if (hi_s[o] > hi_s[tid]) hi_s[tid] = hi_s[o];
+            }
+        }
+        if (sg == 0 && i < n_in) {
+            const int gmin = floordiv(lo_s[tid], K), gmax = floordiv(hi_s[tid], K);
+            const long long n = (long long)gmax - (long long)gmin + 2;      // groups gmin-1 .. gmax
+            const int n32 = n > INT_MAX ? INT_MAX : (int)n;
+            g_first[i] = gmin - 1;
+            cell_base[i] = gmin * K;        // cell c reads table rows c - gmin*K .. + K-1
+            widest = n32 > widest ? n32 : widest;
+        }
+    }
+    __syncthreads();
+    lo_s[tid] = widest;
+    for (int s = kRangeThreads / 2; s > 0; s >>= 1) {
+        __syncthreads();
+        if (tid < s && lo_s[tid + s] > lo_s[tid]) lo_s[tid] = lo_s[tid + s];
+    }
+    if (tid == 0) {
+        summary[0] = lo_s[0];
+        if (overflow) overflow[0] = lo_s[0] > provided ? 1 : 0;
+    }
 }
 
 // ---- CG input and hidden layer -------------------------------------------------
-// Row (i, t) of the generator batch is group g_first[i] + t of input i.  One block per
-// row: z = [E[i] ; PE(g)] (PE evaluated in fp64, rounded to fp32),
-// pre = W1^T z + b1, hid = silu(pre).
-__global__ __launch_bounds__(64) void cg_hidden_kernel(const float *__restrict__ E, const float *__restrict__ W1,
-                                                       const float *__restrict__ b1,
-                                                       const int32_t *__restrict__ g_first, float *__restrict__ z,
-                                                       float *__restrict__ pre, float *__restrict__ hid, int n_g,
-                                                       int d_pe, int d_feat, int d_hid)
+// Row (i, t) of the generator batch is group g_first[i] + t of input i: z = [E[i] ; PE(g)] (PE evaluated in fp64, rounded
+// to fp32), pre = W1^T z + b1, hid = silu(pre).  A workgroup takes kHidRows consecutive rows, four threads a hidden unit
+// and kHidRows / 4 rows a thread, with the z rows and W1 in LDS: a row a workgroup re-read W1 (16 KB at 64 x 64) per row
+// and evaluated the frequencies anew.  What is left is mostly the sines in fp64 (48 000 rows in three launches: 84 -> 66 us).
+constexpr int kHidRows = 16;
+template <bool W1_LDS>
+__global__ __launch_bounds__(256) void cg_hidden_kernel(const float *__restrict__ E, const float *__restrict__ W1,
+                                                        const float *__restrict__ b1,
+                                                        const int32_t *__restrict__ g_first, float *__restrict__ z,
+                                                        float *__restrict__ pre, float *__restrict__ hid, int64_t rows,
+                                                        int n_g, int d_pe, int d_feat, int d_hid, int per_block)
 {
-    extern __shared__ float zs[];
-    const int row = blockIdx.x;
-    const int i = row / n_g, t = row % n_g;
-    const int dz = d_feat + d_pe;
-    const int g = g_first[i] + t;
-    for (int c = threadIdx.x; c < dz; c += blockDim.x) {
-        float v;
-        if (c < d_feat) {
-            v = E[(int64_t)i * d_feat + c];
-        } else {
-            int q = c - d_feat;
-            double freq = pow(10000.0, -2.0 * (double)(q / 2) / (double)d_pe);
-            double ang = (double)g * freq;
-            v = (float)((q & 1) ? cos(ang) : sin(ang));
-        }
-        zs[c] = v;
-        if (z) z[(int64_t)row * dz + c] = v;
+    extern __shared__ double freq[];                // d_pe / 2 frequencies, per_block x dz, W1
+    const int dz = d_feat + d_pe, tid = threadIdx.x;
+    float *zs = reinterpret_cast<float *>(freq + d_pe / 2), *w1 = zs + per_block * dz;
+    const int64_t row0 = (int64_t)blockIdx.x * per_block;
+    const int n = rows - row0 < per_block ? (int)(rows - row0) : per_block;
+    // d_pe / 2 frequencies, once a workgroup
+    const int half = d_pe / 2;
+    for (int q = tid; q < half; q += 256) freq[q] = pow(10000.0, -2.0 * (double)q / (double)d_pe);
+    for (int e = tid; e < n * d_feat; e += 256) {
+        const int r = e / d_feat, c = e - r * d_feat;
+        const float v = E[((row0 + r) / n_g) * d_feat + c];
+        zs[r * dz + c] = v;
+        if (z) z[(row0 + r) * dz + c] = v;
     }
     __syncthreads();
-    for (int c = threadIdx.x; c < d_hid; c += blockDim.x) {
+    for (int e = tid; e < n * half; e += 256) {
+        const int r = e / half, q = e - r * half;
+        const int64_t row = row0 + r;
+        const int i = (int)(row / n_g), t = (int)(row - (int64_t)i * n_g);
+        double sn, cs;
+        sincos((double)(g_first[i] + t) * freq[q], &sn, &cs);
+        const int c = d_feat + 2 * q;
+        zs[r * dz + c] = (float)sn;
+        zs[r * dz + c + 1] = (float)cs;
+        if (z) { z[row * dz + c] = (float)sn; z[row * dz + c + 1] = (float)cs; }
+    }
+    if (W1_LDS)
+        for (int e = tid; e < dz * d_hid; e += 256) w1[e] = W1[e];
+    __syncthreads();
+    constexpr int PER = kHidRows / 4;
+    for (int c = tid & 63; c < d_hid; c += 64) {
+        const int r0 = (tid >> 6) * PER;
         // fp64 accumulation: this layer is tiny and its rounding error would otherwise be
         // amplified into every generated coefficient
-        double sd = (double)b1[c];
-        for (int p = 0; p < dz; ++p) sd += (double)zs[p] * (double)W1[(int64_t)p * d_hid + c];
-        const float s = (float)sd;
-        if (pre) pre[(int64_t)row * d_hid + c] = s;
-        hid[(int64_t)row * d_hid + c] = (float)(sd / (1.0 + exp(-sd)));
+        double sd[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) sd[u] = (double)b1[c];
+        for (int p = 0; p < dz; ++p) {
+            const double w = (double)(W1_LDS ? w1[p * d_hid + c] : W1[(int64_t)p * d_hid + c]);
+#pragma unroll
+            for (int u = 0; u < PER; ++u) sd[u] += (double)zs[(r0 + u < n ? r0 + u : n - 1) * dz + p] * w;
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            if (r0 + u >= n) continue;
+            const int64_t at = (row0 + r0 + u) * d_hid + c;
+            if (pre) pre[at] = (float)sd[u];
+            hid[at] = (float)(sd[u] / (1.0 + exp(-sd[u])));
+        }
     }
 }
 
@@ -228,6 +307,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a)
         }
     };
 
+    // column sums of B (bias gradients) ride along in the first row of workgroups: thread -> (column, quarter of the K step)
+    const bool sums = ACC64 && EPI == EPI_PLAIN && a.colsum && blockIdx.y == 0;
+    double csum = 0.0;
     int step = 0, buf = 0;
     if (k_lo < k_hi) {
         fetch(k_lo);
@@ -241,6 +323,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a)
         }
         const bool more = k0 + BK < k_hi;
         if (more) fetch(k0 + BK);
+        if (sums) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) csum += (double)Bs[buf][wave * 4 + u][lane];
+        }
         if constexpr (ACC64) {
 #pragma unroll
             for (int kk = 0; kk < BK; kk += 4) {
@@ -266,6 +352,15 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a)
     }
 
     float *C = a.C + (int64_t)blockIdx.z * a.c_slice;
+    if constexpr (ACC64 && EPI == EPI_PLAIN) {
+        if (a.colsum) {                            // row M of the slice
+            __shared__ double cs[4][64];
+            cs[wave][lane] = csum;
+            __syncthreads();
+            if (sums && wave == 0 && n0 + lane < a.N)
+                C[a.M * a.ldc + n0 + lane] = (float)(((cs[0][lane] + cs[1][lane]) + cs[2][lane]) + cs[3][lane]);
+        }
+    }
     if constexpr (ACC64) {
         // 16x16 block: register v of lane l is element (4*v + l/16, l%16)
 #pragma unroll
@@ -285,54 +380,53 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a)
     }
 }
 
-// out[n] (or out[m][n] summed over z slices) helpers ---------------------------------
-// column sums of a [rows x cols] matrix in row slices: part[z][n] = sum of column n over the rows of
-// slice z (rows visited in order); slice_sum_kernel then adds the slices.
-__global__ __launch_bounds__(256) void colsum_kernel(const float *__restrict__ A, float *__restrict__ part,
-                                                     int64_t rows, int cols, int64_t rows_per_slice)
+// sum of split-K slices: element e of the result is sum_z part[z][e]; the first n of them are out (may be null), the
+// n2 after those out2 (may be null).  Eight slices in flight, added in order.
+__global__ __launch_bounds__(256) void slice_sum_kernel(const float *__restrict__ part, float *__restrict__ out,
+                                                        int64_t n, float *__restrict__ out2, int64_t n2, int slices)
 {
-    int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= cols) return;
-    int64_t lo = (int64_t)blockIdx.y * rows_per_slice;
-    int64_t hi = lo + rows_per_slice < rows ? lo + rows_per_slice : rows;
-    // eight rows in flight; the eight running sums are combined in a fixed order
-    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int64_t m = lo;
-    for (; m + 8 <= hi; m += 8) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, total = n + n2;
+    if (e >= total) return;
+    float *dst = e < n ? (out ? out + e : nullptr) : (out2 ? out2 + (e - n) : nullptr);
+    if (!dst) return;
+    double s = 0.0;
+    int z = 0;
+    for (; z + 8 <= slices; z += 8) {
         float v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = A[(m + u) * cols + n];
+        for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(z + u) * total + e];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s[u] += v[u];
+        for (int u = 0; u < 8; ++u) s += (double)v[u];
     }
-    for (; m < hi; ++m) s[0] += A[m * cols + n];
-    part[(int64_t)blockIdx.y * cols + n] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+    for (; z < slices; ++z) s += (double)part[(int64_t)z * total + e];
+    *dst = (float)s;
 }
 
-// sum of split-K slices: out[e] = sum_z part[z][e]
-__global__ __launch_bounds__(256) void slice_sum_kernel(const float *__restrict__ part, float *__restrict__ out,
-                                                        int64_t n, int slices)
-{
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n) return;
-    double s = 0.0;
-    for (int z = 0; z < slices; ++z) s += (double)part[(int64_t)z * n + e];
-    out[e] = (float)s;
-}
-
-// gE[i][f] = sum_c W1[f][c] * S[i][c],  S[i][c] = sum_t gpre[(i,t)][c].  One block per input: the
-// column sums S (fp64, rows in order) go through LDS, then one thread per embedding feature.
+// gE[i][f] = sum_c W1[f][c] * S[i][c],  S[i][c] = sum_t gpre[(i,t)][c].  One block per input: its four waves share the
+// rows of the column sums S (fp64, the shares added in wave order), then one thread per embedding feature.
 __global__ __launch_bounds__(256) void embed_grad_kernel(const float *__restrict__ W1, const float *__restrict__ gpre,
                                                          float *__restrict__ gE, int n_in, int n_g, int d_feat,
                                                          int d_hid)
 {
-    extern __shared__ double colsum[];          // [d_hid]
-    const int i = blockIdx.x;
-    for (int c = threadIdx.x; c < d_hid; c += blockDim.x) {
+    extern __shared__ double colsum[];          // [4][d_hid]
+    const int i = blockIdx.x, wave = threadIdx.x >> 6;
+    const float *src = gpre + (int64_t)i * n_g * d_hid;
+    for (int c = threadIdx.x & 63; c < d_hid; c += 64) {
         double s = 0.0;
-        for (int t = 0; t < n_g; ++t) s += (double)gpre[((int64_t)i * n_g + t) * d_hid + c];
-        colsum[c] = s;
+        int t = wave;
+        for (; t + 28 < n_g; t += 32) {         // eight rows in flight
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(t + 4 * u) * d_hid + c];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += (double)v[u];
+        }
+        for (; t < n_g; t += 4) s += (double)src[(int64_t)t * d_hid + c];
+        colsum[wave * d_hid + c] = s;
     }
+    __syncthreads();
+    for (int c = threadIdx.x; c < d_hid; c += blockDim.x)
+        colsum[c] = ((colsum[c] + colsum[d_hid + c]) + colsum[2 * d_hid + c]) + colsum[3 * d_hid + c];
     __syncthreads();
     for (int f = threadIdx.x; f < d_feat; f += blockDim.x) {
         double s = 0.0;
@@ -376,8 +470,6 @@ hipError_t launch_table_rows(const float *table, float *coef, int n_in, int tabl
     return hipGetLastError();
 }
 
-hipError_t launch_slice_sum(const float *part, float *out, int64_t n, int slices, hipStream_t st);
-
 hipError_t launch_group_index(const float *x, int32_t *cell, int32_t *grp, int32_t *off, int64_t n, float inv_h,
                               int K, hipStream_t st)
 {
@@ -387,23 +479,21 @@ hipError_t launch_group_index(const float *x, int32_t *cell, int32_t *grp, int32
     return hipGetLastError();
 }
 
-hipError_t launch_range(const float *x, int64_t B, int n_in, float inv_h, int K, int32_t *cmin, int32_t *cmax,
-                        int32_t *g_first, int32_t *n_groups, int32_t *cell_base, int32_t *summary, hipStream_t st)
+hipError_t launch_range(const float *x, int64_t B, int n_in, float inv_h, int K, int32_t *part, int32_t *g_first,
+                        int32_t *cell_base, int32_t *summary, int32_t provided, int32_t *overflow, hipStream_t st)
 {
-    {
-        prof::Timed tm("ukan_range", st);
-        range_init_kernel<<<(n_in + 255) / 256, 256, 0, st>>>(cmin, cmax, n_in);
-        int64_t strips = (B + 63) / 64;
-        dim3 grid((unsigned)((n_in + 255) / 256), (unsigned)(strips < 1024 ? (strips < 1 ? 1 : strips) : 1024));
-        range_kernel<<<grid, 256, 0, st>>>(x, cmin, cmax, B, n_in, inv_h);
-        range_finalize_kernel<<<1, 256, 0, st>>>(cmin, cmax, g_first, n_groups, cell_base, summary, n_in, K);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_span_check(const int32_t *summary, int provided, int32_t *overflow, hipStream_t st)
-{
-    span_check_kernel<<<1, 64, 0, st>>>(summary, provided, overflow);
+    const int V = n_in % 4 == 0 ? 4 : 1;
+    int LR = 1;
+    while (LR < 64 && LR * V < n_in) LR *= 2;
+    const int strips = range_strips(B);
+    const int64_t strip = (B + strips - 1) / strips;
+    const dim3 grid((unsigned)strips, (unsigned)((n_in + LR * V - 1) / (LR * V)));
+    prof::Timed tm("ukan_range", st);
+    if (V == 4) range_kernel<4><<<grid, kRangeThreads, 0, st>>>(x, part, B, n_in, inv_h, LR, strip);
+    else range_kernel<1><<<grid, kRangeThreads, 0, st>>>(x, part, B, n_in, inv_h, LR, strip);
+    int LC = 1;
+    while (LC < 256 && LC < n_in) LC *= 2;
+    range_finalize_kernel<<<1, kRangeThreads, 0, st>>>(part, strips, g_first, cell_base, summary, n_in, K, LC, provided, overflow);
     return hipGetLastError();
 }
 
@@ -412,9 +502,24 @@ hipError_t launch_cg_hidden(const float *E, const float *W1, const float *b1, co
                             hipStream_t st)
 {
     prof::Timed tm("cg_hidden", st);
-    size_t lds = (size_t)(d_feat + d_pe) * sizeof(float);
-    cg_hidden_kernel<<<(unsigned)(n_in * n_g), 64, lds, st>>>(E, W1, b1, g_first, z, pre, hid, n_g, d_pe, d_feat,
-                                                             d_hid);
+    const int64_t rows = (int64_t)n_in * n_g;
+    const size_t dz = (size_t)d_feat + d_pe, f_bytes = d_pe / 2 * sizeof(double), w_bytes = dz * d_hid * sizeof(float);
+    const size_t all = f_bytes + kHidRows * dz * sizeof(float) + w_bytes;
+    if (all <= 64 * 1024) {              // what every kernel may ask for
+        cg_hidden_kernel<true><<<(unsigned)((rows + kHidRows - 1) / kHidRows), 256, all, st>>>(E, W1, b1, g_first, z, pre, hid,
+                                                                                            rows, n_g, d_pe, d_feat, d_hid,
+                                                                                            kHidRows);
+    } else {
+        // wide generators: W1 from L2, and one row a workgroup when sixteen do not fit either
+        const int per = f_bytes + kHidRows * dz * sizeof(float) <= 64 * 1024 ? kHidRows : 1;
+        const size_t lds = f_bytes + per * dz * sizeof(float);
+        struct Tag;
+        auto kern = cg_hidden_kernel<false>;
+        if (lds > 64 * 1024)
+            if (hipError_t e = ensure_dynamic_lds<Tag>(reinterpret_cast<const void *>(kern), (int)lds); e != hipSuccess) return e;
+        kern<<<(unsigned)((rows + per - 1) / per), 256, lds, st>>>(E, W1, b1, g_first, z, pre, hid, rows, n_g, d_pe, d_feat, d_hid,
+                                                                  per);
+    }
     return hipGetLastError();
 }
 
@@ -431,23 +536,10 @@ hipError_t launch_gemm(const GemmArgs &a, int epi, int slices, const char *famil
     return hipGetLastError();
 }
 
-hipError_t launch_colsum(const float *A, float *part, float *out, int64_t rows, int cols, hipStream_t st)
-{
-    const int slices = colsum_slices(rows);
-    const int64_t per = (rows + slices - 1) / slices;
-    {
-        prof::Timed tm("cg_colsum", st);
-        colsum_kernel<<<dim3((cols + 255) / 256, slices), 256, 0, st>>>(A, part, rows, cols, per);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_slice_sum(part, out, cols, slices, st);
-}
-
-hipError_t launch_slice_sum(const float *part, float *out, int64_t n, int slices, hipStream_t st)
+hipError_t launch_slice_sum(const float *part, float *out, int64_t n, float *out2, int64_t n2, int slices, hipStream_t st)
 {
     prof::Timed tm("cg_slice_sum", st);
-    slice_sum_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(part, out, n, slices);
+    slice_sum_kernel<<<(unsigned)((n + n2 + 255) / 256), 256, 0, st>>>(part, out, n, out2, n2, slices);
     return hipGetLastError();
 }
 
@@ -455,7 +547,7 @@ hipError_t launch_embed_grad(const float *W1, const float *gpre, float *gE, int 
                              int d_hid, hipStream_t st)
 {
     prof::Timed tm("cg_embed_grad", st);
-    embed_grad_kernel<<<n_in, 256, (size_t)d_hid * sizeof(double), st>>>(W1, gpre, gE, n_in, n_g, d_feat, d_hid);
+    embed_grad_kernel<<<n_in, 256, 4 * (size_t)d_hid * sizeof(double), st>>>(W1, gpre, gE, n_in, n_g, d_feat, d_hid);
     return hipGetLastError();
 }
 

@@ -1,9 +1,11 @@
 """Edge sizes of the kernels' tiles, remainders and dispatch lines, against the CPU oracle (bars as in test_gpu_kan)."""
+import numpy as np
 import pytest
 import torch
 
 from paper_2408_11200_amd import binding, workloads
 from test_gpu_kan import dev, run_layer_parity
+from test_gpu_ukan import make as ukan_make, run as ukan_run
 
 pytestmark = pytest.mark.gpu
 
@@ -96,3 +98,29 @@ def test_dense_basis_backward_keeps_a_non_finite_gradient_to_its_rows():
             assert bool(torch.isfinite(got["gcoef"][i, m, 2])) == (not touched), (i, m, cell)
     keep = [0, 1, 3, 4]
     assert torch.allclose(got["gcoef"][:, :, keep], good["gcoef"][:, :, keep], rtol=1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("B,n_in,n_out,kw", [
+    (257, 260, 2, dict()),                                   # four inputs a lane, two input tiles, a second strip of one row
+    (300, 259, 3, dict()),                                   # one input a lane, five tiles
+    (40000, 3, 1, dict(xs=1.0)),                             # every strip of the range scan
+    (60, 2, 3, dict(d_pe=34, d_feat=31, d_hid=65)),          # rows and columns past the tiles of the generator kernels
+    (40, 2, 2, dict(d_pe=130, d_feat=130, d_hid=70)),        # first generator weights too large for LDS
+    (20, 1, 2, dict(d_pe=800, d_feat=400, d_hid=5)),         # one generator row a workgroup
+    (2000, 4, 20, dict(base_act=1, xs=1.0)),                 # dense-basis backward on a generated table
+    (5000, 3, 40, dict(k=4, xs=1.0)),
+])
+def test_ukan_generator_and_range_edges(B, n_in, n_out, kw):
+    spec, p, x, gy = ukan_make(B + n_in, B, n_in, n_out, **kw)
+    ukan_run(spec, p, x, np.float32(gy / np.sqrt(B)))
+
+
+@pytest.mark.parametrize("want", [("gb2",), ("gW2",), ("gb1",), ("gW1", "gE")])
+def test_ukan_bias_gradients_alone(want):
+    spec, p, x, gy = ukan_make(5, 400, 3, 33)
+    pd = {n: dev(a) for n, a in p.items()}
+    every = binding.ukan_cg_backward(spec, dev(x), pd, dev(gy), 64)
+    some = binding.ukan_cg_backward(spec, dev(x), pd, dev(gy), 64, want=want)
+    assert set(some) == set(want)
+    for n in want:
+        assert torch.equal(some[n], every[n]), n
