@@ -178,6 +178,15 @@ __device__ __forceinline__ void store4u(float *p, float4 v)
 }
 __device__ __forceinline__ void store2u(float *p, float2 v) { *reinterpret_cast<Float2U *>(p) = Float2U{v.x, v.y}; }
 
+// First row of a pair's window alone (window_of's row0, without the weights).  Needs rows >= kMaxK.
+__device__ __forceinline__ int window_row(float x, const SplineGeom &g, int i)
+{
+    float t, d;
+    const long long rel = (long long)interval_index(x, g.lo, g.inv_h, &t, &d) - (g.cell_base ? (long long)g.cell_base[i] : 0ll);
+    const int hi = g.rows - kMaxK;
+    return rel < 0 ? 0 : (rel > hi ? hi : (int)rel);
+}
+
 // value of lane `src` (wave-uniform index) as a scalar
 __device__ __forceinline__ float lane_f(float v, int src)
 {

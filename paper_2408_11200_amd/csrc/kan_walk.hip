@@ -36,6 +36,7 @@
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
 #include "kan_highk.hpp"
+#include "kan_sort.hpp"
 
 namespace kan {
 
@@ -59,10 +60,7 @@ __global__ __launch_bounds__(256) void transpose_kernel(const float *__restrict_
 // ---- 2. sort + records ---------------------------------------------------------------------
 // grid (n_chunks, n_in), NW waves.  key = window row << sbits | sample index in the chunk
 // (sbits = log2 S): keys are distinct, and sorting them by the row digits with a stable counting
-// sort keeps samples of equal row in batch order, which fixes the summation order downstream.
-// Each wave owns a contiguous share of the sequence; digit counts are taken per wave, the
-// (digit, wave) prefix gives every wave its first slot per digit, and the wave then places its
-// keys batch by batch (rank inside a batch from ballots), so nothing depends on timing.
+// sort keeps samples of equal row in batch order, which fixes the summation order downstream (kan_sort.hpp).
 // Entries past the end of the batch get the largest row and end up behind every real record.
 template <int NW>
 __global__ __launch_bounds__(64 * NW) void cell_sort_kernel(SplineGeom g, const float *__restrict__ xT, int64_t B,
@@ -72,7 +70,7 @@ __global__ __launch_bounds__(64 * NW) void cell_sort_kernel(SplineGeom g, const 
     extern __shared__ unsigned lds_u[];
     unsigned *src = lds_u, *dst = lds_u + S;
     float *xs = reinterpret_cast<float *>(lds_u + 2 * S);
-    __shared__ unsigned slot[NW][256];
+    unsigned *counters = lds_u + 2 * S + S;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = blockIdx.x, i = blockIdx.y;
     const int64_t b0 = (int64_t)c * S;
@@ -83,72 +81,12 @@ __global__ __launch_bounds__(64 * NW) void cell_sort_kernel(SplineGeom g, const 
         const float xv = live ? xT[(int64_t)i * B + b0 + e] : 0.0f;
         xs[e] = xv;
         int row0 = g.rows - kMaxK;
-        if (live) {
-            const Pair p = pair_eval<false>(xv, g, i);
-            float w[kMaxK], base;
-            window_of<false>(p, g.rows, row0, w, base);
-        }
+        if (live) row0 = window_row(xv, g, i);
         src[e] = ((unsigned)row0 << sbits) | (unsigned)e;
     }
     __syncthreads();
 
-    const int per_wave = S / NW;                    // a multiple of 64
-    const int n_pass = (row_bits + 7) / 8;
-    const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    for (int pass = 0; pass < n_pass; ++pass) {
-        const int shift = sbits + 8 * pass;
-        const int nbits = row_bits - 8 * pass < 8 ? row_bits - 8 * pass : 8;
-        for (int d = tid; d < NW * 256; d += kSortThreads) (&slot[0][0])[d] = 0u;
-        __syncthreads();
-        for (int e = wave * per_wave + lane; e < (wave + 1) * per_wave; e += 64)
-            atomicAdd(&slot[wave][(src[e] >> shift) & 255u], 1u);
-        __syncthreads();
-        // first slot of every (digit, wave): exclusive prefix over digits, then over waves; done by
-        // the first wave, four digits per lane
-        if (wave == 0) {
-            unsigned tot[4], mine_tot = 0;
-#pragma unroll
-            for (int qd = 0; qd < 4; ++qd) {
-                tot[qd] = 0;
-                for (int w2 = 0; w2 < NW; ++w2) tot[qd] += slot[w2][4 * lane + qd];
-                mine_tot += tot[qd];
-            }
-            unsigned inc = mine_tot;
-            for (int o = 1; o < 64; o <<= 1) {
-                const unsigned v = __shfl_up(inc, o, 64);
-                if (lane >= o) inc += v;
-            }
-            unsigned at = inc - mine_tot;
-#pragma unroll
-            for (int qd = 0; qd < 4; ++qd) {
-                unsigned a = at;
-                for (int w2 = 0; w2 < NW; ++w2) {
-                    const unsigned cnt = slot[w2][4 * lane + qd];
-                    slot[w2][4 * lane + qd] = a;
-                    a += cnt;
-                }
-                at += tot[qd];
-            }
-        }
-        __syncthreads();
-        for (int e0 = wave * per_wave; e0 < (wave + 1) * per_wave; e0 += 64) {
-            const unsigned key = src[e0 + lane];
-            const int d = (int)((key >> shift) & 255u);
-            // lanes holding the same digit: intersect, bit by bit, the ballots of "my value of that bit"
-            unsigned long long same = ~0ull;
-            for (int bit = 0; bit < nbits; ++bit) {
-                const bool set = ((d >> bit) & 1) != 0;
-                const unsigned long long m = __ballot(set);
-                same &= set ? m : ~m;
-            }
-            const unsigned rank = (unsigned)__builtin_popcountll(same & below);
-            const unsigned first = slot[wave][d];
-            dst[first + rank] = key;
-            atomicAdd(&slot[wave][d], 1u);
-        }
-        __syncthreads();
-        unsigned *t = src; src = dst; dst = t;
-    }
+    lds_sort<NW>(src, dst, counters, S, sbits, row_bits);
 
     const int64_t list = ((int64_t)c * g.n_in + i) * S;
     for (int p = tid; p < S; p += kSortThreads) {
@@ -363,8 +301,8 @@ hipError_t launch_sorted_records(const SplineGeom &g, const float *x, float *xT,
         prof::Timed tm("walk_transpose", st);
         transpose_kernel<<<grid, 256, 0, st>>>(x, xT, B, g.n_in);
     }
-    const size_t lds = (size_t)S * 12;
     // waves per sort, measured: 16 for chunks of 8192 samples, 8 for 4096, 4 below
+    const size_t lds = (size_t)S * 12 + sort_counter_bytes(S >= 8192 ? 16 : (S >= 4096 ? 8 : 4), row_bits);
     dim3 grid((unsigned)((B + S - 1) / S), (unsigned)g.n_in);
     prof::Timed tm("walk_sort", st);
     struct W16; struct W8; struct W4;

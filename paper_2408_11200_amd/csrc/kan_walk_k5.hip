@@ -16,6 +16,7 @@
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
 #include "kan_highk.hpp"
+#include "kan_sort.hpp"
 
 namespace kan_k5 {
 
@@ -40,9 +41,8 @@ __device__ __forceinline__ void sub_record(const float (&w6)[kMaxK], int row0, i
 }
 
 // grid (n_chunks, n_in), NW waves.  The 2 S keys of a list are  row << (sbits + 1) | (2 * sample + which):
-// distinct, so a stable counting sort by the row digits keeps equal rows in (sample, which) order, which
-// fixes the summation order downstream.  Same radix sort as the four-row kernel (8-bit digits, per-wave
-// digit counts, ranks inside a batch of 64 from ballots).  Entries of samples past the end of the batch get
+// distinct, so a stable counting sort by the row digits (kan_sort.hpp) keeps equal rows in (sample, which) order,
+// which fixes the summation order downstream.  Entries of samples past the end of the batch get
 // the largest row and zero weights and end up behind every real record.
 template <int NW>
 __global__ __launch_bounds__(64 * NW) void cell_sort_two_records_kernel(SplineGeom g, const float *__restrict__ xT,
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(64 * NW) void cell_sort_two_records_kernel(SplineGe
     extern __shared__ unsigned lds_u[];
     unsigned *src = lds_u, *dst = lds_u + L;
     float *xs = reinterpret_cast<float *>(lds_u + 2 * L);
-    __shared__ unsigned slot[NW][256];
+    unsigned *counters = lds_u + 2 * L + S;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = blockIdx.x, i = blockIdx.y;
     const int64_t b0 = (int64_t)c * S;
@@ -71,10 +71,7 @@ __global__ __launch_bounds__(64 * NW) void cell_sort_two_records_kernel(SplineGe
         xs[e] = xv;
         int ra = last, rb = last;
         if (live) {
-            const Pair p = pair_eval<false>(xv, g, i);
-            float w[kMaxK], base;
-            int row0;
-            window_of<false>(p, g.rows, row0, w, base);
+            const int row0 = window_row(xv, g, i);
             ra = row0;                              // <= rows - 6
             rb = row0 + kWalkK < last ? row0 + kWalkK : last;
         }
@@ -83,62 +80,7 @@ __global__ __launch_bounds__(64 * NW) void cell_sort_two_records_kernel(SplineGe
     }
     __syncthreads();
 
-    const int per_wave = L / NW;                    // a multiple of 64
-    const int n_pass = (row_bits + 7) / 8;
-    const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    for (int pass = 0; pass < n_pass; ++pass) {
-        const int shift = lbits + 8 * pass;
-        const int nbits = row_bits - 8 * pass < 8 ? row_bits - 8 * pass : 8;
-        for (int d = tid; d < NW * 256; d += kSortThreads) (&slot[0][0])[d] = 0u;
-        __syncthreads();
-        for (int e = wave * per_wave + lane; e < (wave + 1) * per_wave; e += 64)
-            atomicAdd(&slot[wave][(src[e] >> shift) & 255u], 1u);
-        __syncthreads();
-        // first slot of every (digit, wave): exclusive prefix over digits, then over waves; done by
-        // the first wave, four digits per lane
-        if (wave == 0) {
-            unsigned tot[4], mine_tot = 0;
-#pragma unroll
-            for (int qd = 0; qd < 4; ++qd) {
-                tot[qd] = 0;
-                for (int w2 = 0; w2 < NW; ++w2) tot[qd] += slot[w2][4 * lane + qd];
-                mine_tot += tot[qd];
-            }
-            unsigned inc = mine_tot;
-            for (int o = 1; o < 64; o <<= 1) {
-                const unsigned v = __shfl_up(inc, o, 64);
-                if (lane >= o) inc += v;
-            }
-            unsigned at = inc - mine_tot;
-#pragma unroll
-            for (int qd = 0; qd < 4; ++qd) {
-                unsigned a = at;
-                for (int w2 = 0; w2 < NW; ++w2) {
-                    const unsigned cnt = slot[w2][4 * lane + qd];
-                    slot[w2][4 * lane + qd] = a;
-                    a += cnt;
-                }
-                at += tot[qd];
-            }
-        }
-        __syncthreads();
-        for (int e0 = wave * per_wave; e0 < (wave + 1) * per_wave; e0 += 64) {
-            const unsigned key = src[e0 + lane];
-            const int d = (int)((key >> shift) & 255u);
-            unsigned long long same = ~0ull;
-            for (int bit = 0; bit < nbits; ++bit) {
-                const bool set = ((d >> bit) & 1) != 0;
-                const unsigned long long m = __ballot(set);
-                same &= set ? m : ~m;
-            }
-            const unsigned rank = (unsigned)__builtin_popcountll(same & below);
-            const unsigned first = slot[wave][d];
-            dst[first + rank] = key;
-            atomicAdd(&slot[wave][d], 1u);
-        }
-        __syncthreads();
-        unsigned *t = src; src = dst; dst = t;
-    }
+    lds_sort<NW>(src, dst, counters, L, lbits, row_bits);
 
     const int64_t list = ((int64_t)c * g.n_in + i) * L;
     for (int p = tid; p < L; p += kSortThreads) {
@@ -201,7 +143,8 @@ hipError_t highk_sorted_records(const HighKLayer &l, const float *xT, int64_t B,
     g.lo = l.lo; g.inv_h = l.inv_h; g.cell_base = l.cell_base; g.base_act = l.base_act;
     int sbits = 0;
     while ((1 << sbits) < S) ++sbits;
-    const size_t lds = (size_t)S * 20;              // two key arrays of 2 S entries and the S sample values
+    // two key arrays of 2 S entries, the S sample values, the counters
+    const size_t lds = (size_t)S * 20 + kan_k5::sort_counter_bytes(S >= 2048 ? 16 : 4, row_bits);
     auto kern = S >= 2048 ? kan_k5::cell_sort_two_records_kernel<16> : kan_k5::cell_sort_two_records_kernel<4>;
     struct Long; struct Short;
     hipError_t e = S >= 2048 ? kan_k5::ensure_dynamic_lds<Long>(reinterpret_cast<const void *>(kern), (int)lds)

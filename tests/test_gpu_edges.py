@@ -124,3 +124,13 @@ def test_ukan_bias_gradients_alone(want):
     assert set(some) == set(want)
     for n in want:
         assert torch.equal(some[n], every[n]), n
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (66000, 8, 2, 1022, 2), (66000, 8, 2, 1025, 3),        # lists of 8192 keys: the last table of one pass, the first of two
+    (33000, 16, 66, 2047, 1), (33000, 16, 66, 2050, 1),    # lists of 4096, 11-bit digits
+    (1030, 70, 20, 70, 3), (2500, 5, 20, 2200, 3),         # lists of 256 keys
+    (9000, 8, 20, 2100, 4),                                # two records per pair
+])
+def test_sort_passes(B, n_in, n_out, G, k):
+    run_layer_parity(workloads.random_kan_layer(G, B, n_in, n_out, G, k, outside_frac=0.05), gx_in_grid_units=True)
