@@ -14,6 +14,7 @@
 // Large batches run the same kernel with 16-byte row reads (T = 4) and four samples a workgroup, at the L2 gather rate.
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
+#include "kan_direct_slot.hpp"
 
 namespace KAN_NS {
 
@@ -74,9 +75,8 @@ __global__ __launch_bounds__(64 * NW) void forward_direct_kernel(SplineGeom g, c
     const int tile = (int)(blockIdx.x % n_tiles);
     const int64_t b0 = (int64_t)(blockIdx.x / n_tiles) * NS;
     const int grp = tid / LPS, lj = tid % LPS;
-    const int j = tile * TJ + lj * T;
     // lanes past the last output compute outputs 0 .. and drop them; a lane that straddles it starts at n_out - T
-    const int jc = j >= g.n_out ? 0 : (j + T > g.n_out ? g.n_out - T : j);
+    const int jc = direct_first_output(tile * TJ + lj * T, T, g.n_out);
 
     // two-level sum over the inputs: a lane group's running sums are folded after about 32 of its inputs
     constexpr int kFoldRounds = 32 * NS > LPS ? 32 * NS / LPS : 1;
@@ -146,15 +146,16 @@ __global__ __launch_bounds__(64 * NW) void forward_direct_kernel(SplineGeom g, c
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int r = 0; r < T; ++r)
-            if (j < g.n_out) sums[(grp * NS + s) * TJ + (jc - tile * TJ) + r] = tot[s][r] + acc[s][r];
+        for (int r = 0; r < T; ++r) sums[(grp * NS + s) * TJ + lj * T + r] = tot[s][r] + acc[s][r];
     __syncthreads();
     for (int e = tid; e < NS * TJ; e += NT) {
         const int s = e / TJ, jj = tile * TJ + e % TJ;
+        if (b0 + s >= B || jj >= g.n_out) continue;
+        const float *at = sums + s * TJ + direct_slot(jj, tile * TJ, T, g.n_out);
         float v = 0.0f;
 #pragma unroll 8
-        for (int q = 0; q < NGRP; ++q) v += sums[q * NS * TJ + e];
-        if (b0 + s < B && jj < g.n_out) y[(b0 + s) * g.n_out + jj] = v;
+        for (int q = 0; q < NGRP; ++q) v += at[q * NS * TJ];
+        y[(b0 + s) * g.n_out + jj] = v;
     }
 }
 

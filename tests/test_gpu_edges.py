@@ -35,6 +35,13 @@ def test_small_batch_forward(B, n_in, n_out, G, k):
     assert torch.equal(ws[:table.numel() * 4].view(torch.float32), table.flatten())
 
 
+@pytest.mark.parametrize("k", [3, 5])
+@pytest.mark.parametrize("n_out", [65, 66, 67, 129, 130, 131, 193, 195])
+def test_tile_whose_lane_starts_in_the_tile_before(n_out, k):
+    """One to three outputs past a tile of 64 at four outputs per lane: the last lane's outputs begin in the tile before."""
+    run_layer_parity(workloads.random_kan_layer(n_out, 2051, 9, n_out, 7, k, outside_frac=0.1), check_grads=False)
+
+
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
     (700, 5, 17, 9, 3), (700, 5, 31, 300, 3),       # two outputs per lane, the last lane moved back; sparse walk
     (1100, 4, 33, 9, 3), (900, 4, 63, 12, 2),       # four per lane, four streams
