@@ -159,19 +159,32 @@ __global__ __launch_bounds__(64 * NW) void forward_direct_kernel(SplineGeom g, c
     }
 }
 
+// A launch takes fewer than 2^32 threads (hipModuleLaunchKernel): larger batches go in parts of half that, and so large a
+// fold in a launch of its own.
 template <int LPS, int T, int NS, int NW>
 static hipError_t direct_launch(const SplineGeom &g, const float *x, const float *coef, const float *w_s,
                                 const float *w_b, float *cf, float *y, int64_t B, hipStream_t st)
 {
+    constexpr int64_t kThreads = 64 * NW;
     const int n_tiles = (g.n_out + LPS * T - 1) / (LPS * T);
-    const int64_t n_main = (B + NS - 1) / NS * n_tiles;
-    const int64_t total = (int64_t)g.n_in * (g.rows + 1) * g.n_out, per = 64 * NW * kFoldPerThread;
+    const int64_t total = (int64_t)g.n_in * (g.rows + 1) * g.n_out, per = kThreads * kFoldPerThread;
+    if (cf && total / kFoldPerThread >= 1ll << 31) {
+        if (hipError_t e = launch_fold_scale(coef, w_s, g.base_act ? w_b : nullptr, cf, g.n_in, g.rows, g.n_out, st);
+            e != hipSuccess)
+            return e;
+        cf = nullptr;
+    }
     const int64_t n_fold = cf ? (total + per - 1) / per : 0;
-    if (n_main + n_fold > 0x7fffffffll) return hipErrorInvalidConfiguration;
-    prof::Timed tm("forward_direct", st);
-    forward_direct_kernel<LPS, T, NS, NW><<<(unsigned)(n_main + n_fold), 64 * NW, 0, st>>>(g, x, coef, w_s, w_b, cf, y, B,
-                                                                                        n_tiles, n_main);
-    return hipGetLastError();
+    const int64_t part = ((1ll << 31) / kThreads + n_tiles - 1) / n_tiles * NS;       // samples
+    for (int64_t b0 = 0; b0 < B; b0 += part) {
+        const int64_t n = B - b0 < part ? B - b0 : part, n_main = (n + NS - 1) / NS * n_tiles;
+        const unsigned blocks = (unsigned)(n_main + (b0 == 0 ? n_fold : 0));
+        prof::Timed tm("forward_direct", st);
+        forward_direct_kernel<LPS, T, NS, NW><<<blocks, (unsigned)kThreads, 0, st>>>(g, x + b0 * g.n_in, coef, w_s, w_b, cf,
+                                                                                     y + b0 * g.n_out, n, n_tiles, n_main);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // one sample per workgroup, one output per lane: the most workgroups and the shortest chain

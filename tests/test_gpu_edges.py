@@ -42,6 +42,20 @@ def test_tile_whose_lane_starts_in_the_tile_before(n_out, k):
     run_layer_parity(workloads.random_kan_layer(n_out, 2051, 9, n_out, 7, k, outside_frac=0.1), check_grads=False)
 
 
+def test_batch_past_the_threads_of_one_launch():
+    """64 threads a sample: 2^26 samples are more than one launch takes.  Both ends and the seam between the parts agree
+    with a call on those rows alone."""
+    B, n_out = (1 << 26) + 5, 17
+    w = workloads.random_kan_layer(3, 16, 1, n_out, 6, 3)
+    s, p = w.layers[0], w.params[0]
+    coef, w_s, w_b = (dev(p[n]) for n in ("coef", "w_s", "w_b"))
+    x = torch.rand((B, 1), device="cuda") * 2 - 1
+    y = binding.kan_forward(s, x, coef, w_s, w_b)
+    for lo in (0, (1 << 25) - 2050, B - 4100):
+        part = x[lo:lo + 4100].clone()
+        assert torch.equal(y[lo:lo + 4100], binding.kan_forward(s, part, coef, w_s, w_b)), lo
+
+
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
     (700, 5, 17, 9, 3), (700, 5, 31, 300, 3),       # two outputs per lane, the last lane moved back; sparse walk
     (1100, 4, 33, 9, 3), (900, 4, 63, 12, 2),       # four per lane, four streams
