@@ -403,35 +403,45 @@ __global__ __launch_bounds__(256) void slice_sum_kernel(const float *__restrict_
 }
 
 // gE[i][f] = sum_c W1[f][c] * S[i][c],  S[i][c] = sum_t gpre[(i,t)][c].  One block per input: its four waves share the
-// rows of the column sums S (fp64, the shares added in wave order), then one thread per embedding feature.
+// rows of the column sums S (fp64, the shares added in wave order), then one thread per embedding feature.  The columns go
+// in tiles, so that any d_hid fits; the sums over them run on in order.
+constexpr int kEmbedCols = 512;
 __global__ __launch_bounds__(256) void embed_grad_kernel(const float *__restrict__ W1, const float *__restrict__ gpre,
                                                          float *__restrict__ gE, int n_in, int n_g, int d_feat,
                                                          int d_hid)
 {
-    extern __shared__ double colsum[];          // [4][d_hid]
+    __shared__ double colsum[4][kEmbedCols];
     const int i = blockIdx.x, wave = threadIdx.x >> 6;
     const float *src = gpre + (int64_t)i * n_g * d_hid;
-    for (int c = threadIdx.x & 63; c < d_hid; c += 64) {
-        double s = 0.0;
-        int t = wave;
-        for (; t + 28 < n_g; t += 32) {         // eight rows in flight
-            float v[8];
+    for (int f0 = 0; f0 < d_feat; f0 += 256) {
+        const int f = f0 + threadIdx.x;
+        double e = 0.0;
+        for (int c0 = 0; c0 < d_hid; c0 += kEmbedCols) {
+            const int n_c = d_hid - c0 < kEmbedCols ? d_hid - c0 : kEmbedCols;
+            if (f0 == 0 || d_hid > kEmbedCols) {            // one tile: its sums stay for the features after the first 256
+                __syncthreads();
+                for (int c = threadIdx.x & 63; c < n_c; c += 64) {
+                    double s = 0.0;
+                    int t = wave;
+                    for (; t + 28 < n_g; t += 32) {         // eight rows in flight
+                        float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(t + 4 * u) * d_hid + c];
+                        for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(t + 4 * u) * d_hid + c0 + c];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) s += (double)v[u];
+                        for (int u = 0; u < 8; ++u) s += (double)v[u];
+                    }
+                    for (; t < n_g; t += 4) s += (double)src[(int64_t)t * d_hid + c0 + c];
+                    colsum[wave][c] = s;
+                }
+                __syncthreads();
+                for (int c = threadIdx.x; c < n_c; c += 256)
+                    colsum[0][c] = ((colsum[0][c] + colsum[1][c]) + colsum[2][c]) + colsum[3][c];
+                __syncthreads();
+            }
+            if (f < d_feat)
+                for (int c = 0; c < n_c; ++c) e += (double)W1[(int64_t)f * d_hid + c0 + c] * colsum[0][c];
         }
-        for (; t < n_g; t += 4) s += (double)src[(int64_t)t * d_hid + c];
-        colsum[wave * d_hid + c] = s;
-    }
-    __syncthreads();
-    for (int c = threadIdx.x; c < d_hid; c += blockDim.x)
-        colsum[c] = ((colsum[c] + colsum[d_hid + c]) + colsum[2 * d_hid + c]) + colsum[3 * d_hid + c];
-    __syncthreads();
-    for (int f = threadIdx.x; f < d_feat; f += blockDim.x) {
-        double s = 0.0;
-        for (int c = 0; c < d_hid; ++c) s += (double)W1[(int64_t)f * d_hid + c] * colsum[c];
-        gE[(int64_t)i * d_feat + f] = (float)s;
+        if (f < d_feat) gE[(int64_t)i * d_feat + f] = (float)e;
     }
 }
 
@@ -547,7 +557,7 @@ hipError_t launch_embed_grad(const float *W1, const float *gpre, float *gE, int 
                              int d_hid, hipStream_t st)
 {
     prof::Timed tm("cg_embed_grad", st);
-    embed_grad_kernel<<<n_in, 256, 4 * (size_t)d_hid * sizeof(double), st>>>(W1, gpre, gE, n_in, n_g, d_feat, d_hid);
+    embed_grad_kernel<<<n_in, 256, 0, st>>>(W1, gpre, gE, n_in, n_g, d_feat, d_hid);
     return hipGetLastError();
 }
 

@@ -136,6 +136,13 @@ def test_ukan_generator_and_range_edges(B, n_in, n_out, kw):
     ukan_run(spec, p, x, np.float32(gy / np.sqrt(B)))
 
 
+@pytest.mark.parametrize("d_hid,d_feat", [(512, 300), (513, 300), (2100, 8), (5200, 8)])
+def test_ukan_wide_hidden_layers(d_hid, d_feat):
+    """Embedding gradients: one tile of hidden columns and more, for more features than a workgroup has threads."""
+    spec, p, x, gy = ukan_make(d_hid, 30, 2, 2, d_hid=d_hid, d_feat=d_feat)
+    ukan_run(spec, p, x, np.float32(gy / np.sqrt(30)))
+
+
 @pytest.mark.parametrize("want", [("gb2",), ("gW2",), ("gb1",), ("gW1", "gE")])
 def test_ukan_bias_gradients_alone(want):
     spec, p, x, gy = ukan_make(5, 400, 3, 33)
