@@ -170,7 +170,8 @@ __global__ __launch_bounds__(256) void cg_hidden_kernel(const float *__restrict_
     extern __shared__ double freq[];                // d_pe / 2 frequencies, per_block x dz, W1
     const int dz = d_feat + d_pe, tid = threadIdx.x;
     float *zs = reinterpret_cast<float *>(freq + d_pe / 2), *w1 = zs + per_block * dz;
-    const int64_t row0 = (int64_t)blockIdx.x * per_block;
+    const int64_t row0 = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * per_block;
+    if (row0 >= rows) return;
     const int n = rows - row0 < per_block ? (int)(rows - row0) : per_block;
     // d_pe / 2 frequencies, once a workgroup
     const int half = d_pe / 2;
@@ -527,8 +528,11 @@ hipError_t launch_cg_hidden(const float *E, const float *W1, const float *b1, co
         auto kern = cg_hidden_kernel<false>;
         if (lds > 64 * 1024)
             if (hipError_t e = ensure_dynamic_lds<Tag>(reinterpret_cast<const void *>(kern), (int)lds); e != hipSuccess) return e;
-        kern<<<(unsigned)((rows + per - 1) / per), 256, lds, st>>>(E, W1, b1, g_first, z, pre, hid, rows, n_g, d_pe, d_feat, d_hid,
-                                                                  per);
+        // one dimension of a launch takes fewer than 2^32 threads: 2^20 workgroups a grid row
+        const int64_t blocks = (rows + per - 1) / per, across = blocks < 1 << 20 ? blocks : 1 << 20;
+        kern<<<dim3((unsigned)across, (unsigned)((blocks + across - 1) / across)), 256, lds, st>>>(E, W1, b1, g_first, z, pre, hid,
+                                                                                                rows, n_g, d_pe, d_feat, d_hid,
+                                                                                                per);
     }
     return hipGetLastError();
 }

@@ -143,6 +143,25 @@ def test_ukan_wide_hidden_layers(d_hid, d_feat):
     ukan_run(spec, p, x, np.float32(gy / np.sqrt(30)))
 
 
+def test_ukan_generator_rows_past_one_dimension_of_a_launch():
+    """Wide encodings take a generator row a workgroup; 65535 inputs of 257 groups are more rows than one dimension holds.
+    The layer is the sum of the layers over each half of its inputs."""
+    n_in, cut = 65535, 32768
+    spec, p, x, _ = ukan_make(9, 2, n_in, 1, d_pe=1000, d_feat=4, d_hid=1)
+    x[0], x[1] = -32.0 + np.float32(1e-3), 223.5           # 256 groups of width one, and the one before them
+    P = {n: dev(a) for n, a in p.items()}
+    y = binding.ukan_cg_forward(spec, dev(x), P, 257)
+    parts = []
+    for sl in (slice(0, cut), slice(cut, n_in)):
+        half = workloads.UkanLayerSpec(sl.stop - sl.start, 1, spec.k, spec.h, spec.d_pe, spec.d_feat, spec.d_hidden, 0)
+        Q = {n: (t[sl].clone() if n in ("E", "scale") else t) for n, t in P.items()}
+        parts.append(binding.ukan_cg_forward(half, dev(x[:, sl]), Q, 257).double())
+    total = parts[0] + parts[1]
+    # fp32 sums of 65535 terms, folded every 32: a few units in the last place of the largest part
+    bound = 1e-5 * float(parts[0].abs().max() + parts[1].abs().max() + 1.0)
+    assert float((y.double() - total).abs().max()) <= bound
+
+
 @pytest.mark.parametrize("want", [("gb2",), ("gW2",), ("gb1",), ("gW1", "gE")])
 def test_ukan_bias_gradients_alone(want):
     spec, p, x, gy = ukan_make(5, 400, 3, 33)
