@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2408_11200_amd import binding, workloads
 from test_gpu_kan import dev, run_layer_parity
 from test_gpu_ukan import make as ukan_make, run as ukan_run
@@ -119,6 +120,28 @@ def test_dense_basis_backward_keeps_a_non_finite_gradient_to_its_rows():
             assert bool(torch.isfinite(got["gcoef"][i, m, 2])) == (not touched), (i, m, cell)
     keep = [0, 1, 3, 4]
     assert torch.allclose(got["gcoef"][:, :, keep], good["gcoef"][:, :, keep], rtol=1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("where", ["gy", "coef"])
+def test_dense_basis_backward_multiplies_a_zero_weight(where):
+    """On a knot the last weight of the window and its derivative are zero, and so is SiLU at zero: times an infinite
+    gradient or coefficient they are NaN, not left out."""
+    w = workloads.random_kan_layer(4, 500, 2, 5, 10, 3, outside_frac=0.1)
+    w.x[300] = 0.0
+    s, p = w.layers[0], w.params[0]
+    if where == "gy":
+        w.gy[300, 2] = np.inf
+    else:
+        p["coef"][:, 8, 2] = np.inf
+    x, coef, w_s, w_b, gy = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"], w.gy))
+    got = {n: t.cpu().numpy() for n, t in binding.kan_backward(s, x, coef, w_s, w_b, gy).items()}
+    with np.errstate(invalid="ignore"):
+        ref = oracle.kan_backward(w.x, p["coef"], p["w_s"], p["w_b"], w.gy, s.G, s.k, s.grid_lo, oracle.inv_h_of(s.grid_lo, s.grid_hi, s.G))
+    assert not np.isfinite(ref["gx"][300]).any()
+    for name in ("gx", "gcoef", "gw_b"):
+        np.testing.assert_array_equal(np.isfinite(got[name]), np.isfinite(ref[name]), name)
+    if where == "gy":
+        assert np.isnan(ref["gcoef"][:, 8, 2]).all() and np.isnan(ref["gw_b"][:, 2]).all()
 
 
 @pytest.mark.parametrize("B,n_in,n_out,kw", [
