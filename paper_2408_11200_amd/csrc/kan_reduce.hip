@@ -3,13 +3,15 @@
 // Bound by the read of the partial tables on wide layers and by latency on small ones.  The pass used to be three
 // kernels (carry rows added to the tables; chunk sums, gcoef and the summed table; gw_s and gw_b from that and the
 // coefficients), which read and wrote the summed table an extra time and, with few edges, ran one after the other
-// on a fraction of the chip.  The three against this one: 64 -> 64, G = 10, B = 65536 47 / 17 us; 32 -> 32, G = 1024,
-// B = 131072 85 / 64 us; 32 -> 32, G = 64, k = 5, B = 65536 59 / 30 us; wide layers, bound by the read, 107 / 98 us
-// (512 -> 512, G = 20, B = 16384: 4.3 TB/s, a large copy reaches 5.2).
+// on a fraction of the chip.  The three against this one (with the kernel that adds the slices of gw_s): 64 -> 64, G = 10,
+// B = 65536 47 / 17 us; 32 -> 32, G = 1024, B = 131072 83 / 48 us; 32 -> 32, G = 64, k = 5, B = 65536 59 / 21 us;
+// 16 -> 1, G = 2^18, B = 65536 285 / 119 us; 2 -> 200, G = 2^18, B = 65536 1416 / 1330 us; wide layers, bound by the read,
+// 107 / 99 us (512 -> 512, G = 20, B = 16384: 4.3 TB/s, a large copy reaches 5.2).
 //
 // A workgroup takes one input, a tile of LJ lanes x T outputs and a slice of the table rows.  Its NT threads are
 // LJ lanes x R rows x CS chunk shares (R * CS * LJ == NT, powers of two): with few rows the shares let every partial
 // row of the tile be in flight at once.  All sums are fp64 in a fixed order.
+#include <limits.h>
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
 #include "kan_reduce.hpp"
@@ -19,6 +21,7 @@ namespace kan {
 namespace {
 
 constexpr int kSegStage = 2048;         // segment rows of one input kept in LDS
+constexpr int kMarkBits = 4096;         // marks of the rows that have carry rows
 
 template <int T>
 __device__ __forceinline__ void reduce_load(const float *p, float (&v)[T])
@@ -79,16 +82,32 @@ __global__ __launch_bounds__(NT) void dparam_reduce_kernel(const float *__restri
     const int m_lo = blockIdx.z * per, m_hi = m_lo + per < rows ? m_lo + per : rows;
     const int64_t slab = (int64_t)n_in * rows * n_out, edge = (int64_t)i * n_out + j;
 
-    // the input's segment rows, staged: every row of the slice looks through them
+    // the input's segment rows, staged: rows look through them; and marks for the rows of the slice (2^mark_shift to a
+    // bit) that have carry rows at all: in a long table few do
     __shared__ int seg_lds[kSegStage];
+    __shared__ unsigned marks[kMarkBits / 32];
     const bool staged = cr.n_seg > 1 && n_chunks * cr.n_seg <= kSegStage;
-    if (staged) {
+    int mark_shift = 0;
+    if (cr.n_seg > 1) {
+        while (((m_hi - m_lo) >> mark_shift) >= kMarkBits) ++mark_shift;
+        for (int e = tid; e < kMarkBits / 32; e += NT) marks[e] = 0u;
+        __syncthreads();
         for (int e = tid; e < n_chunks * cr.n_seg; e += NT) {
             const int c = e / cr.n_seg, k = e - c * cr.n_seg;
-            seg_lds[e] = cr.seg_row[((int64_t)c * n_in + i) * cr.n_seg + k];
+            const int first = cr.seg_row[((int64_t)c * n_in + i) * cr.n_seg + k];
+            if (staged) seg_lds[e] = first;
+            const int lo = first > m_lo ? first : m_lo, hi = first + kMaxK < m_hi ? first + kMaxK : m_hi;
+            for (int m = lo; m < hi; ++m) {
+                const int bit = (m - m_lo) >> mark_shift;
+                if (k > 0) atomicOr(&marks[bit >> 5], 1u << (bit & 31));
+            }
         }
         __syncthreads();
     }
+    auto marked = [&](int m) {
+        const int bit = (m - m_lo) >> mark_shift;
+        return ((marks[bit >> 5] >> (bit & 31)) & 1u) != 0u;
+    };
     auto seg_first = [&](int c, int k) {
         return staged ? seg_lds[c * cr.n_seg + k] : cr.seg_row[((int64_t)c * n_in + i) * cr.n_seg + k];
     };
@@ -110,45 +129,45 @@ __global__ __launch_bounds__(NT) void dparam_reduce_kernel(const float *__restri
             double a[T];
 #pragma unroll
             for (int r = 0; r < T; ++r) a[r] = 0.0;
-            int c = share;
-            for (; c + 7 * CS < n_chunks; c += 8 * CS) {          // eight chunks in flight
+            for (int c = share; c < n_chunks; c += 8 * CS) {          // eight chunks in flight, the last ones too
                 float v[8][T];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) reduce_load<T>(part_c + (c + u * CS) * slab + at, v[u]);
+                for (int u = 0; u < 8; ++u)
+                    if (c + u * CS < n_chunks) reduce_load<T>(part_c + (c + u * CS) * slab + at, v[u]);
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
+                    if (c + u * CS < n_chunks) {
 #pragma unroll
-                    for (int r = 0; r < T; ++r) a[r] += (double)v[u][r];
+                        for (int r = 0; r < T; ++r) a[r] += (double)v[u][r];
+                    }
             }
-            for (; c < n_chunks; c += CS) {
-                float v[T];
-                reduce_load<T>(part_c + c * slab + at, v);
+            if (cr.n_seg > 1 && live && marked(m)) {
+                // carry rows: segment k's four rows start at seg_row[k] (non-decreasing in k), so those of row m are
+                // neighbours: the first is searched for, then four at a time are read
+                for (int c = share; c < n_chunks; c += CS) {
+                    const int64_t list = ((int64_t)c * n_in + i) * cr.n_seg;
+                    int k = 1, hi = cr.n_seg;                         // segment 0 has no carry rows
+                    while (k < hi) {
+                        const int mid = (k + hi) >> 1;
+                        if (seg_first(c, mid) < m - (kMaxK - 1)) k = mid + 1;
+                        else hi = mid;
+                    }
+                    for (int hits = 4; hits == 4; k += 4) {
+                        hits = 0;
+                        float v[4][T];
 #pragma unroll
-                for (int r = 0; r < T; ++r) a[r] += (double)v[r];
-            }
-            if (cr.n_seg > 1) {
-                // carry rows: segment k's four rows start at seg_row[k] (non-decreasing in k).  The hits of up to 32
-                // segments are found first, then only those are read.
-                for (int c2 = share; c2 < n_chunks; c2 += CS) {
-                    const int64_t list = ((int64_t)c2 * n_in + i) * cr.n_seg;
-                    for (int k0 = 0; k0 < cr.n_seg; k0 += 32) {
-                        unsigned hits = 0u;
-                        const int nk = cr.n_seg - k0 < 32 ? cr.n_seg - k0 : 32;
-#pragma unroll 4
-                        for (int u = 0; u < nk; ++u) {
-                            const int first = seg_first(c2, k0 + u);
-                            hits |= (unsigned)(m - first) < (unsigned)kMaxK ? 1u << u : 0u;
+                        for (int u = 0; u < 4; ++u) {
+                            const int first = k + u < cr.n_seg ? seg_first(c, k + u) : INT_MAX;
+                            if (first > m) continue;
+                            ++hits;
+                            reduce_load<T>(cr.carry + ((list + k + u) * kMaxK + (m - first)) * n_out + j, v[u]);
                         }
-                        if (k0 == 0) hits &= ~1u;                 // segment 0 has no carry rows
-                        if (!live) hits = 0u;
-                        while (hits) {
-                            const int k = k0 + __builtin_ctz(hits);
-                            hits &= hits - 1;
-                            float v[T];
-                            reduce_load<T>(cr.carry + ((list + k) * kMaxK + (m - seg_first(c2, k))) * n_out + j, v);
 #pragma unroll
-                            for (int r = 0; r < T; ++r) a[r] += (double)v[r];
-                        }
+                        for (int u = 0; u < 4; ++u)
+                            if (u < hits) {
+#pragma unroll
+                                for (int r = 0; r < T; ++r) a[r] += (double)v[u][r];
+                            }
                     }
                 }
             }
@@ -219,21 +238,35 @@ __global__ __launch_bounds__(256) void dparam_reduce_slices_kernel(const double 
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= edges) return;
     double s = 0.0;
-    for (int r = 0; r < n_rs; ++r) s += slice_sums[(int64_t)r * edges + e];
+    for (int r = 0; r < n_rs; r += 8) {                // eight in flight, added in order
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = r + u < n_rs ? slice_sums[(int64_t)(r + u) * edges + e] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
     gw_s[e] = (float)s;
 }
 
 namespace {
 int lanes_of(int n_out) { return n_out > 32 ? 16 : (n_out > 16 ? 8 : 4); }
 int tiles_of(int n_out) { const int w = n_out < 4 ? 4 : lanes_of(n_out) * 4; return (n_out + w - 1) / w; }
-// Row slices: enough workgroups for twice the chip, each with at least 64 rows (below that the extra kernel that adds
-// the slices of gw_s costs more than the slices give).
-int row_slices(int n_in, int rows, int n_out)
+// Row slices: as many workgroups as four for a CU, in slices of a power of two of rows, at least 32 (below, the extra kernel
+// that adds the slices of gw_s costs more than they give; so it does for tables of up to 64 rows).  A workgroup's rows are
+// one chain of reads: 2 -> 512, G = 100, B = 65536: 163 us in one slice, 57 and 6 in four.
+constexpr int kSliceRows = 32;
+int most_slices(int n_in, int n_out)
 {
     const int64_t blocks = (int64_t)n_in * tiles_of(n_out);
-    int64_t n = 512 / (blocks > 0 ? blocks : 1);
-    if (n > rows / 64) n = rows / 64;
-    return (int)(n < 1 ? 1 : n);
+    return (int)(blocks > 1024 ? 1 : 1024 / blocks);
+}
+int row_slices(int n_in, int rows, int n_out)
+{
+    if (rows <= 2 * kSliceRows) return 1;
+    const int most = most_slices(n_in, n_out);
+    int per = kSliceRows;
+    while (per < rows && (rows + per - 1) / per > most) per *= 2;
+    return (rows + per - 1) / per;
 }
 
 template <int T, int LJ, int NT>
@@ -251,7 +284,8 @@ void launch_reduce(dim3 grid, const float *part_c, const float *part_b, const Ca
 
 size_t reduce_scratch_bytes(int n_in, int rows, int n_out)
 {
-    const int n = row_slices(n_in, rows, n_out);
+    // not what row_slices says but its bound: that of a shorter table must fit the space of a longer one
+    const int most = most_slices(n_in, n_out), n = rows / kSliceRows + 1 < most ? rows / kSliceRows + 1 : most;
     return n > 1 ? (size_t)n * n_in * n_out * sizeof(double) : 0;
 }
 
@@ -272,7 +306,9 @@ hipError_t launch_dparam_reduce(const float *part_c, const float *part_b, const 
                                      n_chunks, n_slices_b, st))
     {
         prof::Timed tm("dparam_reduce", st);
-        if (n_out < 4) KAN_REDUCE(1, 4);
+        if (n_out == 1) KAN_REDUCE(1, 1);
+        else if (n_out == 2) KAN_REDUCE(1, 2);
+        else if (n_out == 3) KAN_REDUCE(1, 4);
         else if (lanes_of(n_out) == 4) KAN_REDUCE(4, 4);
         else if (lanes_of(n_out) == 8) KAN_REDUCE(4, 8);
         else KAN_REDUCE(4, 16);

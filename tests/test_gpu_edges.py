@@ -1,4 +1,6 @@
 """Edge sizes of the kernels' tiles, remainders and dispatch lines, against the CPU oracle (bars as in test_gpu_kan)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -9,6 +11,23 @@ from test_gpu_kan import dev, run_layer_parity
 from test_gpu_ukan import make as ukan_make, run as ukan_run
 
 pytestmark = pytest.mark.gpu
+
+
+def run_with_families(w):
+    """Parity of a layer's backward pass; returns the kernel families that it launched."""
+    s, p = w.layers[0], w.params[0]
+    run_layer_parity(w, gx_in_grid_units=s.G > 1000)
+    x, coef, w_s, w_b, gy = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"], w.gy))
+    seen = set()
+    hook = ctypes.CFUNCTYPE(None, ctypes.c_char_p, ctypes.c_void_p)(lambda family, stream: seen.add(family.decode()))
+    none = ctypes.CFUNCTYPE(None, ctypes.c_char_p, ctypes.c_void_p)(lambda family, stream: None)
+    binding.kan_set_launch_observer(hook, none)
+    try:
+        binding.kan_backward(s, x, coef, w_s, w_b, gy)
+    finally:
+        binding.kan_set_launch_observer(None, None)
+    torch.cuda.synchronize()
+    return seen
 
 
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
@@ -94,6 +113,16 @@ def test_ragged_width_on_shared_partial_tables():
 ])
 def test_reduction_over_the_chunks(B, n_in, n_out, G, k):
     run_layer_parity(workloads.random_kan_layer(n_out + 7, B, n_in, n_out, G, k, outside_frac=0.1))
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (300000, 1, 33, 10, 3),                         # more segments than are kept in LDS, many to a row
+    (66000, 2, 1, 140000, 3), (66000, 2, 2, 9000, 3), (33000, 3, 3, 300, 3),    # one, two, three outputs; rows share a mark
+    (33000, 5, 20, 64, 3), (33000, 5, 20, 61, 3),   # 67 rows: the first table in slices; 64: the last that is not
+    (3000, 300, 40, 200, 3),                        # slices of more than the smallest number of rows
+])
+def test_reduction_adds_the_carry_rows(B, n_in, n_out, G, k):
+    assert run_with_families(workloads.random_kan_layer(n_out + 9, B, n_in, n_out, G, k, outside_frac=0.05)) >= {"backward_walk", "dparam_reduce"}
 
 
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
