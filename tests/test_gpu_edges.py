@@ -62,6 +62,13 @@ def test_tile_whose_lane_starts_in_the_tile_before(n_out, k):
     run_layer_parity(workloads.random_kan_layer(n_out, 2051, 9, n_out, 7, k, outside_frac=0.1), check_grads=False)
 
 
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (300, 16, 40, 1700, 3), (300, 16, 40, 1500, 2),         # folds of just more and less than 2^20 floats
+])
+def test_forward_lines(B, n_in, n_out, G, k):
+    run_layer_parity(workloads.random_kan_layer(n_in, B, n_in, n_out, G, k, outside_frac=0.1), check_grads=False)
+
+
 def test_batch_past_the_threads_of_one_launch():
     """64 threads a sample: 2^26 samples are more than one launch takes.  Both ends and the seam between the parts agree
     with a call on those rows alone."""
