@@ -198,36 +198,55 @@ static hipError_t direct_latency(const SplineGeom &g, const float *x, const floa
 }
 
 // Where the line lies.  The direct kernel gathers every window row from L2 once per sample: its time is the edges of the
-// padded width at about 1.8e12 edges/s while the table stays in L2.  The LDS-staged kernels walk the inputs one after the
-// other and, until their workgroups fill the chip, cost a fixed time an input however small the batch (2.6 us for 256-wide
-// tiles of 128 samples, 1.6 us for 512-wide ones, 0.85 us up to 64 outputs and for long tables), so against them the line
-// is one on B * n_out.  Against the kernels that gather from L2 themselves it wins outright on narrow and ragged widths.
-// Measured, other kernel / direct, us:
-//   64 -> 64, G = 10      B = 4096 57 / 14, 16384 59 / 44, 32768 62 / 88       (long-table kernel)
-//   256 -> 256, G = 10    B = 8192 661 / 302, 16384 663 / 594, 32768 666 / 1186       (LDS-staged, 256-wide)
-//   75 -> 130, G = 10     B = 6001 195 / 64, 16384 195 / 159
-//   512 -> 512, G = 10    B = 4096 832 / 600, 8192 836 / 1190                  (LDS-staged, 512-wide)
-//   256 -> 256, G = 200   B = 2048 236 / 152, 4096 260 / 283                   (generic, 256-wide tiles)
-//   32 -> 32, G = 1024    B = 8192 70 / 14, 131072 164 / 114                   (row-stream kernel)
-//   64 -> 64, G = 1024    B = 8192 133 / 63, 65536 273 / 436                   (row-stream kernel; the table is 17 MB)
-//   128 -> 37, G = 200    B = 32768 406 / 167; 100 -> 200, G = 300, B = 16384 413 / 537        (generic)
+// padded width at about 1.8e12 edges/s while the table stays in L2, and at least 2.6 ns for a workgroup of four samples.  The
+// LDS-staged kernels walk the inputs one after the other and, until their workgroups fill the chip, cost a fixed time an
+// input however small the batch, so against them the line is one on B * n_out that falls with the inputs.  With fewer than
+// eight inputs the others cost no more than their launches and the line is on the workgroups alone.  Past L2 the kernels
+// that share a row between samples win from a few thousand samples on; narrow layers win by their shorter rows.
+// Measured, other kernel / direct, us (a fold of more than 2^20 floats in a launch of its own is in both):
+//   two inputs        2 -> 17, G = 20: B = 8192 11 / 9, 65536 18 / 43; 2 -> 200, G = 20: 2048 12 / 10, 8192 12 / 25
+//   long-table        64 -> 64, G = 10: B = 4096 57 / 14, 16384 59 / 44, 32768 62 / 88; 8 -> 64, G = 20: 8192 11 / 10,
+//                     16384 12 / 15; 16 -> 32, G = 5: 16384 24 / 15, 32768 24 / 26
+//   256-wide tiles    256 -> 256, G = 10: B = 8192 661 / 302, 32768 666 / 1186; 8 -> 256, G = 20: 4096 26 / 15, 8192 27 / 27
+//   512-wide tiles    512 -> 512, G = 10: B = 4096 832 / 600, 8192 836 / 1190; 64 -> 300, G = 20: 4096 121 / 74, 8192 122 / 138
+//   row stream        in L2: 32 -> 24, G = 20: B = 131072 153 / 108; 32 -> 64, G = 1000: 32768 80 / 81, 131072 225 / 301;
+//                     past it: 256 -> 32, G = 1000: 32768 507 / 475, 65536 679 / 943
+//   generic           past L2: 256 -> 130, G = 300: B = 2048 244 / 215, 4096 307 / 444; in it: 8 -> 128, G = 100: 8192 14 / 15,
+//                     16384 23 / 27; 128 -> 37, G = 200: 32768 406 / 167
+//   narrow            64 -> 1, G = 20: B = 2048 19 / 12, 8192 19 / 41; 32 -> 4, G = 20: 16384 20 / 15, 65536 31 / 46;
+//                     32 -> 16, G = 1000: 65536 478 / 49
+//   degrees 4 and 5   64 -> 4, G = 10000: B = 65536 481 / 96 (generic); 64 -> 300, G = 20: 4096 283 / 109 (512-wide tiles)
+// (sums of 4 and 6 products cost in proportion: the line counts them)
 int forward_direct_plan(const SplineGeom &g, int64_t B)
 {
-    const int64_t w = g.n_out <= 16 ? 16 : (g.n_out <= 32 ? 32 : (g.n_out + 63) / 64 * 64);
-    const int64_t load = B * w * kMaxK / 4;
-    const bool in_l2 = (int64_t)g.n_in * g.slab_rows * g.n_out * 4 <= 8ll << 20;
-    if (g.n_out < 4) return B <= (g.n_in >= 32 ? 8192 : 2048) ? 1 : 0;        // one output per lane at any batch
+    const int n = g.n_out, ni = g.n_in;
+    const int64_t tiles = (n + 63) / 64, w = n <= 16 ? 16 : (n <= 32 ? 32 : tiles * 64), load = B * w * kMaxK / 4;
+    const bool in_l2 = (int64_t)ni * g.slab_rows * n * 4 <= 8ll << 20;
+    const int lds = forward_lds_plan(g);
 #if KAN_MAXK == 4
-    if (narrow_applicable(g)) return load <= (g.n_in >= 32 ? 1 << 20 : 1 << 17) ? 1 : 0;
-    if ((g.n_out <= 64 || !forward_lds_plan(g)) && forward_lds_rows_plan(g, B)) return load <= 1 << 20 ? 1 : 0;
+    const bool lds_rows = forward_lds_rows_plan(g, B) != 0 && (n <= 64 || !lds), narrow = narrow_applicable(g) != 0;
+#else
+    const bool lds_rows = false, narrow = false;
 #endif
-    if (g.n_out <= 32) return 1;
-    if (g.n_out <= 64) return in_l2 || load <= 1 << 20 ? 1 : 0;
-    switch (forward_lds_plan(g)) {
-    case 4: return load <= (g.n_in >= 32 ? 7 << 19 : 1 << 21) ? 1 : 0;
-    case 8: return load <= 5 << 19 ? 1 : 0;
-    default: return (in_l2 && (g.n_out < 256 || g.n_out % 4 != 0)) || load <= 3 << 18 ? 1 : 0;
+    if (ni < 8) return B * tiles <= (n < 4 ? 1 << 12 : (n >= 128 && (lds || lds_rows) ? 3 << 12 : 1 << 13)) ? 1 : 0;
+    if (n < 4) {                                     // one output per lane at any batch: 16 lanes for at most three
+        if (!narrow) return B <= (ni >= 32 ? 1 << 13 : 1 << 11) ? 1 : 0;
+        const int64_t most = ni < 32 ? 1 << 12 : (n == 1 ? 32 : 64) * (int64_t)ni;
+        return B <= (most < (n == 1 ? 1 << 12 : 1 << 13) ? most : (n == 1 ? 1 << 12 : 1 << 13)) ? 1 : 0;
     }
+    if (narrow) return load <= (ni >= 64 || (ni >= 32 && n >= 8) ? 1 << 20 : (ni >= 32 ? 1 << 18 : 1 << 17)) ? 1 : 0;
+    if (lds_rows) return load <= (ni >= 32 ? 1 << 20 : (ni >= 16 ? 3 << 18 : 1 << 19)) ? 1 : 0;
+    if (forward_rows_plan(g)) {
+        if (!in_l2) return load <= 1 << 20 ? 1 : 0;
+        return n <= 32 || ni >= 64 || load <= (ni >= 32 ? 3 << 20 : 1 << 21) ? 1 : 0;
+    }
+    if (lds == 4) return load <= (ni >= 32 ? 7 << 19 : (ni >= 16 || kMaxK == 6 ? 3 << 20 : 1 << 21)) ? 1 : 0;
+    if (lds == 8 && kMaxK == 6) return load <= (ni >= 16 ? 5 << 19 : 3 << 19) ? 1 : 0;
+    if (lds == 8) return load <= (ni >= 256 ? 1 << 21 : (ni >= 16 ? 3 << 19 : 1 << 20)) ? 1 : 0;
+    // generic
+    if (n <= 32) return ni >= 16 || load <= 1 << 20 ? 1 : 0;
+    if (in_l2 && (n < 256 || n % 4 != 0)) return ni >= 16 || load <= (n >= 128 ? 1 << 20 : 1 << 21) ? 1 : 0;
+    return load <= (in_l2 || kMaxK == 6 ? 3 << 18 : 1 << 19) ? 1 : 0;
 }
 
 hipError_t launch_forward_direct(const SplineGeom &g, const float *x, const float *coef, const float *w_s,

@@ -1,12 +1,12 @@
-// Forward kernel for layers of 33 .. 64 outputs whose tables do not fit an XCD's L2.
+// Forward kernel for layers of 17 .. 64 outputs whose tables do not fit an XCD's L2.
 //
-// With lanes <-> outputs and one sample at a time such a layer fills half of a wave or a
-// little more, and every coefficient load moves 132-256 bytes, so the texture path spends its time on load
+// With lanes <-> outputs and one sample at a time such a layer fills a quarter to a whole of a wave,
+// and every coefficient load moves 68-256 bytes, so the texture path spends its time on load
 // instructions rather than on bytes.  Here a wave works on FOUR samples at once, one per DPP row of
-// 16 lanes; a lane holds T = 4 outputs of its row's sample.  Lane l of a row evaluates the pair
+// 16 lanes; a lane holds T = 2 (up to 32 outputs) or 4 outputs of its row's sample.  Lane l of a row evaluates the pair
 // (row's sample, input i0 + l); the window weights and the window row of input i0 + ii are then read
 // from lane ii of the same row with row_newbcast, so the four rows proceed in lockstep on
-// different samples with no scalar state.  One 16-byte load per lane fetches a table row for all
+// different samples with no scalar state.  One 8- or 16-byte load per lane fetches a table row for all
 // four samples.
 #include <type_traits>
 #include "kan_device.hpp"
@@ -36,11 +36,22 @@ __device__ __forceinline__ void static_for(F &&f)
     }
 }
 
-constexpr int T = 4;                   // outputs per lane
+template <int T>
 __device__ __forceinline__ void load_t(const float *p, float (&v)[T])
 {
-    const float4 t = load4u(p);
-    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+    if constexpr (T == 4) {
+        const float4 t = load4u(p);
+        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+    } else {
+        const float2 t = load2u(p);
+        v[0] = t.x; v[1] = t.y;
+    }
+}
+template <int T>
+__device__ __forceinline__ void store_t(float *p, const float (&v)[T])
+{
+    if constexpr (T == 4) store4u(p, make_float4(v[0], v[1], v[2], v[3]));
+    else store2u(p, make_float2(v[0], v[1]));
 }
 
 constexpr int kSamplesPerRow = 8;      // samples a DPP row handles one after the other
@@ -49,6 +60,7 @@ constexpr int kSamplesPerRow = 8;      // samples a DPP row handles one after th
 
 // grid: ceil(B / (4 waves * 4 rows * kSamplesPerRow)), 256 threads.  Needs rows >= kMaxK, a table with
 // the w_b row appended (slab_rows == rows + 1) and T <= n_out <= 16 * T.
+template <int T>
 __global__ __launch_bounds__(256) void forward_rows_kernel(SplineGeom g, const float *__restrict__ x,
                                                            const float *__restrict__ cf, float *__restrict__ y,
                                                            int64_t B)
@@ -94,8 +106,8 @@ __global__ __launch_bounds__(256) void forward_rows_kernel(SplineGeom g, const f
                 const int o = row_bcast<N>(off) + jc;
                 float c[kMaxK][T], wb[T];
 #pragma unroll
-                for (int s = 0; s < kMaxK; ++s) load_t(slab + s * g.n_out + o, c[s]);
-                load_t(slab + g.rows * g.n_out + jc, wb);
+                for (int s = 0; s < kMaxK; ++s) load_t<T>(slab + s * g.n_out + o, c[s]);
+                load_t<T>(slab + g.rows * g.n_out + jc, wb);
                 float ws[kMaxK];
 #pragma unroll
                 for (int s = 0; s < kMaxK; ++s) ws[s] = row_bcast<N>(w[s]);
@@ -114,14 +126,20 @@ __global__ __launch_bounds__(256) void forward_rows_kernel(SplineGeom g, const f
         }
 #pragma unroll
         for (int r = 0; r < T; ++r) tot[r] += acc[r];
-        if (jok && b < B) store4u(y + b * g.n_out + j, make_float4(tot[0], tot[1], tot[2], tot[3]));
+        if (jok && b < B) store_t<T>(y + b * g.n_out + j, tot);
     }
 }
 
-// 0: not applicable
+// 0: not applicable, else outputs per lane.  A DPP row evaluates and sums 16 inputs at a time, so layers of few inputs do
+// better on the generic kernel (B = 65536, generic / this: 2 -> 31, G = 20 18 / 46 us; 4 -> 64, G = 1000 33 / 46; 16 -> 64,
+// G = 1000 112 / 56; windows of six rows need 16 inputs), and so do nearly full rows that are no multiple of 16 bytes in
+// windows of six past L2 (32 -> 63, G = 10000, k = 5, B = 65536: 331 / 436).
 int forward_rows_plan(const SplineGeom &g)
 {
-    return g.rows >= kMaxK && g.slab_rows == g.rows + 1 && g.n_out > 32 && g.n_out <= 64 ? 1 : 0;
+    if (g.rows < kMaxK || g.slab_rows != g.rows + 1 || g.n_out <= 16 || g.n_out > 64) return 0;
+    if (g.n_in < (kMaxK == 6 ? 16 : 8)) return 0;
+    if (kMaxK == 6 && g.n_out > 48 && g.n_out % 4 != 0 && (int64_t)g.n_in * g.slab_rows * g.n_out * 4 > 8ll << 20) return 0;
+    return g.n_out <= 32 ? 2 : 4;
 }
 
 hipError_t launch_forward_rows(const SplineGeom &g, const float *x, const float *cf, float *y, int64_t B,
@@ -129,7 +147,8 @@ hipError_t launch_forward_rows(const SplineGeom &g, const float *x, const float 
 {
     const unsigned blocks = (unsigned)((B + 16 * kSamplesPerRow - 1) / (16 * kSamplesPerRow));
     prof::Timed tm("forward_rows", st);
-    forward_rows_kernel<<<blocks, 256, 0, st>>>(g, x, cf, y, B);
+    if (forward_rows_plan(g) == 2) forward_rows_kernel<2><<<blocks, 256, 0, st>>>(g, x, cf, y, B);
+    else forward_rows_kernel<4><<<blocks, 256, 0, st>>>(g, x, cf, y, B);
     return hipGetLastError();
 }
 

@@ -63,6 +63,17 @@ def test_tile_whose_lane_starts_in_the_tile_before(n_out, k):
 
 
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (33000, 8, 17, 6, 3), (66000, 33, 31, 9, 1), (40000, 9, 18, 9000, 3),       # two outputs a lane, ragged, an input past 16
+    (33000, 17, 30, 2500, 5), (66000, 16, 33, 9, 4),                            # window of six rows
+])
+def test_row_stream_kernel(B, n_in, n_out, G, k):
+    w = workloads.random_kan_layer(n_in, B, n_in, n_out, G, k, outside_frac=0.1)
+    run_layer_parity(w, check_grads=False)
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (8192, 7, 17, 6, 3), (8193, 7, 17, 6, 3), (4097, 2, 3, 6, 3), (4100, 3, 130, 6, 3),     # few inputs: the line and past it
+    (16500, 7, 62, 30, 5), (2051, 8, 1, 7, 3), (8193, 64, 2, 7, 3),
     (300, 16, 40, 1700, 3), (300, 16, 40, 1500, 2),         # folds of just more and less than 2^20 floats
 ])
 def test_forward_lines(B, n_in, n_out, G, k):
