@@ -444,7 +444,8 @@ int backward_body(const ukan_layer_desc *desc, int64_t B, const float *x, const 
         a.C = split; a.ldc = n_o; a.M = dh; a.N = n_o; a.K = rows;
         a.k_slice = k_slice; a.c_slice = (int64_t)(dh + 1) * n_o; a.colsum = 1;
         const int used = (int)((rows + k_slice - 1) / k_slice);
-        if (launch_gemm(a, EPI_PLAIN, used, "cg_gW2_gemm", st) != hipSuccess) return KAN_ERR_HIP;
+        if ((g->gW2 ? launch_gemm(a, EPI_PLAIN, used, "cg_gW2_gemm", st) : launch_column_sums(a, used, st)) != hipSuccess)
+            return KAN_ERR_HIP;
         if (launch_slice_sum(split, g->gW2, (int64_t)dh * n_o, g->gb2, n_o, used, st) != hipSuccess) return KAN_ERR_HIP;
     }
     if (g->gE || g->gW1 || g->gb1) {
@@ -462,7 +463,8 @@ int backward_body(const ukan_layer_desc *desc, int64_t B, const float *x, const 
             b.C = split; b.ldc = dh; b.M = dz; b.N = dh; b.K = rows;
             b.k_slice = k_slice; b.c_slice = (int64_t)(dz + 1) * dh; b.colsum = 1;
             const int used = (int)((rows + k_slice - 1) / k_slice);
-            if (launch_gemm(b, EPI_PLAIN, used, "cg_gW1_gemm", st) != hipSuccess) return KAN_ERR_HIP;
+            if ((g->gW1 ? launch_gemm(b, EPI_PLAIN, used, "cg_gW1_gemm", st) : launch_column_sums(b, used, st)) != hipSuccess)
+                return KAN_ERR_HIP;
             if (launch_slice_sum(split, g->gW1, (int64_t)dz * dh, g->gb1, dh, used, st) != hipSuccess) return KAN_ERR_HIP;
         }
         if (g->gE && desc->d_feat > 0 &&

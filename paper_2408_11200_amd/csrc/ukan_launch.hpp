@@ -40,6 +40,8 @@ hipError_t launch_fill_int(int32_t *p, int32_t v, int n, hipStream_t st);
 hipError_t launch_table_rows(const float *table, float *coef, int n_in, int table_rows, int coef_rows, int shift,
                              int n_out, hipStream_t st);
 hipError_t launch_gemm(const GemmArgs &a, int epi, int slices, const char *family, hipStream_t st);
+// what launch_gemm(a, EPI_PLAIN, slices, ...) with a.colsum writes to row M of the slices, and nothing else
+hipError_t launch_column_sums(const GemmArgs &a, int slices, hipStream_t st);
 hipError_t launch_slice_sum(const float *part, float *out, int64_t n, float *out2, int64_t n2, int slices, hipStream_t st);
 hipError_t launch_embed_grad(const float *W1, const float *gpre, float *gE, int n_in, int n_g, int d_feat,
                              int d_hid, hipStream_t st);

@@ -232,6 +232,18 @@ def test_ukan_generator_rows_past_one_dimension_of_a_launch():
     assert float((y.double() - total).abs().max()) <= bound
 
 
+@pytest.mark.parametrize("B,n_in,n_out,kw", [
+    (40, 1, 1, dict(d_hid=1)), (300, 40, 17, dict(d_hid=65, xs=10.0)),      # one column; several slices, ragged steps and columns
+])
+def test_ukan_bias_gradients_alone_in_slices(B, n_in, n_out, kw):
+    """Both bias gradients, each without its weights' gradient, are those of the full pass bit for bit."""
+    spec, p, x, gy = ukan_make(B, B, n_in, n_out, **kw)
+    pd = {n: dev(a) for n, a in p.items()}
+    every = binding.ukan_cg_backward(spec, dev(x), pd, dev(gy), 160)
+    some = binding.ukan_cg_backward(spec, dev(x), pd, dev(gy), 160, want=("gb1", "gb2"))
+    assert torch.equal(some["gb1"], every["gb1"]) and torch.equal(some["gb2"], every["gb2"])
+
+
 @pytest.mark.parametrize("want", [("gb2",), ("gW2",), ("gb1",), ("gW1", "gE")])
 def test_ukan_bias_gradients_alone(want):
     spec, p, x, gy = ukan_make(5, 400, 3, 33)
