@@ -158,7 +158,8 @@ __global__ __launch_bounds__(kRangeThreads) void range_finalize_kernel(const int
 // Row (i, t) of the generator batch is group g_first[i] + t of input i: z = [E[i] ; PE(g)] (PE evaluated in fp64, rounded
 // to fp32), pre = W1^T z + b1, hid = silu(pre).  A workgroup takes kHidRows consecutive rows, four threads a hidden unit
 // and kHidRows / 4 rows a thread, with the z rows and W1 in LDS: a row a workgroup re-read W1 (16 KB at 64 x 64) per row
-// and evaluated the frequencies anew.  What is left is mostly the sines in fp64 (48 000 rows in three launches: 84 -> 66 us).
+// and evaluated the frequencies anew.  What is left is mostly the sines in fp64 (48 000 rows in three launches: 84 -> 66 us;
+// 2 176 rows, a load of W1 at a time behind the sines 15 us, eight before them 11, a row a workgroup 10).
 constexpr int kHidRows = 16;
 template <bool W1_LDS>
 __global__ __launch_bounds__(256) void cg_hidden_kernel(const float *__restrict__ E, const float *__restrict__ W1,
@@ -173,6 +174,10 @@ __global__ __launch_bounds__(256) void cg_hidden_kernel(const float *__restrict_
     const int64_t row0 = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * per_block;
     if (row0 >= rows) return;
     const int n = rows - row0 < per_block ? (int)(rows - row0) : per_block;
+    if (W1_LDS) {                                   // first, and several loads in flight: nothing waits for them until the sums
+#pragma unroll 8
+        for (int e = tid; e < dz * d_hid; e += 256) w1[e] = W1[e];
+    }
     // d_pe / 2 frequencies, once a workgroup
     const int half = d_pe / 2;
     for (int q = tid; q < half; q += 256) freq[q] = pow(10000.0, -2.0 * (double)q / (double)d_pe);
@@ -194,8 +199,6 @@ __global__ __launch_bounds__(256) void cg_hidden_kernel(const float *__restrict_
         zs[r * dz + c + 1] = (float)cs;
         if (z) { z[row * dz + c] = (float)sn; z[row * dz + c + 1] = (float)cs; }
     }
-    if (W1_LDS)
-        for (int e = tid; e < dz * d_hid; e += 256) w1[e] = W1[e];
     __syncthreads();
     constexpr int PER = kHidRows / 4;
     for (int c = tid & 63; c < d_hid; c += 64) {
