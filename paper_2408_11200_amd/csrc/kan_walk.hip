@@ -180,25 +180,9 @@ WalkPlan plan_walk(const SplineGeom &g, int64_t B, bool allow_shared, bool high_
     WalkPlan p = {};
     if (g.rows < kMaxK || g.rows > kRtRowMask || B < 1) return p;
     if (high_degree && g.rows < 6) return p;          // a six-row window must fit the table
-    // every width has a variant (widths that are no multiple of T run its ragged build)
-    if (g.n_out > 256) {
-        p.T = 8;            // one tile covers 512 outputs: the per-record work is shared by twice as many
-        p.streams = 1;
-    } else if (g.n_out > 32) {
-        p.T = 4;
-        p.streams = g.n_out > 128 ? 1 : (g.n_out > 64 ? 2 : 4);
-    } else if (g.n_out > 16) {
-        p.T = 2;            // 16 lanes x 2 outputs cover the layer: no idle lanes in a stream
-        p.streams = 4;
-    } else if (g.n_out % 4 == 0) {
-        p.T = 4;
-        p.streams = 4;
-    } else {
-        p.T = 1;
-        p.streams = 4;
-    }
-    const int tile = (64 / p.streams) * p.T;
-    p.n_jt = (g.n_out + tile - 1) / tile;
+    const int64_t slab = (int64_t)g.n_in * g.rows * g.n_out * (int64_t)sizeof(float);
+    const int s_max = high_degree ? 4096 : 8192;       // two records per pair: 2 S keys to sort, 12 bits for the sample
+    auto pow2_floor = [s_max](int64_t v) { int64_t q = 256; while (q * 2 <= v && q < s_max) q *= 2; return (int)q; };
     // chunk length: a power of two between 256 and 8192 samples.  Every chunk writes a partial table that the reduction
     // reads back, so few long chunks are better, as long as
     //   - the gy rows of a chunk stay in cache (at most 8 MiB: twice an XCD's L2, the rest served by the memory-side
@@ -208,17 +192,41 @@ WalkPlan plan_walk(const SplineGeom &g, int64_t B, bool allow_shared, bool high_
     //     (256 -> 256, G = 200, B = 8192: eight chunks 538 us, four 422 us, two 368 us).
     // Raised further until the partial sums fit 2 GiB.  The parallelism of the walk comes from cutting each sorted list
     // into segments (below).
-    // (two records per pair for degrees 4 and 5: the sort holds 2 S keys and a record has 12 bits for the sample)
-    const int s_max = high_degree ? 4096 : 8192;
-    auto pow2_floor = [s_max](int64_t v) { int64_t q = 256; while (q * 2 <= v && q < s_max) q *= 2; return (int)q; };
     int S = pow2_floor((8ll << 20) / ((int64_t)g.n_out * 4));
-    if (p.T == 8 && S > 1024) S = 1024;      // eight outputs per lane: stay with single-level sums (registers)
     int64_t share = B * g.n_in / 512 < B ? B * g.n_in / 512 : B;
     if (share < B / 8) share = B / 8;
     const int s_par = pow2_floor(share);
     S = S < s_par ? S : s_par;
-    const int64_t slab = (int64_t)g.n_in * g.rows * g.n_out * (int64_t)sizeof(float);
-    while (S < s_max && ((B + S - 1) / S) * slab > (2ll << 30)) S *= 2;
+    auto fit_sums = [&](int q) { while (q < s_max && ((B + q - 1) / q) * slab > (2ll << 30)) q *= 2; return q; };
+    // Eight outputs per lane (one tile covers 512 outputs: the per-record work is shared by twice as many) have registers
+    // for single-level sums only, so chunks of at most 1024 samples: not where the partial sums ask for longer ones (two
+    // levels spill: 256 -> 300, G = 1000, B = 8192 walk 15.4 ms against 1.2 with four).  Widths that are no multiple of
+    // eight take it where it pays: many pairs of a short table, and a last tile more than half full (backward pass, four
+    // outputs / eight: 16 -> 300, G = 20, B = 16384 107 / 97 us, 64 -> 300, G = 5, B = 16384 282 / 236; but 2 -> 300, G = 20,
+    // B = 65536 101 / 137, 16 -> 300, G = 1000, B = 16384 214 / 317, 64 -> 515, G = 20, B = 4096 126 / 147).
+    const int s8 = fit_sums(S < 1024 ? S : 1024);
+    const bool pays8 = g.n_out % 8 == 0 ||
+                       (g.n_in >= 16 && B * g.n_in >= 1 << 17 && g.rows <= 128 && (g.n_out - 1) % 512 >= 256);
+    // every width has a variant (widths that are no multiple of T run its ragged build)
+    if (g.n_out > 256 && pays8 && s8 <= 1024) {
+        p.T = 8;
+        p.streams = 1;
+        S = s8;
+    } else {
+        S = fit_sums(S);
+        if (g.n_out > 32) {
+            p.T = 4;
+            p.streams = g.n_out > 128 ? 1 : (g.n_out > 64 ? 2 : 4);
+        } else if (g.n_out > 16) {
+            p.T = 2;        // 16 lanes x 2 outputs cover the layer: no idle lanes in a stream
+            p.streams = 4;
+        } else {
+            p.T = g.n_out % 4 == 0 ? 4 : 1;
+            p.streams = 4;
+        }
+    }
+    const int tile = (64 / p.streams) * p.T;
+    p.n_jt = (g.n_out + tile - 1) / tile;
     p.S = S;
     p.hk = high_degree ? 1 : 0;
     p.L = high_degree ? 2 * S : S;

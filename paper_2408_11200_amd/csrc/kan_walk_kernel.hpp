@@ -467,8 +467,11 @@ void walk_launch(bool dx, unsigned blocks, hipStream_t st, const SplineGeom &g, 
                         int64_t B, const WalkPlan &p, int bpc, int m, int prezeroed, float *carry,
                         int *seg_row, int chunk0, int n_chunks)
 {
-    auto kern = dx ? (p.S > 1024 ? backward_walk_kernel<STREAMS, T, true, true, RAGGED> : backward_walk_kernel<STREAMS, T, true, false, RAGGED>)
-                   : (p.S > 1024 ? backward_walk_kernel<STREAMS, T, false, true, RAGGED> : backward_walk_kernel<STREAMS, T, false, false, RAGGED>);
+    auto kern = dx ? backward_walk_kernel<STREAMS, T, true, false, RAGGED> : backward_walk_kernel<STREAMS, T, false, false, RAGGED>;
+    if constexpr (T != 8) {            // eight outputs per lane: chunks of at most 1024 samples (plan_walk)
+        if (p.S > 1024)
+            kern = dx ? backward_walk_kernel<STREAMS, T, true, true, RAGGED> : backward_walk_kernel<STREAMS, T, false, true, RAGGED>;
+    }
     // the first round of a shared run finds its slabs zero and stores like an unshared run
     kern<<<blocks, 256, 0, st>>>(g, rec, gy, cf, w_b, part_c, part_b, gx, B, p.S, n_chunks, p.n_jt, bpc, m, prezeroed,
                                  p.n_seg, carry, seg_row, chunk0, (p.shared && chunk0 > 0) ? 1 : 0, p.L, p.hk);

@@ -159,7 +159,7 @@ __global__ __launch_bounds__(kRangeThreads) void range_finalize_kernel(const int
 // to fp32), pre = W1^T z + b1, hid = silu(pre).  A workgroup takes kHidRows consecutive rows, four threads a hidden unit
 // and kHidRows / 4 rows a thread, with the z rows and W1 in LDS: a row a workgroup re-read W1 (16 KB at 64 x 64) per row
 // and evaluated the frequencies anew.  What is left is mostly the sines in fp64 (48 000 rows in three launches: 84 -> 66 us;
-// 2 176 rows, a load of W1 at a time behind the sines 15 us, eight before them 11, a row a workgroup 10).
+// 1 400 rows, a load of W1 at a time behind the sines 15 us, eight before them 11, a row a workgroup 10).
 constexpr int kHidRows = 16;
 template <bool W1_LDS>
 __global__ __launch_bounds__(256) void cg_hidden_kernel(const float *__restrict__ E, const float *__restrict__ W1,

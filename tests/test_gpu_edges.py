@@ -107,6 +107,16 @@ def test_widths_that_are_no_multiple_of_the_lanes(B, n_in, n_out, G, k):
 
 
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (8200, 16, 257, 9, 3), (8200, 17, 509, 5, 2), (8200, 16, 777, 5, 3),        # eight outputs per lane, ragged: one tile and two
+    (8191, 16, 257, 9, 3), (8200, 16, 256 + 512, 6, 3), (8200, 15, 301, 9, 3),  # just not; a multiple of eight; too few inputs
+    (14500, 4, 264, 40000, 3),                      # partial sums ask for chunks of 2048: four outputs per lane
+    (4200, 16, 385, 9, 5),
+])
+def test_walk_of_wide_layers(B, n_in, n_out, G, k):
+    assert "backward_walk" in run_with_families(workloads.random_kan_layer(n_out, B, n_in, n_out, G, k, outside_frac=0.05))
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [
     (32800, 7, 30, 20, 3), (16400, 5, 37, 20, 3),                   # long-table kernel, one tile
     (16400, 70, 63, 700, 3),                                        # row-stream kernel
     (16400, 40, 9, 20, 3), (65540, 34, 9, 20, 3),                   # narrow kernel past the direct one
