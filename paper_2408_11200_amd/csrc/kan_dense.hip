@@ -10,7 +10,6 @@
 //   dL/dx:                dP : (gy . C^T)    (per sample the dot product of its derivative row with gy . C^T)
 // with v_mfma_f32_16x16x4_f32, MT tiles of 16 rows by NTL tiles of 16 outputs.  The running sums stay in registers over
 // the sub-chunks of a chunk; chunks are added by the reduction in fp64, so results are bit-reproducible.
-#include <type_traits>
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
 
@@ -21,8 +20,12 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSub = 256;               // samples a workgroup holds at a time, one per thread
-constexpr int kPad = 4;                 // floats a LDS row is padded by: 16 rows x 4 columns then hit 64 banks.  The first
-                                        // of a basis row's holds the sample's cell
+constexpr int kPad = 4;                 // floats a LDS row is padded by: 16 rows x 4 columns then hit 64 banks
+
+// What tells the rows of a sample from the others in its basis row is that their bits are not all zero: a zero weight inside
+// the window is kept as -0.  Multiplied it stays zero, except by an infinity or NaN, which it must not hide.
+__device__ __forceinline__ float in_window(float w) { return w == 0.0f ? -0.0f : w; }
+__device__ __forceinline__ bool is_in_window(float w) { return __float_as_uint(w) != 0u; }
 
 template <int MT, int NTL>
 constexpr size_t dense_lds_bytes()
@@ -52,7 +55,6 @@ __global__ __launch_bounds__(256) void backward_dense_kernel(SplineGeom g, const
 
     for (int e = tid; e < kSub * GS; e += 256) gt[e] = 0.0f;           // columns past n_out stay zero
     for (int e = tid; e < kSub * PS; e += 256) P[e] = 0.0f;
-    bool c_finite = true;
     if (gx) {
         for (int e = tid; e < 16 * MT * GS; e += 256) {
             const int m = e / GS, j = e - m * GS;
@@ -65,7 +67,6 @@ __global__ __launch_bounds__(256) void backward_dense_kernel(SplineGeom g, const
                     v = w_b[(int64_t)i * g.n_out + j];
                 }
             }
-            c_finite &= fabsf(v) <= 3.402823466e38f;
             C[e] = v;
         }
     }
@@ -76,13 +77,7 @@ __global__ __launch_bounds__(256) void backward_dense_kernel(SplineGeom g, const
         for (int b = 0; b < NTL; ++b) acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     const int s_inc = 256 / g.n_out, j_inc = 256 - s_inc * g.n_out;
     float *mine = P + tid * PS;                                        // this thread's sample
-    // whether row m (rows: the base row) belongs to a sample of this cell.  A weight there may be zero and still counts:
-    // zero times an infinite gradient or coefficient is NaN
-    auto touches = [&](int m, float cell) {
-        const bool spline = (unsigned)(m - __float_as_int(cell)) <= (unsigned)g.k && m < g.rows;
-        return spline || (m == g.rows && g.base_act != 0);
-    };
-    c_finite = __syncthreads_and(c_finite ? 1 : 0) != 0;
+    __syncthreads();
 
     for (int64_t b0 = c0; b0 < c1; b0 += kSub) {
         const int n_c = (int)(c1 - b0 < kSub ? c1 - b0 : kSub);
@@ -104,9 +99,8 @@ __global__ __launch_bounds__(256) void backward_dense_kernel(SplineGeom g, const
             p = pair_eval<true>(x[(b0 + tid) * g.n_in + i], g, i);
 #pragma unroll
             for (int q = 0; q < kMaxK; ++q)
-                if (p.cell + q >= 0 && p.cell + q < g.rows) mine[p.cell + q] = p.w[q];
-            mine[g.rows] = p.base;
-            mine[16 * MT] = __int_as_float(p.cell);
+                if (q <= g.k && p.cell + q >= 0 && p.cell + q < g.rows) mine[p.cell + q] = in_window(p.w[q]);
+            if (g.base_act) mine[g.rows] = in_window(p.base);
         }
         // an infinite or NaN gradient must not reach the rows its sample does not touch: such a sub-chunk is summed
         // entry by entry below
@@ -114,17 +108,15 @@ __global__ __launch_bounds__(256) void backward_dense_kernel(SplineGeom g, const
         // each wave its own 64 samples
         const float *gw = gt + wave * 64 * GS, *Pw = P + wave * 64 * PS;
         if (part_c && !all_finite) {
-            for (int s = 0; s < 64 && wave * 64 + s < n_c; ++s)
+            for (int s = 0; s < 64; ++s)
 #pragma unroll
                 for (int a = 0; a < MT; ++a)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const int m = 16 * a + 4 * l4 + v;
-                        const float w = Pw[s * PS + m];
-                        const bool hit = touches(m, Pw[s * PS + 16 * MT]);
+                        const float w = Pw[s * PS + 16 * a + 4 * l4 + v];
 #pragma unroll
                         for (int b = 0; b < NTL; ++b)
-                            if (hit) acc[a][b][v] = fmaf(w, gw[s * GS + 16 * b + l16], acc[a][b][v]);
+                            if (is_in_window(w)) acc[a][b][v] = fmaf(w, gw[s * GS + 16 * b + l16], acc[a][b][v]);
                     }
         } else if (part_c) {
 #pragma unroll 4
@@ -146,14 +138,13 @@ __global__ __launch_bounds__(256) void backward_dense_kernel(SplineGeom g, const
         if (live) {
 #pragma unroll
             for (int q = 0; q < kMaxK; ++q)
-                if (p.cell + q >= 0 && p.cell + q < g.rows) mine[p.cell + q] = gx ? p.dw[q] : 0.0f;
-            mine[g.rows] = gx ? p.dbase : 0.0f;
+                if (q <= g.k && p.cell + q >= 0 && p.cell + q < g.rows) mine[p.cell + q] = gx ? in_window(p.dw[q]) : 0.0f;
+            if (g.base_act) mine[g.rows] = gx ? in_window(p.dbase) : 0.0f;
         }
         if (gx) {
             __syncthreads();
-            // one tile of 16 samples.  Rows outside a sample's window add nothing, whatever they hold; EXACT as touches()
-            // says, else (finite operands) by the zero weight, which costs less
-            auto dx_tile = [&](int st, auto exact) {
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {            // tiles of 16 samples
                 f32x4 h[MT];
 #pragma unroll
                 for (int a = 0; a < MT; ++a) h[a] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -172,9 +163,7 @@ __global__ __launch_bounds__(256) void backward_dense_kernel(SplineGeom g, const
 #pragma unroll
                     for (int a = 0; a < MT; ++a) {
                         const float w = Pw[s * PS + 16 * a + l16];
-                        bool in = w != 0.0f;
-                        if constexpr (decltype(exact)::value) in = touches(16 * a + l16, Pw[s * PS + 16 * MT]);
-                        d = in ? fmaf(w, h[a][v], d) : d;
+                        d = is_in_window(w) ? fmaf(w, h[a][v], d) : d;        // rows outside the window: nothing, whatever they hold
                     }
                     d += __shfl_xor(d, 1, 64);
                     d += __shfl_xor(d, 2, 64);
@@ -183,13 +172,6 @@ __global__ __launch_bounds__(256) void backward_dense_kernel(SplineGeom g, const
                     const int64_t b = b0 + wave * 64 + s;
                     if (l16 == 0 && b < c1) gx[b * g.n_in + i] = d;
                 }
-            };
-            if (all_finite && c_finite) {
-#pragma unroll
-                for (int st = 0; st < 4; ++st) dx_tile(st, std::false_type{});
-            } else {
-#pragma unroll 1
-                for (int st = 0; st < 4; ++st) dx_tile(st, std::true_type{});
             }
             __syncthreads();
             if (live) {
