@@ -473,6 +473,7 @@ __global__ __launch_bounds__(256) void embed_grad_kernel(const float *__restrict
                 __syncthreads();
             }
             if (f < d_feat)
+#pragma unroll 8
                 for (int c = 0; c < n_c; ++c) e += (double)W1[(int64_t)f * d_hid + c0 + c] * colsum[0][c];
         }
         if (f < d_feat) gE[(int64_t)i * d_feat + f] = (float)e;
