@@ -129,13 +129,23 @@ __global__ __launch_bounds__(NT) void dparam_reduce_kernel(const float *__restri
             double a[T];
 #pragma unroll
             for (int r = 0; r < T; ++r) a[r] = 0.0;
-            for (int c = share; c < n_chunks; c += 8 * CS) {          // eight chunks in flight, the last ones too
+            int c = share;
+            for (; c + 7 * CS < n_chunks; c += 8 * CS) {          // eight chunks in flight
                 float v[8][T];
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (c + u * CS < n_chunks) reduce_load<T>(part_c + (c + u * CS) * slab + at, v[u]);
+                for (int u = 0; u < 8; ++u) reduce_load<T>(part_c + (c + u * CS) * slab + at, v[u]);
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
+#pragma unroll
+                    for (int r = 0; r < T; ++r) a[r] += (double)v[u][r];
+            }
+            for (; c < n_chunks; c += 4 * CS) {                   // and four of the last ones
+                float v[4][T];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (c + u * CS < n_chunks) reduce_load<T>(part_c + (c + u * CS) * slab + at, v[u]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
                     if (c + u * CS < n_chunks) {
 #pragma unroll
                         for (int r = 0; r < T; ++r) a[r] += (double)v[u][r];
