@@ -205,8 +205,8 @@ WalkPlan plan_walk(const SplineGeom &g, int64_t B, bool allow_shared, bool high_
     // outputs / eight: 16 -> 300, G = 20, B = 16384 107 / 97 us, 64 -> 300, G = 5, B = 16384 282 / 236; but 2 -> 300, G = 20,
     // B = 65536 101 / 137, 16 -> 300, G = 1000, B = 16384 214 / 317, 64 -> 515, G = 20, B = 4096 126 / 147).
     const int s8 = fit_sums(S < 1024 ? S : 1024);
-    const bool pays8 = g.n_out % 8 == 0 ||
-                       (g.n_in >= 16 && B * g.n_in >= 1 << 17 && g.rows <= 128 && (g.n_out - 1) % 512 >= 256);
+    const bool pays8 = g.n_out % 8 == 0 || (g.n_in >= 16 && B * g.n_in >= 1 << 17 && g.rows <= (B <= 16384 ? 320 : 128) &&
+                                            (g.n_out - 1) % 512 >= 256);
     // every width has a variant (widths that are no multiple of T run its ragged build)
     if (g.n_out > 256 && pays8 && s8 <= 1024) {
         p.T = 8;
