@@ -89,6 +89,22 @@ struct BackwardPlan {
     size_t tail_bytes;      // scratch of the reduction over the chunks (row slices of gw_s)
 };
 
+// Backward pass of few samples and inputs on a long table, at a width the walk has a ragged build for: a list of so few
+// records steps through more rows than it has samples, and the generic kernels gather as well.  Generic / walk, us:
+//   2 -> 37    G = 100: B = 64 26 / 78, 256 49 / 58; G = 1000: B = 2048 99 / 145, 4096 101 / 131
+//   2 -> 65    G = 20: B = 64 36 / 43;    2 -> 75, G = 1000: B = 64 28 / 103;    2 -> 130, G = 1000: B = 512 64 / 81
+//   4 -> 33    G = 100: B = 128 39 / 74
+//   16 -> 33   G = 100: B = 64 50 / 108, 256 75 / 61; G = 1000: B = 512 87 / 149;    64 -> 33, G = 100: B = 64 134 / 110
+bool generic_pays(const SplineGeom &g, int64_t B)
+{
+    const int n = g.n_out, rows = g.rows;
+    const bool ragged = n > 16 && (n <= 32 ? n % 2 : n % 4) != 0, high = g.k > 3;
+    if (!ragged || n > 192 || rows >= (high ? 4096 : 65536)) return false;
+    if (g.n_in < 8)
+        return B <= (rows < 16 ? 16 : rows < 64 ? 64 : rows < 256 ? (n > 64 ? 128 : 256) : (n > 64 || rows >= 4096) ? 512 : 4096);
+    return g.n_in < 32 && n <= 64 && rows >= 64 && rows < 4096 && B <= (high ? 64 : (rows < 256 ? 128 : 512));
+}
+
 BackwardPlan backward_plan(const kan_layer_desc *d, int64_t B)
 {
     SplineGeom g = geom_of(d);
@@ -104,7 +120,7 @@ BackwardPlan backward_plan(const kan_layer_desc *d, int64_t B)
         return bp;
     }
     // degrees 4 and 5 walk two four-row records per pair
-    bp.wp = plan_walk(g, B, true, high_degree(d));
+    bp.wp = generic_pays(g, B) ? WalkPlan{} : plan_walk(g, B, true, high_degree(d));
     bp.walk = bp.wp.ok != 0;
     bp.tail_bytes = align_up(reduce_scratch_bytes(g.n_in, g.rows, g.n_out));
     if (bp.walk) {

@@ -95,15 +95,38 @@ def test_batch_past_the_threads_of_one_launch():
 
 
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
-    (700, 5, 17, 9, 3), (700, 5, 31, 300, 3),       # two outputs per lane, the last lane moved back; sparse walk
-    (1100, 4, 33, 9, 3), (900, 4, 63, 12, 2),       # four per lane, four streams
+    (700, 5, 17, 9, 3), (1100, 4, 33, 9, 3), (900, 4, 63, 12, 2),   # dense basis rows
+    (700, 5, 31, 300, 3),                           # generic: few samples, few inputs, a long table
     (900, 3, 65, 9, 3), (2100, 3, 127, 40, 1),      # two streams
     (900, 3, 130, 9, 3), (700, 3, 255, 10, 3),      # one stream
-    (600, 2, 257, 9, 3), (600, 2, 300, 9, 3), (500, 2, 515, 9, 3),      # eight per lane, one tile and two
+    (600, 2, 257, 9, 3), (600, 2, 300, 9, 3), (500, 2, 515, 9, 3),      # one stream, two tiles and three
     (700, 4, 35, 10, 5),                            # two records per pair
 ])
 def test_widths_that_are_no_multiple_of_the_lanes(B, n_in, n_out, G, k):
     run_layer_parity(workloads.random_kan_layer(n_out, B, n_in, n_out, G, k, outside_frac=0.2))
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k,family", [
+    (256, 7, 37, 100, 3, "dparam_generic"), (257, 7, 37, 100, 3, "backward_walk"),
+    (128, 2, 127, 100, 3, "dparam_generic"), (129, 2, 127, 100, 3, "backward_walk"),
+    (512, 31, 19, 2000, 2, "dparam_generic"), (512, 32, 19, 2000, 2, "backward_walk"),
+    (64, 8, 63, 80, 5, "dparam_generic"), (64, 8, 64, 80, 5, "backward_walk"),
+    (64, 3, 193, 70, 3, "backward_walk"), (64, 3, 20, 70, 3, "backward_walk"),
+])
+def test_few_samples_of_ragged_widths(B, n_in, n_out, G, k, family):
+    assert family in run_with_families(workloads.random_kan_layer(n_out, B, n_in, n_out, G, k, outside_frac=0.1))
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (1500, 33, 31, 100, 3),            # two outputs per lane, the last lane moved back: single-level sums,
+    (20000, 14, 17, 80, 3),            # two-level sums of chunks of 2048,
+    (3000, 40, 19, 1100, 3),           # zeroed tables that the walk jumps through
+    (9000, 9, 37, 70, 3), (9000, 9, 63, 90, 1),     # four per lane, many segments
+    (70000, 8, 18, 9, 3),              # two per lane, many segments of few rows
+    (900, 40, 47, 2000, 3),            # four per lane, zeroed tables
+])
+def test_ragged_walk(B, n_in, n_out, G, k):
+    assert "backward_walk" in run_with_families(workloads.random_kan_layer(n_out + 5, B, n_in, n_out, G, k, outside_frac=0.1))
 
 
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
@@ -135,7 +158,8 @@ def test_ragged_width_on_shared_partial_tables():
 
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
     (8192, 2, 3, 5, 3), (9000, 3, 4, 700, 3),       # one output per lane; row slices added by a second kernel
-    (70000, 2, 18, 9, 3), (33000, 3, 34, 3, 2),     # many segments of few rows, ragged tiles
+    (70000, 2, 18, 9, 3),                           # dense basis rows: many chunks
+    (33000, 3, 34, 3, 2),                           # many segments of few rows, ragged tiles
     (2500, 40, 520, 6, 3),                          # small workgroups (more than 512 of them), two tiles
     (40000, 3, 20, 1030, 5),                        # two records per pair, long table
 ])
@@ -157,7 +181,7 @@ def test_reduction_adds_the_carry_rows(B, n_in, n_out, G, k):
     (1, 2, 1, 1, 1), (255, 3, 5, 12, 3), (257, 2, 16, 12, 3),       # one tile of 16 rows (12 + 3 + the base row) and outputs
     (1000, 2, 17, 13, 3), (700, 3, 32, 28, 3),                      # just past a tile; the last of two tiles
     (600, 2, 33, 29, 3), (513, 2, 64, 60, 3), (513, 2, 64, 61, 3),  # four tiles; the first length left to the walk
-    (65536, 16, 5, 9, 2), (65537, 16, 5, 9, 2),                     # sixteen sub-chunks a chunk; the first batch left to the walk
+    (65536, 16, 5, 9, 2), (65537, 16, 5, 9, 2),                     # eight sub-chunks a chunk; the first batch left to the walk
 ])
 def test_dense_basis_backward(B, n_in, n_out, G, k):
     run_layer_parity(workloads.random_kan_layer(n_out + 11, B, n_in, n_out, G, k, outside_frac=0.2))
