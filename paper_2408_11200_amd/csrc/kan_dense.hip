@@ -229,6 +229,8 @@ hipError_t dense_launch(const SplineGeom &g, const DensePlan &p, const float *x,
 //       16 -> 32, G = 10    B = 1024 34 / 22, 8192 41 / 25, 65536 100 / 149
 //       64 -> 64, G = 10    B = 1024 39 / 31, 8192 60 / 228;       2 -> 64   B = 65536 138 / 80
 //       16 -> 5, G = 55     B = 8192 43 / 36, 65536 87 / 164;      16 -> 32, G = 55   B = 1024 47 / 29, 8192 48 / 54
+// (A line on the pairs alone leaves some to the walk that this kernel would do in less: with two inputs, as 2 -> 64 shows, the
+// walk has few lists.)
 DensePlan plan_dense(const SplineGeom &g, int64_t B)
 {
     DensePlan p = {0, 0, 0};
@@ -238,7 +240,8 @@ DensePlan plan_dense(const SplineGeom &g, int64_t B)
                           : g.n_out <= 32 ? (short_rows ? 1 << 18 : 1 << 16)
                                           : 1 << 16;
     if (B * g.n_in > limit) return p;
-    // sub-chunks per chunk: as many as leave two workgroups per CU, at most 16 (the length of a running sum)
+    // sub-chunks per chunk: as many as leave two workgroups per CU.  Within the limits above that is eight at most (running
+    // sums of 512 samples a wave), or a chunk longer than the batch; the bound of 16 is not reached.
     int64_t sub = 1;
     const int64_t subs = (B + kSub - 1) / kSub;
     while (sub < 16 && (subs + 2 * sub - 1) / (2 * sub) * g.n_in >= 512) sub *= 2;

@@ -213,7 +213,7 @@ static hipError_t direct_latency(const SplineGeom &g, const float *x, const floa
 //                     past it: 256 -> 32, G = 1000: 32768 507 / 475, 65536 679 / 943
 //   generic           past L2: 256 -> 130, G = 300: B = 2048 244 / 215, 4096 307 / 444; in it: 8 -> 128, G = 100: 8192 14 / 15,
 //                     16384 23 / 27; 128 -> 37, G = 200: 32768 406 / 167
-//   narrow            64 -> 1, G = 20: B = 2048 19 / 12, 8192 19 / 41; 32 -> 4, G = 20: 16384 20 / 15, 65536 31 / 46;
+//   narrow            64 -> 1, G = 20: B = 2048 19 / 12, 4096 19 / 22, 8192 19 / 41; 32 -> 1: 2048 13 / 11, 4096 11 / 19; 32 -> 4, G = 20: 16384 20 / 15, 65536 31 / 46;
 //                     32 -> 16, G = 1000: 65536 478 / 49
 //   degrees 4 and 5   64 -> 4, G = 10000: B = 65536 481 / 96 (generic); 64 -> 300, G = 20: 4096 283 / 109 (512-wide tiles)
 // (sums of 4 and 6 products cost in proportion: the line counts them)
@@ -231,8 +231,9 @@ int forward_direct_plan(const SplineGeom &g, int64_t B)
     if (ni < 8) return B * tiles <= (n < 4 ? 1 << 12 : (n >= 128 && (lds || lds_rows) ? 3 << 12 : 1 << 13)) ? 1 : 0;
     if (n < 4) {                                     // one output per lane at any batch: 16 lanes for at most three
         if (!narrow) return B <= (ni >= 32 ? 1 << 13 : 1 << 11) ? 1 : 0;
-        const int64_t most = ni < 32 ? 1 << 12 : (n == 1 ? 32 : 64) * (int64_t)ni;
-        return B <= (most < (n == 1 ? 1 << 12 : 1 << 13) ? most : (n == 1 ? 1 << 12 : 1 << 13)) ? 1 : 0;
+        const int64_t per = (n == 1 ? 32 : 64) * (int64_t)ni, cap = n == 1 ? 1 << 12 : 1 << 13;
+        const int64_t most = ni < 32 ? 1 << 12 : (per < 1 << 11 ? 1 << 11 : (per < cap ? per : cap));
+        return B <= most ? 1 : 0;
     }
     if (narrow) return load <= (ni >= 64 || (ni >= 32 && n >= 8) ? 1 << 20 : (ni >= 32 ? 1 << 18 : 1 << 17)) ? 1 : 0;
     if (lds_rows) return load <= (ni >= 32 ? 1 << 20 : (ni >= 16 ? 3 << 18 : 1 << 19)) ? 1 : 0;
