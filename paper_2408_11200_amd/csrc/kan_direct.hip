@@ -159,9 +159,10 @@ __global__ __launch_bounds__(64 * NW) void forward_direct_kernel(SplineGeom g, c
     }
 }
 
-// A launch takes fewer than 2^32 threads (hipModuleLaunchKernel): larger batches go in parts of half that.  Folds of more
-// than 2^20 floats go in a launch of their own, with wide accesses: at 2^20 floats both take the same, at 2^18 the launch
-// costs 1.5 us more, at 2^24 (16 -> 128, G = 10000) 22 us less.
+// A launch takes fewer than 2^32 threads (hipModuleLaunchKernel): larger batches go in parts of half that.  Large folds
+// go in a launch of their own, with wide accesses: beside many samples at 2^20 floats both take the same, at 2^18 the launch
+// costs 1.5 us more, at 2^24 (16 -> 128, G = 10000) 22 us less; beside few samples the fold in the launch has the chip to itself
+// (32 -> 64, G = 1000, B = 64, 2^21 floats: 9 us in the launch, 12 behind one; 256 -> 33, G = 1000, 2^23: 23 / 32).
 template <int LPS, int T, int NS, int NW>
 static hipError_t direct_launch(const SplineGeom &g, const float *x, const float *coef, const float *w_s,
                                 const float *w_b, float *cf, float *y, int64_t B, hipStream_t st)
@@ -169,7 +170,7 @@ static hipError_t direct_launch(const SplineGeom &g, const float *x, const float
     constexpr int64_t kThreads = 64 * NW;
     const int n_tiles = (g.n_out + LPS * T - 1) / (LPS * T);
     const int64_t total = (int64_t)g.n_in * (g.rows + 1) * g.n_out, per = kThreads * kFoldPerThread;
-    if (cf && total > 1 << 20) {
+    if (cf && total > (B <= 512 ? 1 << 23 : (B <= 2048 ? 1 << 21 : 1 << 20))) {
         if (hipError_t e = launch_fold_scale(coef, w_s, g.base_act ? w_b : nullptr, cf, g.n_in, g.rows, g.n_out, st);
             e != hipSuccess)
             return e;
@@ -215,7 +216,8 @@ static hipError_t direct_latency(const SplineGeom &g, const float *x, const floa
 //                     16384 23 / 27; 128 -> 37, G = 200: 32768 406 / 167
 //   narrow            64 -> 1, G = 20: B = 2048 19 / 12, 4096 19 / 22, 8192 19 / 41; 32 -> 1: 2048 13 / 11, 4096 11 / 19; 32 -> 4, G = 20: 16384 20 / 15, 65536 31 / 46;
 //                     32 -> 16, G = 1000: 65536 478 / 49
-//   degrees 4 and 5   64 -> 4, G = 10000: B = 65536 481 / 96 (generic); 64 -> 300, G = 20: 4096 283 / 109 (512-wide tiles)
+//   degrees 4 and 5   64 -> 4, G = 10000: B = 65536 481 / 96 (generic); 64 -> 300, G = 20: 4096 283 / 109 (512-wide tiles);
+//                     64 -> 64, G = 300: 32768 140 / 131, 65536 252 / 277 (row stream)
 // (sums of 4 and 6 products cost in proportion: the line counts them)
 int forward_direct_plan(const SplineGeom &g, int64_t B)
 {
@@ -231,23 +233,27 @@ int forward_direct_plan(const SplineGeom &g, int64_t B)
     if (ni < 8) return B * tiles <= (n < 4 ? 1 << 12 : (n >= 128 && (lds || lds_rows) ? 3 << 12 : 1 << 13)) ? 1 : 0;
     if (n < 4) {                                     // one output per lane at any batch: 16 lanes for at most three
         if (!narrow) return B <= (ni >= 32 ? 1 << 13 : 1 << 11) ? 1 : 0;
-        const int64_t per = (n == 1 ? 32 : 64) * (int64_t)ni, cap = n == 1 ? 1 << 12 : 1 << 13;
-        const int64_t most = ni < 32 ? 1 << 12 : (per < 1 << 11 ? 1 << 11 : (per < cap ? per : cap));
+        // (longer tables cost the narrow kernel more, whose four lanes a sample read rows one at a time)
+        const int64_t per = n == 1 ? 32ll * ni : (g.rows >= 4096 ? 128ll : 64ll) * ni, cap = n == 1 ? 1 << 12 : 1 << 13;
+        const int64_t low = n == 1 && g.rows >= 128 ? 1 << 10 : 1 << 11;
+        const int64_t most = ni < 32 ? 1 << 12 : (per < low ? low : (per < cap ? per : cap));
         return B <= most ? 1 : 0;
     }
-    if (narrow) return load <= (ni >= 64 || (ni >= 32 && n >= 8) ? 1 << 20 : (ni >= 32 ? 1 << 18 : 1 << 17)) ? 1 : 0;
+    constexpr bool six = kMaxK == 6;
+    if (narrow)
+        return load <= (ni >= 64 || (ni >= 32 && (n >= 8 || g.rows >= 512)) ? 1 << 20 : (ni >= 32 ? 1 << 18 : 1 << 17)) ? 1 : 0;
     if (lds_rows) return load <= (ni >= 32 ? 1 << 20 : (ni >= 16 ? 3 << 18 : 1 << 19)) ? 1 : 0;
     if (forward_rows_plan(g)) {
-        if (!in_l2) return load <= 1 << 20 ? 1 : 0;
-        return n <= 32 || ni >= 64 || load <= (ni >= 32 ? 3 << 20 : 1 << 21) ? 1 : 0;
+        if (!in_l2) return load <= (six && n <= 48 ? 3 << 19 : 1 << 20) ? 1 : 0;
+        if (n <= 32) return ni >= 32 || load <= (six ? 3 << 20 : 1 << 21) ? 1 : 0;
+        return (n <= 48 && ni >= 64) || load <= (ni >= 32 || six ? 3 << 20 : 1 << 21) ? 1 : 0;
     }
-    if (lds == 4) return load <= (ni >= 32 ? 7 << 19 : (ni >= 16 || kMaxK == 6 ? 3 << 20 : 1 << 21)) ? 1 : 0;
-    if (lds == 8 && kMaxK == 6) return load <= (ni >= 16 ? 5 << 19 : 3 << 19) ? 1 : 0;
-    if (lds == 8) return load <= (ni >= 256 ? 1 << 21 : (ni >= 16 ? 3 << 19 : 1 << 20)) ? 1 : 0;
+    if (lds == 4) return load <= (ni >= 32 ? 7 << 19 : (ni >= 16 || six ? 3 << 20 : 1 << 21)) ? 1 : 0;
+    if (lds == 8) return load <= (six ? 5 << 19 : (ni >= 16 ? 1 << 21 : 1 << 20)) ? 1 : 0;
     // generic
-    if (n <= 32) return ni >= 16 || load <= 1 << 20 ? 1 : 0;
-    if (in_l2 && (n < 256 || n % 4 != 0)) return ni >= 16 || load <= (n >= 128 ? 1 << 20 : 1 << 21) ? 1 : 0;
-    return load <= (in_l2 || kMaxK == 6 ? 3 << 18 : 1 << 19) ? 1 : 0;
+    if (n <= 32) return ni >= 16 || load <= (six && n > 16 ? (in_l2 ? 3 << 20 : 3 << 19) : 1 << 20) ? 1 : 0;
+    if (in_l2 && (n < 256 || n % 4 != 0)) return ni >= 16 || load <= (n >= 128 ? 1 << 20 : (six ? 3 << 20 : 1 << 22)) ? 1 : 0;
+    return load <= (in_l2 || six ? 3 << 18 : 1 << 19) ? 1 : 0;
 }
 
 hipError_t launch_forward_direct(const SplineGeom &g, const float *x, const float *coef, const float *w_s,

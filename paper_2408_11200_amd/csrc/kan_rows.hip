@@ -133,12 +133,12 @@ __global__ __launch_bounds__(256) void forward_rows_kernel(SplineGeom g, const f
 // 0: not applicable, else outputs per lane.  A DPP row evaluates and sums 16 inputs at a time, so layers of few inputs do
 // better on the generic kernel (B = 65536, generic / this: 2 -> 31, G = 20 18 / 46 us; 4 -> 64, G = 1000 33 / 46; 16 -> 64,
 // G = 1000 112 / 56; windows of six rows need 16 inputs), and so do nearly full rows that are no multiple of 16 bytes in
-// windows of six past L2 (32 -> 63, G = 10000, k = 5, B = 65536: 331 / 436).
+// windows of six of very long tables (32 -> 63, k = 5, B = 65536: G = 10000 331 / 436, but G = 1000 239 / 171).
 int forward_rows_plan(const SplineGeom &g)
 {
     if (g.rows < kMaxK || g.slab_rows != g.rows + 1 || g.n_out <= 16 || g.n_out > 64) return 0;
     if (g.n_in < (kMaxK == 6 ? 16 : 8)) return 0;
-    if (kMaxK == 6 && g.n_out > 48 && g.n_out % 4 != 0 && (int64_t)g.n_in * g.slab_rows * g.n_out * 4 > 8ll << 20) return 0;
+    if (kMaxK == 6 && g.n_out > 48 && g.n_out % 4 != 0 && g.rows > 4096) return 0;
     return g.n_out <= 32 ? 2 : 4;
 }
 
