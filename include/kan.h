@@ -95,9 +95,14 @@ typedef struct ukan_grads {
 const char *kan_strerror(int status);
 
 /* Scratch bytes needed by kan_forward (pass = KAN_PASS_FORWARD) or kan_backward for batch B.
-   Returns 0 for an invalid descriptor.  Forward: the scale-folded table.  Backward: that, the transposed input, two
-   sorted record arrays (44 bytes per (sample, input) pair) and the per-chunk partial gradient tables: a small multiple
-   of B * n_in * 48 bytes + at most 2 GiB of partial tables (more only when a single table exceeds that). */
+   Returns 0 for an invalid descriptor.  Forward: the scale-folded table.  Backward, on top of that:
+   - ordinarily the transposed input, two sorted record arrays (44 bytes per (sample, input) pair, 88 for degrees 4 and 5)
+     and the per-chunk partial gradient tables: a small multiple of B * n_in * 48 bytes + at most 2 GiB of partial tables
+     (more only when a single table exceeds that).  Widths that are no multiple of four need as much as the others
+     (37 -> 19, G = 12, k = 5, B = 131071: 468 MiB);
+   - layers of at most 63 rows and 64 outputs with few pairs: no records, only partial tables, one for every 256 .. 2048
+     samples; and where the generic kernels take the pass (tables of fewer than four rows or 2^19 and more, few samples of
+     ragged widths): one partial table for every 1024 samples, at most 512 MiB of them. */
 size_t kan_workspace_bytes(const kan_layer_desc *desc, int64_t B, int pass);
 
 /* Forward pass of one layer, Eqs. "activation" + "kanphi" + "matrixform":
