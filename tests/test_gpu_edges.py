@@ -13,21 +13,34 @@ from test_gpu_ukan import make as ukan_make, run as ukan_run
 pytestmark = pytest.mark.gpu
 
 
-def run_with_families(w):
-    """Parity of a layer's backward pass; returns the kernel families that it launched."""
-    s, p = w.layers[0], w.params[0]
-    run_layer_parity(w, gx_in_grid_units=s.G > 1000)
-    x, coef, w_s, w_b, gy = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"], w.gy))
+def families_of(call):
+    """The kernel families that a call launches."""
     seen = set()
     hook = ctypes.CFUNCTYPE(None, ctypes.c_char_p, ctypes.c_void_p)(lambda family, stream: seen.add(family.decode()))
     none = ctypes.CFUNCTYPE(None, ctypes.c_char_p, ctypes.c_void_p)(lambda family, stream: None)
     binding.kan_set_launch_observer(hook, none)
     try:
-        binding.kan_backward(s, x, coef, w_s, w_b, gy)
+        call()
     finally:
         binding.kan_set_launch_observer(None, None)
     torch.cuda.synchronize()
     return seen
+
+
+def run_with_families(w):
+    """Parity of a layer's backward pass; returns the kernel families that it launched."""
+    s, p = w.layers[0], w.params[0]
+    run_layer_parity(w, gx_in_grid_units=s.G > 1000)
+    x, coef, w_s, w_b, gy = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"], w.gy))
+    return families_of(lambda: binding.kan_backward(s, x, coef, w_s, w_b, gy))
+
+
+def forward_with_families(w):
+    """Parity of a layer's forward pass; returns the kernel families that it launched."""
+    s, p = w.layers[0], w.params[0]
+    run_layer_parity(w, check_grads=False)
+    x, coef, w_s, w_b = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"]))
+    return families_of(lambda: binding.kan_forward(s, x, coef, w_s, w_b))
 
 
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
@@ -63,21 +76,27 @@ def test_tile_whose_lane_starts_in_the_tile_before(n_out, k):
 
 
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
-    (33000, 8, 17, 6, 3), (66000, 33, 31, 9, 1), (40000, 9, 18, 9000, 3),       # two outputs a lane, ragged, an input past 16
-    (33000, 17, 30, 2500, 5), (66000, 16, 33, 9, 4),                            # window of six rows
+    (33000, 8, 17, 18000, 3), (40000, 9, 18, 20000, 1),     # two outputs a lane, tables past L2, ragged rows
+    (66000, 17, 31, 5000, 2), (66005, 8, 32, 3000, 3),      # tables in L2, an input past sixteen; a whole tile
+    (33000, 17, 30, 6000, 5),                               # two a lane, window of six rows
+    (16400, 17, 33, 5000, 3), (16403, 9, 64, 9000, 3), (66000, 16, 33, 9, 4),       # four a lane
 ])
 def test_row_stream_kernel(B, n_in, n_out, G, k):
-    w = workloads.random_kan_layer(n_in, B, n_in, n_out, G, k, outside_frac=0.1)
-    run_layer_parity(w, check_grads=False)
+    assert "forward_rows" in forward_with_families(workloads.random_kan_layer(n_in, B, n_in, n_out, G, k, outside_frac=0.1))
 
 
-@pytest.mark.parametrize("B,n_in,n_out,G,k", [
-    (8192, 7, 17, 6, 3), (8193, 7, 17, 6, 3), (4097, 2, 3, 6, 3), (4100, 3, 130, 6, 3),     # few inputs: the line and past it
-    (16500, 7, 62, 30, 5), (2051, 8, 1, 7, 3), (8193, 64, 2, 7, 3),
-    (300, 16, 40, 1700, 3), (300, 16, 40, 1500, 2),         # folds of just more and less than 2^20 floats
+@pytest.mark.parametrize("B,n_in,n_out,G,k,family", [
+    (8192, 7, 17, 6, 3, "direct"), (8193, 7, 17, 6, 3, "generic"),      # few inputs: the line and past it
+    (4097, 2, 3, 6, 3, "narrow"), (4100, 3, 130, 6, 3, "lds"), (16500, 7, 62, 30, 5, "generic"),
+    (2048, 8, 1, 7, 3, "direct"), (2049, 8, 2, 7, 4, "generic"),        # one to three outputs
+    (2051, 8, 1, 7, 3, "direct"), (8193, 64, 2, 7, 3, "narrow"),
+    (65540, 34, 9, 20, 3, "narrow"), (66000, 33, 31, 9, 1, "direct"), (33000, 8, 17, 6, 3, "direct"),
+    (16400, 33, 64, 40, 3, "lds_rows"), (33000, 17, 30, 2500, 5, "direct"),
+    (300, 16, 40, 1700, 3, "direct"), (300, 16, 40, 1500, 2, "direct"),         # folds of just more and less than 2^20 floats
 ])
-def test_forward_lines(B, n_in, n_out, G, k):
-    run_layer_parity(workloads.random_kan_layer(n_in, B, n_in, n_out, G, k, outside_frac=0.1), check_grads=False)
+def test_forward_lines(B, n_in, n_out, G, k, family):
+    w = workloads.random_kan_layer(n_in, B, n_in, n_out, G, k, outside_frac=0.1)
+    assert "forward_" + family in forward_with_families(w)
 
 
 def test_batch_past_the_threads_of_one_launch():
@@ -140,12 +159,12 @@ def test_walk_of_wide_layers(B, n_in, n_out, G, k):
 
 
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
-    (32800, 7, 30, 20, 3), (16400, 5, 37, 20, 3),                   # long-table kernel, one tile
+    (32800, 7, 30, 20, 3), (16400, 5, 37, 20, 3),                   # generic; long-table kernel
     (16400, 70, 63, 700, 3),                                        # row-stream kernel
-    (16400, 40, 9, 20, 3), (65540, 34, 9, 20, 3),                   # narrow kernel past the direct one
-    (8200, 20, 127, 600, 3), (4200, 10, 260, 400, 3),               # long-table kernel with several tiles, generic
+    (16400, 40, 9, 20, 3), (65540, 34, 9, 20, 3),                   # direct, and the narrow kernel past it
+    (8200, 20, 127, 600, 3), (4200, 10, 260, 400, 3),               # direct after the fold kernel, generic
     (11000, 9, 130, 15, 3), (5200, 5, 259, 15, 3),                  # LDS-staged kernels
-    (16400, 8, 50, 700, 5), (7300, 4, 131, 12, 4),                  # window of six rows
+    (16400, 8, 50, 700, 5), (7300, 4, 131, 12, 4),                  # window of six rows: direct, LDS-staged
 ])
 def test_large_batches_of_ragged_widths(B, n_in, n_out, G, k):
     run_layer_parity(workloads.random_kan_layer(n_out + 1, B, n_in, n_out, G, k, outside_frac=0.1))
