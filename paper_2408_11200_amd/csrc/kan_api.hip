@@ -297,7 +297,7 @@ static int backward_impl(const kan_layer_desc *desc, int64_t B, const float *x, 
         float *part_c = (float *)at;
         float *part_b = (float *)((char *)part_c + (size_t)bp.n_slabs * folded_bytes(desc) + bp.tail_bytes);
         // partial slabs are laid out back to back with the unpadded slab size
-        CarryRows cr = {nullptr, nullptr, 1};
+        CarryRows cr = {nullptr, nullptr, 1, 0};
         hipError_t e = bp.dense.ok ? launch_backward_dense(g, bp.dense, x, gy, coef, w_s, w_b, want_params ? part_c : nullptr,
                                                            want_b ? part_b : nullptr, gx, B, st)
                        : bp.walk ? launch_backward_walk(g, bp.wp, x, gy, table, w_b, walk_scratch, fused_dx ? gx : nullptr,

@@ -72,7 +72,7 @@ hipError_t highk_backward(const HighKLayer &l, const float *x, const float *coef
         const bool want_b = gw_b && g.base_act;
         e = kan_k5::launch_dparam_generic(g, x, gy, part_c, want_b ? part_b : nullptr, B, n_chunks, chunk_len, st);
         if (e != hipSuccess) return e;
-        e = launch_dparam_reduce(part_c, want_b ? part_b : nullptr, CarryRows{nullptr, nullptr, 1}, coef, w_s, gcoef, gw_s, gw_b,
+        e = launch_dparam_reduce(part_c, want_b ? part_b : nullptr, CarryRows{nullptr, nullptr, 1, 0}, coef, w_s, gcoef, gw_s, gw_b,
                                  g.n_in, g.rows, g.n_out, n_chunks, n_chunks * kan_k5::dparam_generic_row_blocks(g.rows),
                                  nullptr, st);
         if (e != hipSuccess) return e;

@@ -103,8 +103,8 @@ struct WalkRecords {
     float *dw4;
 };
 
-hipError_t launch_sorted_records(const SplineGeom &g, const float *x, float *xT, int64_t B, int S, int row_bits,
-                                 const WalkRecords &rec, hipStream_t st);
+hipError_t launch_sorted_records(const SplineGeom &g, const float *xT, int64_t B, int S, int row_bits, const WalkRecords &rec,
+                                 hipStream_t st);
 
 // Chunk-sorted walk (large grids, narrow layers).  plan_walk().ok == 0: shape not covered.
 struct WalkPlan {
@@ -120,7 +120,9 @@ struct WalkPlan {
     int hk;              // 1: degrees 4 and 5.  A pair's window of six rows is walked as two records of four
                          // rows (rows 0..3 with the base term, rows 4..5), so a sorted list has L = 2 S entries
                          // and dL/dx is the sum of two partial results per output tile
-    int L;               // entries of one sorted list: S, or 2 S when hk
+    int L;               // entries of one sorted list: S, 2 S when hk, or what padded cells may take (quads)
+    int quads;           // 1: lists of padded cells and the quad walk (kan_quads.hpp), one entry a pair for every degree
+    int window;          // table rows of a window, and carry rows of a segment: 4, or 6 (quads of degrees 4 and 5)
 };
 // allow_shared: tables whose per-chunk partial slabs would not fit the budget are still planned, with the
 // chunks taking turns on the slabs that fit (ok stays 0 for them otherwise).

@@ -1,0 +1,8 @@
+// quad_walk_kernel with 2 streams per wave and 4 outputs per lane (kan_quads_kernel.hpp).
+#include "kan_quads_kernel.hpp"
+
+namespace kan {
+
+void quad_walk_s2t4(const QuadWalkArgs &a, unsigned blocks, hipStream_t st) { quad_walk_launch<2, 4>(a, blocks, st); }
+
+}  // namespace kan

@@ -1,0 +1,8 @@
+// quad_walk_kernel with 4 streams per wave and 2 outputs per lane (kan_quads_kernel.hpp).
+#include "kan_quads_kernel.hpp"
+
+namespace kan {
+
+void quad_walk_s4t2(const QuadWalkArgs &a, unsigned blocks, hipStream_t st) { quad_walk_launch<4, 2>(a, blocks, st); }
+
+}  // namespace kan

@@ -96,7 +96,7 @@ __global__ __launch_bounds__(NT) void dparam_reduce_kernel(const float *__restri
             const int c = e / cr.n_seg, k = e - c * cr.n_seg;
             const int first = cr.seg_row[((int64_t)c * n_in + i) * cr.n_seg + k];
             if (staged) seg_lds[e] = first;
-            const int lo = first > m_lo ? first : m_lo, hi = first + kMaxK < m_hi ? first + kMaxK : m_hi;
+            const int lo = first > m_lo ? first : m_lo, hi = first + cr.window < m_hi ? first + cr.window : m_hi;
             for (int m = lo; m < hi; ++m) {
                 const int bit = (m - m_lo) >> mark_shift;
                 if (k > 0) atomicOr(&marks[bit >> 5], 1u << (bit & 31));
@@ -152,14 +152,14 @@ __global__ __launch_bounds__(NT) void dparam_reduce_kernel(const float *__restri
                     }
             }
             if (cr.n_seg > 1 && live && marked(m)) {
-                // carry rows: segment k's four rows start at seg_row[k] (non-decreasing in k), so those of row m are
+                // carry rows: segment k's rows start at seg_row[k] (non-decreasing in k), so those of row m are
                 // neighbours: the first is searched for, then four at a time are read
                 for (int c = share; c < n_chunks; c += CS) {
                     const int64_t list = ((int64_t)c * n_in + i) * cr.n_seg;
                     int k = 1, hi = cr.n_seg;                         // segment 0 has no carry rows
                     while (k < hi) {
                         const int mid = (k + hi) >> 1;
-                        if (seg_first(c, mid) < m - (kMaxK - 1)) k = mid + 1;
+                        if (seg_first(c, mid) < m - (cr.window - 1)) k = mid + 1;
                         else hi = mid;
                     }
                     for (int hits = 4; hits == 4; k += 4) {
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(NT) void dparam_reduce_kernel(const float *__restri
                             const int first = k + u < cr.n_seg ? seg_first(c, k + u) : INT_MAX;
                             if (first > m) continue;
                             ++hits;
-                            reduce_load<T>(cr.carry + ((list + k + u) * kMaxK + (m - first)) * n_out + j, v[u]);
+                            reduce_load<T>(cr.carry + ((list + k + u) * cr.window + (m - first)) * n_out + j, v[u]);
                         }
 #pragma unroll
                         for (int u = 0; u < 4; ++u)

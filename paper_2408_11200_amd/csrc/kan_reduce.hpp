@@ -6,11 +6,12 @@
 namespace kan {
 
 // What the segments of a sorted list left behind for the rows of the segment after them (kan_walk.hip): carry row s of
-// segment k of list l belongs to table row seg_row[l * n_seg + k] + s.  n_seg == 1: nothing.
+// segment k of list l belongs to table row seg_row[l * n_seg + k] + s, s < window.  n_seg == 1: nothing.
 struct CarryRows {
     const int *seg_row;
     const float *carry;
     int n_seg;
+    int window;
 };
 
 // Sums n_chunks partial tables part_c[c][n_in][rows][n_out] (with their carry rows) and n_slices_b slices part_b[s][n_in][n_out]

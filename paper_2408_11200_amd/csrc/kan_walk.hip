@@ -1,5 +1,7 @@
-// Backward kernels built on pair records that are sorted by window row over a whole chunk of
-// the batch: the parameter gradients of every layer shape they cover, and dL/dx with them where
+// Planning and helper kernels of the backward walk, and its form built on pair records.  Where a chunk has a few samples for
+// every cell the walk goes over lists of padded cells instead (kan_quads_kernel.hpp); what follows here describes the records.
+//
+// Pair records are sorted by window row over a whole chunk of the batch: the parameter gradients of every layer shape they cover, and dL/dx with them where
 // that is the faster way.
 //
 // With many coefficient rows per input (G + k in the hundreds, or a generated UKAN table) a tile of
@@ -36,6 +38,7 @@
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
 #include "kan_highk.hpp"
+#include "kan_quads.hpp"
 #include "kan_sort.hpp"
 
 namespace kan {
@@ -131,7 +134,7 @@ __global__ __launch_bounds__(64 * NW) void cell_sort_kernel(SplineGeom g, const 
 // One thread per (chunk, input, output).  (Slabs of their own: the reduction over the chunks adds the carry rows.)
 __global__ __launch_bounds__(256) void walk_carry_kernel(SplineGeom g, const int *__restrict__ seg_row,
                                                          const float *__restrict__ carry, float *__restrict__ part_c,
-                                                         int n_chunks, int n_seg, int chunk0)
+                                                         int n_chunks, int n_seg, int chunk0, int window)
 {
     // n_chunks chunks starting at chunk0 of the batch; the launch's chunk number l adds to slab l
     const int64_t at = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -141,8 +144,8 @@ __global__ __launch_bounds__(256) void walk_carry_kernel(SplineGeom g, const int
     float *slab = part_c + at / g.n_out * g.rows * g.n_out + j;
     for (int k = 1; k < n_seg; ++k) {
         const int rf = seg_row[ci * n_seg + k];
-        const float *cr = carry + ((ci * n_seg + k) * kMaxK) * g.n_out + j;
-        for (int s = 0; s < kMaxK; ++s)
+        const float *cr = carry + ((ci * n_seg + k) * window) * g.n_out + j;
+        for (int s = 0; s < window; ++s)
             if (rf + s < g.rows) slab[(int64_t)(rf + s) * g.n_out] += cr[(int64_t)s * g.n_out];
     }
 }
@@ -175,13 +178,16 @@ int log2_exact(int v) { int b = 0; while ((1 << b) < v) ++b; return b; }
 
 // ---- planning and launch ---------------------------------------------------------------------
 
-WalkPlan plan_walk(const SplineGeom &g, int64_t B, bool allow_shared, bool high_degree)
+namespace {
+
+// quads: lists of padded cells where the shape allows (p.quads says), else one record a pair
+WalkPlan plan_lists(const SplineGeom &g, int64_t B, bool allow_shared, bool high_degree, bool quads)
 {
     WalkPlan p = {};
     if (g.rows < kMaxK || g.rows > kRtRowMask || B < 1) return p;
     if (high_degree && g.rows < 6) return p;          // a six-row window must fit the table
     const int64_t slab = (int64_t)g.n_in * g.rows * g.n_out * (int64_t)sizeof(float);
-    const int s_max = high_degree ? 4096 : 8192;       // two records per pair: 2 S keys to sort, 12 bits for the sample
+    const int s_max = high_degree && !quads ? 4096 : 8192;       // two records per pair: 2 S keys to sort, 12 bits for the sample
     auto pow2_floor = [s_max](int64_t v) { int64_t q = 256; while (q * 2 <= v && q < s_max) q *= 2; return (int)q; };
     // chunk length: a power of two between 256 and 8192 samples.  Every chunk writes a partial table that the reduction
     // reads back, so few long chunks are better, as long as
@@ -198,17 +204,20 @@ WalkPlan plan_walk(const SplineGeom &g, int64_t B, bool allow_shared, bool high_
     const int s_par = pow2_floor(share);
     S = S < s_par ? S : s_par;
     auto fit_sums = [&](int q) { while (q < s_max && ((B + q - 1) / q) * slab > (2ll << 30)) q *= 2; return q; };
-    // Eight outputs per lane (one tile covers 512 outputs: the per-record work is shared by twice as many) have registers
+    // Eight outputs per lane (one tile covers 512 outputs: the per-record work is shared by twice as many).  The quads take
+    // them with chunks of 2048 samples (512 -> 512, G = 20, B = 16384, walk + reduction: 1024 samples 1181 + 99 us, 2048 1149 +
+    // 52, 4096 1175 + 36 with gy past L2).  Records have registers
     // for single-level sums only, so chunks of at most 1024 samples: not where the partial sums ask for longer ones (two
     // levels spill: 256 -> 300, G = 1000, B = 8192 walk 15.4 ms against 1.2 with four).  Widths that are no multiple of
     // eight take it where it pays: many pairs of a short table, and a last tile more than half full (backward pass, four
     // outputs / eight: 16 -> 300, G = 20, B = 16384 107 / 97 us, 64 -> 300, G = 5, B = 16384 282 / 236; but 2 -> 300, G = 20,
     // B = 65536 101 / 137, 16 -> 300, G = 1000, B = 16384 214 / 317, 64 -> 515, G = 20, B = 4096 126 / 147).
-    const int s8 = fit_sums(S < 1024 ? S : 1024);
+    const int most8 = quads ? 2048 : 1024;
+    const int s8 = fit_sums(S < most8 ? S : most8);
     const bool pays8 = g.n_out % 8 == 0 || (g.n_in >= 16 && B * g.n_in >= 1 << 17 && g.rows <= (B <= 16384 ? 320 : 128) &&
                                             (g.n_out - 1) % 512 >= 256);
     // every width has a variant (widths that are no multiple of T run its ragged build)
-    if (g.n_out > 256 && pays8 && s8 <= 1024) {
+    if (g.n_out > 256 && pays8 && s8 <= most8 && !(quads && high_degree)) {
         p.T = 8;
         p.streams = 1;
         S = s8;
@@ -228,13 +237,14 @@ WalkPlan plan_walk(const SplineGeom &g, int64_t B, bool allow_shared, bool high_
     const int tile = (64 / p.streams) * p.T;
     p.n_jt = (g.n_out + tile - 1) / tile;
     p.S = S;
-    p.hk = high_degree ? 1 : 0;
-    p.L = high_degree ? 2 * S : S;
+    p.window = high_degree && quads ? 6 : kMaxK;
+    p.hk = high_degree && !quads ? 1 : 0;
+    p.L = p.hk ? 2 * S : S;
     p.sbits = log2_exact(S);
     p.n_chunks = (int)((B + S - 1) / S);
     // segments per list: enough for about 2048 waves, at least 64 records each
     int bits = 0;
-    while ((1 << bits) < g.rows - kMaxK + 1) ++bits;
+    while ((1 << bits) < g.rows - p.window + 1) ++bits;
     p.row_bits = bits < 1 ? 1 : bits;
     p.ok = (int64_t)p.n_chunks * slab <= (4ll << 30) ? 1 : 0;
     p.shared = 0;
@@ -257,7 +267,30 @@ WalkPlan plan_walk(const SplineGeom &g, int64_t B, bool allow_shared, bool high_
         p.n_slabs = (int)(fit < 1 ? 1 : (fit > p.n_chunks ? p.n_chunks : fit));
         plan_segments(p.n_slabs);
     }
+    if (quads) {
+        // One counting pass sorts a list; offsets of 30 bits into a chunk's gy and the table (with one stream a wave: an
+        // input's); and samples a cell enough that the padding does not eat the gain.  Backward pass, records / quads, us, by
+        // samples a cell:
+        //   four outputs a lane, one stream   2: 64 -> 256, G = 1000, B = 8192 336 / 368 with 1, 247 / 210 with 20 (256 -> 256)
+        //   eight outputs a lane              2: 256 -> 512, G = 1000, B = 8192 1428 / 1833; 47: 512 -> 512 1452 / 1148
+        //   narrower                          1: 16 -> 32, G = 1000, 0.80 of the time, 8: 32 -> 32, G = 1024 274 / 169
+        //   windows of six rows, one stream   2.6: 2 -> 130, G = 100, B = 1024 45 / 52; two streams 2.6: 51 / 54; 64: 0.6
+        const int64_t most = 1ll << 28, slab_floats = (int64_t)g.slab_rows * g.n_out;
+        const int per_cell = high_degree ? (p.streams == 1 ? 4 : p.streams == 2 ? 3 : 2)
+                                         : (p.T == 8 ? 4 : p.streams == 1 ? 2 : 1);
+        p.quads = p.row_bits <= 10 && S >= per_cell * (g.rows - p.window + 1) && (int64_t)S * g.n_out <= most &&
+                  (p.streams == 1 ? 1 : g.n_in) * slab_floats <= most && (int64_t)g.n_in * g.n_out <= most ? 1 : 0;
+        p.L = quad_list_entries(S, g.rows, p.window);
+    }
     return p;
+}
+
+}  // namespace
+
+WalkPlan plan_walk(const SplineGeom &g, int64_t B, bool allow_shared, bool high_degree)
+{
+    const WalkPlan p = plan_lists(g, B, allow_shared, high_degree, true);
+    return p.quads ? p : plan_lists(g, B, allow_shared, high_degree, false);
 }
 
 // one translation unit per kernel variant (kan_walk_s*t*.hip)
@@ -287,28 +320,26 @@ size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 // per-tile partial gx (layers wider than one tile) | carry rows of the list segments | first row of every segment
 static size_t walk_carry_bytes(const WalkPlan &p, int n_in, int n_out)
 {
-    return up256((size_t)p.n_chunks * n_in * (p.n_seg + 1) * kMaxK * n_out * sizeof(float));
+    return up256((size_t)p.n_chunks * n_in * (p.n_seg + 1) * p.window * n_out * sizeof(float));
 }
 static size_t walk_seg_row_bytes(const WalkPlan &p, int n_in) { return up256((size_t)p.n_chunks * n_in * p.n_seg * sizeof(int)); }
 
 size_t walk_scratch_bytes(const WalkPlan &p, int64_t B, int n_in, int n_out)
 {
-    const size_t n = (size_t)p.n_chunks * n_in * p.L;
+    const size_t n = (size_t)p.n_chunks * n_in * (p.window > kMaxK ? 2 * (size_t)p.S : p.quads ? (size_t)p.S : (size_t)p.L);
     const int n_part = p.n_jt * (p.hk ? 2 : 1);       // partial dL/dx results per (sample, input)
     const size_t gxp = n_part > 1 ? up256((size_t)n_part * B * n_in * sizeof(float)) : 0;
-    return up256((size_t)B * n_in * sizeof(float)) + 3 * up256(n * 4) + 2 * up256(n * 16) + gxp +
+    // the records' size in either case (lists of padded cells take up to 24 bytes a pair, records 44 or 88): the space a layer
+    // asks for does not depend on which of the two its batch and table lead to
+    const size_t lists = 3 * up256(n * 4) + 2 * up256(n * 16);
+    return up256((size_t)B * n_in * sizeof(float)) + lists + gxp +
            walk_carry_bytes(p, n_in, n_out) + walk_seg_row_bytes(p, n_in);
 }
 
-// x -> xT, then per (chunk of S samples, input) the records in sorted order.  S: a power of two >= 256.
-hipError_t launch_sorted_records(const SplineGeom &g, const float *x, float *xT, int64_t B, int S, int row_bits,
-                                 const WalkRecords &rec, hipStream_t st)
+// Per (chunk of S samples, input) the records in sorted order.  S: a power of two >= 256.
+hipError_t launch_sorted_records(const SplineGeom &g, const float *xT, int64_t B, int S, int row_bits, const WalkRecords &rec,
+                                 hipStream_t st)
 {
-    {
-        dim3 grid((unsigned)((B + 63) / 64), (unsigned)((g.n_in + 63) / 64));
-        prof::Timed tm("walk_transpose", st);
-        transpose_kernel<<<grid, 256, 0, st>>>(x, xT, B, g.n_in);
-    }
     // waves per sort, measured: 16 for chunks of 8192 samples, 8 for 4096, 4 below
     const size_t lds = (size_t)S * 12 + sort_counter_bytes(S >= 8192 ? 16 : (S >= 4096 ? 8 : 4), row_bits);
     dim3 grid((unsigned)((B + S - 1) / S), (unsigned)g.n_in);
@@ -342,31 +373,48 @@ hipError_t launch_backward_walk(const SplineGeom &g, const WalkPlan &p, const fl
     const bool dx = gx != nullptr;
     char *at = (char *)scratch;
     float *xT = (float *)at;            at += up256((size_t)B * g.n_in * sizeof(float));
-    WalkRecords rec;
-    rec.rt = (int *)at;                 at += up256(n * 4);
-    rec.base = (float *)at;             at += up256(n * 4);
-    rec.w4 = (float *)at;               at += up256(n * 16);
-    rec.dbase = dx ? (float *)at : nullptr; at += up256(n * 4);
-    rec.dw4 = dx ? (float *)at : nullptr;   at += up256(n * 16);
+    WalkRecords rec = {};
+    QuadWalkArgs qa = {};
+    if (p.quads) {
+        qa.lists.x = (float *)at;           at += up256(n * 4);
+        qa.lists.sample = (uint16_t *)at;   at += up256(n * 2);
+        qa.lists.n_quads = (int *)at;       at += up256((size_t)p.n_chunks * g.n_in * 4);
+        qa.lists.L = p.L;
+    } else {
+        rec.rt = (int *)at;                 at += up256(n * 4);
+        rec.base = (float *)at;             at += up256(n * 4);
+        rec.w4 = (float *)at;               at += up256(n * 16);
+        rec.dbase = dx ? (float *)at : nullptr; at += up256(n * 4);
+        rec.dw4 = dx ? (float *)at : nullptr;   at += up256(n * 16);
+    }
     float *gx_part = (float *)at;       at += n_part > 1 ? up256((size_t)n_part * B * g.n_in * sizeof(float)) : 0;
     float *carry = (float *)at;         at += walk_carry_bytes(p, g.n_in, g.n_out);
     int *seg_row = (int *)at;
     // the chunks' carry rows are added by the reduction over the chunks; shared slabs take theirs below
-    *carry_rows = CarryRows{seg_row, carry, p.shared ? 1 : p.n_seg};
-    if (p.hk) {
+    *carry_rows = CarryRows{seg_row, carry, p.shared ? 1 : p.n_seg, p.window};
+    {
+        dim3 grid((unsigned)((B + 63) / 64), (unsigned)((g.n_in + 63) / 64));
+        prof::Timed tm("walk_transpose", st);
+        transpose_kernel<<<grid, 256, 0, st>>>(x, xT, B, g.n_in);
+    }
+    if (p.quads) {
+        qa.n_in = g.n_in; qa.n_out = g.n_out; qa.rows = g.rows; qa.slab_rows = g.slab_rows; qa.k = g.k; qa.lo = g.lo;
+        qa.inv_h = g.inv_h; qa.cell_base = g.cell_base;
+        qa.base_act = w_b != nullptr ? g.base_act : 0;
+        qa.gy = gy; qa.cf = cf; qa.w_b = w_b; qa.part_c = part_c; qa.part_b = part_b;
+        qa.carry = carry; qa.seg_row = seg_row; qa.B = B; qa.S = p.S; qa.n_seg = p.n_seg; qa.n_jt = p.n_jt;
+        if (hipError_t e = p.window == 6 ? launch_cell_lists6(qa, xT, p.row_bits, st) : launch_cell_lists(qa, xT, p.row_bits, st);
+            e != hipSuccess)
+            return e;
+    } else if (p.hk) {
         // degrees 4 and 5: the records come from the kernel built for a window of six rows
-        {
-            dim3 grid((unsigned)((B + 63) / 64), (unsigned)((g.n_in + 63) / 64));
-            prof::Timed tm("walk_transpose", st);
-            transpose_kernel<<<grid, 256, 0, st>>>(x, xT, B, g.n_in);
-        }
         HighKLayer l = {};
         l.n_in = g.n_in; l.n_out = g.n_out; l.rows = g.rows; l.k = g.k; l.lo = g.lo; l.inv_h = g.inv_h; l.base_act = g.base_act;
         l.slab_rows = g.slab_rows; l.cell_base = g.cell_base;
         if (hipError_t e = highk_sorted_records(l, xT, B, p.S, p.row_bits, rec.rt, rec.base, rec.w4, rec.dbase, rec.dw4, st);
             e != hipSuccess)
             return e;
-    } else if (hipError_t e = launch_sorted_records(g, x, xT, B, p.S, p.row_bits, rec, st); e != hipSuccess) {
+    } else if (hipError_t e = launch_sorted_records(g, xT, B, p.S, p.row_bits, rec, st); e != hipSuccess) {
         return e;
     }
     const int bpc = (p.n_seg * p.n_jt * g.n_in + 4 * p.streams - 1) / (4 * p.streams);
@@ -393,19 +441,35 @@ hipError_t launch_backward_walk(const SplineGeom &g, const WalkPlan &p, const fl
         const int here = p.n_chunks - chunk0 < per_launch ? p.n_chunks - chunk0 : per_launch;
         {
             prof::Timed tm(dx ? "backward_walk" : "dparam_walk", st);
-            const bool ragged = g.n_out % p.T != 0;
-            auto launch = p.T == 8 ? (ragged ? walk_launch_s1t8_ragged : walk_launch_s1t8)
-                          : p.T == 2 ? (ragged ? walk_launch_s4t2_ragged : walk_launch_s4t2)
-                          : p.T == 1 ? walk_launch_s4t1
-                          : p.streams == 1 ? (ragged ? walk_launch_s1t4_ragged : walk_launch_s1t4)
-                          : p.streams == 2 ? (ragged ? walk_launch_s2t4_ragged : walk_launch_s2t4)
-                                           : (ragged ? walk_launch_s4t4_ragged : walk_launch_s4t4);
-            launch(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx_out, B, p, bpc, m, prezeroed, carry, seg_row, chunk0, here);
+            if (p.quads) {
+                qa.gx = gx_out; qa.chunk0 = chunk0; qa.n_chunks = here; qa.blocks_per_chunk = bpc; qa.xcd_groups = m;
+                qa.prezeroed = prezeroed;
+                qa.shared = p.shared && chunk0 > 0 ? 1 : 0;       // the first round finds its slabs zero and stores
+                auto walk = p.window == 6 ? (p.T == 2 ? quad_walk6_s4t2
+                                             : p.T == 1 ? quad_walk6_s4t1
+                                             : p.streams == 1 ? quad_walk6_s1t4
+                                             : p.streams == 2 ? quad_walk6_s2t4 : quad_walk6_s4t4)
+                            : p.T == 8 ? quad_walk_s1t8
+                            : p.T == 2 ? quad_walk_s4t2
+                            : p.T == 1 ? quad_walk_s4t1
+                            : p.streams == 1 ? quad_walk_s1t4
+                            : p.streams == 2 ? quad_walk_s2t4 : quad_walk_s4t4;
+                walk(qa, blocks, st);
+            } else {
+                const bool ragged = g.n_out % p.T != 0;
+                auto launch = p.T == 8 ? (ragged ? walk_launch_s1t8_ragged : walk_launch_s1t8)
+                              : p.T == 2 ? (ragged ? walk_launch_s4t2_ragged : walk_launch_s4t2)
+                              : p.T == 1 ? walk_launch_s4t1
+                              : p.streams == 1 ? (ragged ? walk_launch_s1t4_ragged : walk_launch_s1t4)
+                              : p.streams == 2 ? (ragged ? walk_launch_s2t4_ragged : walk_launch_s2t4)
+                                               : (ragged ? walk_launch_s4t4_ragged : walk_launch_s4t4);
+                launch(dx, blocks, st, g, rec, gy, cf, w_b, part_c, part_b, gx_out, B, p, bpc, m, prezeroed, carry, seg_row, chunk0, here);
+            }
         }
         if (part_c != nullptr && p.n_seg > 1 && p.shared) {
             const int64_t nn = (int64_t)here * g.n_in * g.n_out;
             prof::Timed tm("walk_carry", st);
-            walk_carry_kernel<<<(unsigned)((nn + 255) / 256), 256, 0, st>>>(g, seg_row, carry, part_c, here, p.n_seg, chunk0);
+            walk_carry_kernel<<<(unsigned)((nn + 255) / 256), 256, 0, st>>>(g, seg_row, carry, part_c, here, p.n_seg, chunk0, p.window);
         }
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }

@@ -5,6 +5,7 @@
 #include <type_traits>
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
+#include "kan_wave.hpp"
 
 namespace kan {
 
@@ -22,47 +23,6 @@ __device__ __forceinline__ float row_bcast(float v)
     return __builtin_bit_cast(float, row_bcast<N>(__builtin_bit_cast(int, v)));
 }
 
-// value of the partner lane for the level that pairs lanes differing in bit D (for D = 4 the partner
-// is lane ^ 7: it differs in bit 2, which is all the reduction below needs)
-template <int D>
-__device__ __forceinline__ float partner(float v)
-{
-    const int iv = __builtin_bit_cast(int, v);
-    if constexpr (D >= 16) return __shfl_xor(v, D, 64);
-    else if constexpr (D == 8) return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, iv, 0x128, 0xF, 0xF, true));
-    else if constexpr (D == 4) return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, iv, 0x141, 0xF, 0xF, true));
-    else if constexpr (D == 2) return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, iv, 0x4E, 0xF, 0xF, true));
-    else return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, iv, 0xB1, 0xF, 0xF, true));
-}
-
-// p[0..N) hold, per lane, partial sums of N quantities.  Sums them over groups of LPS lanes while
-// halving the number of quantities a lane carries at each level (lanes whose bit D is set keep the
-// upper half); once one is left the remaining levels are plain sums.  Returns the total of quantity
-// number quantity_of<LPS>(lane).
-template <int D, int N>
-__device__ __forceinline__ float reduce_levels(float (&p)[N], int lane)
-{
-    if constexpr (N > 1) {
-        const bool up = (lane & D) != 0;
-        float h[N / 2];
-#pragma unroll
-        for (int k = 0; k < N / 2; ++k) {
-            const float keep = up ? p[k + N / 2] : p[k];
-            const float send = up ? p[k] : p[k + N / 2];
-            h[k] = keep + partner<D>(send);
-        }
-        if constexpr (D > 1) return reduce_levels<D / 2, N / 2>(h, lane);
-        else return h[0];
-    } else {
-        float v = p[0] + partner<D>(p[0]);
-        if constexpr (D > 1) {
-            float one[1] = {v};
-            return reduce_levels<D / 2, 1>(one, lane);
-        } else {
-            return v;
-        }
-    }
-}
 template <int LPS>
 __device__ __forceinline__ int quantity_of(int lane)      // 16 quantities: the top four levels select
 {

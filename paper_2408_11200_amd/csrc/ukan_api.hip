@@ -401,7 +401,7 @@ int backward_body(const ukan_layer_desc *desc, int64_t B, const float *x, const 
     float *part_c = (float *)(w + L.part_c), *part_b = (float *)(w + L.part_b);
     float *gout = (float *)(w + L.gout);
     int b_slices;
-    CarryRows cr = {nullptr, nullptr, 1};
+    CarryRows cr = {nullptr, nullptr, 1, 0};
     int n_chunks = pr.cp.n_chunks;
     if (dp.ok) {
         part_c = (float *)(w + L.dense);

@@ -316,3 +316,41 @@ def test_ukan_bias_gradients_alone(want):
 ])
 def test_sort_passes(B, n_in, n_out, G, k):
     run_layer_parity(workloads.random_kan_layer(G, B, n_in, n_out, G, k, outside_frac=0.05), gx_in_grid_units=True)
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k,family", [
+    (1000, 4, 64, 256, 3, "walk_cells"), (1000, 4, 64, 257, 3, "walk_sort"),      # a sample a cell, and less
+    (1000, 4, 256, 128, 3, "walk_cells"), (1000, 4, 256, 129, 3, "walk_sort"),    # two at one stream a wave
+    (1000, 4, 128, 86, 4, "walk_cells"), (1000, 4, 128, 87, 4, "walk_sort"),      # three with two streams and six rows
+    (8192, 8, 20, 1024, 3, "walk_cells"), (8192, 8, 20, 1025, 3, "walk_sort"),    # the longest table one counting pass sorts
+    (255, 1, 1, 70, 1, "walk_cells"), (4097, 9, 13, 70, 2, "walk_cells"),         # one output a lane
+    (2100, 33, 300, 30, 3, "walk_cells"), (9000, 67, 515, 7, 3, "walk_cells"),    # eight outputs a lane; a ragged last tile
+    (20000, 70, 33, 30, 3, "walk_cells"),                                         # sums in two levels
+    (5000, 40, 130, 30, 5, "walk_cells"), (5000, 9, 20, 64, 5, "walk_cells"), (700, 3, 96, 12, 4, "walk_cells"),
+])
+def test_walk_over_padded_cells(B, n_in, n_out, G, k, family):
+    """Backward pass over cell lists padded to quads, either side of the lines to the record lists."""
+    assert family in run_with_families(workloads.random_kan_layer(B + n_out, B, n_in, n_out, G, k, outside_frac=0.1))
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G", [(700, 3, 256, 40), (700, 3, 600, 30), (700, 3, 100, 40), (700, 3, 20, 70)])
+def test_walk_over_padded_cells_keeps_infinities_apart(B, n_in, n_out, G):
+    """An infinite and a NaN gradient reach their samples' dL/dx and the rows under their windows, and nothing else: the pads
+    beside them read zeros."""
+    w = workloads.random_kan_layer(n_out, B, n_in, n_out, G, 3)
+    s, p = w.layers[0], w.params[0]
+    x, coef, w_s, w_b, gy = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"], w.gy))
+    gy[[5, 300]] = 0.0
+    clean = binding.kan_backward(s, x, coef, w_s, w_b, gy)
+    gy[5, 1], gy[300, n_out - 1] = float("inf"), float("nan")
+    g = binding.kan_backward(s, x, coef, w_s, w_b, gy)
+    rest = torch.ones(B, dtype=torch.bool, device="cuda")
+    rest[[5, 300]] = False
+    assert torch.equal(g["gx"][rest], clean["gx"][rest]) and not torch.isfinite(g["gx"][~rest]).any()
+    cell = binding.kan_interval_index(s, x).clamp(0, s.G - 1)
+    for i in range(n_in):
+        touched = torch.zeros((s.G + s.k, n_out), dtype=torch.bool, device="cuda")
+        for b, j in ((5, 1), (300, n_out - 1)):
+            touched[cell[b, i]:cell[b, i] + 4, j] = True
+        assert torch.equal(g["gcoef"][i][~touched], clean["gcoef"][i][~touched])
+        assert not torch.isfinite(g["gcoef"][i][touched]).any()
