@@ -177,7 +177,7 @@ def _ptr(t):
     if t is None:
         return None
     assert t.is_cuda and t.is_contiguous(), "device-resident contiguous tensors only"
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _f32(t):
@@ -186,8 +186,10 @@ def _f32(t):
 
 
 def _stream(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    # the handle alone: building a Stream object costs more than a kernel launch
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _on_stream(t, stream):
@@ -373,7 +375,7 @@ _P_NAMES = ("E", "W1", "b1", "W2", "b2", "scale", "w_b")
 
 
 def _ukan_params(p):
-    return UkanParams(*[(_f32(p.get(n)).value if p.get(n) is not None else None) for n in _P_NAMES])
+    return UkanParams(*[_f32(p.get(n)) for n in _P_NAMES])
 
 
 def ukan_workspace_bytes(spec, B, max_groups, which=PASS_FORWARD):

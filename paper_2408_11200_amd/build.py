@@ -7,6 +7,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB_PATH = os.path.join(HERE, "libkan_hip.so")            # the layer library (HIP runtime only)
 BENCH_LIB_PATH = os.path.join(HERE, "libkan_bench.so")    # benchmark companion: event timing, rocBLAS dense baseline
+AUTOGRAD_PATH = os.path.join(HERE, "_autograd.so")        # autograd nodes: links libkan_hip.so and torch
 
 # packed fp32 instructions are switched off for every translation unit
 HIPCC_FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared",
@@ -25,9 +26,22 @@ def bench_sources():
     return sorted(glob.glob(os.path.join(HERE, "csrc_bench", "*.hip")))
 
 
+def autograd_command(out):
+    """Host compiler command of the autograd nodes; libkan_hip.so has to be there."""
+    import sysconfig
+    from torch.utils import cpp_extension
+    torch_lib = os.path.join(os.path.dirname(os.path.abspath(cpp_extension.torch.__file__)), "lib")
+    include = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], "/opt/rocm/include", os.path.join(ROOT, "include")]
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(cpp_extension.torch._C._GLIBCXX_USE_CXX11_ABI)] +
+            [a for d in include for a in ("-isystem", d)] +
+            [os.path.join(HERE, "csrc_torch", "kan_autograd.cpp"), "-o", out, "-L", torch_lib, "-ltorch", "-ltorch_cpu", "-ltorch_python",
+             "-lc10", "-lc10_hip", "-L", HERE, "-l:" + os.path.basename(LIB_PATH), "-Wl,-rpath,$ORIGIN"])
+
+
 def build(verbose=False, jobs=None):
-    """Compile csrc/*.hip into libkan_hip.so and csrc_bench/*.hip into libkan_bench.so next to this file.
-    Always recompiles.
+    """Compile csrc/*.hip into libkan_hip.so, csrc_bench/*.hip into libkan_bench.so and csrc_torch/ into _autograd.so next to
+    this file.  Always recompiles.
 
     Every source is compiled to an object file in its own hipcc process (a few at a time), then each
     library is linked from its own objects; only the benchmark library links rocBLAS."""
@@ -64,10 +78,15 @@ def build(verbose=False, jobs=None):
                 log.append(out)
             if rc != 0:
                 failed.append(out)
+        if not failed:
+            rc, out = run(autograd_command(AUTOGRAD_PATH))
+            if rc != 0:
+                failed.append(out)
+                log.append(out)
     if verbose or failed:
         print("\n".join(log))
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("compilation failed")
     return LIB_PATH
 
 

@@ -70,3 +70,70 @@ def test_ukan_layer_gradients_through_autograd():
         got = t.grad.cpu().numpy().astype(np.float64)
         err = np.abs(got - ref[key]) / (1.0 + np.abs(ref[key]))
         assert err.max() <= 1e-4, (key, err.max())
+
+
+def kan_tensors(B=300, n_in=5, n_out=7):
+    w = workloads.random_kan_layer(11, B, n_in, n_out, 9, 3)
+    return w.layers[0], dev(w.x, True), {n: dev(a, True) for n, a in w.params[0].items()}, dev(w.gy)
+
+
+def test_nodes_keep_autograd_contracts():
+    """What a program may do around a node: hooks on its saved tensors, inputs that need no gradient, views, changes in place
+    between the passes, a second derivative, wrong tensors."""
+    s, x, p, gy = kan_tensors()
+    layer = lambda x, p: autograd.kan_layer(s, x, p["coef"], p["w_s"], p["w_b"])
+    names = ("coef", "w_s", "w_b")
+    want = binding.kan_backward(s, x.detach(), *(p[n].detach() for n in names), gy)
+    seen = []
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: seen.append(t.shape) or t.cpu(), lambda t: t.cuda()):
+        y = layer(x, p)
+    assert len(seen) == 5                                               # x, the parameters and the folded table
+    g = torch.autograd.grad(y, [x] + [p[n] for n in names], gy)
+    assert all(torch.equal(a, want[n]) for a, n in zip(g, ("gx", "gcoef", "gw_s", "gw_b")))
+    only = torch.autograd.grad(layer(x.detach(), {n: p[n] if n == "w_s" else p[n].detach() for n in names}), p["w_s"], gy)[0]
+    assert torch.equal(only, want["gw_s"])
+    xt = x.detach().t().contiguous().t().requires_grad_(True)           # another order of strides
+    assert torch.equal(torch.autograd.grad(layer(xt, p), xt, gy)[0], want["gx"])
+    assert not layer(x.detach(), {n: t.detach() for n, t in p.items()}).requires_grad
+    with torch.no_grad():
+        assert layer(x, p).grad_fn is None
+    y = layer(x, p)
+    with torch.no_grad():
+        p["w_s"].mul_(2.0)
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        y.backward(gy)
+    first = torch.autograd.grad(layer(x, p), x, gy, create_graph=True)[0]
+    assert not first.requires_grad                                      # no second derivative is claimed
+    with pytest.raises(AssertionError):
+        layer(x.double(), p)
+    with pytest.raises(AssertionError):
+        layer(x.detach().cpu(), {n: t.detach().cpu() for n, t in p.items()})
+    with pytest.raises(RuntimeError):
+        torch.func.vmap(lambda a: layer(a, p))(x.detach().reshape(3, 100, 5))
+    bad = workloads.KanLayerSpec(s.n_in, s.n_out, s.G, 6, -1.0, 1.0)
+    with pytest.raises(binding.KanError) as e:
+        autograd.kan_layer(bad, x, p["coef"], p["w_s"], p["w_b"])
+    assert e.value.status == binding.KAN_ERR_UNSUPPORTED
+
+
+def test_nodes_run_on_the_stream_of_their_forward_pass():
+    s, x, p, gy = kan_tensors(B=2000, n_in=16, n_out=20)
+    names = ("coef", "w_s", "w_b")
+    want = binding.kan_backward(s, x.detach(), *(p[n].detach() for n in names), gy)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        y = autograd.kan_layer(s, x, p["coef"], p["w_s"], p["w_b"])
+    g = torch.autograd.grad(y, [x] + [p[n] for n in names], gy)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, want[n]) for a, n in zip(g, ("gx", "gcoef", "gw_s", "gw_b")))
+
+
+def test_ukan_node_reports_a_span_past_the_bound():
+    rng = np.random.default_rng(4)
+    spec = workloads.UkanLayerSpec(3, 4, 3, 0.25, 8, 8, 16)
+    T = {n: dev(a) for n, a in workloads.ukan_params(rng, spec).items() if n != "w_b"}
+    x = dev(np.float32(rng.uniform(-50, 50, (100, 3))))
+    with pytest.raises(binding.KanError) as e:
+        autograd.ukan_layer(spec, x, T, 8)
+    assert e.value.status == binding.KAN_ERR_RANGE
