@@ -14,46 +14,57 @@
 // LDS read per lane fetches a window row for SPW samples at once (each group reads its own row).
 // Every group handles S samples (slots), accumulators for all of them stay in registers
 // (S x 4 per lane) while the workgroup walks over the inputs.  The per-pair quantities (K weights,
-// base value, byte offset of the window row) go through a small per-wave area of LDS, written by the
+// base value, byte offsets of the window rows) go through a small per-wave area of LDS, written by the
 // lane that evaluated the pair and read back by the group that owns the sample.
+//
+// Bound by the multiply-adds and the LDS reads of the window rows, both about 60 % busy; what was beside them and is gone:
+//   - the waves took the parts of a step (copy, pair evaluation, multiply-adds) in the same order, and its barrier kept them
+//     there, so that the two pipes took turns: half the waves go the other way round;
+//   - two groups' 128-byte rows of tiles of 32 met in a bank every other time, and pairs of groups eight samples apart always
+//     (half of all LDS clocks): rows are read by parity, a group's samples are SPW apart;
+//   - a step copied whole multiples of the workgroup, up to nine times its slab, and had a barrier for each input;
+//   - x came one value a cache line, and its way from memory was waited for.
+// us, before / after (the wide layers of 128 -> 256 -> 256 -> 1, B = 32768, tables of 180 and 360 rows::
+// both 1455 / 970, the longer one alone in the new order on the old banks 500 / 362); 32 -> 32, G = 256, B = 131072 76 / 67 with its
+// fold; 64 -> 64, G = 10, B = 65536 103 / 81.
+#include <type_traits>
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
+#include "kan_wave.hpp"
 
 namespace kan {
 
 namespace {
 
-constexpr int kPairFloats = 8;      // w[0..3], base, byte offset of the window row, 2 unused
-
-template <int NQ>
-struct TileMap {
-    int off[NQ];          // float offset of the thread's quads inside one input's block of the table
-    unsigned ok;          // bit c: quad c is a real element
-};
+constexpr int kPairFloats = 8;      // w[0..3], two byte offsets of window rows, base, 1 unused
 
 }  // namespace
 
-// grid (ceil(B / (NW * SPW * S)), ceil(n_out / TJ)), NW waves.  Needs rows >= kMaxK, n_out >= 4.
-// The table has slab_rows rows per input; with slab_rows == rows + 1 the last one is the w_b row.
-template <int LPS, int S, int NW, int NQ>
+// A workgroup per (NW * SPW * S samples, TJ outputs), NW waves.  Needs rows >= kMaxK, n_out >= 4, for S = 8 four inputs.
+// BASE: the table has slab_rows = rows + 1 rows per input, the last one the w_b row.  P (a divisor of IPV): inputs a step.
+template <int LPS, int S, int NW, int NQ, bool BASE>
 __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g, const float *__restrict__ x,
                                                                    const float *__restrict__ cf,
-                                                                   float *__restrict__ y, int64_t B)
+                                                                   float *__restrict__ y, int64_t B, int P, int n_tiles)
 {
     constexpr int TJ = LPS * 4, SPW = 64 / LPS, NT = 64 * NW;
     constexpr int SMP = SPW * S;                        // samples per wave
     constexpr int IPV = 64 / SMP;                       // inputs one round of pair evaluations covers
-    constexpr int slab_floats = NQ * NT * 4;            // padded slab
+    constexpr int slab_floats = NQ * NT * 4;            // padded slabs of a step
     static_assert(SMP <= 64 && 64 % SMP == 0, "the wave's samples must tile its lanes");
-    extern __shared__ float lds[];                      // two slabs, then NW areas of 64 pairs
+    extern __shared__ float lds[];                      // two steps' slabs, then NW areas of 64 pairs
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = lane / LPS, lj = lane % LPS;
-    const int64_t b0 = ((int64_t)blockIdx.x * NW + wave) * SMP;
-    const int j0 = blockIdx.y * TJ;
+    // Workgroups go to the 8 XCDs round-robin; an XCD takes neighbours in the order of the tiles, so that the workgroups that
+    // copy the same slabs at the same time share an L2.
+    const int n_rows = (int)((B + NW * SMP - 1) / (NW * SMP));
+    const int id = (int)(blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8);
+    if (id >= n_rows * n_tiles) return;
+    const int64_t b0 = ((int64_t)(id % n_rows) * NW + wave) * SMP;
+    const int j0 = id / n_rows * TJ;
     const int j = j0 + lj * 4;
     float *pairs = lds + 2 * slab_floats + wave * (64 * kPairFloats);
-    const bool has_base = g.slab_rows == g.rows + 1;
 
     // two-level sum over the inputs (acc is folded into tot every 32 inputs): keeps the rounding error
     // of a sum over hundreds of inputs inside the forward tolerance
@@ -64,80 +75,112 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
 #pragma unroll
         for (int r = 0; r < 4; ++r) { acc[q][r] = 0.0f; tot[q][r] = 0.0f; }
 
-    // pair evaluation: lane <-> (input my_ii of the round, sample my_smp of the wave)
-    const int my_smp = lane % SMP, my_ii = lane / SMP;
-    int64_t my_b = b0 + my_smp;
-    if (my_b >= B) my_b = B - 1;
-
-    // slab copy: thread tid moves quads tid, tid + NT, ... of the padded slab
-    TileMap<NQ> map;
-    map.ok = 0u;
+    // slab copy: thread tid moves quads tid, tid + NT, ... of a step's rows (the table's rows follow each other over the
+    // inputs).  Zeros are copied for rows and outputs that are not there.
+    const int step_rows = P * g.slab_rows;
+    int off[NQ];                                        // in bytes; past the end of every buffer for what is not there
 #pragma unroll
     for (int c = 0; c < NQ; ++c) {
         const int e = tid + c * NT;
         const int row = e / LPS, jj = j0 + (e % LPS) * 4;
-        const bool ok = row < g.slab_rows && jj < g.n_out;
-        map.off[c] = ok ? row * g.n_out + (jj + 4 > g.n_out ? g.n_out - 4 : jj) : 0;     // a row's last quad: n_out - 4 ..
-        map.ok |= ok ? (1u << c) : 0u;
+        off[c] = row < step_rows && jj < g.n_out ? (row * g.n_out + (jj + 4 > g.n_out ? g.n_out - 4 : jj)) * 4 : INT32_MIN;     // a row's last quad: n_out - 4 ..
     }
-    const int64_t block_floats = (int64_t)g.slab_rows * g.n_out;
-    float4 qd[NQ];
-    auto fetch = [&](const float *__restrict__ block) {
+    const int copies = (step_rows * LPS - wave * 64 + NT - 1) / NT;      // of the wave; the others are padding only
+    const int n_steps = (g.n_in + P - 1) / P;
+    const int64_t step_floats = (int64_t)step_rows * g.n_out;
+    f32x4 qd[NQ];
+    auto fetch = [&](int t) {
+        const int at = t < n_steps ? t : n_steps - 1;
+        const int inputs = g.n_in - at * P < P ? g.n_in - at * P : P;      // loads past the table's end return zeros
+        const i32x4 block = buffer_of(cf + (int64_t)at * step_floats, (unsigned)(inputs * g.slab_rows * g.n_out) * 4u);
 #pragma unroll
-        for (int c = 0; c < NQ; ++c) qd[c] = load4u(block + map.off[c]);
+        for (int c = 0; c < NQ; ++c)
+            if (c < copies) qd[c] = buffer_load4(block, off[c], 0, 0);
     };
     auto stage = [&](float *slab) {
 #pragma unroll
-        for (int c = 0; c < NQ; ++c) {
-            float4 v = qd[c];
-            const bool ok = (map.ok >> c) & 1u;
-            v.x = ok ? v.x : 0.f; v.y = ok ? v.y : 0.f; v.z = ok ? v.z : 0.f; v.w = ok ? v.w : 0.f;
-            *reinterpret_cast<float4 *>(slab + (int64_t)(tid + c * NT) * 4) = v;
+        for (int c = 0; c < NQ; ++c)
+            if (c < copies) *reinterpret_cast<f32x4 *>(slab + (tid + c * NT) * 4) = qd[c];
+    };
+
+    // pair evaluation: lane <-> (input my_ii of the round, sample my_smp of the wave); what it reads is asked for a round
+    // ahead, four inputs at a time where the lanes are all samples (a row of x is a cache line of its own)
+    const int my_smp = lane % SMP;
+    int my_ii = lane / SMP;
+    asm("" : "+v"(my_ii));             // keeps cell_base's load a vector one, which does not hold up the waits for LDS
+    const int64_t my_b = b0 + my_smp < B ? b0 + my_smp : B - 1;
+    const float *__restrict__ xrow = x + my_b * g.n_in;
+    float xv[IPV == 1 ? 4 : 1];
+    int cell_base = 0;
+    auto ask = [&](int round) {
+        const int mi = round * IPV + my_ii;
+        const int ic = mi < g.n_in ? mi : g.n_in - 1;
+        if constexpr (IPV == 1) {
+            if (round % 4 == 0) {
+                const float4 v = load4u(xrow + (ic < g.n_in - 4 ? ic : g.n_in - 4));
+                xv[0] = v.x; xv[1] = v.y; xv[2] = v.z; xv[3] = v.w;
+            }
+        } else {
+            xv[0] = xrow[ic];
+        }
+        if (g.cell_base) cell_base = g.cell_base[ic];
+    };
+    auto evaluate = [&](int round) {
+        float v = xv[0];
+        if constexpr (IPV == 1) {
+            const int first = round / 4 * 4;
+            const int c = round - (first < g.n_in - 4 ? first : g.n_in - 4);
+            v = c == 0 ? xv[0] : c == 1 ? xv[1] : c == 2 ? xv[2] : xv[3];
+        }
+        SplineGeom gi = g;
+        gi.cell_base = &cell_base;
+        gi.base_act = BASE ? 1 : 0;
+        const Pair pr = pair_eval<false>(v, gi, 0);
+        int row0;
+        float w[kMaxK], base;
+        window_of<false>(pr, g.rows, row0, w, base);
+        row0 += my_ii % P * g.slab_rows;
+        // pair (input ii of the round, sample smp) sits at index ii * SMP + smp == the lane that evaluated it
+        float *pair = pairs + lane * kPairFloats;
+        if constexpr (LPS == 16) {
+            *reinterpret_cast<float4 *>(pair) = make_float4(w[0], w[1], w[2], w[3]);
+            *reinterpret_cast<float2 *>(pair + 4) = make_float2(__int_as_float(row0 * TJ * 4), base);
+        } else {
+            // A row is half the banks: neighbouring groups start with rows of different parity and swap rows 0 and 1, 2 and 3
+            // of the window accordingly, so that their reads never meet in a bank.
+            const bool swap = (row0 + my_smp) & 1;
+            *reinterpret_cast<float4 *>(pair) = make_float4(swap ? w[1] : w[0], swap ? w[0] : w[1], swap ? w[3] : w[2], swap ? w[2] : w[3]);
+            *reinterpret_cast<float4 *>(pair + 4) = make_float4(__int_as_float((row0 + (swap ? 1 : 0)) * TJ * 4),
+                                                                __int_as_float((row0 + (swap ? 0 : 1)) * TJ * 4), base, 0.0f);
         }
     };
-    fetch(cf);
-    stage(lds);
-    __syncthreads();
 
-    for (int i0 = 0; i0 < g.n_in; i0 += IPV) {
-        if (i0 % kFoldInputs == 0 && i0 > 0) {
+    auto compute = [&](int t) {
+        const int i0 = t * P;
+        const float *cur = lds + (t & 1) * slab_floats;
+        if (i0 % kFoldInputs == 0) {
 #pragma unroll
             for (int q = 0; q < S; ++q)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) { tot[q][r] += acc[q][r]; acc[q][r] = 0.0f; }
         }
-        const int mi = i0 + my_ii;
-        const int ic = mi < g.n_in ? mi : g.n_in - 1;
-        {
-            const Pair pr = pair_eval<false>(x[my_b * g.n_in + ic], g, ic);
-            int row0;
-            float w[kMaxK], base;
-            window_of<false>(pr, g.rows, row0, w, base);
-            // pair (input i0 + ii, sample smp) sits at index ii * SMP + smp == the lane that evaluated it
-            *reinterpret_cast<float4 *>(pairs + lane * kPairFloats) = make_float4(w[0], w[1], w[2], w[3]);
-            *reinterpret_cast<float2 *>(pairs + lane * kPairFloats + 4) =
-                make_float2(has_base ? base : 0.0f, __int_as_float(row0 * TJ * 4));
-        }
-        const int n_ii = (g.n_in - i0 < IPV) ? g.n_in - i0 : IPV;
+        const int n_ii = g.n_in - i0 < P ? g.n_in - i0 : P;
+#pragma clang loop unroll(disable)
         for (int ii = 0; ii < n_ii; ++ii) {
-            const int i = i0 + ii;
-            const float *cur = lds + (i & 1) * slab_floats;
-            float *nxt = lds + ((i + 1) & 1) * slab_floats;
-            // prefetch the next slab (the last iteration re-fetches its own slab: harmless)
-            fetch(cf + (int64_t)(i + 1 < g.n_in ? i + 1 : i) * block_floats);
-
             float4 wb = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (has_base) wb = *reinterpret_cast<const float4 *>(cur + g.rows * TJ + lj * 4);
-            const float *pp = pairs + (ii * SMP + grp * S) * kPairFloats;     // the group's S samples
+            if constexpr (BASE) wb = *reinterpret_cast<const float4 *>(cur + (ii * g.slab_rows + g.rows) * TJ + lj * 4);
+            const float *pp = pairs + (((i0 + ii) % IPV) * SMP + grp) * kPairFloats;     // samples grp, grp + SPW, ...
 #pragma unroll
             for (int q = 0; q < S; ++q) {
-                const float4 wv = *reinterpret_cast<const float4 *>(pp + q * kPairFloats);
-                const float2 bv = *reinterpret_cast<const float2 *>(pp + q * kPairFloats + 4);
-                const float *win = reinterpret_cast<const float *>(reinterpret_cast<const char *>(cur) +
-                                                                   __float_as_int(bv.y)) + lj * 4;
-                float4 c[kMaxK];
-#pragma unroll
-                for (int s = 0; s < kMaxK; ++s) c[s] = *reinterpret_cast<const float4 *>(win + s * TJ);
+                const float *pq = pp + q * (SPW * kPairFloats);
+                const float4 wv = *reinterpret_cast<const float4 *>(pq);
+                const float2 at = *reinterpret_cast<const float2 *>(pq + 4);
+                const float base = !BASE ? 0.0f : LPS == 16 ? at.y : pq[6];
+                const char *win = reinterpret_cast<const char *>(cur + lj * 4);
+                const float *w0 = reinterpret_cast<const float *>(win + __float_as_int(at.x));
+                const float *w1 = LPS == 16 ? w0 + TJ : reinterpret_cast<const float *>(win + __float_as_int(at.y));
+                const float4 c[kMaxK] = {*reinterpret_cast<const float4 *>(w0), *reinterpret_cast<const float4 *>(w1),
+                                         *reinterpret_cast<const float4 *>(w0 + 2 * TJ), *reinterpret_cast<const float4 *>(w1 + 2 * TJ)};
                 const float ws[kMaxK] = {wv.x, wv.y, wv.z, wv.w};
 #pragma unroll
                 for (int s = 0; s < kMaxK; ++s) {
@@ -146,20 +189,58 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
                     acc[q][2] = fmaf(ws[s], c[s].z, acc[q][2]);
                     acc[q][3] = fmaf(ws[s], c[s].w, acc[q][3]);
                 }
-                acc[q][0] = fmaf(bv.x, wb.x, acc[q][0]);
-                acc[q][1] = fmaf(bv.x, wb.y, acc[q][1]);
-                acc[q][2] = fmaf(bv.x, wb.z, acc[q][2]);
-                acc[q][3] = fmaf(bv.x, wb.w, acc[q][3]);
+                if constexpr (BASE) {
+                    acc[q][0] = fmaf(base, wb.x, acc[q][0]);
+                    acc[q][1] = fmaf(base, wb.y, acc[q][1]);
+                    acc[q][2] = fmaf(base, wb.z, acc[q][2]);
+                    acc[q][3] = fmaf(base, wb.w, acc[q][3]);
+                }
+                if constexpr (S > 4) {                   // more rows in flight would spill
+                    if (q % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+    };
+
+    // Two of a SIMD's four waves (one of two) take the steps' parts in the opposite order, so that LDS writes, pair evaluation
+    // and multiply-adds of different waves overlap between two barriers.  A wave's pairs are its own.
+    const bool early = (wave >> 2) & 1;
+    const int per_round = IPV / P;
+    fetch(0);
+    ask(0);
+    stage(lds);
+    fetch(1);
+    if (!early) {
+        evaluate(0);
+        ask(1);
+    }
+    __syncthreads();
+    for (int t = 0; t < n_steps; ++t) {
+        float *nxt = lds + ((t + 1) & 1) * slab_floats;
+        if (early) {
+            if (t % per_round == 0) {
+                evaluate(t / per_round);
+                ask(t / per_round + 1);
             }
             stage(nxt);
-            __syncthreads();
+            fetch(t + 2);
         }
+        compute(t);
+        if (!early) {
+            stage(nxt);
+            fetch(t + 2);
+            if ((t + 1) % per_round == 0) {
+                evaluate((t + 1) / per_round);
+                ask((t + 1) / per_round + 1);
+            }
+        }
+        __syncthreads();
     }
 
     if (j < g.n_out) {
 #pragma unroll
         for (int q = 0; q < S; ++q) {
-            const int64_t b = b0 + grp * S + q;
+            const int64_t b = b0 + q * SPW + grp;
             if (b < B)
                 store4u(y + b * g.n_out + (j + 4 > g.n_out ? g.n_out - 4 : j),
                         make_float4(tot[q][0] + acc[q][0], tot[q][1] + acc[q][1], tot[q][2] + acc[q][2], tot[q][3] + acc[q][3]));
@@ -170,16 +251,26 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
 namespace {
 
 constexpr size_t kLdsBudget = 160 * 1024;
-constexpr int kSlots = 4;           // S: samples a lane group works through
 
-struct RowsPlan { int lps, nw, nq; };
+struct RowsPlan { int lps, slots, nw, nq, inputs; };
 
-// tile width, workgroup size and copy depth for a layer (lps == 0: not applicable)
+// copies a thread makes of a step's slabs: what the kernel is built for, 0 if that is too few
+int copies_of(int nw, int64_t quads)
+{
+    const int64_t need = (quads + 64 * nw - 1) / (64 * nw);
+    if (nw == 16) return need <= 4 ? (int)need : 0;
+    return need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : need <= 8 ? 8 : 0;
+}
+
+size_t lds_bytes(int nw, int nq) { return 2ull * nq * 64 * nw * 16 + (size_t)nw * 64 * kPairFloats * sizeof(float); }
+
+// tile width, samples a group, workgroup size, copy depth and inputs a step for a layer (lps == 0: not applicable)
 RowsPlan plan_of(const SplineGeom &g, int64_t B)
 {
-    RowsPlan none = {0, 0, 0};
+    RowsPlan none = {0, 0, 0, 0, 0};
     if (g.rows < kMaxK || g.n_out < 32) return none;
     if (g.slab_rows != g.rows + 1 && (g.slab_rows != g.rows || g.base_act != 0)) return none;
+    if ((int64_t)g.slab_rows * g.n_out >= 1ll << 29) return none;           // the copies' offsets have 31 bits
     const int lps_opts[] = {16, 8};
     for (int lps : lps_opts) {
         const int tj = lps * 4, spw = 64 / lps;
@@ -188,7 +279,7 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
         // 16 waves when that still leaves about a workgroup per CU, else 8
         const int nw_opts[] = {16, 8};
         for (int nw : nw_opts) {
-            const int64_t per_wg = (int64_t)nw * spw * kSlots;
+            const int64_t per_wg = (int64_t)nw * spw * 4;
             const int64_t wgs = (B + per_wg - 1) / per_wg * tiles;
             if (nw == 16 && wgs < 256) continue;
             // eight waves (two per SIMD) only when one tile covers the layer: with several tiles every tile
@@ -196,51 +287,65 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             // G = 200, B = 8192: 0.38 ms against 0.34 ms)
             if (nw == 8 && tiles > 1) continue;
             const int64_t quads = (int64_t)g.slab_rows * lps;
-            const int64_t need = (quads + 64 * nw - 1) / (64 * nw);
-            const int sizes[] = {2, 4, 8, 16};
-            int nq = 0;
-            for (int s2 : sizes)
-                if (need <= s2) { nq = s2; break; }
-            if (!nq) continue;
-            const size_t lds = 2ull * nq * 64 * nw * 16 + (size_t)nw * 64 * kPairFloats * sizeof(float);
-            if (lds > kLdsBudget) continue;
+            const int nq = copies_of(nw, quads);
+            if (!nq || lds_bytes(nw, nq) > kLdsBudget) continue;
             // worth it only when a staged row serves many samples (the copy into LDS costs as much LDS
             // time per row as several reads of it): samples * K >= 4 * slab rows
             if (per_wg * kMaxK < 4 * (int64_t)g.slab_rows) continue;
-            RowsPlan p = {lps, nw, nq};
+            RowsPlan p = {lps, 4, nw, nq, 1};
+            // Eight samples a group halve the copies a sample (256 -> 256, 180 rows, B = 32768: 608 us, with four 756).  A CU
+            // works through its workgroups in rounds of 256; a step of four samples a group takes about 2200 clocks beside
+            // the copies, which go at 64 bytes a clock.
+            if (nw == 16 && g.n_in >= 4) {
+                const int64_t rounds4 = (wgs + 255) / 256, rounds8 = ((B + 2 * per_wg - 1) / (2 * per_wg) * tiles + 255) / 256;
+                if (rounds8 * (4400 + quads / 4) < rounds4 * (2200 + quads / 4)) p.slots = 8;
+            }
+            // several inputs a step where their slabs fit: one barrier for all of them
+            const int most = 64 / (spw * p.slots);
+            for (int n = 2; n <= most; n *= 2) {
+                const int q = copies_of(nw, n * quads);
+                if (q && lds_bytes(nw, q) <= kLdsBudget && n * (int64_t)g.slab_rows * g.n_out < 1ll << 29) { p.inputs = n; p.nq = q; }
+            }
             return p;
         }
     }
     return none;
 }
 
-template <int LPS, int NW, int NQ>
-hipError_t launch_variant(const SplineGeom &g, const float *x, const float *cf, float *y, int64_t B, hipStream_t st)
+template <int LPS, int S, int NW, int NQ, bool BASE>
+hipError_t launch_variant(const SplineGeom &g, const float *x, const float *cf, float *y, int64_t B, int inputs, hipStream_t st)
 {
     constexpr int SPW = 64 / LPS;
-    const size_t lds = 2ull * NQ * 64 * NW * 16 + (size_t)NW * 64 * kPairFloats * sizeof(float);
-    auto kern = forward_lds_rows_kernel<LPS, kSlots, NW, NQ>;
+    const size_t lds = lds_bytes(NW, NQ);
+    auto kern = forward_lds_rows_kernel<LPS, S, NW, NQ, BASE>;
     struct Tag;
     hipError_t e = ensure_dynamic_lds<Tag>(reinterpret_cast<const void *>(kern), (int)lds);
     if (e != hipSuccess) return e;
-    const int64_t per_wg = (int64_t)NW * SPW * kSlots;
-    dim3 grid((unsigned)((B + per_wg - 1) / per_wg), (unsigned)((g.n_out + LPS * 4 - 1) / (LPS * 4)));
+    const int64_t per_wg = (int64_t)NW * SPW * S, n_tiles = (g.n_out + LPS * 4 - 1) / (LPS * 4);
+    const int64_t wgs = (B + per_wg - 1) / per_wg * n_tiles;
+    if ((wgs + 7) * (64 * NW) >= (1ll << 32)) return hipErrorInvalidValue;      // a launch takes fewer threads (512 GiB of x and y)
     prof::Timed tm("forward_lds_rows", st);
-    kern<<<grid, 64 * NW, lds, st>>>(g, x, cf, y, B);
+    kern<<<(unsigned)((wgs + 7) / 8 * 8), 64 * NW, lds, st>>>(g, x, cf, y, B, inputs, (int)n_tiles);
     return hipGetLastError();
 }
 
-template <int LPS, int NW>
-hipError_t launch_by_quads(int nq, const SplineGeom &g, const float *x, const float *cf, float *y, int64_t B,
+template <int LPS, int S, int NW>
+hipError_t launch_by_quads(const RowsPlan &p, const SplineGeom &g, const float *x, const float *cf, float *y, int64_t B,
                            hipStream_t st)
 {
-    switch (nq) {
-    case 2: return launch_variant<LPS, NW, 2>(g, x, cf, y, B, st);
-    case 4: return launch_variant<LPS, NW, 4>(g, x, cf, y, B, st);
-    case 8: return launch_variant<LPS, NW, 8>(g, x, cf, y, B, st);
-    case 16: return launch_variant<LPS, NW, 16>(g, x, cf, y, B, st);
-    default: return hipErrorInvalidValue;
+    auto by_base = [&](auto n) {
+        constexpr int NQ = decltype(n)::value;
+        return g.base_act != 0 ? launch_variant<LPS, S, NW, NQ, true>(g, x, cf, y, B, p.inputs, st)
+                               : launch_variant<LPS, S, NW, NQ, false>(g, x, cf, y, B, p.inputs, st);
+    };
+    switch (p.nq) {
+    case 1: return by_base(std::integral_constant<int, 1>{});
+    case 2: return by_base(std::integral_constant<int, 2>{});
+    case 3: if constexpr (NW == 16) return by_base(std::integral_constant<int, 3>{}); break;
+    case 4: return by_base(std::integral_constant<int, 4>{});
+    case 8: if constexpr (NW == 8) return by_base(std::integral_constant<int, 8>{}); break;
     }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -251,10 +356,12 @@ hipError_t launch_forward_lds_rows(const SplineGeom &g, const float *x, const fl
                                    hipStream_t st)
 {
     const RowsPlan p = plan_of(g, B);
-    if (p.lps == 16 && p.nw == 16) return launch_by_quads<16, 16>(p.nq, g, x, cf, y, B, st);
-    if (p.lps == 16 && p.nw == 8) return launch_by_quads<16, 8>(p.nq, g, x, cf, y, B, st);
-    if (p.lps == 8 && p.nw == 16) return launch_by_quads<8, 16>(p.nq, g, x, cf, y, B, st);
-    if (p.lps == 8 && p.nw == 8) return launch_by_quads<8, 8>(p.nq, g, x, cf, y, B, st);
+    if (p.lps == 16 && p.slots == 8) return launch_by_quads<16, 8, 16>(p, g, x, cf, y, B, st);
+    if (p.lps == 16 && p.nw == 16) return launch_by_quads<16, 4, 16>(p, g, x, cf, y, B, st);
+    if (p.lps == 16 && p.nw == 8) return launch_by_quads<16, 4, 8>(p, g, x, cf, y, B, st);
+    if (p.lps == 8 && p.slots == 8) return launch_by_quads<8, 8, 16>(p, g, x, cf, y, B, st);
+    if (p.lps == 8 && p.nw == 16) return launch_by_quads<8, 4, 16>(p, g, x, cf, y, B, st);
+    if (p.lps == 8 && p.nw == 8) return launch_by_quads<8, 4, 8>(p, g, x, cf, y, B, st);
     return hipErrorInvalidValue;
 }
 

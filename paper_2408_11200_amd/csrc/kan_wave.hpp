@@ -4,6 +4,24 @@
 
 namespace KAN_NS {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+// Buffer loads by the compiler's intrinsics (hipcc 7.2 builds __builtin_amdgcn_raw_buffer_load_b64 as a load of 32 bits).
+__device__ f32x4 buffer_load4(i32x4 rsrc, int off, int soff, int aux) __asm("llvm.amdgcn.raw.buffer.load.v4f32");
+__device__ f32x2 buffer_load2(i32x4 rsrc, int off, int soff, int aux) __asm("llvm.amdgcn.raw.buffer.load.v2f32");
+__device__ float buffer_load1(i32x4 rsrc, int off, int soff, int aux) __asm("llvm.amdgcn.raw.buffer.load.f32");
+
+// a buffer of `bytes` bytes at the wave-uniform address p: loads past its end return zeros
+__device__ __forceinline__ i32x4 buffer_of(const float *p, unsigned bytes)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    return i32x4{(int)__builtin_amdgcn_readfirstlane((int)(uint32_t)a), (int)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32)),
+                 (int)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+}
+
 // value of the partner lane for the level that pairs lanes differing in bit D (for D = 4 the partner
 // is lane ^ 7: it differs in bit 2, which is all the reduction below needs)
 template <int D>

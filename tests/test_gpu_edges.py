@@ -99,6 +99,19 @@ def test_forward_lines(B, n_in, n_out, G, k, family):
     assert "forward_" + family in forward_with_families(w)
 
 
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (16400, 33, 64, 40, 3), (16403, 37, 35, 17, 1),             # eight waves: steps of four inputs, the last one of one
+    (20000, 34, 63, 100, 3), (33000, 9, 32, 240, 3),            # steps of two; tiles of 32
+    (65500, 11, 64, 10, 3), (131000, 3, 32, 256, 3),            # sixteen waves: steps of four inputs, of one
+    (66000, 35, 33, 40, 2), (70001, 5, 64, 150, 3), (70000, 66, 47, 240, 3),    # eight samples a group: one to four copies a thread
+    (131100, 4, 32, 60, 3), (131072 + 512, 7, 32, 100, 3), (131073, 34, 32, 300, 3),       # the same on tiles of 32, x by fours
+    (45000, 9, 70, 300, 3),                                     # three tiles, the last of six outputs
+])
+@pytest.mark.parametrize("outside", [0.0, 0.1])
+def test_lds_rows_kernel(B, n_in, n_out, G, k, outside):
+    assert "forward_lds_rows" in forward_with_families(workloads.random_kan_layer(n_in, B, n_in, n_out, G, k, outside_frac=outside))
+
+
 def test_batch_past_the_threads_of_one_launch():
     """64 threads a sample: 2^26 samples are more than one launch takes.  Both ends and the seam between the parts agree
     with a call on those rows alone."""
