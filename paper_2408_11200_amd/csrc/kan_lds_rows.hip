@@ -24,9 +24,11 @@
 //     (half of all LDS clocks): rows are read by parity, a group's samples are SPW apart;
 //   - a step copied whole multiples of the workgroup, up to nine times its slab, and had a barrier for each input;
 //   - x came one value a cache line, and its way from memory was waited for.
-// us, before / after (the wide layers of 128 -> 256 -> 256 -> 1, B = 32768, tables of 180 and 360 rows::
-// both 1455 / 970, the longer one alone in the new order on the old banks 500 / 362); 32 -> 32, G = 256, B = 131072 76 / 67 with its
-// fold; 64 -> 64, G = 10, B = 65536 103 / 81.
+//   - a spill, or a use of an older load after a younger one was sent, waits for the copy under way.
+// us, before / after: the wide layers of 128 -> 256 -> 256 -> 1, B = 32768, tables of 180 and 360 rows 1455 / 920 (the longer
+// tables 500 on the old banks, 362 on these); 32 -> 32, G = 256, B = 131072 with its fold 76 / 57; 64 -> 64, G = 10, B = 65536
+// 103 / 79.  Layers of two to twelve inputs, whose few steps do not hide the first copy: 0.88 of the time over all, 1.09 at most
+// (3 -> 100, G = 64, B = 65536: 19.6 / 21.3).
 #include <type_traits>
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
@@ -90,9 +92,8 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
     const int64_t step_floats = (int64_t)step_rows * g.n_out;
     f32x4 qd[NQ];
     auto fetch = [&](int t) {
-        const int at = t < n_steps ? t : n_steps - 1;
-        const int inputs = g.n_in - at * P < P ? g.n_in - at * P : P;      // loads past the table's end return zeros
-        const i32x4 block = buffer_of(cf + (int64_t)at * step_floats, (unsigned)(inputs * g.slab_rows * g.n_out) * 4u);
+        const int inputs = g.n_in - t * P < P ? g.n_in - t * P : P;      // loads past the table's end return zeros
+        const i32x4 block = buffer_of(cf + (int64_t)t * step_floats, (unsigned)(inputs * g.slab_rows * g.n_out) * 4u);
 #pragma unroll
         for (int c = 0; c < NQ; ++c)
             if (c < copies) qd[c] = buffer_load4(block, off[c], 0, 0);
@@ -135,10 +136,9 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
         SplineGeom gi = g;
         gi.cell_base = &cell_base;
         gi.base_act = BASE ? 1 : 0;
-        const Pair pr = pair_eval<false>(v, gi, 0);
         int row0;
-        float w[kMaxK], base;
-        window_of<false>(pr, g.rows, row0, w, base);
+        float w[kMaxK], dw[kMaxK], base, dbase;
+        wave_windows<false>(v, gi, 0, row0, w, base, dw, dbase);
         row0 += my_ii % P * g.slab_rows;
         // pair (input ii of the round, sample smp) sits at index ii * SMP + smp == the lane that evaluated it
         float *pair = pairs + lane * kPairFloats;
@@ -155,6 +155,8 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
         }
     };
 
+    // slots whose rows are in flight together: with more the kernel spills, and every spill waits for the copies on their way
+    constexpr int kAtOnce = S == 8 ? (NQ + BASE < 4 ? 2 : 1) : NQ + BASE < 5 ? 4 : 2;
     auto compute = [&](int t) {
         const int i0 = t * P;
         const float *cur = lds + (t & 1) * slab_floats;
@@ -195,45 +197,37 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
                     acc[q][2] = fmaf(base, wb.z, acc[q][2]);
                     acc[q][3] = fmaf(base, wb.w, acc[q][3]);
                 }
-                if constexpr (S > 4) {                   // more rows in flight would spill
-                    if (q % 2 == 1) __builtin_amdgcn_sched_barrier(0);
-                }
+                if ((q + 1) % kAtOnce == 0) __builtin_amdgcn_sched_barrier(0);
             }
         }
     };
 
     // Two of a SIMD's four waves (one of two) take the steps' parts in the opposite order, so that LDS writes, pair evaluation
     // and multiply-adds of different waves overlap between two barriers.  A wave's pairs are its own.
+    // Loads are waited for in order, so those for later come after the uses of the earlier ones.
     const bool early = (wave >> 2) & 1;
     const int per_round = IPV / P;
-    fetch(0);
     ask(0);
+    fetch(0);
+    if (!early) evaluate(0);
     stage(lds);
-    fetch(1);
-    if (!early) {
-        evaluate(0);
-        ask(1);
-    }
+    if (n_steps > 1) fetch(1);
+    if (!early && per_round < n_steps) ask(1);
     __syncthreads();
-    for (int t = 0; t < n_steps; ++t) {
+    // beside the multiply-adds of step t: the copy for t + 1, the wave's pairs of the round that begins with step `of`
+    auto prepare = [&](int t, int of, bool early) {
         float *nxt = lds + ((t + 1) & 1) * slab_floats;
-        if (early) {
-            if (t % per_round == 0) {
-                evaluate(t / per_round);
-                ask(t / per_round + 1);
-            }
-            stage(nxt);
-            fetch(t + 2);
-        }
+        const bool begins = of % per_round == 0 && of < n_steps;
+        if (early && begins) evaluate(of / per_round);
+        if (t + 1 < n_steps) stage(nxt);
+        if (!early && begins) evaluate(of / per_round);
+        if (t + 2 < n_steps) fetch(t + 2);
+        if (begins && of + per_round < n_steps) ask(of / per_round + 1);
+    };
+    for (int t = 0; t < n_steps; ++t) {
+        if (early) prepare(t, t, true);
         compute(t);
-        if (!early) {
-            stage(nxt);
-            fetch(t + 2);
-            if ((t + 1) % per_round == 0) {
-                evaluate((t + 1) / per_round);
-                ask((t + 1) / per_round + 1);
-            }
-        }
+        if (!early) prepare(t, t + 1, false);
         __syncthreads();
     }
 
@@ -296,15 +290,20 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             // Eight samples a group halve the copies a sample (256 -> 256, 180 rows, B = 32768: 608 us, with four 756).  A CU
             // works through its workgroups in rounds of 256; a step of four samples a group takes about 2200 clocks beside
             // the copies, which go at 64 bytes a clock.
-            if (nw == 16 && g.n_in >= 4) {
+            if (nw == 16 && g.n_in >= 4 && (lps == 16 || nq < 4 || g.base_act == 0)) {       // (with all of it the kernel spills)
                 const int64_t rounds4 = (wgs + 255) / 256, rounds8 = ((B + 2 * per_wg - 1) / (2 * per_wg) * tiles + 255) / 256;
                 if (rounds8 * (4400 + quads / 4) < rounds4 * (2200 + quads / 4)) p.slots = 8;
             }
-            // several inputs a step where their slabs fit: one barrier for all of them
+            // several inputs a step where their slabs fit: one barrier for all of them.  The first step's copy is waited for, so
+            // there have to be steps enough, or a copy of one quad a thread (8 -> 100, G = 120, B = 32768: 19 us an input a
+            // step, 21 two)
             const int most = 64 / (spw * p.slots);
             for (int n = 2; n <= most; n *= 2) {
                 const int q = copies_of(nw, n * quads);
-                if (q && lds_bytes(nw, q) <= kLdsBudget && n * (int64_t)g.slab_rows * g.n_out < 1ll << 29) { p.inputs = n; p.nq = q; }
+                if (q && (q == 1 || 8 * n <= g.n_in) && lds_bytes(nw, q) <= kLdsBudget && n * (int64_t)g.slab_rows * g.n_out < 1ll << 29) {
+                    p.inputs = n;
+                    p.nq = q;
+                }
             }
             return p;
         }

@@ -17,7 +17,9 @@
 // 1149 (mixed instead of in blocks 1444), 256 -> 256, G = 200, B = 8192 285 / 210, 64 -> 64, G = 10, B = 65536 150 / 127,
 // 32 -> 32, G = 1024, B = 131072 270 / 169, 32 -> 32, G = 64, k = 5, B = 65536 108 / 82, 128 -> 256 -> 256 -> 1 with tables of
 // 360 rows, B = 32768 2000 / 1464; the lists (walk_cells) against the records of the sort: 90 / 29, 25 / 15, 53 / 22, 60 / 31,
-// 76 / 15, 288 / 138.
+// 76 / 15, 288 / 138.  An evaluation
+// is 100 .. 200 instructions a batch of 64 entries, as much as the quads of a narrow layer: without masks and shifts inside the table
+// (wave_windows) the whole pass went 181 -> 168 (32 -> 32, k = 5), 376 -> 371 (G = 1024), 626 -> 622 (256 -> 256).
 #pragma once
 #include <type_traits>
 #include "kan_device.hpp"
@@ -271,11 +273,15 @@ __global__ __launch_bounds__(256) void quad_walk_kernel(QuadWalkArgs p)
     };
     auto evaluate = [&]() {
         const bool in = fe < e1, live = in && fs != kQuadPad;
-        const Pair pr = pair_eval<DX>(fx, g, i);
         float w[kMaxK], dw[kMaxK], base, dbase;
         int row0;
-        window_of<false>(pr, g.rows, row0, w, base);
-        if constexpr (DX) window_of<true>(pr, g.rows, row0, dw, dbase);
+        if constexpr (T < 8) {
+            wave_windows<DX>(fx, g, i, row0, w, base, dw, dbase);
+        } else {                            // 512 outputs share an evaluation: two ways of it gain nothing (2158 .. 2295 us either way)
+            const Pair pr = pair_eval<DX>(fx, g, i);
+            window_of<false>(pr, g.rows, row0, w, base);
+            if constexpr (DX) window_of<true>(pr, g.rows, row0, dw, dbase);
+        }
 #pragma unroll
         for (int s = 0; s < kWinSlots; ++s) ar.w[lane >> 2][s][l4] = s < kMaxK && live ? w[s < kMaxK ? s : 0] : 0.0f;
         if constexpr (DX) {
