@@ -218,6 +218,8 @@ static hipError_t direct_latency(const SplineGeom &g, const float *x, const floa
 //                     32 -> 16, G = 1000: 65536 478 / 49
 //   degrees 4 and 5   64 -> 4, G = 10000: B = 65536 481 / 96 (generic); 64 -> 300, G = 20: 4096 283 / 109 (512-wide tiles);
 //                     64 -> 64, G = 300: 32768 140 / 131, 65536 252 / 277 (row stream)
+//   degrees 4 and 5, staged slabs   128 -> 32, G = 30: B = 32768 122 / 153, 65536 243 / 120; 32 -> 64, G = 64: 16384 34 / 41; 16 -> 32, G = 30: 32768
+//                     32 / 23; 16 -> 48: 16384 21 / 24; 8 -> 64: 8192 13 / 16; 8 -> 32, G = 8: 131072 95 / 22
 // (sums of 4 and 6 products cost in proportion: the line counts them)
 int forward_direct_plan(const SplineGeom &g, int64_t B)
 {
@@ -225,10 +227,11 @@ int forward_direct_plan(const SplineGeom &g, int64_t B)
     const int64_t tiles = (n + 63) / 64, w = n <= 16 ? 16 : (n <= 32 ? 32 : tiles * 64), load = B * w * kMaxK / 4;
     const bool in_l2 = (int64_t)ni * g.slab_rows * n * 4 <= 8ll << 20;
     const int lds = forward_lds_plan(g);
+    const bool lds_rows = forward_lds_rows_plan(g, B) != 0 && (n <= 64 || !lds);
 #if KAN_MAXK == 4
-    const bool lds_rows = forward_lds_rows_plan(g, B) != 0 && (n <= 64 || !lds), narrow = narrow_applicable(g) != 0;
+    const bool narrow = narrow_applicable(g) != 0;
 #else
-    const bool lds_rows = false, narrow = false;
+    const bool narrow = false;
 #endif
     if (ni < 8) return B * tiles <= (n < 4 ? 1 << 12 : (n >= 128 && (lds || lds_rows) ? 3 << 12 : 1 << 13)) ? 1 : 0;
     if (n < 4) {                                     // one output per lane at any batch: 16 lanes for at most three
@@ -242,6 +245,7 @@ int forward_direct_plan(const SplineGeom &g, int64_t B)
     constexpr bool six = kMaxK == 6;
     if (narrow)
         return load <= (ni >= 64 || (ni >= 32 && (n >= 8 || g.rows >= 512)) ? 1 << 20 : (ni >= 32 ? 1 << 18 : 1 << 17)) ? 1 : 0;
+    if (lds_rows && six) return load <= (ni >= 32 || (ni >= 16 && n > 32) ? 3 << 19 : (ni >= 16 ? 1 << 20 : 3 << 18)) ? 1 : 0;
     if (lds_rows) return load <= (ni >= 32 ? 1 << 20 : (ni >= 16 ? 3 << 18 : 1 << 19)) ? 1 : 0;
     if (forward_rows_plan(g)) {
         if (!in_l2) return load <= (six && n <= 48 ? 3 << 19 : 1 << 20) ? 1 : 0;

@@ -26,6 +26,7 @@ hipError_t highk_table_forward(const HighKLayer &l, const float *x, const float 
     const kan_k5::SplineGeom g = geom_of(l);
     if (kan_k5::forward_direct_plan(g, B))
         return kan_k5::launch_forward_direct(g, x, table, nullptr, w_b, nullptr, y, B, st);
+    if (kan_k5::forward_lds_rows_plan(g, B)) return kan_k5::launch_forward_lds_rows(g, x, table, y, B, st);
     return kan_k5::launch_forward_generic(g, x, table, w_b, y, B, st);
 }
 
@@ -51,8 +52,10 @@ hipError_t highk_forward(const HighKLayer &l, const float *x, const float *coef,
         return kan_k5::launch_forward_direct(g, x, coef, w_s, w_b, keep_table ? cf : nullptr, y, B, st);
     hipError_t e = kan_k5::launch_fold_scale(coef, w_s, g.base_act ? w_b : nullptr, cf, g.n_in, g.rows, g.n_out, st);
     if (e != hipSuccess) return e;
+    if (g.n_out <= 64 && kan_k5::forward_lds_rows_plan(g, B)) return kan_k5::launch_forward_lds_rows(g, x, cf, y, B, st);
     if (kan_k5::forward_rows_plan(g)) return kan_k5::launch_forward_rows(g, x, cf, y, B, st);
     if (kan_k5::forward_lds_plan(g)) return kan_k5::launch_forward_lds(g, x, cf, y, B, st);
+    if (kan_k5::forward_lds_rows_plan(g, B)) return kan_k5::launch_forward_lds_rows(g, x, cf, y, B, st);
     return kan_k5::launch_forward_generic(g, x, cf, w_b, y, B, st);
 }
 

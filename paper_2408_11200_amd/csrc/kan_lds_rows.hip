@@ -29,16 +29,19 @@
 // tables 500 on the old banks, 362 on these); 32 -> 32, G = 256, B = 131072 with its fold 76 / 57; 64 -> 64, G = 10, B = 65536
 // 103 / 79.  Layers of two to twelve inputs, whose few steps do not hide the first copy: 0.88 of the time over all, 1.09 at most
 // (3 -> 100, G = 64, B = 65536: 19.6 / 21.3).
+// Windows of six rows (degrees 4 and 5, kan_lds_rows_k5.hip) against the direct and the row-stream kernel they had: 32 -> 32,
+// G = 64, k = 5, B = 65536 with the fold 80 / 50; 600 calls of 8..128 inputs, 32..256 outputs: 0.69 of the time, 1.08 at most.
 #include <type_traits>
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
 #include "kan_wave.hpp"
 
-namespace kan {
+namespace KAN_NS {
 
 namespace {
 
-constexpr int kPairFloats = 8;      // w[0..3], two byte offsets of window rows, base, 1 unused
+// w[0..K), then two byte offsets of window rows and the base value; a tile of 64 has one offset and the base value
+constexpr int kPairFloats = kMaxK == 4 ? 8 : 12;
 
 }  // namespace
 
@@ -142,7 +145,14 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
         row0 += my_ii % P * g.slab_rows;
         // pair (input ii of the round, sample smp) sits at index ii * SMP + smp == the lane that evaluated it
         float *pair = pairs + lane * kPairFloats;
-        if constexpr (LPS == 16) {
+        if constexpr (kMaxK == 6) {
+            const bool swap = LPS == 8 && ((row0 + my_smp) & 1);       // as below, rows 4 and 5 too
+            *reinterpret_cast<float4 *>(pair) = make_float4(w[swap ? 1 : 0], w[swap ? 0 : 1], w[swap ? 3 : 2], w[swap ? 2 : 3]);
+            *reinterpret_cast<float4 *>(pair + 4) =
+                make_float4(w[swap ? kMaxK - 1 : kMaxK - 2], w[swap ? kMaxK - 2 : kMaxK - 1], __int_as_float((row0 + (swap ? 1 : 0)) * TJ * 4),
+                            LPS == 16 ? base : __int_as_float((row0 + (swap ? 0 : 1)) * TJ * 4));
+            if constexpr (LPS == 8 && BASE) pair[8] = base;
+        } else if constexpr (LPS == 16) {
             *reinterpret_cast<float4 *>(pair) = make_float4(w[0], w[1], w[2], w[3]);
             *reinterpret_cast<float2 *>(pair + 4) = make_float2(__int_as_float(row0 * TJ * 4), base);
         } else {
@@ -156,7 +166,7 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
     };
 
     // slots whose rows are in flight together: with more the kernel spills, and every spill waits for the copies on their way
-    constexpr int kAtOnce = S == 8 ? (NQ + BASE < 4 ? 2 : 1) : NQ + BASE < 5 ? 4 : 2;
+    constexpr int kAtOnce = S == 8 ? (kMaxK == 4 && NQ + BASE < 4 ? 2 : 1) : NW == 8 || (kMaxK == 4 && NQ + BASE < 5) ? 4 : 2;
     auto compute = [&](int t) {
         const int i0 = t * P;
         const float *cur = lds + (t & 1) * slab_floats;
@@ -175,15 +185,24 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
 #pragma unroll
             for (int q = 0; q < S; ++q) {
                 const float *pq = pp + q * (SPW * kPairFloats);
-                const float4 wv = *reinterpret_cast<const float4 *>(pq);
-                const float2 at = *reinterpret_cast<const float2 *>(pq + 4);
-                const float base = !BASE ? 0.0f : LPS == 16 ? at.y : pq[6];
+                float ws[kMaxK];
+                float2 at;
+                const float4 wa = *reinterpret_cast<const float4 *>(pq);
+                ws[0] = wa.x; ws[1] = wa.y; ws[2] = wa.z; ws[3] = wa.w;
+                if constexpr (kMaxK == 4) {
+                    at = *reinterpret_cast<const float2 *>(pq + 4);
+                } else {
+                    const float4 wc = *reinterpret_cast<const float4 *>(pq + 4);
+                    ws[4] = wc.x; ws[5] = wc.y;
+                    at = make_float2(wc.z, wc.w);
+                }
+                const float base = !BASE ? 0.0f : LPS == 16 ? at.y : pq[kMaxK + 2];
                 const char *win = reinterpret_cast<const char *>(cur + lj * 4);
                 const float *w0 = reinterpret_cast<const float *>(win + __float_as_int(at.x));
                 const float *w1 = LPS == 16 ? w0 + TJ : reinterpret_cast<const float *>(win + __float_as_int(at.y));
-                const float4 c[kMaxK] = {*reinterpret_cast<const float4 *>(w0), *reinterpret_cast<const float4 *>(w1),
-                                         *reinterpret_cast<const float4 *>(w0 + 2 * TJ), *reinterpret_cast<const float4 *>(w1 + 2 * TJ)};
-                const float ws[kMaxK] = {wv.x, wv.y, wv.z, wv.w};
+                float4 c[kMaxK];
+#pragma unroll
+                for (int s = 0; s < kMaxK; ++s) c[s] = *reinterpret_cast<const float4 *>((s % 2 ? w1 : w0) + s / 2 * 2 * TJ);
 #pragma unroll
                 for (int s = 0; s < kMaxK; ++s) {
                     acc[q][0] = fmaf(ws[s], c[s].x, acc[q][0]);
@@ -263,6 +282,9 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
 {
     RowsPlan none = {0, 0, 0, 0, 0};
     if (g.rows < kMaxK || g.n_out < 32) return none;
+    // Windows of six: layers of few inputs gain least, and those of up to 16 inputs with 33 .. 35 outputs are what is left to the
+    // row stream (65536 x 16 -> 33, G = 30, k = 5: 68 us there, 29 here; 16 -> 40 69 / 30)
+    if (kMaxK == 6 && (g.n_in < 8 || (g.n_in <= 16 && g.n_out > 32 && g.n_out < 36))) return none;
     if (g.slab_rows != g.rows + 1 && (g.slab_rows != g.rows || g.base_act != 0)) return none;
     if ((int64_t)g.slab_rows * g.n_out >= 1ll << 29) return none;           // the copies' offsets have 31 bits
     const int lps_opts[] = {16, 8};
@@ -290,9 +312,11 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             // Eight samples a group halve the copies a sample (256 -> 256, 180 rows, B = 32768: 608 us, with four 756).  A CU
             // works through its workgroups in rounds of 256; a step of four samples a group takes about 2200 clocks beside
             // the copies, which go at 64 bytes a clock.
-            if (nw == 16 && g.n_in >= 4 && (lps == 16 || nq < 4 || g.base_act == 0)) {       // (with all of it the kernel spills)
+            // (Not where the kernel would spill.)
+            const bool room = kMaxK == 4 ? lps == 16 || nq < 4 || g.base_act == 0 : nq < (lps == 16 ? 3 : 2);
+            if (nw == 16 && g.n_in >= 4 && room) {
                 const int64_t rounds4 = (wgs + 255) / 256, rounds8 = ((B + 2 * per_wg - 1) / (2 * per_wg) * tiles + 255) / 256;
-                if (rounds8 * (4400 + quads / 4) < rounds4 * (2200 + quads / 4)) p.slots = 8;
+                if (rounds8 * (1100 * kMaxK + quads / 4) < rounds4 * (550 * kMaxK + quads / 4)) p.slots = 8;
             }
             // several inputs a step where their slabs fit: one barrier for all of them.  The first step's copy is waited for, so
             // there have to be steps enough, or a copy of one quad a thread (8 -> 100, G = 120, B = 32768: 19 us an input a
@@ -300,7 +324,7 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             const int most = 64 / (spw * p.slots);
             for (int n = 2; n <= most; n *= 2) {
                 const int q = copies_of(nw, n * quads);
-                if (q && (q == 1 || 8 * n <= g.n_in) && lds_bytes(nw, q) <= kLdsBudget && n * (int64_t)g.slab_rows * g.n_out < 1ll << 29) {
+                if (q && (q == 1 || 8 * n <= g.n_in) && (kMaxK == 4 || p.slots == 4 || q < 3) && lds_bytes(nw, q) <= kLdsBudget && n * (int64_t)g.slab_rows * g.n_out < 1ll << 29) {
                     p.inputs = n;
                     p.nq = q;
                 }
@@ -364,4 +388,4 @@ hipError_t launch_forward_lds_rows(const SplineGeom &g, const float *x, const fl
     return hipErrorInvalidValue;
 }
 
-}  // namespace kan
+}  // namespace KAN_NS

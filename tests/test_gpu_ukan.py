@@ -97,6 +97,12 @@ def test_ukan_degrees_four_and_five(B, n_in, n_out, k, base_act):
         assert torch.equal(g[n], g_ref[n]), n
 
 
+@pytest.mark.parametrize("B,n_in,n_out,k", [(20000, 9, 64, 5), (33000, 8, 32, 4), (22000, 9, 96, 5)])
+def test_ukan_degrees_four_and_five_on_staged_slabs(B, n_in, n_out, k):
+    spec, p, x, gy = make(60 + k, B, n_in, n_out, k=k, base_act=0)
+    run(spec, p, x, np.float32(gy / np.sqrt(B)), max_groups=64)
+
+
 def _random_ukan_shapes(n, seed):
     rng = np.random.default_rng(seed)
     return [(int(rng.integers(1, 1500)), int(rng.integers(1, 20)), int(rng.choice([1, 5, 8, 32, 64, 100, 256, 260])),
