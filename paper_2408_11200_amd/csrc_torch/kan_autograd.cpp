@@ -6,7 +6,9 @@
 // of GPU work, and a layer's backward node needs the interpreter lock here no more.  Tensors of a forward pass are kept
 // through save_for_backward only, so hooks on saved tensors and the checks for changes in place see them.
 #include <torch/csrc/autograd/custom_function.h>
+#include <torch/csrc/jit/frontend/tracer.h>
 #include <torch/csrc/utils/pybind.h>
+#include <torch/library.h>
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
 #include "kan.h"
@@ -163,21 +165,55 @@ struct UkanLayer : torch::autograd::Function<UkanLayer> {
     }
 };
 
+Tensor kan_layer(const Tensor &x, const Tensor &coef, const Tensor &w_s, const std::optional<Tensor> &w_b, int64_t n_in, int64_t n_out,
+                 int64_t G, int64_t k, double lo, double hi, int64_t base_act)
+{
+    const kan_layer_desc d = {(int32_t)n_in, (int32_t)n_out, (int32_t)G, (int32_t)k, (float)lo, (float)hi, (int32_t)base_act};
+    return KanLayer::apply(x, coef, w_s, w_b, d);
+}
+
+Tensor ukan_layer(const Tensor &x, const Tensor &E, const Tensor &W1, const Tensor &b1, const Tensor &W2, const Tensor &b2,
+                  const Tensor &scale, const std::optional<Tensor> &w_b, int64_t n_in, int64_t n_out, int64_t k, double h, int64_t d_pe,
+                  int64_t d_feat, int64_t d_hidden, int64_t base_act, int64_t max_groups)
+{
+    const UkanCall c = {{(int32_t)n_in, (int32_t)n_out, (int32_t)k, (float)h, (int32_t)d_pe, (int32_t)d_feat, (int32_t)d_hidden,
+                         (int32_t)base_act}, (int32_t)max_groups, 0};
+    return UkanLayer::apply(x, E, W1, b1, W2, b2, scale, w_b, c);
+}
+
+// The layers as operators of torch's dispatcher: what torch.jit.trace records.  It sees dispatched calls only, so a node applied
+// directly would leave nothing in the graph but the allocation of its result.  Outside a trace the dispatcher is passed by.
+constexpr const char *kKanOp = "paper_2408_11200_amd::kan_layer", *kUkanOp = "paper_2408_11200_amd::ukan_layer";
+
+template <class F, class... A>
+Tensor call(const char *op, F f, const A &...a)
+{
+    py::gil_scoped_release unlock;
+    if (!torch::jit::tracer::isTracing()) return f(a...);
+    return c10::Dispatcher::singleton().findSchemaOrThrow(op, "").typed<std::remove_pointer_t<F>>().call(a...);
+}
+
 }  // namespace
+
+TORCH_LIBRARY(paper_2408_11200_amd, m)
+{
+    m.def("kan_layer(Tensor x, Tensor coef, Tensor w_s, Tensor? w_b, int n_in, int n_out, int G, int k, float grid_lo, float grid_hi, "
+          "int base_act) -> Tensor", &kan_layer);
+    m.def("ukan_layer(Tensor x, Tensor E, Tensor W1, Tensor b1, Tensor W2, Tensor b2, Tensor scale, Tensor? w_b, int n_in, int n_out, "
+          "int k, float h, int d_pe, int d_feat, int d_hidden, int base_act, int max_groups) -> Tensor", &ukan_layer);
+}
 
 PYBIND11_MODULE(_autograd, m)
 {
     m.def("kan_layer", [](int32_t n_in, int32_t n_out, int32_t G, int32_t k, float lo, float hi, int32_t base_act, const Tensor &x,
                           const Tensor &coef, const Tensor &w_s, const std::optional<Tensor> &w_b) {
-        const kan_layer_desc d = {n_in, n_out, G, k, lo, hi, base_act};
-        py::gil_scoped_release unlock;
-        return KanLayer::apply(x, coef, w_s, w_b, d);
+        return call(kKanOp, &kan_layer, x, coef, w_s, w_b, (int64_t)n_in, (int64_t)n_out, (int64_t)G, (int64_t)k, (double)lo, (double)hi,
+                    (int64_t)base_act);
     });
     m.def("ukan_layer", [](int32_t n_in, int32_t n_out, int32_t k, float h, int32_t d_pe, int32_t d_feat, int32_t d_hidden, int32_t base_act,
                            int32_t max_groups, const Tensor &x, const Tensor &E, const Tensor &W1, const Tensor &b1, const Tensor &W2,
                            const Tensor &b2, const Tensor &scale, const std::optional<Tensor> &w_b) {
-        const UkanCall c = {{n_in, n_out, k, h, d_pe, d_feat, d_hidden, base_act}, max_groups, 0};
-        py::gil_scoped_release unlock;
-        return UkanLayer::apply(x, E, W1, b1, W2, b2, scale, w_b, c);
+        return call(kUkanOp, &ukan_layer, x, E, W1, b1, W2, b2, scale, w_b, (int64_t)n_in, (int64_t)n_out, (int64_t)k, (double)h, (int64_t)d_pe,
+                    (int64_t)d_feat, (int64_t)d_hidden, (int64_t)base_act, (int64_t)max_groups);
     });
 }

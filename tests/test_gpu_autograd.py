@@ -137,3 +137,38 @@ def test_ukan_node_reports_a_span_past_the_bound():
     with pytest.raises(binding.KanError) as e:
         autograd.ukan_layer(spec, x, T, 8)
     assert e.value.status == binding.KAN_ERR_RANGE
+
+
+class Layers(torch.nn.Module):
+    """A UKAN layer on top of a KAN layer, its parameters the module's own."""
+
+    def __init__(self, kan, p, ukan, q):
+        super().__init__()
+        self.specs = (kan, ukan)
+        own = lambda p: torch.nn.ParameterDict({n: torch.nn.Parameter(t.detach().clone()) for n, t in p.items()})
+        self.p, self.q = own(p), own(q)
+
+    def forward(self, x):
+        h = autograd.kan_layer(self.specs[0], x, self.p["coef"], self.p["w_s"], self.p["w_b"])
+        return autograd.ukan_layer(self.specs[1], h, dict(self.q.items()), 256)
+
+
+def test_traced_module_runs_the_layers(tmp_path):
+    """torch.jit.trace records the layers: the traced module gives the module's own bits on inputs that the trace has not seen,
+    trains, and can be saved; parameters that are no part of the module are refused as for any operator."""
+    s, x, p, _ = kan_tensors()
+    spec = workloads.UkanLayerSpec(s.n_out, 4, 3, 0.5, 8, 8, 16)
+    q = {n: dev(a) for n, a in workloads.ukan_params(np.random.default_rng(4), spec).items() if n != "w_b"}
+    m = Layers(s, p, spec, q)
+    traced = torch.jit.trace(m, (x.detach(),))
+    traced.save(str(tmp_path / "layers.pt"))
+    loaded = torch.jit.load(str(tmp_path / "layers.pt"))
+    for scale in (0.5, 0.25, 1.0):
+        xs = (x.detach() * scale).requires_grad_(True)
+        want = m(xs)
+        assert torch.equal(traced(xs), want) and torch.equal(loaded(xs), want)
+        leaves = [xs] + list(m.parameters())
+        for a, b in zip(torch.autograd.grad(traced(xs).sum(), leaves), torch.autograd.grad(want.sum(), leaves)):
+            assert torch.equal(a, b)
+    with pytest.raises(RuntimeError, match="requires grad"):
+        torch.jit.trace(lambda a: autograd.kan_layer(s, a, p["coef"], p["w_s"], p["w_b"]), (x.detach(),))
