@@ -32,16 +32,26 @@ void check(int status, const char *where)
     if (status != KAN_OK) raise_kan_error(status, where);
 }
 
+[[noreturn]] void refuse(const char *what)
+{
+    py::gil_scoped_acquire lock;
+    PyErr_SetString(PyExc_AssertionError, what);
+    throw py::error_already_set();
+}
+
 // pointer of a device-resident contiguous fp32 tensor (null: no tensor); anything else is refused as binding.py refuses it
 float *f32(const Tensor &t)
 {
     if (!t.defined()) return nullptr;
-    if (t.scalar_type() != at::kFloat || !t.is_cuda() || !t.is_contiguous()) {
-        py::gil_scoped_acquire lock;
-        PyErr_SetString(PyExc_AssertionError, "device-resident contiguous float32 tensors only");
-        throw py::error_already_set();
-    }
+    if (t.scalar_type() != at::kFloat || !t.is_cuda() || !t.is_contiguous()) refuse("device-resident contiguous float32 tensors only");
     return static_cast<float *>(t.data_ptr());
+}
+
+// What a forward pass left for its backward pass, as the graph hands it back: a hook on saved tensors may have replaced it.
+void *kept(const Tensor &t)
+{
+    if (!t.is_cuda() || !t.is_contiguous()) refuse("device-resident contiguous tensors only");
+    return t.data_ptr();
 }
 
 Tensor or_none(const std::optional<Tensor> &t) { return t ? *t : Tensor(); }
@@ -98,7 +108,7 @@ struct KanLayer : torch::autograd::Function<KanLayer> {
         if (need[2]) g[2] = at::empty({d.n_in, d.n_out}, f);
         if (need[3]) g[3] = at::empty({d.n_in, d.n_out}, f);
         const Tensor bws = bytes_like(xc, kan_workspace_bytes(&d, B, KAN_PASS_BACKWARD));
-        check(kan_backward_saved(&d, B, f32(xc), f32(cc), f32(sc), f32(bc), f32(gy), ws.data_ptr(), f32(g[0]), f32(g[1]), f32(g[2]),
+        check(kan_backward_saved(&d, B, f32(xc), f32(cc), f32(sc), f32(bc), f32(gy), kept(ws), f32(g[0]), f32(g[1]), f32(g[2]),
                                  f32(g[3]), bws.data_ptr(), (size_t)bws.numel(), stream()),
               "kan_backward_saved");
         return g;
@@ -158,7 +168,7 @@ struct UkanLayer : torch::autograd::Function<UkanLayer> {
         const ukan_params p = params_of(tensors);
         const ukan_grads gg = {f32(g[1]), f32(g[2]), f32(g[3]), f32(g[4]), f32(g[5]), f32(g[6]), f32(g[7])};
         const Tensor ws = bytes_like(xc, ukan_workspace_bytes(&c.d, B, c.max_groups, KAN_PASS_BACKWARD));
-        check(ukan_cg_backward_saved(&c.d, B, f32(xc), &p, f32(gy), f32(g[0]), &gg, c.max_groups, held.data_ptr(), (size_t)held.numel(),
+        check(ukan_cg_backward_saved(&c.d, B, f32(xc), &p, f32(gy), f32(g[0]), &gg, c.max_groups, kept(held), (size_t)held.numel(),
                                      c.span, ws.data_ptr(), (size_t)ws.numel(), stream()),
               "ukan_cg_backward_saved");
         return g;

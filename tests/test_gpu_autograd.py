@@ -116,6 +116,22 @@ def test_nodes_keep_autograd_contracts():
     assert e.value.status == binding.KAN_ERR_UNSUPPORTED
 
 
+@pytest.mark.parametrize("unpack", [lambda t: t.cpu(), lambda t: torch.stack((t, t), 1)[:, 0]])
+def test_what_a_forward_pass_left_is_checked_again(unpack):
+    """The folded table and the UKAN intermediates go through the hooks on saved tensors: one that comes back on the host or
+    with gaps is refused, as binding.py refuses it."""
+    s, x, p, gy = kan_tensors()
+    rng = np.random.default_rng(4)
+    spec = workloads.UkanLayerSpec(3, 4, 3, 0.25, 8, 8, 16)
+    T = {n: dev(a, True) for n, a in workloads.ukan_params(rng, spec).items() if n != "w_b"}
+    xu = dev(np.float32(rng.uniform(-1, 1, (100, 3))), True)
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t, lambda t: unpack(t) if t.dtype == torch.uint8 else t):
+        outs = [autograd.kan_layer(s, x, p["coef"], p["w_s"], p["w_b"]), autograd.ukan_layer(spec, xu, T, 64)]
+    for y in outs:
+        with pytest.raises(AssertionError):
+            y.sum().backward()
+
+
 def test_nodes_run_on_the_stream_of_their_forward_pass():
     s, x, p, gy = kan_tensors(B=2000, n_in=16, n_out=20)
     names = ("coef", "w_s", "w_b")
