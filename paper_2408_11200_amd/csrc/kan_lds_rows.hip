@@ -237,9 +237,15 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
     auto prepare = [&](int t, int of, bool early) {
         float *nxt = lds + ((t + 1) & 1) * slab_floats;
         const bool begins = of % per_round == 0 && of < n_steps;
-        if (early && begins) evaluate(of / per_round);
+        if (early && begins) {
+            evaluate(of / per_round);
+            wave_lds_sync();               // compute() reads what other lanes wrote, with no barrier in between
+        }
         if (t + 1 < n_steps) stage(nxt);
-        if (!early && begins) evaluate(of / per_round);
+        if (!early && begins) {
+            wave_lds_sync();               // compute() has read what is overwritten here
+            evaluate(of / per_round);
+        }
         if (t + 2 < n_steps) fetch(t + 2);
         if (begins && of + per_round < n_steps) ask(of / per_round + 1);
     };

@@ -115,6 +115,23 @@ def test_lds_rows_kernel(B, n_in, n_out, G, k, outside):
     assert "forward_lds_rows" in forward_with_families(workloads.random_kan_layer(n_in, B, n_in, n_out, G, k, outside_frac=outside))
 
 
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (16448, 33, 64, 40, 3), (20032, 37, 35, 17, 1), (33024, 9, 32, 240, 3),     # eight waves, tiles of 64 and 32
+    (65600, 11, 64, 10, 3), (131072, 35, 64, 40, 2), (131136, 34, 32, 300, 3),  # sixteen, four and eight samples a group
+    (16448, 33, 64, 40, 5), (33024, 9, 32, 60, 4), (66048, 35, 50, 40, 4), (131136, 9, 32, 60, 5),
+])
+def test_lds_rows_waves_in_either_order_give_the_same_bits(B, n_in, n_out, G, k):
+    """Half of a workgroup's waves evaluate their pairs before the multiply-adds of a step and half behind them: the same 64
+    samples over and over, so in every wave, have to give the same bits, inputs of several rounds included."""
+    w = workloads.random_kan_layer(n_in, 64, n_in, n_out, G, k, outside_frac=0.1)
+    s, p = w.layers[0], w.params[0]
+    x, coef, w_s, w_b = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"]))
+    x = x.repeat(B // 64, 1)
+    out = []
+    assert "forward_lds_rows" in families_of(lambda: out.append(binding.kan_forward(s, x, coef, w_s, w_b)))
+    assert torch.equal(out[0], out[0][:64].repeat(B // 64, 1))
+
+
 def test_batch_past_the_threads_of_one_launch():
     """64 threads a sample: 2^26 samples are more than one launch takes.  Both ends and the seam between the parts agree
     with a call on those rows alone."""
