@@ -387,3 +387,12 @@ def test_walk_over_padded_cells_keeps_infinities_apart(B, n_in, n_out, G):
             touched[cell[b, i]:cell[b, i] + 4, j] = True
         assert torch.equal(g["gcoef"][i][~touched], clean["gcoef"][i][~touched])
         assert not torch.isfinite(g["gcoef"][i][touched]).any()
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [
+    (256, 3, 256, 14, 3), (2430, 66, 260, 14, 3), (2313, 58, 384, 13, 2), (1900, 32, 515, 56, 4), (300, 2, 100, 30, 5), (300, 5, 40, 70, 3),
+    (1111, 9, 20, 70, 3), (700, 7, 13, 70, 2),
+])
+def test_quads_past_a_batch(B, n_in, n_out, G, k):
+    """Segments of a little more than a batch of 64 entries: their last batch holds a few quads, in streams of unequal length."""
+    assert "walk_cells" in run_with_families(workloads.random_kan_layer(B + n_out, B, n_in, n_out, G, k, outside_frac=0.1))
