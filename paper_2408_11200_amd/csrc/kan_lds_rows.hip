@@ -46,7 +46,7 @@ constexpr int kPairFloats = kMaxK == 4 ? 8 : 12;
 }  // namespace
 
 // A workgroup per (NW * SPW * S samples, TJ outputs), NW waves.  Needs rows >= kMaxK, n_out >= 4, for S = 8 four inputs.
-// BASE: the table has slab_rows = rows + 1 rows per input, the last one the w_b row.  P (a divisor of IPV): inputs a step.
+// BASE: the table has slab_rows = rows + 1 rows per input, the last one the w_b row.  P (a power of two up to IPV): inputs a step.
 template <int LPS, int S, int NW, int NQ, bool BASE>
 __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g, const float *__restrict__ x,
                                                                    const float *__restrict__ cf,
@@ -91,7 +91,10 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
         off[c] = row < step_rows && jj < g.n_out ? (row * g.n_out + (jj + 4 > g.n_out ? g.n_out - 4 : jj)) * 4 : INT32_MIN;     // a row's last quad: n_out - 4 ..
     }
     const int copies = (step_rows * LPS - wave * 64 + NT - 1) / NT;      // of the wave; the others are padding only
-    const int n_steps = (g.n_in + P - 1) / P;
+    // shifts: a division by P costs a step of few multiply-adds as much as one of its LDS round trips (9 -> 40, G = 59, k = 2,
+    // B = 25352 14.2 / 13.9 us, 1 -> 34, G = 74, B = 145799 18.3 / 17.1)
+    const int log_p = __builtin_ctz(P), log_round = __builtin_ctz(IPV) - log_p;     // a round of evaluations: 1 << log_round steps
+    const int n_steps = (g.n_in + P - 1) >> log_p;
     const int64_t step_floats = (int64_t)step_rows * g.n_out;
     f32x4 qd[NQ];
     auto fetch = [&](int t) {
@@ -142,7 +145,7 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
         int row0;
         float w[kMaxK], dw[kMaxK], base, dbase;
         wave_windows<false>(v, gi, 0, row0, w, base, dw, dbase);
-        row0 += my_ii % P * g.slab_rows;
+        row0 += (my_ii & (P - 1)) * g.slab_rows;
         // pair (input ii of the round, sample smp) sits at index ii * SMP + smp == the lane that evaluated it
         float *pair = pairs + lane * kPairFloats;
         if constexpr (kMaxK == 6) {
@@ -225,7 +228,7 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
     // and multiply-adds of different waves overlap between two barriers.  A wave's pairs are its own.
     // Loads are waited for in order, so those for later come after the uses of the earlier ones.
     const bool early = (wave >> 2) & 1;
-    const int per_round = IPV / P;
+    const int per_round = 1 << log_round;
     ask(0);
     fetch(0);
     if (!early) evaluate(0);
@@ -236,18 +239,18 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
     // beside the multiply-adds of step t: the copy for t + 1, the wave's pairs of the round that begins with step `of`
     auto prepare = [&](int t, int of, bool early) {
         float *nxt = lds + ((t + 1) & 1) * slab_floats;
-        const bool begins = of % per_round == 0 && of < n_steps;
+        const bool begins = (of & (per_round - 1)) == 0 && of < n_steps;
         if (early && begins) {
-            evaluate(of / per_round);
+            evaluate(of >> log_round);
             wave_lds_sync();               // compute() reads what other lanes wrote, with no barrier in between
         }
         if (t + 1 < n_steps) stage(nxt);
         if (!early && begins) {
             wave_lds_sync();               // compute() has read what is overwritten here
-            evaluate(of / per_round);
+            evaluate(of >> log_round);
         }
         if (t + 2 < n_steps) fetch(t + 2);
-        if (begins && of + per_round < n_steps) ask(of / per_round + 1);
+        if (begins && of + per_round < n_steps) ask((of >> log_round) + 1);
     };
     for (int t = 0; t < n_steps; ++t) {
         if (early) prepare(t, t, true);
