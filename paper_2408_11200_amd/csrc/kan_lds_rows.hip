@@ -18,8 +18,8 @@
 // lane that evaluated the pair and read back by the group that owns the sample.
 //
 // Bound by the multiply-adds and the LDS reads of the window rows, both about 60 % busy; what was beside them and is gone:
-//   - the waves took the parts of a step (copy, pair evaluation, multiply-adds) in the same order, and its barrier kept them
-//     there, so that the two pipes took turns: half the waves go the other way round;
+//   - the multiply-adds waited for the evaluation of their pairs' x, and the copy for the multiply-adds: what a step reads from
+//     memory is asked for a step or a round ahead (of windows of six rows half the waves take the parts the other way round);
 //   - two groups' 128-byte rows of tiles of 32 met in a bank every other time, and pairs of groups eight samples apart always
 //     (half of all LDS clocks): rows are read by parity, a group's samples are SPW apart;
 //   - a step copied whole multiples of the workgroup, up to nine times its slab, and had a barrier for each input;
@@ -224,10 +224,16 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
         }
     };
 
-    // Two of a SIMD's four waves (one of two) take the steps' parts in the opposite order, so that LDS writes, pair evaluation
-    // and multiply-adds of different waves overlap between two barriers.  A wave's pairs are its own.
+    // A step's copy and pair evaluation come before its multiply-adds, or behind them for the next one; a wave's pairs are its own.
+    // Windows of six rows with sixteen waves: two of a SIMD's four waves take the parts in the opposite order, so that LDS writes,
+    // evaluation and multiply-adds of different waves overlap between two barriers.  Both orders together are twice the code, which
+    // costs more than it gives elsewhere (us, mixed / before / behind:
+    //   four rows              32 -> 32, G = 256, B = 131072 56.2 / 55.2 / 58.5; 256 -> 256, G = 176, B = 32768 558 / 553 / 571;
+    //                          9 -> 40, G = 59, k = 2, B = 25352 14.4 / 13.2 / 13.3; 14 -> 40, G = 17, B = 9972 17.4 / 16.1 / 16.1
+    //   six rows, sixteen      32 -> 32, G = 64, B = 65536 39.7 / 41.6 / 40.4
+    //             eight        46 -> 36, G = 131, B = 16813 63.6 / 58.4 / 55.7; 63 -> 32, G = 6, B = 33887 67.3 / 72.3 / 70.3)
     // Loads are waited for in order, so those for later come after the uses of the earlier ones.
-    const bool early = (wave >> 2) & 1;
+    const bool early = kMaxK == 4 || (NW == 16 && ((wave >> 2) & 1));
     const int per_round = 1 << log_round;
     ask(0);
     fetch(0);

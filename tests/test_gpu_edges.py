@@ -121,8 +121,8 @@ def test_lds_rows_kernel(B, n_in, n_out, G, k, outside):
     (16448, 33, 64, 40, 5), (33024, 9, 32, 60, 4), (66048, 35, 50, 40, 4), (131136, 9, 32, 60, 5),
 ])
 def test_lds_rows_waves_in_either_order_give_the_same_bits(B, n_in, n_out, G, k):
-    """Half of a workgroup's waves evaluate their pairs before the multiply-adds of a step and half behind them: the same 64
-    samples over and over, so in every wave, have to give the same bits, inputs of several rounds included."""
+    """A wave evaluates its pairs before the multiply-adds of a step or behind them, of windows of six rows half a workgroup's waves
+    each: the same 64 samples over and over, so in every wave, have to give the same bits, inputs of several rounds included."""
     w = workloads.random_kan_layer(n_in, 64, n_in, n_out, G, k, outside_frac=0.1)
     s, p = w.layers[0], w.params[0]
     x, coef, w_s, w_b = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"]))
