@@ -336,10 +336,14 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             // several inputs a step where their slabs fit: one barrier for all of them.  The first step's copy is waited for, so
             // there have to be steps enough, or a copy of one quad a thread (8 -> 100, G = 120, B = 32768: 19 us an input a
             // step, 21 two)
+            // (Nor where it costs the CU its second workgroup of eight waves and there is one: 21 -> 64, G = 79, k = 2, B = 37888, 296
+            // workgroups: 45.6 us with two inputs a step, 33 with one.)
+            const auto per_cu = [nw](int q) { return nw == 16 || 2 * lds_bytes(nw, q) > kLdsBudget ? 1 : 2; };
             const int most = 64 / (spw * p.slots);
             for (int n = 2; n <= most; n *= 2) {
                 const int q = copies_of(nw, n * quads);
-                if (q && (q == 1 || 8 * n <= g.n_in) && (kMaxK == 4 || p.slots == 4 || q < 3) && lds_bytes(nw, q) <= kLdsBudget && n * (int64_t)g.slab_rows * g.n_out < 1ll << 29) {
+                if (q && (q == 1 || 8 * n <= g.n_in) && (wgs <= 256 || per_cu(q) == per_cu(nq)) && (kMaxK == 4 || p.slots == 4 || q < 3) &&
+                    lds_bytes(nw, q) <= kLdsBudget && n * (int64_t)g.slab_rows * g.n_out < 1ll << 29) {
                     p.inputs = n;
                     p.nq = q;
                 }
