@@ -218,8 +218,15 @@ static hipError_t direct_latency(const SplineGeom &g, const float *x, const floa
 //                     32 -> 16, G = 1000: 65536 478 / 49
 //   degrees 4 and 5   64 -> 4, G = 10000: B = 65536 481 / 96 (generic); 64 -> 300, G = 20: 4096 283 / 109 (512-wide tiles);
 //                     64 -> 64, G = 300: 32768 140 / 131, 65536 252 / 277 (row stream)
-//   degrees 4 and 5, staged slabs   128 -> 32, G = 30: B = 32768 122 / 153, 65536 243 / 120; 32 -> 64, G = 64: 16384 34 / 41; 16 -> 32, G = 30: 32768
-//                     32 / 23; 16 -> 48: 16384 21 / 24; 8 -> 64: 8192 13 / 16; 8 -> 32, G = 8: 131072 95 / 22
+//   degrees 4 and 5, staged slabs (a round of workgroups costs an input the same whether the chip is full or not, and a copied row
+//                     has to serve enough samples)
+//       up to 32 outputs   32 -> 32, G = 200: B = 34453 48 / 40, 48062 48 / 55, 66594 (a second round begins) 84 / 73; 63 -> 32, G = 131:
+//                          34443 84 / 67; 23 -> 32, G = 20: 27322 34 / 27; 24 -> 32, G = 200: 34170 34 / 35; 16 -> 32: G = 140 23905 25 / 23,
+//                          G = 80 34771 23 / 32; 14 -> 32, G = 324: 19738 25 / 20; 12 -> 32, G = 200: 24358 21 / 23; 8 -> 32, G = 6: 24141 15 / 21
+//       more, long tables  32 -> 48, G = 131: 17406 42 / 33; 100 -> 48, G = 131: 17140 113 / 94; 16 -> 40, G = 131: 17881 24 / 22, G = 80
+//                          24000 20 / 29; 13 -> 59, G = 85: 12493 19 / 16; 128 -> 36, G = 131: 34624 (two rounds) 284 / 258
+//             short        32 -> 48, G = 30: 24000 32 / 45; 32 -> 64, G = 30: 17647 29 / 37; 8 -> 40, G = 30: 9448 12.5 / 11.6, 13107
+//                          12.5 / 14.4; 12 -> 40, G = 30: 9649 17 / 13
 // (sums of 4 and 6 products cost in proportion: the line counts them)
 int forward_direct_plan(const SplineGeom &g, int64_t B)
 {
@@ -245,7 +252,13 @@ int forward_direct_plan(const SplineGeom &g, int64_t B)
     constexpr bool six = kMaxK == 6;
     if (narrow)
         return load <= (ni >= 64 || (ni >= 32 && (n >= 8 || g.rows >= 512)) ? 1 << 20 : (ni >= 32 ? 1 << 18 : 1 << 17)) ? 1 : 0;
-    if (lds_rows && six) return load <= (ni >= 32 || (ni >= 16 && n > 32) ? 3 << 19 : (ni >= 16 ? 1 << 20 : 3 << 18)) ? 1 : 0;
+    if (lds_rows && six) {
+        const int64_t round = 7ll << 18, rounds = forward_lds_rows_rounds(g, B);
+        if (n <= 32)
+            return load <= (ni >= 32 ? rounds * round : ni >= 20 ? 3ll << 19 : ni >= 16 ? 5ll << 18 : ni >= 10 ? 1ll << 20 : 3ll << 18) ? 1 : 0;
+        if (g.rows <= 64) return load <= (ni < 16 ? 1 << 20 : 3 << 19) ? 1 : 0;
+        return load <= (ni < 16 ? 5ll << 18 : ni < 64 ? round : rounds * round) ? 1 : 0;
+    }
     if (lds_rows) return load <= (ni >= 32 ? 1 << 20 : (ni >= 16 ? 3 << 18 : 1 << 19)) ? 1 : 0;
     if (forward_rows_plan(g)) {
         if (!in_l2) return load <= (six && n <= 48 ? 3 << 19 : 1 << 20) ? 1 : 0;

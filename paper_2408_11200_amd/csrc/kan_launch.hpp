@@ -85,6 +85,7 @@ hipError_t launch_forward_lds(const SplineGeom &g, const float *x, const float *
 // LDS-staged kernel for long tables (narrow output tile, many samples per workgroup); the plan
 // returns 0 when the shape does not qualify
 int forward_lds_rows_plan(const SplineGeom &g, int64_t B);
+int forward_lds_rows_rounds(const SplineGeom &g, int64_t B);      // of workgroups on the chip; 0: no plan
 hipError_t launch_forward_lds_rows(const SplineGeom &g, const float *x, const float *cf, float *y, int64_t B,
                                    hipStream_t st);
 

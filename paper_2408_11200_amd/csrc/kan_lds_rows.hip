@@ -292,6 +292,7 @@ int copies_of(int nw, int64_t quads)
 }
 
 size_t lds_bytes(int nw, int nq) { return 2ull * nq * 64 * nw * 16 + (size_t)nw * 64 * kPairFloats * sizeof(float); }
+int workgroups_a_cu(int nw, int nq) { return nw == 16 || 2 * lds_bytes(nw, nq) > kLdsBudget ? 1 : 2; }
 
 // tile width, samples a group, workgroup size, copy depth and inputs a step for a layer (lps == 0: not applicable)
 RowsPlan plan_of(const SplineGeom &g, int64_t B)
@@ -339,11 +340,10 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             // step, 21 two)
             // (Nor where it costs the CU its second workgroup of eight waves and there is one: 21 -> 64, G = 79, k = 2, B = 37888, 296
             // workgroups: 45.6 us with two inputs a step, 33 with one.)
-            const auto per_cu = [nw](int q) { return nw == 16 || 2 * lds_bytes(nw, q) > kLdsBudget ? 1 : 2; };
             const int most = 64 / (spw * p.slots);
             for (int n = 2; n <= most; n *= 2) {
                 const int q = copies_of(nw, n * quads);
-                if (q && (q == 1 || 8 * n <= g.n_in) && (wgs <= 256 || per_cu(q) == per_cu(nq)) && (kMaxK == 4 || p.slots == 4 || q < 3) &&
+                if (q && (q == 1 || 8 * n <= g.n_in) && (wgs <= 256 || workgroups_a_cu(nw, q) == workgroups_a_cu(nw, nq)) && (kMaxK == 4 || p.slots == 4 || q < 3) &&
                     lds_bytes(nw, q) <= kLdsBudget && n * (int64_t)g.slab_rows * g.n_out < 1ll << 29) {
                     p.inputs = n;
                     p.nq = q;
@@ -394,6 +394,15 @@ hipError_t launch_by_quads(const RowsPlan &p, const SplineGeom &g, const float *
 }  // namespace
 
 int forward_lds_rows_plan(const SplineGeom &g, int64_t B) { return plan_of(g, B).lps; }
+
+int forward_lds_rows_rounds(const SplineGeom &g, int64_t B)
+{
+    const RowsPlan p = plan_of(g, B);
+    if (p.lps == 0) return 0;
+    const int64_t per_wg = (int64_t)p.nw * (64 / p.lps) * p.slots, tiles = (g.n_out + p.lps * 4 - 1) / (p.lps * 4);
+    const int64_t at_once = 256 * workgroups_a_cu(p.nw, p.nq);
+    return (int)(((B + per_wg - 1) / per_wg * tiles + at_once - 1) / at_once);
+}
 
 hipError_t launch_forward_lds_rows(const SplineGeom &g, const float *x, const float *cf, float *y, int64_t B,
                                    hipStream_t st)

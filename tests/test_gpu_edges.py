@@ -99,6 +99,17 @@ def test_forward_lines(B, n_in, n_out, G, k, family):
     assert "forward_" + family in forward_with_families(w)
 
 
+@pytest.mark.parametrize("B,n_in,n_out,G,k,family", [
+    (34443, 32, 32, 131, 4, "direct"), (40000, 32, 32, 131, 4, "lds_rows"),     # a round of workgroups full enough
+    (66594, 32, 32, 200, 5, "direct"),                                          # a second round of five
+    (19738, 14, 32, 324, 5, "direct"), (23000, 14, 32, 324, 5, "lds_rows"),
+    (12493, 13, 59, 85, 5, "direct"), (14800, 13, 59, 85, 5, "lds_rows"),
+    (9649, 12, 40, 30, 4, "direct"), (12000, 12, 40, 30, 4, "lds_rows"),
+])
+def test_forward_lines_of_six_rows(B, n_in, n_out, G, k, family):
+    assert "forward_" + family in forward_with_families(workloads.random_kan_layer(n_in, B, n_in, n_out, G, k))
+
+
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
     (16400, 33, 64, 40, 3), (16403, 37, 35, 17, 1),             # eight waves: steps of four inputs, the last one of one
     (20000, 34, 63, 100, 3), (33000, 9, 32, 240, 3),            # steps of two; tiles of 32
