@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from paper_2408_11200_amd import binding, workloads
-from test_gpu_kan import dev, run_layer_parity
+from test_gpu_kan import GRAD_TOL, assert_close, dev, run_layer_parity
 from test_gpu_ukan import make as ukan_make, run as ukan_run
 
 pytestmark = pytest.mark.gpu
@@ -407,3 +407,34 @@ def test_walk_over_padded_cells_keeps_infinities_apart(B, n_in, n_out, G):
 def test_quads_past_a_batch(B, n_in, n_out, G, k):
     """Segments of a little more than a batch of 64 entries: their last batch holds a few quads, in streams of unequal length."""
     assert "walk_cells" in run_with_families(workloads.random_kan_layer(B + n_out, B, n_in, n_out, G, k, outside_frac=0.1))
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [(66000, 512, 259, 1000, 3), (66000, 1000, 130, 1000, 5)])
+def test_quads_on_shared_partial_tables(B, n_in, n_out, G, k):
+    """Tables whose nine partial slabs (half a gigabyte each) pass the budget, short enough for cell lists: the last chunk adds to
+    what the first left in its slab, outputs two lanes share once.  Every run gives the same bits; an input's gradients depend on
+    no other input, so three of them are compared with the oracle."""
+    s = workloads.KanLayerSpec(n_in, n_out, G, k, -1.0, 1.0)
+    gen = torch.Generator(device="cuda").manual_seed(B + n_in)
+    rand = lambda std, *shape: torch.randn(shape, generator=gen, device="cuda") * std
+    x = torch.rand((B, n_in), generator=gen, device="cuda") * 2.1 - 1.05
+    coef, w_s, w_b, gy = rand(0.1, n_in, s.M, n_out), rand(1.0, n_in, n_out), rand(1.0, n_in, n_out), rand(B ** -0.5, B, n_out)
+    seen = []
+    hook = ctypes.CFUNCTYPE(None, ctypes.c_char_p, ctypes.c_void_p)(lambda family, stream: seen.append(family.decode()))
+    none = ctypes.CFUNCTYPE(None, ctypes.c_char_p, ctypes.c_void_p)(lambda family, stream: None)
+    binding.kan_set_launch_observer(hook, none)
+    try:
+        g = binding.kan_backward(s, x, coef, w_s, w_b, gy)
+    finally:
+        binding.kan_set_launch_observer(None, None)
+    assert "walk_cells" in seen and seen.count("backward_walk") == 2       # eight or more chunks, then what is left
+    again = binding.kan_backward(s, x, coef, w_s, w_b, gy)
+    assert all(torch.equal(g[n], again[n]) for n in g)
+    sel = [0, 7, n_in - 1]
+    inv_h = oracle.inv_h_of(s.grid_lo, s.grid_hi, G)
+    host = lambda t: np.ascontiguousarray(t.cpu().numpy())
+    ref = oracle.kan_backward(host(x[:, sel]), host(coef[sel]), host(w_s[sel]), host(w_b[sel]), host(gy), G, k, s.grid_lo, inv_h)
+    unit = 1.0 / float(inv_h)
+    assert_close(g["gx"][:, sel].double() * unit, ref["gx"] * unit, GRAD_TOL, "gx")
+    for n in ("gcoef", "gw_s", "gw_b"):
+        assert_close(g[n][sel], ref[n], GRAD_TOL, n)
