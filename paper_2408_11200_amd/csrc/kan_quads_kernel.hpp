@@ -276,7 +276,10 @@ __global__ __launch_bounds__(256) void quad_walk_kernel(QuadWalkArgs p)
         float w[kMaxK], dw[kMaxK], base, dbase;
         int row0;
         if constexpr (T < 8) {
-            wave_windows<DX>(fx, g, i, row0, w, base, dw, dbase);
+            // A pad takes the x of its quad's first entry, which is none: stored as zero, one pad in a batch would put the whole wave
+            // on the masked way wherever the table does not hold zero
+            const float first = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, fx), 0, 0xF, 0xF, true));
+            wave_windows<DX>(fs == kQuadPad ? first : fx, g, i, row0, w, base, dw, dbase);
         } else {                            // 512 outputs share an evaluation: two ways of it gain nothing (2158 .. 2295 us either way)
             const Pair pr = pair_eval<DX>(fx, g, i);
             window_of<false>(pr, g.rows, row0, w, base);

@@ -438,3 +438,10 @@ def test_quads_on_shared_partial_tables(B, n_in, n_out, G, k):
     assert_close(g["gx"][:, sel].double() * unit, ref["gx"] * unit, GRAD_TOL, "gx")
     for n in ("gcoef", "gw_s", "gw_b"):
         assert_close(g[n][sel], ref[n], GRAD_TOL, n)
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [(9000, 9, 64, 100, 3), (3000, 33, 256, 40, 2), (5000, 9, 20, 64, 5), (2100, 33, 300, 30, 3)])
+@pytest.mark.parametrize("lo,hi", [(0.5, 2.0), (-7.0, -3.0)])
+def test_walk_over_padded_cells_of_a_grid_without_zero(B, n_in, n_out, G, k, lo, hi):
+    """The pads between the cells are stored as x = 0, which lies outside these grids."""
+    assert "walk_cells" in run_with_families(workloads.random_kan_layer(B + n_out, B, n_in, n_out, G, k, lo, hi, outside_frac=0.1))
