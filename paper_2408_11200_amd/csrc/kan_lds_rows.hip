@@ -291,7 +291,13 @@ int copies_of(int nw, int64_t quads)
     return need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : need <= 8 ? 8 : 0;
 }
 
-size_t lds_bytes(int nw, int nq) { return 2ull * nq * 64 * nw * 16 + (size_t)nw * 64 * kPairFloats * sizeof(float); }
+constexpr size_t lds_bytes(int nw, int nq) { return 2ull * nq * 64 * nw * 16 + (size_t)nw * 64 * kPairFloats * sizeof(float); }
+
+// the variants that there are: the others would spill registers (eight samples a group), or need more LDS than a CU has
+constexpr bool variant_built(int lps, int slots, int nw, int nq, bool base)
+{
+    return lds_bytes(nw, nq) <= kLdsBudget && (slots == 4 || (kMaxK == 4 ? lps == 16 || nq < 4 || !base : nq < (lps == 16 ? 3 : 2)));
+}
 int workgroups_a_cu(int nw, int nq) { return nw == 16 || 2 * lds_bytes(nw, nq) > kLdsBudget ? 1 : 2; }
 
 // tile width, samples a group, workgroup size, copy depth and inputs a step for a layer (lps == 0: not applicable)
@@ -321,7 +327,7 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             if (nw == 8 && tiles > 1) continue;
             const int64_t quads = (int64_t)g.slab_rows * lps;
             const int nq = copies_of(nw, quads);
-            if (!nq || lds_bytes(nw, nq) > kLdsBudget) continue;
+            if (!nq || !variant_built(lps, 4, nw, nq, g.base_act != 0)) continue;
             // worth it only when a staged row serves many samples (the copy into LDS costs as much LDS
             // time per row as several reads of it): samples * K >= 4 * slab rows
             if (per_wg * kMaxK < 4 * (int64_t)g.slab_rows) continue;
@@ -329,9 +335,7 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             // Eight samples a group halve the copies a sample (256 -> 256, 180 rows, B = 32768: 608 us, with four 756).  A CU
             // works through its workgroups in rounds of 256; a step of four samples a group takes about 2200 clocks beside
             // the copies, which go at 64 bytes a clock.
-            // (Not where the kernel would spill.)
-            const bool room = kMaxK == 4 ? lps == 16 || nq < 4 || g.base_act == 0 : nq < (lps == 16 ? 3 : 2);
-            if (nw == 16 && g.n_in >= 4 && room) {
+            if (nw == 16 && g.n_in >= 4 && variant_built(lps, 8, nw, nq, g.base_act != 0)) {
                 const int64_t rounds4 = (wgs + 255) / 256, rounds8 = ((B + 2 * per_wg - 1) / (2 * per_wg) * tiles + 255) / 256;
                 if (rounds8 * (1100 * kMaxK + quads / 4) < rounds4 * (550 * kMaxK + quads / 4)) p.slots = 8;
             }
@@ -343,8 +347,8 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             const int most = 64 / (spw * p.slots);
             for (int n = 2; n <= most; n *= 2) {
                 const int q = copies_of(nw, n * quads);
-                if (q && (q == 1 || 8 * n <= g.n_in) && (wgs <= 256 || workgroups_a_cu(nw, q) == workgroups_a_cu(nw, nq)) && (kMaxK == 4 || p.slots == 4 || q < 3) &&
-                    lds_bytes(nw, q) <= kLdsBudget && n * (int64_t)g.slab_rows * g.n_out < 1ll << 29) {
+                if (q && (q == 1 || 8 * n <= g.n_in) && (wgs <= 256 || workgroups_a_cu(nw, q) == workgroups_a_cu(nw, nq)) &&
+                    variant_built(lps, p.slots, nw, q, g.base_act != 0) && n * (int64_t)g.slab_rows * g.n_out < 1ll << 29) {
                     p.inputs = n;
                     p.nq = q;
                 }
@@ -376,11 +380,13 @@ template <int LPS, int S, int NW>
 hipError_t launch_by_quads(const RowsPlan &p, const SplineGeom &g, const float *x, const float *cf, float *y, int64_t B,
                            hipStream_t st)
 {
-    auto by_base = [&](auto n) {
+    auto with = [&](auto n, auto base) {
         constexpr int NQ = decltype(n)::value;
-        return g.base_act != 0 ? launch_variant<LPS, S, NW, NQ, true>(g, x, cf, y, B, p.inputs, st)
-                               : launch_variant<LPS, S, NW, NQ, false>(g, x, cf, y, B, p.inputs, st);
+        constexpr bool BASE = decltype(base)::value;
+        if constexpr (variant_built(LPS, S, NW, NQ, BASE)) return launch_variant<LPS, S, NW, NQ, BASE>(g, x, cf, y, B, p.inputs, st);
+        else return hipErrorInvalidValue;
     };
+    auto by_base = [&](auto n) { return g.base_act != 0 ? with(n, std::true_type{}) : with(n, std::false_type{}); };
     switch (p.nq) {
     case 1: return by_base(std::integral_constant<int, 1>{});
     case 2: return by_base(std::integral_constant<int, 2>{});
