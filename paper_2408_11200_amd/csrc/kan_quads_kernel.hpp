@@ -403,14 +403,15 @@ __global__ __launch_bounds__(256) void quad_walk_kernel(QuadWalkArgs p)
         gather(*reinterpret_cast<const uint4 *>(&ar.off[sub][0]), gr);
         // the quads between two moves of a window are a loop of their own, whose registers stay where they are
         const int here = n_quads - bi * QPB < QPB ? n_quads - bi * QPB : QPB;
-        for (int b = 0; b < here;) {
+        int b = 0;
+        do {
             int row = ar.row[sub * QPB + b];
             if constexpr (STREAMS == 1) row = __builtin_amdgcn_readfirstlane(row);
             if (row > cur) advance(row);
 #pragma clang loop unroll(disable)
             do work(b);
             while (++b < here && ((turns >> (4 * b)) & streams) == 0);
-        }
+        } while (b < here);                 // (tested behind: the first quad is there, and a way past it costs the folded builds a copy of their sums)
         if constexpr (DX) {
             // lane -> entry 4 * (position in its quarter) + quarter of the stream's batch
             const unsigned smp = ar.sample[sub * LPS + (q % QPB) * 4 + q / QPB];
