@@ -9,6 +9,8 @@ experiments section need nothing else).
 """
 import os
 
+import torch
+
 from . import binding
 
 _nodes = None
@@ -23,6 +25,9 @@ def _load():
         if not os.path.exists(path):
             raise RuntimeError("%s is missing: build it with `python -m paper_2408_11200_amd.build`" % path)
         from . import _autograd
+        if _autograd.torch_version != torch.__version__:
+            raise RuntimeError("%s was built with torch %s, this is %s: build it again with `python -m paper_2408_11200_amd.build`"
+                               % (path, _autograd.torch_version, torch.__version__))
         _nodes = _autograd
     return _nodes
 

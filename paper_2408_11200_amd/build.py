@@ -33,7 +33,8 @@ def autograd_command(out):
     torch_lib = os.path.join(os.path.dirname(os.path.abspath(cpp_extension.torch.__file__)), "lib")
     include = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], "/opt/rocm/include", os.path.join(ROOT, "include")]
     return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(cpp_extension.torch._C._GLIBCXX_USE_CXX11_ABI)] +
+             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(cpp_extension.torch._C._GLIBCXX_USE_CXX11_ABI),
+             '-DKAN_TORCH_VERSION="%s"' % cpp_extension.torch.__version__] +
             [a for d in include for a in ("-isystem", d)] +
             [os.path.join(HERE, "csrc_torch", "kan_autograd.cpp"), "-o", out, "-L", torch_lib, "-ltorch", "-ltorch_cpu", "-ltorch_python",
              "-lc10", "-lc10_hip", "-L", HERE, "-l:" + os.path.basename(LIB_PATH), "-Wl,-rpath,$ORIGIN"])

@@ -215,6 +215,7 @@ TORCH_LIBRARY(paper_2408_11200_amd, m)
 
 PYBIND11_MODULE(_autograd, m)
 {
+    m.attr("torch_version") = KAN_TORCH_VERSION;    // of the torch the nodes are built on: autograd.py refuses another
     m.def("kan_layer", [](int32_t n_in, int32_t n_out, int32_t G, int32_t k, float lo, float hi, int32_t base_act, const Tensor &x,
                           const Tensor &coef, const Tensor &w_s, const std::optional<Tensor> &w_b) {
         return call(kKanOp, &kan_layer, x, coef, w_s, w_b, (int64_t)n_in, (int64_t)n_out, (int64_t)G, (int64_t)k, (double)lo, (double)hi,

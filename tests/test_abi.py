@@ -120,3 +120,14 @@ def test_workspace_planning_limits(lib):
     assert lib.ukan_saved_bytes(ctypes.byref(u), 1) == 0
     a, b = lib.ukan_saved_bytes(ctypes.byref(u), 64), lib.ukan_saved_bytes(ctypes.byref(u), 128)
     assert 2 * 128 * 64 * 4 * 256 * 4 < a < b < 2.1 * a
+
+
+def test_autograd_nodes_of_another_torch_are_refused(lib, monkeypatch):
+    """The nodes' classes are laid out by the torch they were built with; under another one they are not to run."""
+    import torch
+    from paper_2408_11200_amd import autograd
+    assert autograd._load().torch_version == torch.__version__
+    monkeypatch.setattr(autograd, "_nodes", None)
+    monkeypatch.setattr(torch, "__version__", "1.0.0")
+    with pytest.raises(RuntimeError, match="built with torch"):
+        autograd._load()
