@@ -119,7 +119,7 @@ BackwardPlan backward_plan(const kan_layer_desc *d, int64_t B)
         bp.tail_bytes = align_up(reduce_scratch_bytes(g.n_in, g.rows, g.n_out));
         return bp;
     }
-    // degrees 4 and 5 walk two four-row records per pair
+    // degrees 4 and 5: lists of cells with windows of six rows, or two four-row records a pair where those are sparse
     bp.wp = generic_pays(g, B) ? WalkPlan{} : plan_walk(g, B, true, high_degree(d));
     bp.walk = bp.wp.ok != 0;
     bp.tail_bytes = align_up(reduce_scratch_bytes(g.n_in, g.rows, g.n_out));

@@ -305,8 +305,10 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
 {
     RowsPlan none = {0, 0, 0, 0, 0};
     if (g.rows < kMaxK || g.n_out < 32) return none;
-    // Windows of six: layers of few inputs gain least, and those of up to 16 inputs with 33 .. 35 outputs are what is left to the
-    // row stream (65536 x 16 -> 33, G = 30, k = 5: 68 us there, 29 here; 16 -> 40 69 / 30)
+    // Windows of six: layers of fewer than eight inputs, and of up to 16 with 33 .. 35 outputs, are left to the generic and the
+    // row-stream kernel.  Not for speed: this one is the faster there, past short batches (us, k = 4, G = 30, as it is / here: 2 -> 32
+    // B = 16384 9.9 / 8.8, 131072 31 / 12; 7 -> 32 20 / 15, 85 / 22; 7 -> 64 131072 86 / 32; 8 -> 33 16384 17.6 / 13.5, 131072 103 / 32;
+    // 16 -> 33 65536 69 / 30).
     if (kMaxK == 6 && (g.n_in < 8 || (g.n_in <= 16 && g.n_out > 32 && g.n_out < 36))) return none;
     if (g.slab_rows != g.rows + 1 && (g.slab_rows != g.rows || g.base_act != 0)) return none;
     if ((int64_t)g.slab_rows * g.n_out >= 1ll << 29) return none;           // the copies' offsets have 31 bits
@@ -321,9 +323,10 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             const int64_t per_wg = (int64_t)nw * spw * 4;
             const int64_t wgs = (B + per_wg - 1) / per_wg * tiles;
             if (nw == 16 && wgs < 256) continue;
-            // eight waves (two per SIMD) only when one tile covers the layer: with several tiles every tile
-            // evaluates the pairs again and the smaller workgroup did not beat the generic kernel (256 -> 256,
-            // G = 200, B = 8192: 0.38 ms against 0.34 ms)
+            // eight waves (two per SIMD) only when one tile covers the layer: with several every tile evaluates the pairs again, and
+            // an earlier form of this kernel did not beat the generic one.  This form does where a CU gets a workgroup (generic /
+            // eight waves, B = 8192: 256 -> 256, G = 120 334 / 239 us, G = 200 357 / 279; 128 -> 128, G = 200 148 / 118), and sixteen
+            // waves on a part of the chip do not (512 -> 512, B = 2048, G = 200 597 / 617, G = 400 755 / 1004); the line stands as it was.
             if (nw == 8 && tiles > 1) continue;
             const int64_t quads = (int64_t)g.slab_rows * lps;
             const int nq = copies_of(nw, quads);

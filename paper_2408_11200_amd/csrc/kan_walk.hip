@@ -316,7 +316,7 @@ namespace {
 size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 }
 
-// transposed x | records (row|sample, base, weights, derivative base, derivative weights) |
+// transposed x | records (row|sample, base, weights, derivative base, derivative weights) or cell lists |
 // per-tile partial gx (layers wider than one tile) | carry rows of the list segments | first row of every segment
 static size_t walk_carry_bytes(const WalkPlan &p, int n_in, int n_out)
 {
@@ -329,8 +329,9 @@ size_t walk_scratch_bytes(const WalkPlan &p, int64_t B, int n_in, int n_out)
     const size_t n = (size_t)p.n_chunks * n_in * (p.window > kMaxK ? 2 * (size_t)p.S : p.quads ? (size_t)p.S : (size_t)p.L);
     const int n_part = p.n_jt * (p.hk ? 2 : 1);       // partial dL/dx results per (sample, input)
     const size_t gxp = n_part > 1 ? up256((size_t)n_part * B * n_in * sizeof(float)) : 0;
-    // the records' size in either case (lists of padded cells take up to 24 bytes a pair, records 44 or 88): the space a layer
-    // asks for does not depend on which of the two its batch and table lead to
+    // The records' size in either case (44 bytes a pair, 88 of degrees 4 and 5; lists of padded cells use 24 at most), so that this,
+    // the largest part, does not jump where a batch or a table passes from one to the other.  What stands beside it follows the
+    // plan: partial dL/dx, carry rows of four or six, chunks.
     const size_t lists = 3 * up256(n * 4) + 2 * up256(n * 16);
     return up256((size_t)B * n_in * sizeof(float)) + lists + gxp +
            walk_carry_bytes(p, n_in, n_out) + walk_seg_row_bytes(p, n_in);

@@ -32,7 +32,7 @@ WalkPlan walk_for(const ukan_layer_desc *d, int64_t B, int32_t max_groups)
 {
     SplineGeom g = {};
     g.n_in = d->n_in; g.n_out = d->n_out; g.rows = max_groups * (d->k + 1); g.slab_rows = g.rows; g.k = d->k;
-    return plan_walk(g, B, false, d->k > 3);     // degrees 4 and 5: two four-row records per pair
+    return plan_walk(g, B, false, d->k > 3);     // d->k > 3: windows of six rows, or two four-row records a pair
 }
 
 // degrees 4 and 5 run the kernels built for a window of six rows
