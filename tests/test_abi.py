@@ -99,8 +99,8 @@ def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
 
 def test_workspace_planning_limits(lib):
     """Host-side planning seen through the workspace queries: unsupported shapes report 0 bytes, tables too large
-    for one partial table per chunk stay within the partial-table budget, and the degree-5 backward pass (two
-    records per pair) asks for about twice the record space of the cubic one."""
+    for one partial table per chunk stay within the partial-table budget, and the degree-5 backward pass (room for
+    two records per pair) asks for about twice the record space of the cubic one."""
     lib.kan_workspace_bytes.restype = ctypes.c_size_t
     lib.kan_workspace_bytes.argtypes = [ctypes.POINTER(binding.KanLayerDesc), ctypes.c_int64, ctypes.c_int]
     ws = lambda *a, B=1 << 17, which=binding.PASS_BACKWARD: lib.kan_workspace_bytes(

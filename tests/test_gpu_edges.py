@@ -128,8 +128,9 @@ def test_lds_rows_kernel(B, n_in, n_out, G, k, outside):
 
 @pytest.mark.parametrize("B,n_in,n_out,G,k", [
     (16448, 33, 64, 40, 3), (20032, 37, 35, 17, 1), (33024, 9, 32, 240, 3),     # eight waves, tiles of 64 and 32
-    (65600, 11, 64, 10, 3), (131072, 35, 64, 40, 2), (131136, 34, 32, 300, 3),  # sixteen, four and eight samples a group
-    (16448, 33, 64, 40, 5), (33024, 9, 32, 60, 4), (66048, 35, 50, 40, 4), (131136, 9, 32, 60, 5),
+    (65536, 11, 64, 10, 3), (131072, 3, 32, 256, 3),                            # sixteen, four samples a group
+    (65600, 11, 64, 10, 3), (131072, 35, 64, 40, 2), (131136, 34, 32, 300, 3),  # eight samples
+    (16448, 33, 64, 40, 5), (33024, 9, 32, 60, 4), (65536, 18, 64, 10, 5), (66048, 35, 50, 40, 4), (131136, 9, 32, 60, 5),
 ])
 def test_lds_rows_waves_in_either_order_give_the_same_bits(B, n_in, n_out, G, k):
     """A wave evaluates its pairs before the multiply-adds of a step or behind them, of windows of six rows half a workgroup's waves
