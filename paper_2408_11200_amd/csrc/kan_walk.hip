@@ -216,11 +216,25 @@ WalkPlan plan_lists(const SplineGeom &g, int64_t B, bool allow_shared, bool high
     const int s8 = fit_sums(S < most8 ? S : most8);
     const bool pays8 = g.n_out % 8 == 0 || (g.n_in >= 16 && B * g.n_in >= 1 << 17 && g.rows <= (B <= 16384 ? 320 : 128) &&
                                             (g.n_out - 1) % 512 >= 256);
+    // Chunk c is walked by XCD c mod 8, and eight outputs a lane leave a SIMD two waves: chunks of 2048 samples may leave most of the
+    // chip without work in the last round of waves, or of chunks.  The time of a pass with either length, us: a SIMD's waves two at
+    // a time (a single one takes 0.65 of two), 0.2 an entry, and the partial tables written and read.  Full pass / parameter
+    // gradients only, 1024 : 2048: 203 -> 260, G = 15, k = 1, B = 22307 0.68 / 0.65 (11 chunks, two for three XCDs), 58 -> 384, G = 21, B = 88501
+    // 0.79 / 0.77; 512 -> 512, G = 20, B = 16384 1.03 / 1.05; 13 -> 512, G = 100, B = 63709 1.22 / 1.39.
+    auto pass_us = [&](int q) {
+        const int64_t chunks = (B + q - 1) / q, work = (int64_t)g.n_in * ((g.n_out + 511) / 512);
+        int64_t groups = 1, segs = 1;
+        while (groups * 2 <= 8 && groups * 2 <= chunks) groups *= 2;
+        while (q / (segs * 2) >= 64 && chunks * segs * work < 2048) segs *= 2;
+        const int64_t simds = 1024 / groups, deep = ((chunks + groups - 1) / groups * work * segs + simds - 1) / simds;
+        return (deep / 2 + deep % 2 * 0.65) * (q / segs) * 0.2 + chunks * slab * 2 / 5e6;
+    };
     // every width has a variant (widths that are no multiple of T run its ragged build)
     if (g.n_out > 256 && pays8 && s8 <= most8 && !(quads && high_degree)) {
         p.T = 8;
         p.streams = 1;
-        S = s8;
+        // (of tables that leave the lists dense enough for quads, below)
+        S = s8 == 2048 && g.rows - kMaxK + 1 <= 256 && fit_sums(1024) == 1024 && pass_us(1024) < pass_us(2048) ? 1024 : s8;
     } else {
         S = fit_sums(S);
         if (g.n_out > 32) {

@@ -122,6 +122,21 @@ def test_workspace_planning_limits(lib):
     assert 2 * 128 * 64 * 4 * 256 * 4 < a < b < 2.1 * a
 
 
+@pytest.mark.parametrize("B,n_in,n_out,G,k,samples", [
+    (22307, 203, 260, 15, 1, 1024),     # eleven chunks of 2048 would give three of the eight XCDs twice the others' work
+    (16600, 16, 260, 7, 3, 1024),
+    (16384, 512, 512, 20, 3, 2048),     # eight even ones
+    (63709, 13, 512, 100, 3, 2048),     # a table whose partial sums cost more than the waves' last round
+])
+def test_chunks_of_layers_with_eight_outputs_a_lane(lib, B, n_in, n_out, G, k, samples):
+    """The backward pass has a partial table for every chunk of samples: a cell more asks for a row more in each of them."""
+    lib.kan_workspace_bytes.restype = ctypes.c_size_t
+    lib.kan_workspace_bytes.argtypes = [ctypes.POINTER(binding.KanLayerDesc), ctypes.c_int64, ctypes.c_int]
+    ws = lambda G: lib.kan_workspace_bytes(ctypes.byref(binding.KanLayerDesc(n_in, n_out, G, k, -1.0, 1.0, 1)), B, binding.PASS_BACKWARD)
+    tables = (ws(G + 1) - ws(G)) / (n_in * n_out * 4)
+    assert 0 <= tables - -(-B // samples) < 3
+
+
 def test_autograd_nodes_of_another_torch_are_refused(lib, monkeypatch):
     """The nodes' classes are laid out by the torch they were built with; under another one they are not to run."""
     import torch

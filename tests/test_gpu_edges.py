@@ -370,6 +370,7 @@ def test_sort_passes(B, n_in, n_out, G, k):
     (8192, 8, 20, 1024, 3, "walk_cells"), (8192, 8, 20, 1025, 3, "walk_sort"),    # the longest table one counting pass sorts
     (255, 1, 1, 70, 1, "walk_cells"), (4097, 9, 13, 70, 2, "walk_cells"),         # one output a lane
     (2100, 33, 300, 30, 3, "walk_cells"), (9000, 67, 515, 7, 3, "walk_cells"),    # eight outputs a lane; a ragged last tile
+    (16600, 16, 260, 7, 3, "walk_cells"), (16385, 40, 510, 21, 2, "walk_cells"),  # chunks of 1024 for the balance of the XCDs
     (20000, 70, 33, 30, 3, "walk_cells"),                                         # sums in two levels
     (5000, 40, 130, 30, 5, "walk_cells"), (5000, 9, 20, 64, 5, "walk_cells"), (700, 3, 96, 12, 4, "walk_cells"),
 ])
