@@ -231,6 +231,7 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
     // costs more than it gives elsewhere (us, mixed / before / behind:
     //   four rows              32 -> 32, G = 256, B = 131072 56.2 / 55.2 / 58.5; 256 -> 256, G = 176, B = 32768 558 / 553 / 571;
     //                          9 -> 40, G = 59, k = 2, B = 25352 14.4 / 13.2 / 13.3; 14 -> 40, G = 17, B = 9972 17.4 / 16.1 / 16.1
+    //                          but 64 -> 64, G = 10, B = 65536, four inputs a step 81.7 / 84.7
     //   six rows, sixteen      32 -> 32, G = 64, B = 65536 39.7 / 41.6 / 40.4
     //             eight        46 -> 36, G = 131, B = 16813 63.6 / 58.4 / 55.7; 63 -> 32, G = 6, B = 33887 67.3 / 72.3 / 70.3)
     // Loads are waited for in order, so those for later come after the uses of the earlier ones.
