@@ -3,6 +3,7 @@
 #include <mutex>
 #include "kan.h"
 #include "kan_launch.hpp"
+#include "kan_matrix.hpp"
 #include "kan_highk.hpp"
 
 using namespace kan;
@@ -70,6 +71,12 @@ HighKLayer highk_of(const kan_layer_desc *d)
 size_t folded_bytes(const kan_layer_desc *d)
 {
     return align_up((size_t)d->n_in * (size_t)(d->G + d->k + 1) * (size_t)d->n_out * sizeof(float));
+}
+
+// the split table of the matrix-core forward kernel, behind the folded one (0: the shape does not qualify)
+size_t matrix_bytes(const kan_layer_desc *d)
+{
+    return high_degree(d) ? 0 : ::kan::matrix_table(d->n_in, d->n_out, d->G + d->k, kMaxK).bytes;
 }
 
 size_t edge_bytes(const kan_layer_desc *d)
@@ -156,7 +163,7 @@ extern "C" const char *kan_strerror(int status)
 extern "C" size_t kan_workspace_bytes(const kan_layer_desc *desc, int64_t B, int pass)
 {
     if (check_desc(desc) != KAN_OK || B < 0) return 0;
-    if (pass == KAN_PASS_FORWARD) return folded_bytes(desc);
+    if (pass == KAN_PASS_FORWARD) return folded_bytes(desc) + matrix_bytes(desc);
     if (pass != KAN_PASS_BACKWARD) return 0;
     const BackwardPlan bp = backward_plan(desc, B);
     return folded_bytes(desc) + bp.rec_bytes + (size_t)bp.n_slabs * folded_bytes(desc) + bp.tail_bytes +
@@ -165,9 +172,10 @@ extern "C" size_t kan_workspace_bytes(const kan_layer_desc *desc, int64_t B, int
 
 // Forward pass with the scratch space given explicitly; shared by kan_forward and kan_forward_static.
 // keep_table: the caller may hand the workspace to kan_backward_saved, so the folded table must be in it.
+// need: bytes without which the call is refused; the matrix-core kernel runs where its table fits as well.
 static int forward_impl(const kan_layer_desc *desc, int64_t B, const float *x, const float *coef,
                         const float *w_s, const float *w_b, float *y, void *ws, size_t ws_bytes,
-                        void *stream, bool keep_table)
+                        void *stream, bool keep_table, size_t need)
 {
     int rc = check_desc(desc);
     if (rc != KAN_OK) return rc;
@@ -176,11 +184,16 @@ static int forward_impl(const kan_layer_desc *desc, int64_t B, const float *x, c
     if (!x || !coef || !w_s || !y) return KAN_ERR_INVALID_ARG;
     if (desc->base_act != KAN_BASE_NONE && !w_b) return KAN_ERR_INVALID_ARG;
     if (misaligned(x) || misaligned(coef) || misaligned(w_s) || misaligned(w_b) || misaligned(y)) return KAN_ERR_INVALID_ARG;
-    if (!ws || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < kan_workspace_bytes(desc, B, KAN_PASS_FORWARD))
-        return KAN_ERR_WORKSPACE;
+    if (!ws || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < need) return KAN_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     SplineGeom g = geom_of(desc);
     float *cf = (float *)ws;
+    const size_t split = matrix_bytes(desc);
+    if (split && ws_bytes >= folded_bytes(desc) + split && forward_matrix_plan(g, B))
+        return launch_forward_matrix(g, x, coef, w_s, g.base_act ? w_b : nullptr, cf, (char *)ws + folded_bytes(desc), y, B, st) ==
+                       hipSuccess
+                   ? KAN_OK
+                   : KAN_ERR_HIP;
     if (high_degree(desc))
         return highk_forward(highk_of(desc), x, coef, w_s, w_b, cf, y, B, keep_table, st) == hipSuccess ? KAN_OK : KAN_ERR_HIP;
     if (forward_direct_plan(g, B))
@@ -200,7 +213,7 @@ extern "C" int kan_forward(const kan_layer_desc *desc, int64_t B, const float *x
                            const float *w_s, const float *w_b, float *y, void *ws, size_t ws_bytes,
                            void *stream)
 {
-    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, ws_bytes, stream, true);
+    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, ws_bytes, stream, true, kan_workspace_bytes(desc, B, KAN_PASS_FORWARD));
 }
 
 // ---- forward pass for callers that cannot allocate -------------------------------------------
@@ -239,10 +252,10 @@ extern "C" int kan_forward_static(const kan_layer_desc *desc, int64_t B, const f
     if (rc != KAN_OK) return rc;
     if (B < 0) return KAN_ERR_INVALID_ARG;
     if (B == 0) return KAN_OK;
-    if (kan_workspace_bytes(desc, B, KAN_PASS_FORWARD) > (size_t)KAN_STATIC_SCRATCH_BYTES) return KAN_ERR_WORKSPACE;
+    if (folded_bytes(desc) > (size_t)KAN_STATIC_SCRATCH_BYTES) return KAN_ERR_WORKSPACE;
     void *ws = static_scratch();
     if (!ws) return KAN_ERR_HIP;
-    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, KAN_STATIC_SCRATCH_BYTES, stream, false);
+    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, KAN_STATIC_SCRATCH_BYTES, stream, false, folded_bytes(desc));
 }
 
 // Backward pass; `folded` (may be null) is the scale-folded table a forward pass left in its workspace.

@@ -1,0 +1,464 @@
+// Matrix-core forward kernel of the local B-spline layer for short tables (up to 31 rows).
+//
+// y = sum over (input, table row) of basis(x) * table is a dense product whose left operand holds at most kMaxK + 1 values per
+// input.  Sparse matrix instructions (two values of every four positions along the sum, v_smfmac_f32_32x32x32_bf16) skip half
+// of the zeros: table row r of an input goes to group r mod G, position r / G of the G groups of four (mx_groups), so that the
+// rows of a window fall into different groups; w_b, the last position of the last group, meets at most one row there.  Each group
+// then has one row in slot 0 (positions 0..2) or slot 1 (position 3), and every index pair is (position, 3).
+// The precision is that of fp32: every float is split into three bf16 parts (8 bits each, 24 in all), and the six products of
+// the parts that reach 2^-27 of the whole are summed in fp32; the parts have the exponent range of a float.  Values that do not
+// split (infinite, NaN, or so large that rounding up overflows) are found where they are split and the sums that
+// read them are done in plain fp32 at the end.
+//
+// Error against fp64 (2-norm): 512 -> 512, G = 20 4.9e-7 (the LDS-staged kernel 9.0e-7); 256 -> 256, G = 28 1.3e-7 (6.4e-7);
+// 75 -> 130, G = 12, k = 2 0.96e-7 (direct kernel 1.14e-7); 128 -> 128, G = 10 1.07e-7 (1.38e-7).
+//
+// What bounds it, 512 -> 512, G = 20, B = 16384, 583 us (the staged kernel, bound by its LDS reads: 900): the matrix instructions
+// alone take 360, evaluating the pairs 66 more, fetching the right operands from L2 63, reading the left ones from LDS 31;
+// 47 % of the matrix cores' clocks are used.
+#include "kan_device.hpp"
+#include "kan_launch.hpp"
+#include "kan_matrix.hpp"
+
+namespace KAN_NS {
+
+using ::kan::MatrixTable;
+using ::kan::kMxInputs;
+using ::kan::kMxTile;
+using ::kan::kMxSplits;
+
+namespace {
+
+typedef __bf16 Bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 Bf16 __attribute__((ext_vector_type(16)));
+typedef __bf16 Bf2 __attribute__((ext_vector_type(2)));
+typedef float F2 __attribute__((ext_vector_type(2)));
+typedef float F16 __attribute__((ext_vector_type(16)));
+typedef unsigned U4 __attribute__((ext_vector_type(4)));
+typedef unsigned U8 __attribute__((ext_vector_type(8)));
+
+constexpr float kMxLargest = 0x1p+120f;
+
+// two floats rounded to bf16, low and high half
+__device__ __forceinline__ unsigned bf16_pair(float a, float b)
+{
+    F2 v = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, Bf2));
+}
+
+// the three parts of two floats, each the pair's low and high half; the differences are exact
+__device__ __forceinline__ void split_pair(float a, float b, unsigned (&p)[kMxSplits])
+{
+#pragma unroll
+    for (int s = 0; s < kMxSplits; ++s) {
+        p[s] = bf16_pair(a, b);
+        a -= __builtin_bit_cast(float, p[s] << 16);
+        b -= __builtin_bit_cast(float, p[s] & 0xffff0000u);
+    }
+}
+
+}  // namespace
+
+// ---- the table: scale folded in, and split ----------------------------------------
+// One workgroup per (step of four inputs, tile of 32 outputs), lane l of wave t <-> lane l of instruction t: column l % 32 and four
+// of the instruction's eight groups, whose left operands are spread over both halves of the wave: with h = l / 32 groups
+// 2 h, 2 h + 1, 4 + 2 h, 5 + 2 h, four table rows each.  Writes cf as fold_scale_kernel does and the operands
+// of the forward kernel; rows past the table and columns past the layer are zero.
+template <int NG>
+__global__ __launch_bounds__(32 * NG) void matrix_table_kernel(const float *__restrict__ coef, const float *__restrict__ w_s,
+                                                               const float *__restrict__ w_b, float *__restrict__ cf,
+                                                               U4 *__restrict__ frag, int *__restrict__ odd, int n_in, int rows,
+                                                               int n_out)
+{
+    const int lane = threadIdx.x & 63, t = threadIdx.x >> 6, step = blockIdx.x, tile = blockIdx.y;
+    const int j = tile * kMxTile + (lane & 31), half = lane >> 5;
+    float v[16];
+    bool bad = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int grp = 8 * t + 4 * (e / 2) + 2 * half + e % 2, i = step * kMxInputs + grp / NG, g = grp % NG;
+        const bool ok = i < n_in && j < n_out;
+        const float s = ok ? w_s[(int64_t)i * n_out + j] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int row = g + NG * q;
+            const bool base = row == 4 * NG - 1;
+            float c = 0.0f;
+            if (ok && (base || row < rows)) {
+                if (!base) c = coef[((int64_t)i * rows + row) * n_out + j] * s;
+                else if (w_b) c = w_b[(int64_t)i * n_out + j];
+                cf[((int64_t)i * (rows + 1) + (base ? rows : row)) * n_out + j] = c;
+            }
+            const bool fits = fabsf(c) < kMxLargest;
+            bad |= !fits;
+            v[4 * e + q] = fits ? c : 0.0f;
+        }
+    }
+    unsigned p[8][kMxSplits];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) split_pair(v[2 * e], v[2 * e + 1], p[e]);
+    U4 *at = frag + ((((int64_t)tile * gridDim.x + step) * (NG / 2) + t) * kMxSplits) * 128 + lane;
+#pragma unroll
+    for (int s = 0; s < kMxSplits; ++s) {
+        at[s * 128] = U4{p[0][s], p[1][s], p[2][s], p[3][s]};
+        at[s * 128 + 64] = U4{p[4][s], p[5][s], p[6][s], p[7][s]};
+    }
+    const int any = __syncthreads_or(bad);
+    if (threadIdx.x == 0) odd[(int64_t)tile * gridDim.x + step] = any;
+}
+
+// ---- forward ----------------------------------------------------------------------
+// A workgroup of WM x WN waves owns 32 * MT * WM samples and 32 * WN outputs; a wave MT tiles of 32 samples and one tile of
+// outputs.  Per step of SI inputs all lanes evaluate the step's pairs and write the left operands (three parts, indices)
+// to LDS for the step after; the right operands come from L2 straight into the registers that the instructions read, an
+// instruction's worth ahead (prefetching them into L2 two steps ahead: 580 -> 653 us).  SI inputs a step: eight where a
+// workgroup owns 64 samples, so that every lane has a pair (four, half of them idle: 75 -> 130, B = 6001 43 -> 37 us); 128
+// samples have no room for eight in LDS.  FOLD > 0: the products of the leading parts are folded into a second sum every FOLD steps,
+// as exact as the two-level kernels that this one stands in for; the form with 128 samples, which has no registers for it, only
+// takes layers whose other kernel has one level.
+template <int NG, int SI>
+struct MxArea {                              // left operands of one step of SI inputs in LDS, per sample
+    // words of a sample's row of one part: 16-byte reads of eight samples fall into different banks
+    static constexpr int kRow = SI * NG % 16 == 0 ? SI * NG + 4 : SI * NG;
+    static constexpr int kIdx = SI * NG / 8;                                // words of a sample's indices
+    template <int S> static constexpr int words() { return S * (kMxSplits * kRow + kIdx); }
+};
+
+// A pair's left operands: out[part][group], and the indices of its groups, four bits each.
+template <int NG>
+__device__ __forceinline__ void pair_operands(int row0, const float (&w)[kMaxK], float base, unsigned (&out)[kMxSplits][NG],
+                                              unsigned &index)
+{
+    const int q0 = row0 / NG, c0 = row0 - q0 * NG;
+    unsigned part[(kMaxK + 1) / 2][kMxSplits], pb[kMxSplits];
+#pragma unroll
+    for (int s = 0; s < kMaxK; s += 2) split_pair(w[s], s + 1 < kMaxK ? w[s + 1] : 0.0f, part[s / 2]);
+    split_pair(0.0f, base, pb);
+    index = 0xCCCCCCCCu;
+#pragma unroll
+    for (int p = 0; p < kMxSplits; ++p)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) out[p][g] = 0u;
+#pragma unroll
+    for (int s = 0; s < kMaxK; ++s) {
+        const bool wrap = c0 + s >= NG;
+        const int q = q0 + (wrap ? 1 : 0), g = c0 + s - (wrap ? NG : 0);
+        const bool last = q == 3;
+        index |= (last ? 0u : (unsigned)q) << (4 * g);
+#pragma unroll
+        for (int p = 0; p < kMxSplits; ++p) {
+            const unsigned v = part[s / 2][p], low = s % 2 ? v >> 16 : v & 0xffffu, high = s % 2 ? v & 0xffff0000u : v << 16;
+            out[p][s] = last ? high : low;
+        }
+    }
+    // rows 0 .. of the window stand at groups 0 ..: turn them to group c0
+#pragma unroll
+    for (int bit = 1; bit < NG; bit *= 2) {
+        const bool on = (c0 & bit) != 0;
+#pragma unroll
+        for (int p = 0; p < kMxSplits; ++p) {
+            unsigned t[NG];
+#pragma unroll
+            for (int g = 0; g < NG; ++g) t[g] = out[p][(g + NG - bit % NG) % NG];
+#pragma unroll
+            for (int g = 0; g < NG; ++g) out[p][g] = on ? t[g] : out[p][g];
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < kMxSplits; ++p) out[p][NG - 1] |= pb[p] & 0xffff0000u;      // (the zero in the low half may carry a sign)      // (the zero in the low half may carry a sign)
+}
+
+template <int NG, int SI, int MT, int WM, int WN, int FOLD, bool AHEAD>
+__global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_matrix_kernel(SplineGeom g, const float *__restrict__ x,
+                                                                      const float *__restrict__ cf, const U4 *__restrict__ frag,
+                                                                      const int *__restrict__ odd, float *__restrict__ y,
+                                                                      int64_t B, int n_tiles)
+{
+    constexpr int NT = 64 * WM * WN, S = 32 * MT * WM, EP = S * SI / NT, KS = SI * NG / 8;
+    static_assert(S * SI % NT == 0 && SI % kMxInputs == 0, "");
+    typedef MxArea<NG, SI> A;
+    constexpr int kArea = A::template words<S>();
+    extern __shared__ unsigned lds[];
+    int *special = reinterpret_cast<int *>(lds + 2 * kArea);           // per sample: a value that does not split
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave / WN;
+    const int tile = blockIdx.y * WN + wave % WN, tc = tile < n_tiles ? tile : n_tiles - 1;
+    const int64_t b0 = (int64_t)blockIdx.x * S;
+    const int n_steps = (g.n_in + SI - 1) / SI, n_parts = (g.n_in + kMxInputs - 1) / kMxInputs;      // of the table
+
+    for (int s = tid; s < S; s += NT) special[s] = 0;
+
+    // two sums: the products of the leading parts, and the others, whose roundings are 2^-8 of the former's
+    F16 acc[MT], low[MT], tot[FOLD > 0 ? MT : 1];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { acc[m][r] = low[m][r] = 0.0f; if (FOLD > 0) tot[m][r] = 0.0f; }
+
+    // this lane's pairs of a step: sample e / SI, input e % SI of e = tid + c * NT
+    auto load_x = [&](int step, float (&v)[EP]) {
+#pragma unroll
+        for (int c = 0; c < EP; ++c) {
+            const int e = tid + c * NT;
+            int64_t b = b0 + e / SI;
+            b = b < B ? b : B - 1;
+            int i = step * SI + e % SI;
+            i = i < g.n_in ? i : g.n_in - 1;
+            v[c] = x[b * g.n_in + i];
+        }
+    };
+    auto evaluate = [&](int step, const float (&v)[EP], unsigned *area) {
+#pragma unroll
+        for (int c = 0; c < EP; ++c) {
+            const int e = tid + c * NT, s = e / SI, ii = e % SI, i = step * SI + ii;
+            float w[kMaxK], dw[kMaxK], base, dbase;
+            int row0;
+            wave_windows<false>(v[c], g, i < g.n_in ? i : g.n_in - 1, row0, w, base, dw, dbase);
+            const bool fits = fabsf(base) < kMxLargest;
+            if (!fits) special[s] = 1;
+            if (!fits || i >= g.n_in) base = 0.0f;
+#pragma unroll
+            for (int k = 0; k < kMaxK; ++k) w[k] = i < g.n_in ? w[k] : 0.0f;
+            unsigned out[kMxSplits][NG], index;
+            pair_operands<NG>(row0, w, base, out, index);
+#pragma unroll
+            for (int p = 0; p < kMxSplits; ++p) {
+                if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+                unsigned *at = area + (p * S + s) * A::kRow + ii * NG;
+                if constexpr (NG % 4 == 0) {
+#pragma unroll
+                    for (int q = 0; q < NG; q += 4)
+                        *reinterpret_cast<U4 *>(at + q) = U4{out[p][q], out[p][q + 1], out[p][q + 2], out[p][q + 3]};
+                } else {
+#pragma unroll
+                    for (int q = 0; q < NG; q += 2) *reinterpret_cast<uint2 *>(at + q) = make_uint2(out[p][q], out[p][q + 1]);
+                }
+            }
+            unsigned char *ix = reinterpret_cast<unsigned char *>(area + kMxSplits * S * A::kRow + s * A::kIdx) + ii * (NG / 2);
+            if constexpr (NG == 8) *reinterpret_cast<unsigned *>(ix) = index;
+            else if constexpr (NG == 4) *reinterpret_cast<unsigned short *>(ix) = (unsigned short)index;
+            else { ix[0] = (unsigned char)index; ix[1] = (unsigned char)(index >> 8); ix[2] = (unsigned char)(index >> 16); }
+        }
+    };
+
+    const U4 *bp = frag + (int64_t)tc * n_parts * (NG / 2) * kMxSplits * 128 + lane;
+    const int64_t last = (int64_t)n_parts * (NG / 2) - 1;
+    auto load_b = [&](int64_t k, U4 (&b)[kMxSplits][2]) {
+        const U4 *at = bp + (k < last ? k : last) * (kMxSplits * 128);
+#pragma unroll
+        for (int p = 0; p < kMxSplits; ++p) { b[p][0] = at[p * 128]; b[p][1] = at[p * 128 + 64]; }
+    };
+
+    float xv[EP];
+    U4 bn[2][kMxSplits][2];
+    load_x(0, xv);
+    load_b(0, bn[0]);
+    __syncthreads();                                   // special[] is cleared
+    evaluate(0, xv, lds);
+    load_x(n_steps > 1 ? 1 : 0, xv);
+    __syncthreads();
+
+    // An instruction's right operands are asked for one instruction step ahead and, with AHEAD, the left ones a tile ahead in a
+    // pinned order (left to itself the compiler moves the loads down to their uses); four tiles leave no registers for that.
+    auto multiply = [&](int step) {
+        constexpr int MG = AHEAD ? 1 : 2, GPT = MT / MG, NGRP = KS * GPT;          // MG tiles' chains take turns
+        const unsigned *area = lds + (step & 1) * kArea;
+        const unsigned short *idx = reinterpret_cast<const unsigned short *>(area + kMxSplits * S * A::kRow);
+        Bf8 a[2][MG][kMxSplits];
+        int ix[2][MG];
+        auto read_a = [&](int t, int m0, int to) {
+#pragma unroll
+            for (int m = 0; m < MG; ++m) {
+                const int s = (wm * MT + m0 + m) * 32 + (lane & 31), h = 2 * t + (lane >> 5);
+                ix[to][m] = idx[s * (2 * A::kIdx) + h];
+#pragma unroll
+                for (int p = 0; p < kMxSplits; ++p)
+                    a[to][m][p] = __builtin_bit_cast(Bf8, *reinterpret_cast<const U4 *>(area + (p * S + s) * A::kRow + 4 * h));
+            }
+        };
+        if (AHEAD) read_a(0, 0, 0);
+#pragma unroll
+        for (int gi = 0; gi < NGRP; ++gi) {
+            const int t = gi / GPT, m0 = gi % GPT * MG, at = AHEAD ? gi & 1 : 0;
+            if (gi % GPT == 0) load_b((int64_t)step * KS + t + 1, bn[(t + 1) & 1]);
+            if (!AHEAD) read_a(t, m0, 0);
+            else if (gi + 1 < NGRP) read_a((gi + 1) / GPT, (gi + 1) % GPT * MG, (gi + 1) & 1);
+            if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+            Bf16 b[kMxSplits];
+#pragma unroll
+            for (int p = 0; p < kMxSplits; ++p)
+                b[p] = __builtin_bit_cast(Bf16, __builtin_shufflevector(bn[t & 1][p][0], bn[t & 1][p][1], 0, 1, 2, 3, 4, 5, 6, 7));
+            auto product = [&](F16 (&sum)[MT], int pa, int pb) {
+#pragma unroll
+                for (int m = 0; m < MG; ++m)
+                    sum[m0 + m] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a[at][m][pa], b[pb], sum[m0 + m], ix[at][m], 0, 0);
+            };
+            product(low, 2, 0);
+            product(low, 0, 2);
+            product(acc, 0, 0);
+            product(low, 1, 1);
+            product(low, 1, 0);
+            product(low, 0, 1);
+            if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (KS % 2 != 0) {
+#pragma unroll
+            for (int p = 0; p < kMxSplits; ++p) { bn[0][p][0] = bn[1][p][0]; bn[0][p][1] = bn[1][p][1]; }
+        }
+        if constexpr (FOLD > 0) {
+            if ((step + 1) % FOLD == 0) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) { tot[m][r] += acc[m][r]; acc[m][r] = 0.0f; }
+            }
+        }
+    };
+    // half of the waves take the parts of a step in the opposite order, so that the evaluation of one wave runs beside the matrix
+    // instructions of the other on its SIMD
+    const int late = WM * WN >= 8 ? wave >= WM * WN / 2 : 0;
+    for (int step = 0; step < n_steps; ++step) {
+#pragma unroll 1
+        for (int part = 0; part < 2; ++part) {
+            if (part == late) {
+                if (step + 1 < n_steps) {
+                    evaluate(step + 1, xv, lds + ((step + 1) & 1) * kArea);
+                    load_x(step + 2 < n_steps ? step + 2 : n_steps - 1, xv);
+                }
+            } else {
+                multiply(step);
+            }
+        }
+        __syncthreads();
+    }
+
+    if (tile >= n_tiles) return;
+    const int j = tile * kMxTile + (lane & 31);
+    int flag = 0;
+    for (int s = lane; s < n_parts; s += 64) flag |= odd[(int64_t)tile * n_parts + s];
+    const bool all_odd = __any(flag != 0);
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int s = (wm * MT + m) * 32 + 8 * (r / 4) + 4 * (lane >> 5) + r % 4;
+            const int64_t b = b0 + s;
+            if (b < B && j < g.n_out && !all_odd && !special[s]) y[b * g.n_out + j] = (FOLD > 0 ? tot[m][r] + acc[m][r] : acc[m][r]) + low[m][r];
+        }
+    // the sums that read a value which does not split: half a wave takes every other input
+    const int jc = j < g.n_out ? j : g.n_out - 1;
+    for (int s = wm * MT * 32; s < (wm + 1) * MT * 32; ++s) {
+        const int64_t b = b0 + s;
+        if (b >= B || !(all_odd || special[s])) continue;
+        float sum = 0.0f;
+        for (int i = lane >> 5; i < g.n_in; i += 2) {
+            const Pair p = pair_eval<false>(x[b * g.n_in + i], g, i);
+            float w[kMaxK], base;
+            int row0;
+            window_of<false>(p, g.rows, row0, w, base);
+            const float *row = cf + ((int64_t)i * g.slab_rows + row0) * g.n_out + jc;
+#pragma unroll
+            for (int k = 0; k < kMaxK; ++k) sum = fmaf(w[k], row[(int64_t)k * g.n_out], sum);
+            sum = fmaf(base, cf[((int64_t)i * g.slab_rows + g.rows) * g.n_out + jc], sum);
+        }
+        sum += __shfl_xor(sum, 32);
+        if (lane < 32 && j < g.n_out) y[b * g.n_out + j] = sum;
+    }
+}
+
+// ---- host -------------------------------------------------------------------------
+template <int NG, int SI, int MT, int WM, int WN, int FOLD, bool AHEAD>
+static hipError_t matrix_launch(const SplineGeom &g, const MatrixTable &t, const float *x, const float *cf, const void *table,
+                                float *y, int64_t B, hipStream_t st)
+{
+    constexpr int S = 32 * MT * WM, bytes = (2 * MxArea<NG, SI>::template words<S>() + S) * 4;
+    struct Tag {};
+    auto kern = forward_matrix_kernel<NG, SI, MT, WM, WN, FOLD, AHEAD>;
+    if (hipError_t e = ensure_dynamic_lds<Tag>((const void *)kern, bytes); e != hipSuccess) return e;
+    const U4 *frag = (const U4 *)table;
+    const int *odd = (const int *)((const char *)table + t.frag_bytes);
+    const int64_t part = (int64_t)S << 20;                        // samples of one launch: fewer than 2^32 threads
+    for (int64_t b0 = 0; b0 < B; b0 += part) {
+        const int64_t n = B - b0 < part ? B - b0 : part;
+        const dim3 grid((unsigned)((n + S - 1) / S), (unsigned)((t.n_tiles + WN - 1) / WN));
+        prof::Timed tm("forward_matrix", st);
+        kern<<<grid, 64 * WM * WN, bytes, st>>>(g, x + b0 * g.n_in, cf, frag, odd, y + b0 * g.n_out, n, t.n_tiles);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+template <int NG>
+static hipError_t matrix_forward(const SplineGeom &g, const MatrixTable &t, int form, const float *x, const float *coef,
+                                 const float *w_s, const float *w_b, float *cf, void *table, float *y, int64_t B, hipStream_t st)
+{
+    {
+        prof::Timed tm("matrix_table", st);
+        matrix_table_kernel<NG><<<dim3((unsigned)t.n_steps, (unsigned)t.n_tiles), 32 * NG, 0, st>>>(
+            coef, w_s, w_b, cf, (U4 *)table, (int *)((char *)table + t.frag_bytes), g.n_in, g.rows, g.n_out);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    switch (form) {
+    case 1:
+        if constexpr (NG < 8) return matrix_launch<NG, 4, 4, 1, 8, 0, false>(g, t, x, cf, table, y, B, st);
+        return hipErrorInvalidValue;
+    case 2: return matrix_launch<NG, 8, 2, 1, 8, 2, true>(g, t, x, cf, table, y, B, st);
+    case 3: return matrix_launch<NG, 8, 1, 2, 4, 2, true>(g, t, x, cf, table, y, B, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+// The form with the shortest estimated time, if that is shorter than the other kernels' by a tenth; 0 otherwise.  Each form
+// costs a fixed time, and per round of 256 workgroups a fixed time and so much a step (us; least squares over 779 layers of
+// 65..512 outputs, 4..512 inputs, G = 5..28, B = 1024..65536: every one within 0.79..1.13 of its time).  The others: the direct
+// kernel by its edges (its table in L2 or past it), the LDS-staged ones by the rounds of their workgroups.  Of the layers with
+// eight inputs and more the line picks 297, at 0.55 of the time in the mean (0.24 at the least, 0.99 at most); 56 that it leaves
+// would gain a tenth or more.  Other kernel / this one, us: 512 -> 512, G = 20, B = 16384 914 / 603; 256 -> 256, G = 28, B = 16384
+// 684 / 235; 128 -> 128, G = 10, B = 16384 170 / 54; 75 -> 130, G = 12, B = 6001 58 / 37; not taken: 64 -> 130, G = 28, B = 1024 12 / 48,
+// 32 -> 96, G = 12, B = 32768 39 / 40.  Up to 64 outputs the evaluation of the pairs is not shared by enough of them (64 -> 64,
+// G = 10, B = 65536: 75 / 78 in the best of the forms tried).
+int forward_matrix_plan(const SplineGeom &g, int64_t B)
+{
+    const MatrixTable t = ::kan::matrix_table(g.n_in, g.n_out, g.rows, kMaxK);
+    if (t.groups == 0) return 0;
+    struct Form { int samples, tiles, inputs; float fixed, round, step[3]; };
+    static const Form forms[] = {{128, 8, 4, 4.0f, 25.0f, {2.96f, 4.12f, 5.67f}},
+                                 {64, 8, 8, 5.0f, 13.0f, {2.74f, 4.01f, 5.64f}},
+                                 {64, 4, 8, 6.3f, 7.5f, {2.32f, 3.19f, 4.48f}}};
+    int best = 0;
+    float least = 0.0f;
+    for (int f = t.groups == 8 ? 1 : 0; f < 3; ++f) {            // (eight groups: the first is never the shortest)
+        const Form &o = forms[f];
+        const int64_t groups = ((B + o.samples - 1) / o.samples) * ((t.n_tiles + o.tiles - 1) / o.tiles);
+        const float steps = (float)((g.n_in + o.inputs - 1) / o.inputs);
+        const float us = o.fixed + (float)((groups + 255) / 256) * (o.round + steps * o.step[t.groups / 2 - 2]);
+        if (best == 0 || us < least) { best = f + 1; least = us; }
+    }
+    const int64_t padded = (int64_t)g.n_in * ((g.n_out + 63) / 64 * 64);
+    const bool in_l2 = (int64_t)g.n_in * g.slab_rows * g.n_out * 4 < 6ll << 20;
+    const float direct = 5.0f + (float)B * (float)padded / (in_l2 ? 1.75e6f : 1.2e6f);
+    float other = direct;
+    if (g.n_out >= 128) {
+        const bool wide = g.n_out > 256;
+        const float staged = 8.0f + (float)((g.n_out + 511) / 512 * ((B + (wide ? 16383 : 32767)) / (wide ? 16384 : 32768))) *
+                                        (wide ? 1.78f : 2.62f) * (float)g.n_in;
+        other = staged < direct ? staged : direct;
+    } else if (B >= 28000) {
+        other = 10.0f + (float)B * (float)padded / 4.1e6f;
+    }
+    return least < 0.9f * other ? best : 0;
+}
+
+hipError_t launch_forward_matrix(const SplineGeom &g, const float *x, const float *coef, const float *w_s, const float *w_b,
+                                 float *cf, void *table, float *y, int64_t B, hipStream_t st)
+{
+    const MatrixTable t = ::kan::matrix_table(g.n_in, g.n_out, g.rows, kMaxK);
+    const int form = forward_matrix_plan(g, B);
+    switch (t.groups) {
+    case 4: return matrix_forward<4>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
+    case 6: return matrix_forward<6>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
+    case 8: return matrix_forward<8>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace KAN_NS

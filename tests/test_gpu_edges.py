@@ -447,3 +447,75 @@ def test_quads_on_shared_partial_tables(B, n_in, n_out, G, k):
 def test_walk_over_padded_cells_of_a_grid_without_zero(B, n_in, n_out, G, k, lo, hi):
     """The pads between the cells are stored as x = 0, which lies outside these grids."""
     assert "walk_cells" in run_with_families(workloads.random_kan_layer(B + n_out, B, n_in, n_out, G, k, lo, hi, outside_frac=0.1))
+
+
+MATRIX_SHAPES = [
+    # sixteen positions an input, rows up to the last one; odd numbers of inputs, of outputs and of samples
+    (12001, 37, 97, 10, 3), (12033, 64, 65, 13, 2), (12001, 40, 128, 14, 1),
+    (12001, 33, 100, 15, 1), (12002, 39, 97, 20, 3),           # twenty-four: the first and the last row count
+    (12001, 73, 127, 21, 3), (12031, 66, 130, 28, 3),          # thirty-two: the same
+    (16001, 65, 256, 20, 3), (16001, 66, 255, 10, 3), (16001, 63, 193, 28, 2),      # sixty-four samples a workgroup
+    (32700, 67, 300, 20, 3), (32641, 42, 512, 10, 3),          # a hundred and twenty-eight
+]
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", MATRIX_SHAPES)
+def test_matrix_forward(B, n_in, n_out, G, k):
+    w = workloads.random_kan_layer(B + n_in, B, n_in, n_out, G, k, outside_frac=0.05)
+    s, p = w.layers[0], w.params[0]
+    x, coef, w_s, w_b = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"]))
+    y = []
+    assert "forward_matrix" in families_of(lambda: y.append(binding.kan_forward(s, x, coef, w_s, w_b)))
+    rows = np.r_[0:70, B // 2:B // 2 + 70, B - 200:B]
+    ref = oracle.kan_forward(w.x[rows], p["coef"], p["w_s"], p["w_b"], G, k, s.grid_lo, oracle.inv_h_of(s.grid_lo, s.grid_hi, G))
+    got = y[0].cpu().numpy()
+    assert_close(y[0][torch.from_numpy(rows).cuda()], ref, 1e-5, "y")
+    # in the 2-norm: up to 33 additions of partial sums and 3 products of leading parts an addition, each rounded to about half a
+    # unit of 2^-24 of a sum that grows to the result: sqrt(4 * 33) / 2 * 0.6 units.  (One part of one factor lost: 4e-7 and more.)
+    err = np.linalg.norm(got[rows] - ref) / np.linalg.norm(ref)
+    assert err < 3.5 * 2.0 ** -24, err
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G", [(12001, 37, 97, 12), (16001, 65, 256, 20), (32700, 67, 300, 20)])
+def test_matrix_forward_keeps_infinities_apart(B, n_in, n_out, G):
+    """Inputs and parameters that do not split into parts reach their own samples and outputs only."""
+    w = workloads.random_kan_layer(B, B, n_in, n_out, G, 3)
+    s, p = w.layers[0], w.params[0]
+    odd = [3, 64, 4100, B - 1]
+    w.x[3, 2], w.x[64, 0], w.x[4100, n_in - 1], w.x[B - 1, 5] = np.inf, -np.inf, np.nan, 3e38
+    p["coef"][7, G // 2, 5] = np.inf
+    p["w_b"][9, n_out - 1] = np.nan
+    p["coef"][n_in - 1, 3, 40] = 3e38
+    x, coef, w_s, w_b = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"]))
+    y = []
+    assert "forward_matrix" in families_of(lambda: y.append(binding.kan_forward(s, x, coef, w_s, w_b)))
+    rows = np.r_[0:200, 4090:4110, B - 130:B]
+    with np.errstate(all="ignore"):
+        ref = oracle.kan_forward(w.x[rows], p["coef"], p["w_s"], p["w_b"], G, 3, s.grid_lo, oracle.inv_h_of(s.grid_lo, s.grid_hi, G))
+        got = y[0].cpu().numpy()[rows].astype(np.float64)
+        ref = ref.astype(np.float32).astype(np.float64)         # past the range of a float: infinite
+    assert np.isin(odd, rows).all() and not np.isfinite(ref[np.isin(rows, odd)]).all()
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    big = ~np.isnan(ref) & ((np.abs(ref) > 1e30) | (np.abs(got) > 1e30))
+    np.testing.assert_allclose(got[big], ref[big], rtol=1e-5)
+    ok = ~np.isnan(ref) & ~big
+    assert (np.abs(got[ok] - ref[ok]) <= 1e-5 * (1.0 + np.abs(ref[ok]))).all()
+    assert ok.sum() > 0.8 * ok.size
+
+
+def test_matrix_forward_workspace():
+    """A workspace without room for the split table is refused, as before; the built-in scratch array takes the other kernel."""
+    s = workloads.KanLayerSpec(560, 512, 20, 3, -1.0, 1.0)            # 27 MB folded, 69 with the split table
+    B = 4096
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.rand((B, s.n_in), generator=g, device="cuda") * 2 - 1
+    coef, w_s, w_b = (torch.randn(d, generator=g, device="cuda") * 0.04 for d in ((s.n_in, s.M, s.n_out), (s.n_in, s.n_out), (s.n_in, s.n_out)))
+    n = binding.kan_workspace_bytes(s, B, binding.PASS_FORWARD)
+    with pytest.raises(binding.KanError):
+        binding.kan_forward(s, x, coef, w_s, w_b, ws=torch.empty(n - 256, dtype=torch.uint8, device="cuda"))
+    y = []
+    assert "forward_matrix" in families_of(lambda: y.append(binding.kan_forward(s, x, coef, w_s, w_b)))
+    z = torch.empty_like(y[0])
+    assert n > binding.kan_static_scratch_bytes()
+    assert "forward_matrix" not in families_of(lambda: binding.kan_forward_static(s, x, coef, w_s, w_b, z))
+    assert ((z - y[0]).norm() / y[0].norm()).item() < 3e-6
