@@ -301,6 +301,22 @@ constexpr bool variant_built(int lps, int slots, int nw, int nq, bool base)
 }
 int workgroups_a_cu(int nw, int nq) { return nw == 16 || 2 * lds_bytes(nw, nq) > kLdsBudget ? 1 : 2; }
 
+// Eight waves on several tiles against the kernels that gather (generic and direct), in clocks an input: a step takes 390 a
+// window row beside the copies at 64 bytes a clock, for each round of workgroups, and 1.4 times that where a CU works on two; the
+// others take an edge of the padded width in 1.5e-6 us (windows of six: 2.2e-6), more on ragged rows and past L2.  Over 326
+// layers of 65..512 outputs, 8..400 inputs, 31..251 rows and B = 2048..20000 the line takes 198 to 0.79 of their time in the mean
+// (1.04 at most, where runs of one side differ by as much); of the other 128 those that it would slow reach 1.5 times.
+// Other kernel / this one, us: 256 -> 256, G = 200, B = 8192 346 / 279; 400 -> 100, G = 60, B = 20000 1517 / 438; 256 -> 200, G = 80,
+// B = 8192 522 / 212; left: 50 -> 256, G = 230, k = 1, B = 10000 (316 workgroups, one a CU: two rounds) 85 / 129; 32 -> 96, G = 230,
+// B = 20000 62 / 87.  Not below a workgroup a CU: 512 -> 512, B = 2048, G = 200 597 / 617 (on sixteen waves), G = 400 755 / 1004.
+bool eight_waves_pay(int64_t wgs, int a_cu, int64_t quads, int64_t padded_edges)
+{
+    const int64_t at_once = 256 * a_cu, full = (wgs - 1) / at_once;
+    const float step = (float)(390 * kMaxK) + (float)quads / 4;
+    const float clocks = ((float)full * (a_cu == 2 ? 1.4f : 1.0f) + (wgs - full * at_once > 256 ? 1.4f : 1.0f)) * step;
+    return clocks < 0.92f * 2200.0f * (kMaxK == 4 ? 1.0f : 1.5f) * (float)padded_edges / 1.5e6f;
+}
+
 // tile width, samples a group, workgroup size, copy depth and inputs a step for a layer (lps == 0: not applicable)
 RowsPlan plan_of(const SplineGeom &g, int64_t B)
 {
@@ -324,17 +340,17 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             const int64_t per_wg = (int64_t)nw * spw * 4;
             const int64_t wgs = (B + per_wg - 1) / per_wg * tiles;
             if (nw == 16 && wgs < 256) continue;
-            // eight waves (two per SIMD) only when one tile covers the layer: with several every tile evaluates the pairs again, and
-            // an earlier form of this kernel did not beat the generic one.  This form does where a CU gets a workgroup (generic /
-            // eight waves, B = 8192: 256 -> 256, G = 120 334 / 239 us, G = 200 357 / 279; 128 -> 128, G = 200 148 / 118), and sixteen
-            // waves on a part of the chip do not (512 -> 512, B = 2048, G = 200 597 / 617, G = 400 755 / 1004); the line stands as it was.
-            if (nw == 8 && tiles > 1) continue;
+            // eight waves (two per SIMD) on several tiles, of which each evaluates the pairs again: eight_waves_pay
+            const bool eight_tiled = nw == 8 && tiles > 1;
+            if (eight_tiled && wgs < 256) continue;
             const int64_t quads = (int64_t)g.slab_rows * lps;
             const int nq = copies_of(nw, quads);
             if (!nq || !variant_built(lps, 4, nw, nq, g.base_act != 0)) continue;
             // worth it only when a staged row serves many samples (the copy into LDS costs as much LDS
             // time per row as several reads of it): samples * K >= 4 * slab rows
-            if (per_wg * kMaxK < 4 * (int64_t)g.slab_rows) continue;
+            if (eight_tiled ? !eight_waves_pay(wgs, workgroups_a_cu(nw, nq), quads, B * ((g.n_out + 63) / 64 * 64))
+                            : per_wg * kMaxK < 4 * (int64_t)g.slab_rows)
+                continue;
             RowsPlan p = {lps, 4, nw, nq, 1};
             // Eight samples a group halve the copies a sample (256 -> 256, 180 rows, B = 32768: 608 us, with four 756).  A CU
             // works through its workgroups in rounds of 256; a step of four samples a group takes about 2200 clocks beside

@@ -117,6 +117,7 @@ def test_forward_lines_of_six_rows(B, n_in, n_out, G, k, family):
     (66000, 35, 33, 40, 2), (70001, 5, 64, 150, 3), (70000, 66, 47, 240, 3),    # eight samples a group: one to four copies a thread
     (131100, 4, 32, 60, 3), (131072 + 512, 7, 32, 100, 3), (131073, 34, 32, 300, 3),       # the same on tiles of 32, x by fours
     (45000, 9, 70, 300, 3),                                     # three tiles, the last of six outputs
+    (8190, 21, 255, 200, 3), (16300, 17, 67, 50, 2), (8192, 19, 256, 245, 5),       # eight waves on several tiles
     (16400, 33, 64, 40, 5), (20000, 37, 35, 17, 4), (40000, 9, 32, 240, 5),     # windows of six rows: eight waves,
     (65500, 18, 64, 10, 5), (45000, 9, 70, 300, 4),             # sixteen,
     (66000, 35, 50, 40, 4), (131100, 9, 32, 60, 5),             # eight samples a group
