@@ -129,6 +129,7 @@ struct WalkPlan {
                          // and dL/dx is the sum of two partial results per output tile
     int L;               // entries of one sorted list: S, 2 S when hk, or what padded cells may take (quads)
     int quads;           // 1: lists of padded cells and the quad walk (kan_quads.hpp), one entry a pair for every degree
+    int one;             // 1: one output, lists of one segment (kan_walk_one.hip)
     int window;          // table rows of a window, and carry rows of a segment: 4, or 6 (quads of degrees 4 and 5)
 };
 // allow_shared: tables whose per-chunk partial slabs would not fit the budget are still planned, with the

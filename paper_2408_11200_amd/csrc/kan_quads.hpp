@@ -44,6 +44,9 @@ inline int quad_list_entries(int S, int rows, int window)
 hipError_t launch_cell_lists(const QuadWalkArgs &a, const float *xT, int row_bits, hipStream_t st);
 hipError_t launch_cell_lists6(const QuadWalkArgs &a, const float *xT, int row_bits, hipStream_t st);
 
+// layers of one output: one launch over all chunks, lists of one segment
+hipError_t walk_one(const QuadWalkArgs &a, hipStream_t st);
+
 // name: streams a wave, outputs a lane; 6: window of six rows (degrees 4 and 5)
 void quad_walk_s1t8(const QuadWalkArgs &a, unsigned blocks, hipStream_t st);
 void quad_walk_s1t4(const QuadWalkArgs &a, unsigned blocks, hipStream_t st);

@@ -295,6 +295,10 @@ WalkPlan plan_lists(const SplineGeom &g, int64_t B, bool allow_shared, bool high
         p.quads = p.row_bits <= 10 && S >= per_cell * (g.rows - p.window + 1) && (int64_t)S * g.n_out <= most &&
                   (p.streams == 1 ? 1 : g.n_in) * slab_floats <= most && (int64_t)g.n_in * g.n_out <= most ? 1 : 0;
         p.L = quad_list_entries(S, g.rows, p.window);
+        // one output: a workgroup a list (kan_walk_one.hip), where there is one a CU (256 -> 1, B = 32768: 204 us / 74); fewer leave
+        // CUs idle that segments of a list would fill
+        p.one = p.quads && g.n_out == 1 && !high_degree && !p.shared && (int64_t)p.n_chunks * g.n_in >= 256 ? 1 : 0;
+        if (p.one) p.n_seg = 1;
     }
     return p;
 }
@@ -460,6 +464,10 @@ hipError_t launch_backward_walk(const SplineGeom &g, const WalkPlan &p, const fl
                 qa.gx = gx_out; qa.chunk0 = chunk0; qa.n_chunks = here; qa.blocks_per_chunk = bpc; qa.xcd_groups = m;
                 qa.prezeroed = prezeroed;
                 qa.shared = p.shared && chunk0 > 0 ? 1 : 0;       // the first round finds its slabs zero and stores
+                if (p.one) {
+                    if (hipError_t e = walk_one(qa, st); e != hipSuccess) return e;
+                    continue;
+                }
                 auto walk = p.window == 6 ? (p.T == 2 ? quad_walk6_s4t2
                                              : p.T == 1 ? quad_walk6_s4t1
                                              : p.streams == 1 ? quad_walk6_s1t4

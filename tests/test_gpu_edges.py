@@ -520,3 +520,35 @@ def test_matrix_forward_workspace():
     assert n > binding.kan_static_scratch_bytes()
     assert "forward_matrix" not in families_of(lambda: binding.kan_forward_static(s, x, coef, w_s, w_b, z))
     assert ((z - y[0]).norm() / y[0].norm()).item() < 3e-6
+
+
+@pytest.mark.parametrize("B,n_in,G,k,base", [
+    (5001, 257, 30, 3, 1), (4099, 130, 12, 1, 1),              # a chunk's last list is short; a group of one and of two inputs
+    (33000, 40, 60, 3, 0), (70000, 33, 900, 2, 1),             # no base term; more cells than a wave has quads at a time
+    (2048, 300, 1, 3, 1), (70000, 300, 5, 3, 1),               # one cell in the grid; cells that go on from wave to wave
+])
+def test_walk_of_one_output(B, n_in, G, k, base):
+    w = workloads.random_kan_layer(B, B, n_in, 1, G, k, base_act=base, outside_frac=0.1)
+    s, p = w.layers[0], w.params[0]
+    _, g = run_layer_parity(w, gx_in_grid_units=G > 500)
+    x, coef, w_s, w_b, gy = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"], w.gy))
+    again = binding.kan_backward(s, x, coef, w_s, w_b, gy)
+    only = binding.kan_backward(s, x, coef, w_s, w_b, gy, want=("gcoef", "gw_s", "gw_b"))
+    for n in ("gx", "gcoef", "gw_s", "gw_b"):
+        assert torch.equal(g[n], again[n]), n
+        assert n == "gx" or torch.equal(g[n], only[n]), n
+
+
+def test_walk_of_one_output_keeps_infinities_apart():
+    w = workloads.random_kan_layer(3, 9000, 64, 1, 40, 3)
+    s, p = w.layers[0], w.params[0]
+    w.gy[5, 0], w.gy[4000, 0] = np.inf, np.nan
+    x, coef, w_s, w_b, gy = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"], w.gy))
+    g = binding.kan_backward(s, x, coef, w_s, w_b, gy)
+    ref = oracle.kan_backward(w.x, p["coef"], p["w_s"], p["w_b"], w.gy, s.G, s.k, s.grid_lo, oracle.inv_h_of(s.grid_lo, s.grid_hi, s.G))
+    for n in ("gx", "gcoef"):
+        got, want = g[n].cpu().numpy(), ref[n]
+        assert np.array_equal(np.isfinite(got), np.isfinite(want)), n
+        ok = np.isfinite(want)
+        assert ok.any() and not ok.all()
+        assert (np.abs(got[ok] - want[ok]) <= GRAD_TOL * (1.0 + np.abs(want[ok]))).all(), n
