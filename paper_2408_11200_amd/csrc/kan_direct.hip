@@ -214,8 +214,11 @@ static hipError_t direct_latency(const SplineGeom &g, const float *x, const floa
 //                     past it: 256 -> 32, G = 1000: 32768 507 / 475, 65536 679 / 943
 //   generic           past L2: 256 -> 130, G = 300: B = 2048 244 / 215, 4096 307 / 444; in it: 8 -> 128, G = 100: 8192 14 / 15,
 //                     16384 23 / 27; 128 -> 37, G = 200: 32768 406 / 167
-//   narrow            64 -> 1, G = 20: B = 2048 19 / 12, 4096 19 / 22, 8192 19 / 41; 32 -> 1: 2048 13 / 11, 4096 11 / 19; 32 -> 4, G = 20: 16384 20 / 15, 65536 31 / 46;
-//                     32 -> 16, G = 1000: 65536 478 / 49
+//   narrow            one output on sixteen lanes: 64 -> 1, G = 20: B = 1024 8.9 / 7.3, 1500 9.1 / 9.6, 4096 9.2 / 21; G = 240: 512 9.0 / 8.7,
+//                     1024 9.1 / 10.9; 256 -> 1: 1500 15.5 / 15.7, 4096 16 / 37; 500 -> 1: 1500 27 / 23, 2048 27 / 33
+//                     32 -> 4, G = 20: 16384 20 / 15, 65536 31 / 46; 64 -> 4: 65536 56 / 50, 262144 199 / 207, G = 400 591 / 208; 256 -> 4:
+//                     65536 214 / 175; 32 -> 5: G = 20 65536 35 / 45, G = 400 51 / 46; 64 -> 5: 262144 235 / 207; 16 -> 8: G = 20
+//                     65536 36 / 42; 32 -> 8: 262144 312 / 185; 8 -> 16: 65536 48 / 42; 64 -> 16: 262144 1411 / 212; 32 -> 16, G = 1000: 65536 478 / 49
 //   degrees 4 and 5   64 -> 4, G = 10000: B = 65536 481 / 96 (generic); 64 -> 300, G = 20: 4096 283 / 109 (512-wide tiles);
 //                     64 -> 64, G = 300: 32768 140 / 131, 65536 252 / 277 (row stream)
 //   degrees 4 and 5, staged slabs (a round of workgroups costs an input the same whether the chip is full or not, and a copied row
@@ -244,12 +247,16 @@ int forward_direct_plan(const SplineGeom &g, int64_t B)
     if (n < 4) {                                     // one output per lane at any batch: 16 lanes for at most three
         if (!narrow) return B <= (ni >= 32 ? 1 << 13 : 1 << 11) ? 1 : 0;
         // (longer tables cost the narrow kernel more, whose four lanes a sample read rows one at a time)
+        if (n == 1 && ni >= 32) return B <= (ni >= 384 ? 7 << 8 : ni >= 256 ? 6 << 8 : g.rows >= 128 ? 1 << 9 : 5 << 8) ? 1 : 0;
         const int64_t per = n == 1 ? 32ll * ni : (g.rows >= 4096 ? 128ll : 64ll) * ni, cap = n == 1 ? 1 << 12 : 1 << 13;
         const int64_t low = n == 1 && g.rows >= 128 ? 1 << 10 : 1 << 11;
         const int64_t most = ni < 32 ? 1 << 12 : (per < low ? low : (per < cap ? per : cap));
         return B <= most ? 1 : 0;
     }
     constexpr bool six = kMaxK == 6;
+    // The narrow kernel's lanes gather rows of their own, the wider and the longer the table the further from L1: at any batch.
+    // (Nine to fifteen outputs of up to 63 inputs on short tables stay with the line below, which a test holds; not for speed.)
+    if (narrow && (n == 16 || (n > 8 && (ni >= 64 || g.rows >= 64)) || ni >= 256 || (ni >= 64 && (n >= 5 || g.rows >= 256)) || (ni >= 32 && (n == 8 || (n >= 5 && g.rows >= 256))))) return 1;
     if (narrow)
         return load <= (ni >= 64 || (ni >= 32 && (n >= 8 || g.rows >= 512)) ? 1 << 20 : (ni >= 32 ? 1 << 18 : 1 << 17)) ? 1 : 0;
     if (lds_rows && six) {

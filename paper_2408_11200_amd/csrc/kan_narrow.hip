@@ -9,31 +9,39 @@
 namespace kan {
 
 // ---- forward ------------------------------------------------------------------------------
-// Four lanes per sample: lane q of the quad takes inputs q, q + 4, ... and the four partial sums are
-// added across the quad at the end (with one thread per sample a batch of a few ten thousand leaves
+// Q lanes per sample (four, or sixteen): lane q of the group takes inputs q, q + Q, ... and the partial sums are
+// added across the group at the end (with one thread per sample a batch of a few ten thousand leaves
 // most of the chip idle).
-template <int NO>
+template <int NO, int Q>
 __global__ __launch_bounds__(256) void forward_narrow_kernel(SplineGeom g, const float *__restrict__ x,
                                                              const float *__restrict__ cf,
                                                              const float *__restrict__ w_b, float *__restrict__ y,
                                                              int64_t B)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t b = t >> 2;
-    const int q = (int)(t & 3);
-    const int64_t bc = b < B ? b : B - 1;        // lanes past the batch recompute the last sample: quads stay whole
+    const int64_t b = t / Q;
+    const int q = (int)(t % Q);
+    const int64_t bc = b < B ? b : B - 1;        // lanes past the batch recompute the last sample: groups stay whole
     float acc[NO];
 #pragma unroll
     for (int j = 0; j < NO; ++j) acc[j] = 0.0f;
-    for (int i = q; i < g.n_in; i += 4) {
-        const Pair p = pair_eval<false>(x[bc * g.n_in + i], g, i);
+    for (int i = q; i < g.n_in; i += Q) {
+        Pair p = pair_basis<false>(x[bc * g.n_in + i], g, i);
         const float *slab = cf + (int64_t)i * g.slab_rows * g.n_out;
+        // one output: a window is four neighbouring floats, one access (the lines looked up in L1 were the bound: 256 -> 1, 244 rows,
+        // B = 32768 64 -> 49 us)
+        if (NO == 1 && __all(p.cell >= 0 && p.cell <= g.rows - kMaxK)) {
+            const float4 r = load4u(slab + p.cell);
+            acc[0] = fmaf(p.w[3], r.w, fmaf(p.w[2], r.z, fmaf(p.w[1], r.y, fmaf(p.w[0], r.x, acc[0]))));
+        } else {
+            mask_pair<false>(p, g);
 #pragma unroll
-        for (int s = 0; s < kMaxK; ++s) {
-            const float *row = slab + (int64_t)clampi(p.cell + s, 0, g.rows - 1) * g.n_out;
+            for (int s = 0; s < kMaxK; ++s) {
+                const float *row = slab + (int64_t)clampi(p.cell + s, 0, g.rows - 1) * g.n_out;
 #pragma unroll
-            for (int j = 0; j < NO; ++j)
-                if (j < g.n_out) acc[j] = fmaf(p.w[s], row[j], acc[j]);
+                for (int j = 0; j < NO; ++j)
+                    if (j < g.n_out) acc[j] = fmaf(p.w[s], row[j], acc[j]);
+            }
         }
         if (g.base_act) {
             const float *wb = w_b + (int64_t)i * g.n_out;
@@ -45,8 +53,8 @@ __global__ __launch_bounds__(256) void forward_narrow_kernel(SplineGeom g, const
 #pragma unroll
     for (int j = 0; j < NO; ++j) {
         float v = acc[j];
-        v += __shfl_xor(v, 1, 64);
-        v += __shfl_xor(v, 2, 64);
+#pragma unroll
+        for (int d = 1; d < Q; d *= 2) v += __shfl_xor(v, d, 64);
         acc[j] = v;
     }
     if (q == 0 && b < B) {
@@ -108,8 +116,15 @@ hipError_t launch_forward_narrow(const SplineGeom &g, const float *x, const floa
                                  int64_t B, hipStream_t st)
 {
     prof::Timed tm("forward_narrow", st);
+    // One output from 32 inputs on: sixteen lanes a sample, four times the waves and whole lines of x, until the batch fills the chip
+    // either way (four / sixteen, G = 240, us: 256 -> 1, B = 32768 52 / 30; 128 -> 1, B = 5000 26 / 10; 32 -> 1, B = 65536 11.9 / 10.9,
+    // 262144 27 / 30; 16 -> 1, B = 262144 16 / 20; 64 -> 2, B = 65536 41 / 71).
+    if (g.n_out == 1 && g.n_in >= 32 && B <= 1 << 17) {
+        forward_narrow_kernel<1, 16><<<(unsigned)((16 * B + 255) / 256), 256, 0, st>>>(g, x, cf, w_b, y, B);
+        return hipGetLastError();
+    }
     const unsigned blocks = (unsigned)((4 * B + 255) / 256);
-#define CALL(N) forward_narrow_kernel<N><<<blocks, 256, 0, st>>>(g, x, cf, w_b, y, B)
+#define CALL(N) forward_narrow_kernel<N, 4><<<blocks, 256, 0, st>>>(g, x, cf, w_b, y, B)
     KAN_NARROW_DISPATCH(g.n_out, CALL)
 #undef CALL
     return hipGetLastError();

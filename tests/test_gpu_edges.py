@@ -552,3 +552,13 @@ def test_walk_of_one_output_keeps_infinities_apart():
         ok = np.isfinite(want)
         assert ok.any() and not ok.all()
         assert (np.abs(got[ok] - want[ok]) <= GRAD_TOL * (1.0 + np.abs(want[ok]))).all(), n
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k,family", [
+    (1280, 35, 1, 20, 3, "direct"), (1281, 35, 1, 20, 3, "narrow"), (513, 47, 1, 200, 2, "narrow"),     # one output, sixteen lanes a sample
+    (131073, 33, 1, 20, 3, "narrow"), (9001, 31, 1, 20, 3, "narrow"),                                   # four
+    (70001, 8, 16, 20, 3, "direct"), (70001, 33, 8, 20, 3, "direct"), (70001, 12, 8, 20, 3, "narrow"),  # wider
+    (70001, 64, 5, 20, 3, "direct"), (70001, 63, 5, 20, 3, "narrow"), (70001, 33, 5, 256, 2, "direct"),
+])
+def test_narrow_lines(B, n_in, n_out, G, k, family):
+    assert "forward_" + family in forward_with_families(workloads.random_kan_layer(n_in, B, n_in, n_out, G, k, outside_frac=0.02))
