@@ -94,7 +94,14 @@ struct Layout {
     size_t total;
 };
 
-int split_slices(int64_t rows) { int64_t s = (rows + 511) / 512; return (int)(s < 1 ? 1 : (s > 64 ? 64 : s)); }
+// Slices of the sums over the table rows that give the generator's M x N weight gradients.  A slice's workgroup takes a step of
+// rows in a little over a microsecond, however few there are: an output of a few tiles is cut into more slices, until their
+// sum costs as much (64 x 64 of 13400 rows: 27 slices 37 + 5 us, 64 20 + 5).
+int split_slices(int64_t rows, int64_t M, int64_t N)
+{
+    const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64), per = tiles >= 8 ? 512 : 128, s = (rows + per - 1) / per;
+    return (int)(s < 1 ? 1 : (s > 64 ? 64 : s));
+}
 
 Layout make_layout(const ukan_layer_desc *d, int64_t B, int64_t n_g, int n_chunks, size_t rec_bytes, int b_slices,
                    int pass)
@@ -121,8 +128,8 @@ Layout make_layout(const ukan_layer_desc *d, int64_t B, int64_t n_g, int n_chunk
         L.dense = take(dense_part_bytes(d, B));
         L.gout = take(table);
         L.gpre = take(rows * dh * 4);
-        size_t s1 = (size_t)split_slices((int64_t)rows) * (dh + 1) * n_o * 4;      // gW2 and gb2 partials
-        size_t s2 = (size_t)split_slices((int64_t)rows) * (dz + 1) * dh * 4;       // gW1 and gb1 partials
+        size_t s1 = (size_t)split_slices((int64_t)rows, dh, n_o) * (dh + 1) * n_o * 4;      // gW2 and gb2 partials
+        size_t s2 = (size_t)split_slices((int64_t)rows, dz, dh) * (dz + 1) * dh * 4;       // gW1 and gb1 partials
         L.split = take(s1 > s2 ? s1 : s2);
     }
     L.total = at;
@@ -433,17 +440,18 @@ int backward_body(const ukan_layer_desc *desc, int64_t B, const float *x, const 
     float *split = (float *)(w + L.split);
     const float *hid = pr.hid;
     float *gpre = (float *)(w + L.gpre);
-    const int slices = split_slices(rows);
-    int64_t k_slice = (rows + slices - 1) / slices;
-    k_slice = (k_slice + 15) / 16 * 16;
+    auto slice_of = [rows](int64_t M, int64_t N) {
+        const int slices = split_slices(rows, M, N);
+        return ((rows + slices - 1) / slices + 15) / 16 * 16;
+    };
 
     if (g->gW2 || g->gb2) {       // gW2[c][o] = sum_rows hid[row][c] * gout[row][o], gb2[o] = sum_rows gout[row][o]
         GemmArgs a = {};
         a.A = hid; a.a_rs = 1; a.a_cs = dh;
         a.B = gout; a.b_rs = n_o; a.b_cs = 1;
         a.C = split; a.ldc = n_o; a.M = dh; a.N = n_o; a.K = rows;
-        a.k_slice = k_slice; a.c_slice = (int64_t)(dh + 1) * n_o; a.colsum = 1;
-        const int used = (int)((rows + k_slice - 1) / k_slice);
+        a.k_slice = slice_of(dh, n_o); a.c_slice = (int64_t)(dh + 1) * n_o; a.colsum = 1;
+        const int used = (int)((rows + a.k_slice - 1) / a.k_slice);
         if ((g->gW2 ? launch_gemm(a, EPI_PLAIN, used, "cg_gW2_gemm", st) : launch_column_sums(a, used, st)) != hipSuccess)
             return KAN_ERR_HIP;
         if (launch_slice_sum(split, g->gW2, (int64_t)dh * n_o, g->gb2, n_o, used, st) != hipSuccess) return KAN_ERR_HIP;
@@ -461,8 +469,8 @@ int backward_body(const ukan_layer_desc *desc, int64_t B, const float *x, const 
             b.A = pr.z; b.a_rs = 1; b.a_cs = dz;
             b.B = gpre; b.b_rs = dh; b.b_cs = 1;
             b.C = split; b.ldc = dh; b.M = dz; b.N = dh; b.K = rows;
-            b.k_slice = k_slice; b.c_slice = (int64_t)(dz + 1) * dh; b.colsum = 1;
-            const int used = (int)((rows + k_slice - 1) / k_slice);
+            b.k_slice = slice_of(dz, dh); b.c_slice = (int64_t)(dz + 1) * dh; b.colsum = 1;
+            const int used = (int)((rows + b.k_slice - 1) / b.k_slice);
             if ((g->gW1 ? launch_gemm(b, EPI_PLAIN, used, "cg_gW1_gemm", st) : launch_column_sums(b, used, st)) != hipSuccess)
                 return KAN_ERR_HIP;
             if (launch_slice_sum(split, g->gW1, (int64_t)dz * dh, g->gb1, dh, used, st) != hipSuccess) return KAN_ERR_HIP;
