@@ -225,13 +225,15 @@ __global__ __launch_bounds__(256) void cg_hidden_kernel(const float *__restrict_
 
 // ---- matrix-core GEMM ------------------------------------------------------------
 // C(m,n) = sum_k A(m,k) B(k,n), fp32 operands addressed through (row, column) strides so that
-// transposed views need no copy.  One block = 4 waves = one 64x64 tile of C; each wave owns a
-// 32x32 quadrant; K-slices are staged through LDS.  blockIdx.z selects a slice of K (split-K):
+// transposed views need no copy.  One block = 4 waves = one BM x 64 tile of C; each wave owns a
+// 32x32 quadrant of 64x64; K-slices are staged through LDS.  blockIdx.z selects a slice of K (split-K):
 // slice z writes its own copy of C at C + z*c_slice.
 //   ACC64 = false: v_mfma_f32_32x32x2_f32, fp32 accumulation folded every 64 terms (forward).
 //   ACC64 = true : operands widened to fp64, v_mfma_f64_16x16x4_f64.  Used by the CG backward
 //                  pass, whose long sums cancel heavily; the products are then exact and the
 //                  only rounding is the final conversion to fp32.
+//   BM = 32 : 32x64 tiles, a wave 32x16: twice the workgroups where all of K is one slice and N one tile (the hidden layer's
+//             gradient, 13400 x 64 from 1024: 210 workgroups 75 us, 420 67, beside about 30 for the matrix instructions).
 using f32x16 = __attribute__((__vector_size__(16 * sizeof(float)))) float;
 using f64x4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
 
@@ -255,10 +257,11 @@ __device__ __forceinline__ void gemm_store(const GemmArgs &a, float *C, int64_t 
     }
 }
 
-template <int EPI, bool ACC64>
+template <int EPI, bool ACC64, int BM>
 __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a)
 {
-    constexpr int BM = 64, BN = 64, BK = 16, PAD = 4;
+    static_assert(BM == 64 || (BM == 32 && ACC64), "");
+    constexpr int BN = 64, BK = 16, PAD = 4, BJ = BM / 32;             // 16-column blocks of a wave
     // two LDS stages: the next K step is fetched into registers while the current one is multiplied,
     // then parked in the other stage; one barrier per step
     __shared__ float As[2][BK][BM + PAD];
@@ -267,48 +270,53 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a)
     const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
     const int64_t k_lo = (int64_t)blockIdx.z * a.k_slice;
     const int64_t k_hi = (k_lo + a.k_slice < a.K) ? k_lo + a.k_slice : a.K;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    const int wm = BM == 64 ? (wave >> 1) * 32 : 0, wn = BM == 64 ? (wave & 1) * 32 : wave * 16;
 
     f32x16 acc, tot;
-    f64x4 dacc[2][2];
+    f64x4 dacc[2][BJ];
 #pragma unroll
     for (int v = 0; v < 16; ++v) { acc[v] = 0.0f; tot[v] = 0.0f; }
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
+        for (int bj = 0; bj < BJ; ++bj)
 #pragma unroll
             for (int v = 0; v < 4; ++v) dacc[bi][bj][v] = 0.0;
 
     // A[BM x BK] and B[BK x BN] of one K step: four elements of each per thread; the thread -> element
     // map follows whichever stride is 1
-    constexpr int PER = BM * BK / 256;
-    float ra[PER], rb[PER];
+    constexpr int PA = BM * BK / 256, PB = BN * BK / 256;
+    float ra[PA], rb[PB];
+    auto at_a = [&](int u, int &mm, int &kk) {
+        const int e = tid + u * 256;
+        if (a.a_cs == 1) { kk = e % BK; mm = e / BK; } else { mm = e % BM; kk = e / BM; }
+    };
+    auto at_b = [&](int u, int &nn, int &kk) {
+        const int e = tid + u * 256;
+        if (a.b_cs == 1) { nn = e % BN; kk = e / BN; } else { kk = e % BK; nn = e / BK; }
+    };
     auto fetch = [&](int64_t k0) {
 #pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int e = tid + u * 256;
+        for (int u = 0; u < PA; ++u) {
             int mm, kk;
-            if (a.a_cs == 1) { kk = e % BK; mm = e / BK; } else { mm = e % BM; kk = e / BM; }
+            at_a(u, mm, kk);
             const int64_t m = m0 + mm, k = k0 + kk;
             ra[u] = (m < a.M && k < k_hi) ? a.A[m * a.a_rs + k * a.a_cs] : 0.0f;
-            int nn;
-            if (a.b_cs == 1) { nn = e % BN; kk = e / BN; } else { kk = e % BK; nn = e / BK; }
+        }
+#pragma unroll
+        for (int u = 0; u < PB; ++u) {
+            int nn, kk;
+            at_b(u, nn, kk);
             const int64_t n = n0 + nn, kb = k0 + kk;
             rb[u] = (n < a.N && kb < k_hi) ? a.B[kb * a.b_rs + n * a.b_cs] : 0.0f;
         }
     };
     auto park = [&](int buf) {
+        int mm, nn, kk;
 #pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int e = tid + u * 256;
-            int mm, kk;
-            if (a.a_cs == 1) { kk = e % BK; mm = e / BK; } else { mm = e % BM; kk = e / BM; }
-            As[buf][kk][mm] = ra[u];
-            int nn;
-            if (a.b_cs == 1) { nn = e % BN; kk = e / BN; } else { kk = e % BK; nn = e / BK; }
-            Bs[buf][kk][nn] = rb[u];
-        }
+        for (int u = 0; u < PA; ++u) { at_a(u, mm, kk); As[buf][kk][mm] = ra[u]; }
+#pragma unroll
+        for (int u = 0; u < PB; ++u) { at_b(u, nn, kk); Bs[buf][kk][nn] = rb[u]; }
     };
 
     // column sums of B (bias gradients) ride along in the first row of workgroups: thread -> (column, quarter of the K step)
@@ -336,11 +344,12 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a)
             for (int kk = 0; kk < BK; kk += 4) {
                 const int kr = kk + (lane >> 4), c = lane & 15;
                 const double a0 = (double)As[buf][kr][wm + c], a1 = (double)As[buf][kr][wm + 16 + c];
-                const double b0 = (double)Bs[buf][kr][wn + c], b1 = (double)Bs[buf][kr][wn + 16 + c];
-                dacc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, dacc[0][0], 0, 0, 0);
-                dacc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, dacc[0][1], 0, 0, 0);
-                dacc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, dacc[1][0], 0, 0, 0);
-                dacc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, dacc[1][1], 0, 0, 0);
+#pragma unroll
+                for (int bj = 0; bj < BJ; ++bj) {
+                    const double bv = (double)Bs[buf][kr][wn + 16 * bj + c];
+                    dacc[0][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, bv, dacc[0][bj], 0, 0, 0);
+                    dacc[1][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, bv, dacc[1][bj], 0, 0, 0);
+                }
             }
         } else {
 #pragma unroll
@@ -370,7 +379,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a)
 #pragma unroll
         for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-            for (int bj = 0; bj < 2; ++bj)
+            for (int bj = 0; bj < BJ; ++bj)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     gemm_store<EPI, double>(a, C, m0 + wm + 16 * bi + 4 * v + (lane >> 4),
@@ -577,9 +586,9 @@ hipError_t launch_gemm(const GemmArgs &a, int epi, int slices, const char *famil
     prof::Timed tm(family, st);
     dim3 grid((unsigned)((a.N + 63) / 64), (unsigned)((a.M + 63) / 64), (unsigned)slices);
     switch (epi) {
-    case EPI_PLAIN: gemm_mfma_kernel<EPI_PLAIN, true><<<grid, 256, 0, st>>>(a); break;
-    case EPI_CG_OUT: gemm_mfma_kernel<EPI_CG_OUT, false><<<grid, 256, 0, st>>>(a); break;
-    default: gemm_mfma_kernel<EPI_SILU_GRAD, true><<<grid, 256, 0, st>>>(a); break;
+    case EPI_PLAIN: gemm_mfma_kernel<EPI_PLAIN, true, 64><<<grid, 256, 0, st>>>(a); break;
+    case EPI_CG_OUT: gemm_mfma_kernel<EPI_CG_OUT, false, 64><<<grid, 256, 0, st>>>(a); break;
+    default: gemm_mfma_kernel<EPI_SILU_GRAD, true, 32><<<dim3(grid.x, (unsigned)((a.M + 31) / 32), grid.z), 256, 0, st>>>(a); break;
     }
     return hipGetLastError();
 }
