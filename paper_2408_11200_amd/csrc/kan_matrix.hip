@@ -376,10 +376,11 @@ static hipError_t matrix_launch(const SplineGeom &g, const MatrixTable &t, const
     if (hipError_t e = ensure_dynamic_lds<Tag>((const void *)kern, bytes); e != hipSuccess) return e;
     const U4 *frag = (const U4 *)table;
     const int *odd = (const int *)((const char *)table + t.frag_bytes);
-    const int64_t part = (int64_t)S << 20;                        // samples of one launch: fewer than 2^32 threads
+    const unsigned across = (unsigned)((t.n_tiles + WN - 1) / WN);
+    const int64_t part = (int64_t)S * ((1 << 22) / across);       // samples of one launch: fewer than 2^32 threads
     for (int64_t b0 = 0; b0 < B; b0 += part) {
         const int64_t n = B - b0 < part ? B - b0 : part;
-        const dim3 grid((unsigned)((n + S - 1) / S), (unsigned)((t.n_tiles + WN - 1) / WN));
+        const dim3 grid((unsigned)((n + S - 1) / S), across);
         prof::Timed tm("forward_matrix", st);
         kern<<<grid, 64 * WM * WN, bytes, st>>>(g, x + b0 * g.n_in, cf, frag, odd, y + b0 * g.n_out, n, t.n_tiles);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;

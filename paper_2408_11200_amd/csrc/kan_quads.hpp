@@ -45,6 +45,8 @@ hipError_t launch_cell_lists(const QuadWalkArgs &a, const float *xT, int row_bit
 hipError_t launch_cell_lists6(const QuadWalkArgs &a, const float *xT, int row_bits, hipStream_t st);
 
 // layers of one output: one launch over all chunks, lists of one segment
+constexpr int kOneWaves = 8;
+inline size_t walk_one_lds_bytes(int rows, int S) { return ((size_t)4 * kOneWaves * (rows - 3) + S + rows) * sizeof(float); }
 hipError_t walk_one(const QuadWalkArgs &a, hipStream_t st);
 
 // name: streams a wave, outputs a lane; 6: window of six rows (degrees 4 and 5)

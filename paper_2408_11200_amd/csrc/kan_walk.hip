@@ -296,8 +296,10 @@ WalkPlan plan_lists(const SplineGeom &g, int64_t B, bool allow_shared, bool high
                   (p.streams == 1 ? 1 : g.n_in) * slab_floats <= most && (int64_t)g.n_in * g.n_out <= most ? 1 : 0;
         p.L = quad_list_entries(S, g.rows, p.window);
         // one output: a workgroup a list (kan_walk_one.hip), where there is one a CU (256 -> 1, B = 32768: 204 us / 74); fewer leave
-        // CUs idle that segments of a list would fill
-        p.one = p.quads && g.n_out == 1 && !high_degree && !p.shared && (int64_t)p.n_chunks * g.n_in >= 256 ? 1 : 0;
+        // CUs idle that segments of a list would fill.  Its sums and the chunk's gy have to fit LDS (and past 144 KB
+        // it does not pay: 500 -> 1, G = 1000, B = 32768 672 / 698), its launch 2^32 threads.
+        p.one = p.quads && g.n_out == 1 && !high_degree && !p.shared && (int64_t)p.n_chunks * g.n_in >= 256 &&
+                (int64_t)p.n_chunks * g.n_in <= 1 << 22 && walk_one_lds_bytes(g.rows, S) <= 144 * 1024 ? 1 : 0;
         if (p.one) p.n_seg = 1;
     }
     return p;

@@ -17,7 +17,6 @@ namespace kan {
 
 namespace {
 
-constexpr int kOneWaves = 8;
 constexpr int kOneInputs = 32;          // neighbouring inputs of one XCD: a 128-byte line of gx
 
 template <bool DX, bool BASE>
@@ -139,7 +138,7 @@ __global__ __launch_bounds__(64 * kOneWaves) void walk_one_kernel(QuadWalkArgs p
 
 hipError_t walk_one(const QuadWalkArgs &a, hipStream_t st)
 {
-    const size_t bytes = ((size_t)4 * kOneWaves * (a.rows - kMaxK + 1) + a.S + a.rows) * sizeof(float);
+    const size_t bytes = walk_one_lds_bytes(a.rows, a.S);
     const int64_t units = (int64_t)a.n_chunks * ((a.n_in + kOneInputs - 1) / kOneInputs);
     const unsigned blocks = (unsigned)((units + 7) / 8 * 8 * kOneInputs);
     auto launch = [&](auto dx, auto base) {

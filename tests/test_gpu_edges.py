@@ -524,6 +524,7 @@ def test_matrix_forward_workspace():
 
 @pytest.mark.parametrize("B,n_in,G,k,base", [
     (5001, 257, 30, 3, 1), (4099, 130, 12, 1, 1),              # a chunk's last list is short; a group of one and of two inputs
+    (70000, 150, 1000, 3, 1),                                  # past what fits LDS: the other walk
     (33000, 40, 60, 3, 0), (70000, 33, 900, 2, 1),             # no base term; more cells than a wave has quads at a time
     (2048, 300, 1, 3, 1), (70000, 300, 5, 3, 1),               # one cell in the grid; cells that go on from wave to wave
 ])
