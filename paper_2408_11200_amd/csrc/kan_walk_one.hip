@@ -86,9 +86,10 @@ __global__ __launch_bounds__(64 * kOneWaves) void walk_one_kernel(QuadWalkArgs p
             for (int s = 0; s < kMaxK; ++s) v[s] = ok ? fmaf(w[s], gv, v[s]) : v[s];
             if constexpr (BASE) bsum = ok ? fmaf(base, gv, bsum) : bsum;
             if constexpr (DX) {
-                float d = BASE ? dbase * wb : 0.0f;
+                float d = 0.0f;
 #pragma unroll
                 for (int s = 0; s < kMaxK; ++s) d = fmaf(dw[s], tv[s], d);
+                if constexpr (BASE) d = fmaf(dbase, wb, d);
                 if (ok) p.gx[(b0 + ss[u]) * p.n_in + i] = gv * d;
             }
         }
