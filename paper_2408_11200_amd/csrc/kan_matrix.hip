@@ -1,4 +1,4 @@
-// Matrix-core forward kernel of the local B-spline layer for short tables (up to 31 rows).
+// Matrix-core forward kernel of the local B-spline layer for short tables (up to 47 rows).
 //
 // y = sum over (input, table row) of basis(x) * table is a dense product whose left operand holds at most kMaxK + 1 values per
 // input.  Sparse matrix instructions (two values of every four positions along the sum, v_smfmac_f32_32x32x32_bf16) skip half
@@ -19,6 +19,7 @@
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
 #include "kan_matrix.hpp"
+#include <type_traits>
 
 namespace KAN_NS {
 
@@ -124,17 +125,20 @@ struct MxArea {                              // left operands of one step of SI 
     template <int S> static constexpr int words() { return S * (kMxSplits * kRow + kIdx); }
 };
 
+template <int NG>
+using IndexBits = std::conditional_t<(NG > 8), uint64_t, unsigned>;
+
 // A pair's left operands: out[part][group], and the indices of its groups, four bits each.
 template <int NG>
 __device__ __forceinline__ void pair_operands(int row0, const float (&w)[kMaxK], float base, unsigned (&out)[kMxSplits][NG],
-                                              unsigned &index)
+                                              IndexBits<NG> &index)
 {
     const int q0 = row0 / NG, c0 = row0 - q0 * NG;
     unsigned part[(kMaxK + 1) / 2][kMxSplits], pb[kMxSplits];
 #pragma unroll
     for (int s = 0; s < kMaxK; s += 2) split_pair(w[s], s + 1 < kMaxK ? w[s + 1] : 0.0f, part[s / 2]);
     split_pair(0.0f, base, pb);
-    index = 0xCCCCCCCCu;
+    index = (IndexBits<NG>)0xCCCCCCCCCCCCCCCCull;
 #pragma unroll
     for (int p = 0; p < kMxSplits; ++p)
 #pragma unroll
@@ -144,7 +148,7 @@ __device__ __forceinline__ void pair_operands(int row0, const float (&w)[kMaxK],
         const bool wrap = c0 + s >= NG;
         const int q = q0 + (wrap ? 1 : 0), g = c0 + s - (wrap ? NG : 0);
         const bool last = q == 3;
-        index |= (last ? 0u : (unsigned)q) << (4 * g);
+        index |= (IndexBits<NG>)(last ? 0u : (unsigned)q) << (4 * g);
 #pragma unroll
         for (int p = 0; p < kMxSplits; ++p) {
             const unsigned v = part[s / 2][p], low = s % 2 ? v >> 16 : v & 0xffffu, high = s % 2 ? v & 0xffff0000u : v << 16;
@@ -218,7 +222,8 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
             if (!fits || i >= g.n_in) base = 0.0f;
 #pragma unroll
             for (int k = 0; k < kMaxK; ++k) w[k] = i < g.n_in ? w[k] : 0.0f;
-            unsigned out[kMxSplits][NG], index;
+            unsigned out[kMxSplits][NG];
+            IndexBits<NG> index;
             pair_operands<NG>(row0, w, base, out, index);
 #pragma unroll
             for (int p = 0; p < kMxSplits; ++p) {
@@ -234,9 +239,15 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
                 }
             }
             unsigned char *ix = reinterpret_cast<unsigned char *>(area + kMxSplits * S * A::kRow + s * A::kIdx) + ii * (NG / 2);
-            if constexpr (NG == 8) *reinterpret_cast<unsigned *>(ix) = index;
-            else if constexpr (NG == 4) *reinterpret_cast<unsigned short *>(ix) = (unsigned short)index;
-            else { ix[0] = (unsigned char)index; ix[1] = (unsigned char)(index >> 8); ix[2] = (unsigned char)(index >> 16); }
+            if constexpr (NG % 8 == 0) {
+                *reinterpret_cast<unsigned *>(ix) = (unsigned)index;
+            } else if constexpr (NG % 4 == 0) {
+#pragma unroll
+                for (int h = 0; h < NG / 4; ++h) reinterpret_cast<unsigned short *>(ix)[h] = (unsigned short)(index >> (16 * h));
+            } else {
+#pragma unroll
+                for (int h = 0; h < NG / 2; ++h) ix[h] = (unsigned char)(index >> (8 * h));
+            }
         }
     };
 
@@ -416,18 +427,20 @@ static hipError_t matrix_forward(const SplineGeom &g, const MatrixTable &t, int 
 // would gain a tenth or more.  Other kernel / this one, us: 512 -> 512, G = 20, B = 16384 914 / 603; 256 -> 256, G = 28, B = 16384
 // 684 / 235; 128 -> 128, G = 10, B = 16384 170 / 54; 75 -> 130, G = 12, B = 6001 58 / 37; not taken: 64 -> 130, G = 28, B = 1024 12 / 48,
 // 32 -> 96, G = 12, B = 32768 39 / 40.  Up to 64 outputs the evaluation of the pairs is not shared by enough of them (64 -> 64,
-// G = 10, B = 65536: 75 / 78 in the best of the forms tried).
+// G = 10, B = 65536: 75 / 78 in the best of the forms tried).  Ten and twelve groups (32..47 rows; step costs extrapolated) spill in
+// the form of two tiles a wave and still gain where they are taken, 13 of 110 layers: 233 -> 270, G = 44, B = 5204 605 / 226;
+// 120 -> 138, G = 32, k = 1, B = 41515 706 / 443; not taken: 262 -> 85, G = 40, B = 27764 278 / 416.  More groups do not fit LDS.
 int forward_matrix_plan(const SplineGeom &g, int64_t B)
 {
     const MatrixTable t = ::kan::matrix_table(g.n_in, g.n_out, g.rows, kMaxK);
     if (t.groups == 0) return 0;
-    struct Form { int samples, tiles, inputs; float fixed, round, step[3]; };
-    static const Form forms[] = {{128, 8, 4, 4.0f, 25.0f, {2.96f, 4.12f, 5.67f}},
-                                 {64, 8, 8, 5.0f, 13.0f, {2.74f, 4.01f, 5.64f}},
-                                 {64, 4, 8, 6.3f, 7.5f, {2.32f, 3.19f, 4.48f}}};
+    struct Form { int samples, tiles, inputs; float fixed, round, step[5]; };
+    static const Form forms[] = {{128, 8, 4, 4.0f, 25.0f, {2.96f, 4.12f, 5.67f, 0.0f, 0.0f}},
+                                 {64, 8, 8, 5.0f, 13.0f, {2.74f, 4.01f, 5.64f, 7.2f, 8.8f}},
+                                 {64, 4, 8, 6.3f, 7.5f, {2.32f, 3.19f, 4.48f, 5.7f, 6.9f}}};
     int best = 0;
     float least = 0.0f;
-    for (int f = t.groups == 8 ? 1 : 0; f < 3; ++f) {            // (eight groups: the first is never the shortest)
+    for (int f = t.groups >= 8 ? 1 : 0; f < 3; ++f) {            // (from eight groups on the first is never the shortest)
         const Form &o = forms[f];
         const int64_t groups = ((B + o.samples - 1) / o.samples) * ((t.n_tiles + o.tiles - 1) / o.tiles);
         const float steps = (float)((g.n_in + o.inputs - 1) / o.inputs);
@@ -443,8 +456,9 @@ int forward_matrix_plan(const SplineGeom &g, int64_t B)
         const float staged = 8.0f + (float)((g.n_out + 511) / 512 * ((B + (wide ? 16383 : 32767)) / (wide ? 16384 : 32768))) *
                                         (wide ? 1.78f : 2.62f) * (float)g.n_in;
         other = staged < direct ? staged : direct;
-    } else if (B >= 28000) {
-        other = 10.0f + (float)B * (float)padded / 4.1e6f;
+    } else if (B >= (t.groups > 8 ? 127 * 128 + 1 : 28000)) {        // (long tables: from a workgroup of eight waves a CU on)
+        const float staged = 10.0f + (float)B * (float)padded / 4.1e6f;
+        other = staged < direct ? staged : direct;
     }
     return least < 0.9f * other ? best : 0;
 }
@@ -457,6 +471,8 @@ hipError_t launch_forward_matrix(const SplineGeom &g, const float *x, const floa
     switch (t.groups) {
     case 4: return matrix_forward<4>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
     case 6: return matrix_forward<6>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
+    case 10: return matrix_forward<10>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
+    case 12: return matrix_forward<12>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
     case 8: return matrix_forward<8>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
     default: return hipErrorInvalidValue;
     }

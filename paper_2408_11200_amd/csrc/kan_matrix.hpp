@@ -8,7 +8,7 @@ namespace kan {
 constexpr int kMxInputs = 4;       // inputs of one step
 constexpr int kMxTile = 32;        // outputs of one tile
 constexpr int kMxSplits = 3;       // bf16 parts of a float
-constexpr int kMxMaxGroups = 8;
+constexpr int kMxMaxGroups = 12;
 
 // Groups of four positions an input's rows + 1 table rows (the last one w_b) are dealt to; even, so that the groups of a step
 // fill whole instructions of eight; at least as many as a window has rows, so that no two rows of a window share a group.
