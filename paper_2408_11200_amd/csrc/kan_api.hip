@@ -76,7 +76,7 @@ size_t folded_bytes(const kan_layer_desc *d)
 // the split table of the matrix-core forward kernel, behind the folded one (0: the shape does not qualify)
 size_t matrix_bytes(const kan_layer_desc *d)
 {
-    return high_degree(d) ? 0 : ::kan::matrix_table(d->n_in, d->n_out, d->G + d->k, kMaxK).bytes;
+    return matrix_table(d->n_in, d->n_out, d->G + d->k, high_degree(d) ? 6 : kMaxK).bytes;
 }
 
 size_t edge_bytes(const kan_layer_desc *d)
@@ -189,11 +189,14 @@ static int forward_impl(const kan_layer_desc *desc, int64_t B, const float *x, c
     SplineGeom g = geom_of(desc);
     float *cf = (float *)ws;
     const size_t split = matrix_bytes(desc);
-    if (split && ws_bytes >= folded_bytes(desc) + split && forward_matrix_plan(g, B))
-        return launch_forward_matrix(g, x, coef, w_s, g.base_act ? w_b : nullptr, cf, (char *)ws + folded_bytes(desc), y, B, st) ==
-                       hipSuccess
-                   ? KAN_OK
-                   : KAN_ERR_HIP;
+    void *table = (char *)ws + folded_bytes(desc);
+    if (split && ws_bytes >= folded_bytes(desc) + split &&
+        (high_degree(desc) ? highk_matrix_plan(highk_of(desc), B) : forward_matrix_plan(g, B))) {
+        const float *wb = g.base_act ? w_b : nullptr;
+        const hipError_t e = high_degree(desc) ? highk_matrix_forward(highk_of(desc), x, coef, w_s, wb, cf, table, y, B, st)
+                                               : launch_forward_matrix(g, x, coef, w_s, wb, cf, table, y, B, st);
+        return e == hipSuccess ? KAN_OK : KAN_ERR_HIP;
+    }
     if (high_degree(desc))
         return highk_forward(highk_of(desc), x, coef, w_s, w_b, cf, y, B, keep_table, st) == hipSuccess ? KAN_OK : KAN_ERR_HIP;
     if (forward_direct_plan(g, B))

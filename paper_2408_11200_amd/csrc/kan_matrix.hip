@@ -430,6 +430,8 @@ static hipError_t matrix_forward(const SplineGeom &g, const MatrixTable &t, int 
 // G = 10, B = 65536: 75 / 78 in the best of the forms tried).  Ten and twelve groups (32..47 rows; step costs extrapolated) spill in
 // the form of two tiles a wave and still gain where they are taken, 13 of 110 layers: 233 -> 270, G = 44, B = 5204 605 / 226;
 // 120 -> 138, G = 32, k = 1, B = 41515 706 / 443; not taken: 262 -> 85, G = 40, B = 27764 278 / 416.  More groups do not fit LDS.
+// Degrees 4 and 5 (kan_matrix_k5.hip): 225 -> 296, G = 4, k = 5, B = 6869 602 / 137; 104 -> 161, G = 14, k = 4, B = 6803 161 / 62; 52 of 110
+// layers, 0.41 of the time in the mean.
 int forward_matrix_plan(const SplineGeom &g, int64_t B)
 {
     const MatrixTable t = ::kan::matrix_table(g.n_in, g.n_out, g.rows, kMaxK);
@@ -460,7 +462,8 @@ int forward_matrix_plan(const SplineGeom &g, int64_t B)
         const float staged = 10.0f + (float)B * (float)padded / 4.1e6f;
         other = staged < direct ? staged : direct;
     }
-    return least < 0.9f * other ? best : 0;
+    // (windows of six cost the other kernels half as much again, these nothing)
+    return least < 0.9f * (kMaxK == 6 ? 1.3f : 1.0f) * other ? best : 0;
 }
 
 hipError_t launch_forward_matrix(const SplineGeom &g, const float *x, const float *coef, const float *w_s, const float *w_b,
@@ -469,7 +472,9 @@ hipError_t launch_forward_matrix(const SplineGeom &g, const float *x, const floa
     const MatrixTable t = ::kan::matrix_table(g.n_in, g.n_out, g.rows, kMaxK);
     const int form = forward_matrix_plan(g, B);
     switch (t.groups) {
-    case 4: return matrix_forward<4>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
+    case 4:
+        if constexpr (kMaxK <= 4) return matrix_forward<4>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
+        return hipErrorInvalidValue;
     case 6: return matrix_forward<6>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
     case 10: return matrix_forward<10>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
     case 12: return matrix_forward<12>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);

@@ -458,6 +458,8 @@ MATRIX_SHAPES = [
     (16001, 65, 256, 20, 3), (16001, 66, 255, 10, 3), (16001, 63, 193, 28, 2),      # sixty-four samples a workgroup
     (32700, 67, 300, 20, 3), (32641, 42, 512, 10, 3),          # a hundred and twenty-eight
     (12900, 139, 139, 29, 3), (5201, 231, 270, 38, 1), (5201, 232, 270, 38, 2), (12900, 137, 140, 44, 3),      # up to 47 rows
+    (8096, 163, 230, 3, 4), (13457, 94, 136, 18, 5), (10900, 58, 123, 19, 5), (6801, 105, 161, 26, 5), (5200, 159, 446, 42, 5),      # windows of six
+    (30001, 100, 417, 11, 4),
 ]
 
 
@@ -478,10 +480,10 @@ def test_matrix_forward(B, n_in, n_out, G, k):
     assert err < 3.5 * 2.0 ** -24, err
 
 
-@pytest.mark.parametrize("B,n_in,n_out,G", [(12001, 37, 97, 12), (16001, 65, 256, 20), (32700, 67, 300, 20)])
-def test_matrix_forward_keeps_infinities_apart(B, n_in, n_out, G):
+@pytest.mark.parametrize("B,n_in,n_out,G,k", [(12001, 37, 97, 12, 3), (16001, 65, 256, 20, 3), (32700, 67, 300, 20, 3), (6801, 104, 161, 14, 5)])
+def test_matrix_forward_keeps_infinities_apart(B, n_in, n_out, G, k):
     """Inputs and parameters that do not split into parts reach their own samples and outputs only."""
-    w = workloads.random_kan_layer(B, B, n_in, n_out, G, 3)
+    w = workloads.random_kan_layer(B, B, n_in, n_out, G, k)
     s, p = w.layers[0], w.params[0]
     odd = [3, 64, 4100, B - 1]
     w.x[3, 2], w.x[64, 0], w.x[4100, n_in - 1], w.x[B - 1, 5] = np.inf, -np.inf, np.nan, 3e38
@@ -493,7 +495,7 @@ def test_matrix_forward_keeps_infinities_apart(B, n_in, n_out, G):
     assert "forward_matrix" in families_of(lambda: y.append(binding.kan_forward(s, x, coef, w_s, w_b)))
     rows = np.r_[0:200, 4090:4110, B - 130:B]
     with np.errstate(all="ignore"):
-        ref = oracle.kan_forward(w.x[rows], p["coef"], p["w_s"], p["w_b"], G, 3, s.grid_lo, oracle.inv_h_of(s.grid_lo, s.grid_hi, G))
+        ref = oracle.kan_forward(w.x[rows], p["coef"], p["w_s"], p["w_b"], G, k, s.grid_lo, oracle.inv_h_of(s.grid_lo, s.grid_hi, G))
         got = y[0].cpu().numpy()[rows].astype(np.float64)
         ref = ref.astype(np.float32).astype(np.float64)         # past the range of a float: infinite
     assert np.isin(odd, rows).all() and not np.isfinite(ref[np.isin(rows, odd)]).all()
