@@ -446,7 +446,9 @@ int forward_matrix_plan(const SplineGeom &g, int64_t B)
         const Form &o = forms[f];
         const int64_t groups = ((B + o.samples - 1) / o.samples) * ((t.n_tiles + o.tiles - 1) / o.tiles);
         const float steps = (float)((g.n_in + o.inputs - 1) / o.inputs);
-        const float us = o.fixed + (float)((groups + 255) / 256) * (o.round + steps * o.step[t.groups / 2 - 2]);
+        const float rounds = (float)((groups + 255) / 256);
+        // (the second form's steps take longer behind one another: 512 -> 512, G = 20, B = 16384 603 in the first, 640 in it)
+        const float us = o.fixed + rounds * (o.round + steps * o.step[t.groups / 2 - 2] * (f == 1 && rounds > 1.0f ? 1.08f : 1.0f));
         if (best == 0 || us < least) { best = f + 1; least = us; }
     }
     const int64_t padded = (int64_t)g.n_in * ((g.n_out + 63) / 64 * 64);
