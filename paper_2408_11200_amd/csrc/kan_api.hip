@@ -188,7 +188,8 @@ static int forward_impl(const kan_layer_desc *desc, int64_t B, const float *x, c
     hipStream_t st = (hipStream_t)stream;
     SplineGeom g = geom_of(desc);
     float *cf = (float *)ws;
-    const size_t split = matrix_bytes(desc);
+    // (fewer edges an input never pay for the matrix-core kernel's steps: a small call is spared the estimate)
+    const size_t split = B * desc->n_out >= 1 << 18 ? matrix_bytes(desc) : 0;
     void *table = (char *)ws + folded_bytes(desc);
     if (split && ws_bytes >= folded_bytes(desc) + split &&
         (high_degree(desc) ? highk_matrix_plan(highk_of(desc), B) : forward_matrix_plan(g, B))) {

@@ -31,7 +31,9 @@ inline MatrixTable matrix_table(int n_in, int n_out, int rows, int window)
     t.groups = mx_groups(rows, window);
     t.n_steps = (n_in + kMxInputs - 1) / kMxInputs;
     t.n_tiles = (n_out + kMxTile - 1) / kMxTile;
-    if (rows < window || n_in < 8 || n_out <= 64 || n_out > 1 << 20 || t.groups > kMxMaxGroups) return MatrixTable{};
+    if (rows < window || n_in < 8 || n_out <= 64 || n_out > 1 << 20 || t.groups > kMxMaxGroups ||
+        (int64_t)t.n_steps * t.n_tiles * 32 * t.groups >= 1ll << 31)        // (threads of the launch that splits the table)
+        return MatrixTable{};
     t.frag_bytes = (size_t)t.n_tiles * t.n_steps * (t.groups / 2) * kMxSplits * 2048;
     t.bytes = (t.frag_bytes + (size_t)t.n_tiles * t.n_steps * 4 + 255) / 256 * 256;
     return t;
