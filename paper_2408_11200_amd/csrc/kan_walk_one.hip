@@ -12,6 +12,7 @@
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
 #include "kan_quads.hpp"
+#include "kan_wave.hpp"
 
 namespace kan {
 
@@ -109,6 +110,7 @@ __global__ __launch_bounds__(64 * kOneWaves) void walk_one_kernel(QuadWalkArgs p
             const float4 o = mine[row];
             mine[row] = make_float4(o.x + v[0], o.y + v[1], o.z + v[2], o.w + v[3]);
         }
+        wave_lds_sync();                   // the next round's lanes read what these wrote
     }
     if constexpr (BASE) {
 #pragma unroll
