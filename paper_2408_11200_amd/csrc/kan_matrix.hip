@@ -7,8 +7,9 @@
 // then has one row in slot 0 (positions 0..2) or slot 1 (position 3), and every index pair is (position, 3).
 // The precision is that of fp32: every float is split into three bf16 parts (8 bits each, 24 in all), and the six products of
 // the parts that reach 2^-27 of the whole are summed in fp32; the parts have the exponent range of a float.  Values that do not
-// split (infinite, NaN, or so large that rounding up overflows) are found where they are split and the sums that
-// read them are done in plain fp32 at the end.
+// split (infinite, NaN, or so large that rounding up overflows) are found where they are split; the sums that
+// read them, and those that come out infinite or NaN (two factors that split may have a product of parts that does not fit),
+// are done in plain fp32 at the end.
 //
 // Error against fp64 (2-norm): 512 -> 512, G = 20 4.9e-7 (the LDS-staged kernel 9.0e-7); 256 -> 256, G = 28 1.3e-7 (6.4e-7);
 // 75 -> 130, G = 12, k = 2 0.96e-7 (direct kernel 1.14e-7); 128 -> 128, G = 10 1.07e-7 (1.38e-7).
@@ -19,6 +20,7 @@
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
 #include "kan_matrix.hpp"
+#include <cfloat>
 #include <type_traits>
 
 namespace KAN_NS {
@@ -169,7 +171,7 @@ __device__ __forceinline__ void pair_operands(int row0, const float (&w)[kMaxK],
         }
     }
 #pragma unroll
-    for (int p = 0; p < kMxSplits; ++p) out[p][NG - 1] |= pb[p] & 0xffff0000u;      // (the zero in the low half may carry a sign)      // (the zero in the low half may carry a sign)
+    for (int p = 0; p < kMxSplits; ++p) out[p][NG - 1] |= pb[p] & 0xffff0000u;      // (the zero in the low half may carry a sign)
 }
 
 template <int NG, int SI, int MT, int WM, int WN, int FOLD, bool AHEAD>
@@ -347,19 +349,35 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
     int flag = 0;
     for (int s = lane; s < n_parts; s += 64) flag |= odd[(int64_t)tile * n_parts + s];
     const bool all_odd = __any(flag != 0);
+    // Samples of the wave's tiles with sums that are done again, a bit each: those that read a value which does not split, and
+    // those with a sum that is not finite, where the products of parts may have passed the range of a float in either direction.
+    const int up = 4 * (lane >> 5);
+    unsigned again[MT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+    for (int m = 0; m < MT; ++m) {
+        const int s0 = (wm * MT + m) * 32;
+        again[m] = (unsigned)__ballot(all_odd || special[s0 + (lane & 31)]);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int s = (wm * MT + m) * 32 + 8 * (r / 4) + 4 * (lane >> 5) + r % 4;
-            const int64_t b = b0 + s;
-            if (b < B && j < g.n_out && !all_odd && !special[s]) y[b * g.n_out + j] = (FOLD > 0 ? tot[m][r] + acc[m][r] : acc[m][r]) + low[m][r];
+            acc[m][r] = (FOLD > 0 ? tot[m][r] + acc[m][r] : acc[m][r]) + low[m][r];
+            const uint64_t past = __ballot(!(fabsf(acc[m][r]) <= FLT_MAX));
+            again[m] |= ((unsigned)past ? 1u : 0u) << (8 * (r / 4) + r % 4) | ((past >> 32) ? 1u : 0u) << (8 * (r / 4) + 4 + r % 4);
         }
-    // the sums that read a value which does not split: half a wave takes every other input
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int s = 8 * (r / 4) + up + r % 4;
+            const int64_t b = b0 + s0 + s;
+            if (b < B && j < g.n_out && !(again[m] >> s & 1)) y[b * g.n_out + j] = acc[m][r];
+        }
+    }
+    // these in plain fp32: half a wave takes every other input
     const int jc = j < g.n_out ? j : g.n_out - 1;
-    for (int s = wm * MT * 32; s < (wm + 1) * MT * 32; ++s) {
-        const int64_t b = b0 + s;
-        if (b >= B || !(all_odd || special[s])) continue;
+    for (int s = 0; s < MT * 32; ++s) {
+        const int64_t b = b0 + wm * MT * 32 + s;
+        unsigned bits = again[0];
+#pragma unroll
+        for (int m = 1; m < MT; ++m) bits = s / 32 == m ? again[m] : bits;
+        if (b >= B || !(bits >> s % 32 & 1)) continue;
         float sum = 0.0f;
         for (int i = lane >> 5; i < g.n_in; i += 2) {
             const Pair p = pair_eval<false>(x[b * g.n_in + i], g, i);

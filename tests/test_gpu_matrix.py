@@ -1,0 +1,47 @@
+"""The matrix-core forward kernel and the kernels beside it at the ends of the float range, and their sums' accuracy."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2408_11200_amd import binding, workloads
+from test_gpu_edges import families_of
+from test_gpu_kan import dev
+
+pytestmark = pytest.mark.gpu
+
+
+def run_rows(w, rows, family):
+    """The layer's outputs at some rows and the oracle's, on the kernel family that is meant."""
+    s, p = w.layers[0], w.params[0]
+    x, coef, w_s, w_b = (dev(a) for a in (w.x, p["coef"], p["w_s"], p["w_b"]))
+    y = []
+    assert "forward_" + family in families_of(lambda: y.append(binding.kan_forward(s, x, coef, w_s, w_b)))
+    with np.errstate(all="ignore"):
+        ref = oracle.kan_forward(w.x[rows], p["coef"], p["w_s"], p["w_b"], s.G, s.k, s.grid_lo, oracle.inv_h_of(s.grid_lo, s.grid_hi, s.G))
+    return y[0].cpu().numpy()[rows].astype(np.float64), ref
+
+
+# one form each: 64 samples a workgroup with four and eight tiles, 128; windows of six
+MATRIX_FORMS = [(12001, 37, 97, 12, 3), (16001, 65, 256, 20, 3), (32700, 67, 300, 20, 3), (6801, 104, 161, 14, 5)]
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", MATRIX_FORMS)
+def test_matrix_forward_overflows_to_infinity(B, n_in, n_out, G, k):
+    """Factors that split and a product that is past the range of a float, or up to its last percent: as in plain fp32."""
+    w = workloads.random_kan_layer(B + 1, B, n_in, n_out, G, k)
+    p = w.params[0]
+    g = np.random.default_rng(3)
+    rows = np.r_[0:160, B - 70:B]
+    for n, b in enumerate(rows[::3]):
+        w.x[b, n % 7] = 10.0 ** g.uniform(30, 34)               # an input of each of these samples, on large weights of either sign
+    p["w_b"][:7] = 10.0 ** g.uniform(12, 16, (7, n_out)) * g.choice([-1.0, 1.0], (7, n_out))
+    w.x[rows[1]] = 0.0
+    w.x[rows[1], 0], p["w_b"][0, 3] = 1e20, 3.38e18             # 0.993 of the largest float
+    got, ref = run_rows(w, rows, "matrix")
+    with np.errstate(all="ignore"):
+        ref = ref.astype(np.float32).astype(np.float64)
+    assert not np.isnan(ref).any() and np.isinf(ref).sum() > 1000 and np.isfinite(ref[1, 3])
+    assert np.array_equal(np.isinf(got), np.isinf(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    ok = np.isfinite(ref)
+    np.testing.assert_allclose(got[ok], ref[ok], rtol=1e-5, atol=1e-5 * np.abs(p["w_b"][:7]).max())
