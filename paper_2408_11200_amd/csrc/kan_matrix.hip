@@ -6,10 +6,10 @@
 // rows of a window fall into different groups; w_b, the last position of the last group, meets at most one row there.  Each group
 // then has one row in slot 0 (positions 0..2) or slot 1 (position 3), and every index pair is (position, 3).
 // The precision is that of fp32: every float is split into three bf16 parts (8 bits each, 24 in all), and the six products of
-// the parts that reach 2^-27 of the whole are summed in fp32; the parts have the exponent range of a float.  Values that do not
-// split (infinite, NaN, or so large that rounding up overflows) are found where they are split; the sums that
-// read them, and those that come out infinite or NaN (two factors that split may have a product of parts that does not fit),
-// are done in plain fp32 at the end.
+// the parts that reach 2^-27 of the whole are summed in fp32; the parts have the exponent range of a float, and a common power of
+// two keeps the lowest ones off its end.  Values that do not split (infinite, NaN, or too large for that) are found where they are
+// split; the sums that read them, and those that come out infinite or NaN (two factors that split may have a product of parts
+// that does not fit), are done in plain fp32 at the end.
 //
 // Error against fp64 (2-norm): 512 -> 512, G = 20 4.9e-7 (the LDS-staged kernel 9.0e-7); 256 -> 256, G = 28 1.3e-7 (6.4e-7);
 // 75 -> 130, G = 12, k = 2 0.96e-7 (direct kernel 1.14e-7); 128 -> 128, G = 10 1.07e-7 (1.38e-7).
@@ -40,7 +40,9 @@ typedef float F16 __attribute__((ext_vector_type(16)));
 typedef unsigned U4 __attribute__((ext_vector_type(4)));
 typedef unsigned U8 __attribute__((ext_vector_type(8)));
 
-constexpr float kMxLargest = 0x1p+120f;
+// Both operands are split times 2^24, which makes the lowest bit of the smallest float a bf16 number that is not subnormal; what
+// is larger than kMxLargest then leaves the parts' range.
+constexpr float kMxScale = 0x1p+24f, kMxLargest = 0x1p+96f;
 
 // two floats rounded to bf16, low and high half
 __device__ __forceinline__ unsigned bf16_pair(float a, float b)
@@ -94,7 +96,7 @@ __global__ __launch_bounds__(32 * NG) void matrix_table_kernel(const float *__re
             }
             const bool fits = fabsf(c) < kMxLargest;
             bad |= !fits;
-            v[4 * e + q] = fits ? c : 0.0f;
+            v[4 * e + q] = fits ? c * kMxScale : 0.0f;
         }
     }
     unsigned p[8][kMxSplits];
@@ -221,9 +223,10 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
             wave_windows<false>(v[c], g, i < g.n_in ? i : g.n_in - 1, row0, w, base, dw, dbase);
             const bool fits = fabsf(base) < kMxLargest;
             if (!fits) special[s] = 1;
-            if (!fits || i >= g.n_in) base = 0.0f;
+            const float scale = i < g.n_in ? kMxScale : 0.0f;
+            base = fits ? base * scale : 0.0f;
 #pragma unroll
-            for (int k = 0; k < kMaxK; ++k) w[k] = i < g.n_in ? w[k] : 0.0f;
+            for (int k = 0; k < kMaxK; ++k) w[k] *= scale;
             unsigned out[kMxSplits][NG];
             IndexBits<NG> index;
             pair_operands<NG>(row0, w, base, out, index);
@@ -359,7 +362,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
         again[m] = (unsigned)__ballot(all_odd || special[s0 + (lane & 31)]);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            acc[m][r] = (FOLD > 0 ? tot[m][r] + acc[m][r] : acc[m][r]) + low[m][r];
+            acc[m][r] = ((FOLD > 0 ? tot[m][r] + acc[m][r] : acc[m][r]) + low[m][r]) * (1.0f / (kMxScale * kMxScale));
             const uint64_t past = __ballot(!(fabsf(acc[m][r]) <= FLT_MAX));
             again[m] |= ((unsigned)past ? 1u : 0u) << (8 * (r / 4) + r % 4) | ((past >> 32) ? 1u : 0u) << (8 * (r / 4) + 4 + r % 4);
         }

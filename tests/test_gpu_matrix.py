@@ -22,6 +22,10 @@ def run_rows(w, rows, family):
     return y[0].cpu().numpy()[rows].astype(np.float64), ref
 
 
+def rel(got, ref):
+    return np.linalg.norm(got - ref) / np.linalg.norm(ref)
+
+
 # one form each: 64 samples a workgroup with four and eight tiles, 128; windows of six
 MATRIX_FORMS = [(12001, 37, 97, 12, 3), (16001, 65, 256, 20, 3), (32700, 67, 300, 20, 3), (6801, 104, 161, 14, 5)]
 
@@ -45,3 +49,15 @@ def test_matrix_forward_overflows_to_infinity(B, n_in, n_out, G, k):
     assert np.array_equal(np.isinf(got), np.isinf(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
     ok = np.isfinite(ref)
     np.testing.assert_allclose(got[ok], ref[ok], rtol=1e-5, atol=1e-5 * np.abs(p["w_b"][:7]).max())
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", MATRIX_FORMS)
+def test_matrix_forward_of_small_values(B, n_in, n_out, G, k):
+    """Parameters whose lower parts are below the smallest bf16 number keep their 24 bits."""
+    w = workloads.random_kan_layer(B + 2, B, n_in, n_out, G, k)
+    p = w.params[0]
+    p["coef"] = (p["coef"] * 2.0 ** -112).astype(np.float32)
+    p["w_b"] = (p["w_b"] * 2.0 ** -112).astype(np.float32)
+    rows = np.r_[0:70, B - 70:B]
+    got, ref = run_rows(w, rows, "matrix")
+    assert rel(got, ref) < 3.5 * 2.0 ** -24
