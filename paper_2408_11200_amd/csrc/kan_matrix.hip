@@ -381,17 +381,21 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
 #pragma unroll
         for (int m = 1; m < MT; ++m) bits = s / 32 == m ? again[m] : bits;
         if (b >= B || !(bits >> s % 32 & 1)) continue;
-        float sum = 0.0f;
+        float sum = 0.0f, part = 0.0f;                   // two levels, as in the kernels this one stands in for
+        int n = 0;
         for (int i = lane >> 5; i < g.n_in; i += 2) {
-            const Pair p = pair_eval<false>(x[b * g.n_in + i], g, i);
-            float w[kMaxK], base;
-            int row0;
-            window_of<false>(p, g.rows, row0, w, base);
-            const float *row = cf + ((int64_t)i * g.slab_rows + row0) * g.n_out + jc;
+            const Pair p = pair_basis<false>(x[b * g.n_in + i], g, i);
+            const float *slab = cf + (int64_t)i * g.slab_rows * g.n_out + jc;
 #pragma unroll
-            for (int k = 0; k < kMaxK; ++k) sum = fmaf(w[k], row[(int64_t)k * g.n_out], sum);
-            sum = fmaf(base, cf[((int64_t)i * g.slab_rows + g.rows) * g.n_out + jc], sum);
+            for (int k = 0; k < kMaxK; ++k) {
+                const int m = p.cell + k;                // rows that are not there take no part, whatever stands beside them
+                const float c = slab[(int64_t)clampi(m, 0, g.rows - 1) * g.n_out];
+                part = k <= g.k && m >= 0 && m < g.rows ? fmaf(p.w[k], c, part) : part;
+            }
+            part = fmaf(p.base, slab[(int64_t)g.rows * g.n_out], part);
+            if (++n == 8) { sum += part; part = 0.0f; n = 0; }
         }
+        sum += part;
         sum += __shfl_xor(sum, 32);
         if (lane < 32 && j < g.n_out) y[b * g.n_out + j] = sum;
     }

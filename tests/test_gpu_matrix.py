@@ -26,6 +26,13 @@ def rel(got, ref):
     return np.linalg.norm(got - ref) / np.linalg.norm(ref)
 
 
+def chain_bound(chain, parts):
+    """2-norm error of a sum of `parts` partial sums of `chain` terms each, all one behind another, in the mean: an addition rounds to
+    0.42 * 2^-24 of its sum and the sums grow like the root of their terms, which makes 0.42 * sqrt((chain + parts) / 2); the
+    weights and base values come with 0.7.  A sixth is left for what the terms of a layer differ."""
+    return 1.16 * np.hypot(0.42 * np.sqrt((chain + parts) / 2), 0.7) * 2.0 ** -24
+
+
 # one form each: 64 samples a workgroup with four and eight tiles, 128; windows of six
 MATRIX_FORMS = [(12001, 37, 97, 12, 3), (16001, 65, 256, 20, 3), (32700, 67, 300, 20, 3), (6801, 104, 161, 14, 5)]
 
@@ -61,3 +68,14 @@ def test_matrix_forward_of_small_values(B, n_in, n_out, G, k):
     rows = np.r_[0:70, B - 70:B]
     got, ref = run_rows(w, rows, "matrix")
     assert rel(got, ref) < 3.5 * 2.0 ** -24
+
+
+def test_matrix_forward_beside_values_that_do_not_split():
+    """The other outputs of a tile with an infinite parameter are summed as accurately as ever."""
+    B, n_in, n_out, G, k = 9001, 400, 100, 12, 3
+    w = workloads.random_kan_layer(5, B, n_in, n_out, G, k)
+    w.params[0]["w_b"][7, 33] = np.inf
+    rows = np.r_[0:70, B - 70:B]
+    got, ref = run_rows(w, rows, "matrix")
+    cols = np.r_[32:33, 34:64]
+    assert rel(got[:, cols], ref[:, cols]) < chain_bound(5 * 32, 13)
