@@ -118,9 +118,9 @@ __global__ __launch_bounds__(32 * NG) void matrix_table_kernel(const float *__re
 // to LDS for the step after; the right operands come from L2 straight into the registers that the instructions read, an
 // instruction's worth ahead (prefetching them into L2 two steps ahead: 580 -> 653 us).  SI inputs a step: eight where a
 // workgroup owns 64 samples, so that every lane has a pair (four, half of them idle: 75 -> 130, B = 6001 43 -> 37 us); 128
-// samples have no room for eight in LDS.  FOLD > 0: the products of the leading parts are folded into a second sum every FOLD steps,
+// samples have no room for eight in LDS.  FOLD: the products of the leading parts are folded into a second sum every other step,
 // as exact as the two-level kernels that this one stands in for; the form with 128 samples, which has no registers for it, only
-// takes layers whose other kernel has one level.
+// takes layers whose other kernel has one level (forward_matrix_plan).
 template <int NG, int SI>
 struct MxArea {                              // left operands of one step of SI inputs in LDS, per sample
     // words of a sample's row of one part: 16-byte reads of eight samples fall into different banks
@@ -176,7 +176,7 @@ __device__ __forceinline__ void pair_operands(int row0, const float (&w)[kMaxK],
     for (int p = 0; p < kMxSplits; ++p) out[p][NG - 1] |= pb[p] & 0xffff0000u;      // (the zero in the low half may carry a sign)
 }
 
-template <int NG, int SI, int MT, int WM, int WN, int FOLD, bool AHEAD>
+template <int NG, int SI, int MT, int WM, int WN, bool FOLD, bool AHEAD>
 __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_matrix_kernel(SplineGeom g, const float *__restrict__ x,
                                                                       const float *__restrict__ cf, const U4 *__restrict__ frag,
                                                                       const int *__restrict__ odd, float *__restrict__ y,
@@ -196,11 +196,11 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
     for (int s = tid; s < S; s += NT) special[s] = 0;
 
     // two sums: the products of the leading parts, and the others, whose roundings are 2^-8 of the former's
-    F16 acc[MT], low[MT], tot[FOLD > 0 ? MT : 1];
+    F16 acc[MT], low[MT], tot[FOLD ? MT : 1];
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { acc[m][r] = low[m][r] = 0.0f; if (FOLD > 0) tot[m][r] = 0.0f; }
+        for (int r = 0; r < 16; ++r) { acc[m][r] = low[m][r] = 0.0f; if (FOLD) tot[m][r] = 0.0f; }
 
     // this lane's pairs of a step: sample e / SI, input e % SI of e = tid + c * NT
     auto load_x = [&](int step, float (&v)[EP]) {
@@ -320,8 +320,8 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
 #pragma unroll
             for (int p = 0; p < kMxSplits; ++p) { bn[0][p][0] = bn[1][p][0]; bn[0][p][1] = bn[1][p][1]; }
         }
-        if constexpr (FOLD > 0) {
-            if ((step + 1) % FOLD == 0) {
+        if constexpr (FOLD) {
+            if (step % 2 != 0) {
 #pragma unroll
                 for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
         again[m] = (unsigned)__ballot(all_odd || special[s0 + (lane & 31)]);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            acc[m][r] = ((FOLD > 0 ? tot[m][r] + acc[m][r] : acc[m][r]) + low[m][r]) * (1.0f / (kMxScale * kMxScale));
+            acc[m][r] = ((FOLD ? tot[m][r] + acc[m][r] : acc[m][r]) + low[m][r]) * (1.0f / (kMxScale * kMxScale));
             const uint64_t past = __ballot(!(fabsf(acc[m][r]) <= FLT_MAX));
             again[m] |= ((unsigned)past ? 1u : 0u) << (8 * (r / 4) + r % 4) | ((past >> 32) ? 1u : 0u) << (8 * (r / 4) + 4 + r % 4);
         }
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
 }
 
 // ---- host -------------------------------------------------------------------------
-template <int NG, int SI, int MT, int WM, int WN, int FOLD, bool AHEAD>
+template <int NG, int SI, int MT, int WM, int WN, bool FOLD, bool AHEAD>
 static hipError_t matrix_launch(const SplineGeom &g, const MatrixTable &t, const float *x, const float *cf, const void *table,
                                 float *y, int64_t B, hipStream_t st)
 {
@@ -436,10 +436,10 @@ static hipError_t matrix_forward(const SplineGeom &g, const MatrixTable &t, int 
     }
     switch (form) {
     case 1:
-        if constexpr (NG < 8) return matrix_launch<NG, 4, 4, 1, 8, 0, false>(g, t, x, cf, table, y, B, st);
+        if constexpr (NG < 8) return matrix_launch<NG, 4, 4, 1, 8, false, false>(g, t, x, cf, table, y, B, st);
         return hipErrorInvalidValue;
-    case 2: return matrix_launch<NG, 8, 2, 1, 8, 2, true>(g, t, x, cf, table, y, B, st);
-    case 3: return matrix_launch<NG, 8, 1, 2, 4, 2, true>(g, t, x, cf, table, y, B, st);
+    case 2: return matrix_launch<NG, 8, 2, 1, 8, true, true>(g, t, x, cf, table, y, B, st);
+    case 3: return matrix_launch<NG, 8, 1, 2, 4, true, true>(g, t, x, cf, table, y, B, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -467,7 +467,10 @@ int forward_matrix_plan(const SplineGeom &g, int64_t B)
                                  {64, 4, 8, 6.3f, 7.5f, {2.32f, 3.19f, 4.48f, 5.7f, 6.9f}}};
     int best = 0;
     float least = 0.0f;
-    for (int f = t.groups >= 8 ? 1 : 0; f < 3; ++f) {            // (from eight groups on the first is never the shortest)
+    // The first form has one level of sums: not where another kernel with two would take the layer (403 -> 164, G = 19, k = 1,
+    // B = 16510: error 3.3e-7, the direct kernel's 2.0e-7).  (From eight groups on it is never the shortest.)
+    const bool one_level = forward_lds_plan(g) != 0 && !forward_direct_plan(g, B);
+    for (int f = t.groups >= 8 || !one_level ? 1 : 0; f < 3; ++f) {
         const Form &o = forms[f];
         const int64_t groups = ((B + o.samples - 1) / o.samples) * ((t.n_tiles + o.tiles - 1) / o.tiles);
         const float steps = (float)((g.n_in + o.inputs - 1) / o.inputs);

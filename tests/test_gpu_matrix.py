@@ -79,3 +79,14 @@ def test_matrix_forward_beside_values_that_do_not_split():
     got, ref = run_rows(w, rows, "matrix")
     cols = np.r_[32:33, 34:64]
     assert rel(got[:, cols], ref[:, cols]) < chain_bound(5 * 32, 13)
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k,family,chain,parts", [
+    (16510, 403, 164, 19, 1, "matrix", 75, 16), (18893, 169, 141, 8, 2, "matrix", 42, 16), (18327, 243, 158, 16, 3, "matrix", 76, 16),
+])
+def test_forward_sums(B, n_in, n_out, G, k, family, chain, parts):
+    """No longer sums than those of the direct kernel, whose sixteen groups of lanes share the inputs."""
+    rows = np.r_[0:100, B - 100:B]
+    got, ref = run_rows(workloads.random_kan_layer(B, B, n_in, n_out, G, k), rows, family)
+    err = rel(got, ref)
+    assert err < chain_bound(chain, parts), err * 2 ** 24
