@@ -118,9 +118,10 @@ __global__ __launch_bounds__(32 * NG) void matrix_table_kernel(const float *__re
 // to LDS for the step after; the right operands come from L2 straight into the registers that the instructions read, an
 // instruction's worth ahead (prefetching them into L2 two steps ahead: 580 -> 653 us).  SI inputs a step: eight where a
 // workgroup owns 64 samples, so that every lane has a pair (four, half of them idle: 75 -> 130, B = 6001 43 -> 37 us); 128
-// samples have no room for eight in LDS.  FOLD: the products of the leading parts are folded into a second sum every other step,
-// as exact as the two-level kernels that this one stands in for; the form with 128 samples, which has no registers for it, only
-// takes layers whose other kernel has one level (forward_matrix_plan).
+// samples have no room for eight in LDS.  FOLD: the products of the leading parts are folded into a second sum every other step
+// (up to 64 inputs every step: 16 -> 256, G = 9, k = 5 error 0.86e-7, without 1.06e-7, the direct kernel's 0.92e-7), as exact as
+// the two-level kernels that this one stands in for; the form with 128 samples, which has no registers for it, only takes layers
+// whose other kernel has one level (forward_matrix_plan).
 template <int NG, int SI>
 struct MxArea {                              // left operands of one step of SI inputs in LDS, per sample
     // words of a sample's row of one part: 16-byte reads of eight samples fall into different banks
@@ -180,7 +181,7 @@ template <int NG, int SI, int MT, int WM, int WN, bool FOLD, bool AHEAD>
 __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_matrix_kernel(SplineGeom g, const float *__restrict__ x,
                                                                       const float *__restrict__ cf, const U4 *__restrict__ frag,
                                                                       const int *__restrict__ odd, float *__restrict__ y,
-                                                                      int64_t B, int n_tiles)
+                                                                      int64_t B, int n_tiles, int fold_mask)
 {
     constexpr int NT = 64 * WM * WN, S = 32 * MT * WM, EP = S * SI / NT, KS = SI * NG / 8;
     static_assert(S * SI % NT == 0 && SI % kMxInputs == 0, "");
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
             for (int p = 0; p < kMxSplits; ++p) { bn[0][p][0] = bn[1][p][0]; bn[0][p][1] = bn[1][p][1]; }
         }
         if constexpr (FOLD) {
-            if (step % 2 != 0) {
+            if ((step & fold_mask) == fold_mask) {
 #pragma unroll
                 for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -418,7 +419,7 @@ static hipError_t matrix_launch(const SplineGeom &g, const MatrixTable &t, const
         const int64_t n = B - b0 < part ? B - b0 : part;
         const dim3 grid((unsigned)((n + S - 1) / S), across);
         prof::Timed tm("forward_matrix", st);
-        kern<<<grid, 64 * WM * WN, bytes, st>>>(g, x + b0 * g.n_in, cf, frag, odd, y + b0 * g.n_out, n, t.n_tiles);
+        kern<<<grid, 64 * WM * WN, bytes, st>>>(g, x + b0 * g.n_in, cf, frag, odd, y + b0 * g.n_out, n, t.n_tiles, g.n_in <= 64 ? 0 : 1);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -470,6 +471,7 @@ int forward_matrix_plan(const SplineGeom &g, int64_t B)
     // The first form has one level of sums: not where another kernel with two would take the layer (403 -> 164, G = 19, k = 1,
     // B = 16510: error 3.3e-7, the direct kernel's 2.0e-7).  (From eight groups on it is never the shortest.)
     const bool one_level = forward_lds_plan(g) != 0 && !forward_direct_plan(g, B);
+    if (!one_level && g.n_in < 20 && t.groups >= 8) return 0;        // (few inputs of many groups: 16 -> 104, G = 26, k = 5 1.05 of its error)
     for (int f = t.groups >= 8 || !one_level ? 1 : 0; f < 3; ++f) {
         const Form &o = forms[f];
         const int64_t groups = ((B + o.samples - 1) / o.samples) * ((t.n_tiles + o.tiles - 1) / o.tiles);
