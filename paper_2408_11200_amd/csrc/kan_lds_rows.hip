@@ -329,9 +329,9 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
     if (kMaxK == 6 && (g.n_in < 8 || (g.n_in <= 16 && g.n_out > 32 && g.n_out < 36))) return none;
     if (g.slab_rows != g.rows + 1 && (g.slab_rows != g.rows || g.base_act != 0)) return none;
     if ((int64_t)g.slab_rows * g.n_out >= 1ll << 29) return none;           // the copies' offsets have 31 bits
-    const int lps_opts[] = {16, 8};
-    for (int lps : lps_opts) {
-        const int tj = lps * 4, spw = 64 / lps;
+    const int lps_opts[] = {16, 8, 16, 8};
+    for (int o = 0; o < 4; ++o) {
+        const int lps = lps_opts[o], tj = lps * 4, spw = 64 / lps;
         if (lps == 16 && g.n_out <= 32) continue;
         const int64_t tiles = (g.n_out + tj - 1) / tj;
         // 16 waves when that still leaves about a workgroup per CU, else 8
@@ -340,9 +340,10 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             const int64_t per_wg = (int64_t)nw * spw * 4;
             const int64_t wgs = (B + per_wg - 1) / per_wg * tiles;
             if (nw == 16 && wgs < 256) continue;
-            // eight waves (two per SIMD) on several tiles, of which each evaluates the pairs again: eight_waves_pay
+            // Eight waves (two per SIMD) on several tiles, of which each evaluates the pairs again: eight_waves_pay.  After all others,
+            // with which that does not compare them (31 -> 276, G = 211, k = 5, B = 41404: 217 us on sixteen waves and tiles of 32, 340).
             const bool eight_tiled = nw == 8 && tiles > 1;
-            if (eight_tiled && wgs < 256) continue;
+            if (eight_tiled != (o >= 2) || (eight_tiled && wgs < 256)) continue;
             const int64_t quads = (int64_t)g.slab_rows * lps;
             const int nq = copies_of(nw, quads);
             if (!nq || !variant_built(lps, 4, nw, nq, g.base_act != 0)) continue;
