@@ -46,11 +46,13 @@ constexpr int kPairFloats = kMaxK == 4 ? 8 : 12;
 }  // namespace
 
 // A workgroup per (NW * SPW * S samples, TJ outputs), NW waves.  Needs rows >= kMaxK, n_out >= 4, for S = 8 four inputs.
-// BASE: the table has slab_rows = rows + 1 rows per input, the last one the w_b row.  P (a power of two up to IPV): inputs a step.
+// BASE: the table has slab_rows = rows + 1 rows per input, the last one the w_b row.  P (a power of two up to IPV): inputs a step;
+// the sums are folded every `fold` inputs (a power of two).
 template <int LPS, int S, int NW, int NQ, bool BASE>
 __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g, const float *__restrict__ x,
                                                                    const float *__restrict__ cf,
-                                                                   float *__restrict__ y, int64_t B, int P, int n_tiles)
+                                                                   float *__restrict__ y, int64_t B, int P, int fold,
+                                                                   int n_tiles)
 {
     constexpr int TJ = LPS * 4, SPW = 64 / LPS, NT = 64 * NW;
     constexpr int SMP = SPW * S;                        // samples per wave
@@ -72,9 +74,8 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
     const int j = j0 + lj * 4;
     float *pairs = lds + 2 * slab_floats + wave * (64 * kPairFloats);
 
-    // two-level sum over the inputs (acc is folded into tot every 32 inputs): keeps the rounding error
-    // of a sum over hundreds of inputs inside the forward tolerance
-    constexpr int kFoldInputs = 32;
+    // two-level sum over the inputs (acc is folded into tot every 32 inputs, or more often where the plan says so): keeps the
+    // rounding error of a sum over hundreds of inputs inside the forward tolerance
     float acc[S][4], tot[S][4];
 #pragma unroll
     for (int q = 0; q < S; ++q)
@@ -174,7 +175,7 @@ __global__ __launch_bounds__(64 * NW) void forward_lds_rows_kernel(SplineGeom g,
     auto compute = [&](int t) {
         const int i0 = t * P;
         const float *cur = lds + (t & 1) * slab_floats;
-        if (i0 % kFoldInputs == 0) {
+        if ((i0 & (fold - 1)) == 0) {
 #pragma unroll
             for (int q = 0; q < S; ++q)
 #pragma unroll
@@ -282,7 +283,7 @@ namespace {
 
 constexpr size_t kLdsBudget = 160 * 1024;
 
-struct RowsPlan { int lps, slots, nw, nq, inputs; };
+struct RowsPlan { int lps, slots, nw, nq, inputs, fold; };
 
 // copies a thread makes of a step's slabs: what the kernel is built for, 0 if that is too few
 int copies_of(int nw, int64_t quads)
@@ -320,7 +321,7 @@ bool eight_waves_pay(int64_t wgs, int a_cu, int64_t quads, int64_t padded_edges)
 // tile width, samples a group, workgroup size, copy depth and inputs a step for a layer (lps == 0: not applicable)
 RowsPlan plan_of(const SplineGeom &g, int64_t B)
 {
-    RowsPlan none = {0, 0, 0, 0, 0};
+    RowsPlan none = {0, 0, 0, 0, 0, 0};
     if (g.rows < kMaxK || g.n_out < 32) return none;
     // Windows of six: layers of fewer than eight inputs, and of up to 16 with 33 .. 35 outputs, are left to the generic and the
     // row-stream kernel.  Not for speed: this one is the faster there, past short batches (us, k = 4, G = 30, as it is / here: 2 -> 32
@@ -352,7 +353,9 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             if (eight_tiled ? !eight_waves_pay(wgs, workgroups_a_cu(nw, nq), quads, B * ((g.n_out + 63) / 64 * 64))
                             : per_wg * kMaxK < 4 * (int64_t)g.slab_rows)
                 continue;
-            RowsPlan p = {lps, 4, nw, nq, 1};
+            // sums as short as those of the direct kernel, whose sixteen lane groups share the inputs and which eight waves mostly
+            // stand in for (25 -> 83, G = 5, B = 19696: its error 0.95e-7, folded every 32 inputs 1.9e-7, this way 0.93e-7)
+            RowsPlan p = {lps, 4, nw, nq, 1, !eight_tiled ? 32 : g.n_in < 16 ? 1 : g.n_in < 40 ? 2 : g.n_in < 160 ? 4 : 8};
             // Eight samples a group halve the copies a sample (256 -> 256, 180 rows, B = 32768: 608 us, with four 756).  A CU
             // works through its workgroups in rounds of 256; a step of four samples a group takes about 2200 clocks beside
             // the copies, which go at 64 bytes a clock.
@@ -381,7 +384,7 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
 }
 
 template <int LPS, int S, int NW, int NQ, bool BASE>
-hipError_t launch_variant(const SplineGeom &g, const float *x, const float *cf, float *y, int64_t B, int inputs, hipStream_t st)
+hipError_t launch_variant(const SplineGeom &g, const float *x, const float *cf, float *y, int64_t B, const RowsPlan &p, hipStream_t st)
 {
     constexpr int SPW = 64 / LPS;
     const size_t lds = lds_bytes(NW, NQ);
@@ -393,7 +396,7 @@ hipError_t launch_variant(const SplineGeom &g, const float *x, const float *cf, 
     const int64_t wgs = (B + per_wg - 1) / per_wg * n_tiles;
     if ((wgs + 7) * (64 * NW) >= (1ll << 32)) return hipErrorInvalidValue;      // a launch takes fewer threads (512 GiB of x and y)
     prof::Timed tm("forward_lds_rows", st);
-    kern<<<(unsigned)((wgs + 7) / 8 * 8), 64 * NW, lds, st>>>(g, x, cf, y, B, inputs, (int)n_tiles);
+    kern<<<(unsigned)((wgs + 7) / 8 * 8), 64 * NW, lds, st>>>(g, x, cf, y, B, p.inputs, p.fold, (int)n_tiles);
     return hipGetLastError();
 }
 
@@ -404,7 +407,7 @@ hipError_t launch_by_quads(const RowsPlan &p, const SplineGeom &g, const float *
     auto with = [&](auto n, auto base) {
         constexpr int NQ = decltype(n)::value;
         constexpr bool BASE = decltype(base)::value;
-        if constexpr (variant_built(LPS, S, NW, NQ, BASE)) return launch_variant<LPS, S, NW, NQ, BASE>(g, x, cf, y, B, p.inputs, st);
+        if constexpr (variant_built(LPS, S, NW, NQ, BASE)) return launch_variant<LPS, S, NW, NQ, BASE>(g, x, cf, y, B, p, st);
         else return hipErrorInvalidValue;
     };
     auto by_base = [&](auto n) { return g.base_act != 0 ? with(n, std::true_type{}) : with(n, std::false_type{}); };

@@ -84,6 +84,8 @@ def test_matrix_forward_beside_values_that_do_not_split():
 @pytest.mark.parametrize("B,n_in,n_out,G,k,family,chain,parts", [
     (16510, 403, 164, 19, 1, "matrix", 75, 16), (18893, 169, 141, 8, 2, "matrix", 42, 16), (18327, 243, 158, 16, 3, "matrix", 76, 16),
     (5074, 23, 332, 36, 5, "matrix", 10, 16), (8161, 16, 256, 9, 5, "matrix", 7, 16), (8245, 32, 128, 8, 5, "matrix", 14, 16),
+    (19696, 25, 83, 5, 3, "lds_rows", 8, 16), (30106, 43, 93, 32, 3, "lds_rows", 14, 16), (26437, 74, 85, 80, 3, "lds_rows", 24, 16),
+    (22677, 64, 128, 134, 5, "lds_rows", 28, 16), (21483, 238, 105, 62, 1, "lds_rows", 45, 16),
 ])
 def test_forward_sums(B, n_in, n_out, G, k, family, chain, parts):
     """No longer sums than those of the direct kernel, whose sixteen groups of lanes share the inputs."""
