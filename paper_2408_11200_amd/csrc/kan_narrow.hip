@@ -12,7 +12,7 @@ namespace kan {
 // Q lanes per sample (four, or sixteen): lane q of the group takes inputs q, q + Q, ... and the partial sums are
 // added across the group at the end (with one thread per sample a batch of a few ten thousand leaves
 // most of the chip idle).
-template <int NO, int Q>
+template <int NO, int Q>                         // Q = 16: NO = 1
 __global__ __launch_bounds__(256) void forward_narrow_kernel(SplineGeom g, const float *__restrict__ x,
                                                              const float *__restrict__ cf,
                                                              const float *__restrict__ w_b, float *__restrict__ y,
@@ -25,6 +25,8 @@ __global__ __launch_bounds__(256) void forward_narrow_kernel(SplineGeom g, const
     float acc[NO];
 #pragma unroll
     for (int j = 0; j < NO; ++j) acc[j] = 0.0f;
+    float tot = 0.0f;                            // sixteen lanes: folded every eight inputs, as the direct kernel's sums are short
+    int n = 0;
     for (int i = q; i < g.n_in; i += Q) {
         Pair p = pair_basis<false>(x[bc * g.n_in + i], g, i);
         const float *slab = cf + (int64_t)i * g.slab_rows * g.n_out;
@@ -49,7 +51,9 @@ __global__ __launch_bounds__(256) void forward_narrow_kernel(SplineGeom g, const
             for (int j = 0; j < NO; ++j)
                 if (j < g.n_out) acc[j] = fmaf(p.base, wb[j], acc[j]);
         }
+        if (Q == 16 && ++n == 8) { tot += acc[0]; acc[0] = 0.0f; n = 0; }
     }
+    if (Q == 16) acc[0] += tot;
 #pragma unroll
     for (int j = 0; j < NO; ++j) {
         float v = acc[j];

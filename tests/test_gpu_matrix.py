@@ -86,9 +86,10 @@ def test_matrix_forward_beside_values_that_do_not_split():
     (5074, 23, 332, 36, 5, "matrix", 10, 16), (8161, 16, 256, 9, 5, "matrix", 7, 16), (8245, 32, 128, 8, 5, "matrix", 14, 16),
     (19696, 25, 83, 5, 3, "lds_rows", 8, 16), (30106, 43, 93, 32, 3, "lds_rows", 14, 16), (26437, 74, 85, 80, 3, "lds_rows", 24, 16),
     (22677, 64, 128, 134, 5, "lds_rows", 28, 16), (21483, 238, 105, 62, 1, "lds_rows", 45, 16),
+    (2422, 700, 1, 20, 3, "narrow", 55, 64),
 ])
 def test_forward_sums(B, n_in, n_out, G, k, family, chain, parts):
-    """No longer sums than those of the direct kernel, whose sixteen groups of lanes share the inputs."""
+    """No longer sums than those of the direct kernel, whose groups of lanes, sixteen or 64, share the inputs."""
     rows = np.r_[0:100, B - 100:B]
     got, ref = run_rows(workloads.random_kan_layer(B, B, n_in, n_out, G, k), rows, family)
     err = rel(got, ref)
