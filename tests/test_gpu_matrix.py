@@ -87,6 +87,7 @@ def test_matrix_forward_beside_values_that_do_not_split():
     (19696, 25, 83, 5, 3, "lds_rows", 8, 16), (30106, 43, 93, 32, 3, "lds_rows", 14, 16), (26437, 74, 85, 80, 3, "lds_rows", 24, 16),
     (22677, 64, 128, 134, 5, "lds_rows", 28, 16), (21483, 238, 105, 62, 1, "lds_rows", 45, 16),
     (2422, 700, 1, 20, 3, "narrow", 55, 64),
+    (60000, 64, 16, 20, 3, "direct", 5, 15),            # 64 groups, eight in pairs and the eights in a row: three levels and 8 / 2 of them
 ])
 def test_forward_sums(B, n_in, n_out, G, k, family, chain, parts):
     """No longer sums than those of the direct kernel, whose groups of lanes, sixteen or 64, share the inputs."""
