@@ -13,7 +13,8 @@
  *     and keeps no state between calls (the two exceptions, the launch observer
  *     and the built-in array of kan_forward_static, say so where they are
  *     declared); scratch space comes in through (ws, ws_bytes) and must be at
- *     least what the matching *_workspace_bytes call returns (256-byte aligned).
+ *     least what the matching *_workspace_bytes call returns (256-byte aligned;
+ *     kan_forward: see kan_workspace_bytes).
  *   - `stream` is a hipStream_t passed as void*.  All work is enqueued on it.
  *     kan_* calls never synchronise; ukan_cg_forward, ukan_cg_backward and
  *     ukan_cg_forward_saved synchronise the stream once to read back the group
@@ -95,7 +96,10 @@ typedef struct ukan_grads {
 const char *kan_strerror(int status);
 
 /* Scratch bytes needed by kan_forward (pass = KAN_PASS_FORWARD) or kan_backward for batch B.
-   Returns 0 for an invalid descriptor.  Forward: the scale-folded table.  Backward, on top of that:
+   Returns 0 for an invalid descriptor.  Forward: the scale-folded table (n_in * (G + k + 1) * n_out floats, rounded up to 256
+   bytes; kan_forward takes a workspace of that size for every B) and, for the batches of wide layers on short tables that the
+   matrix-core kernel takes, that table once more in split form (1.5 to 10 times its size): a workspace without room for it
+   gets another kernel and the same result to rounding.  Backward, on top of the folded table:
    - ordinarily the transposed input, two sorted record arrays (44 bytes per (sample, input) pair, 88 for degrees 4 and 5)
      and the per-chunk partial gradient tables: a small multiple of B * n_in * 48 bytes + at most 2 GiB of partial tables
      (more only when a single table exceeds that).  Widths that are no multiple of four need as much as the others
@@ -125,8 +129,8 @@ int kan_backward(const kan_layer_desc *desc, int64_t B, const float *x, const fl
                  float *gw_s, float *gw_b, void *ws, size_t ws_bytes, void *stream);
 
 /* kan_backward for a training step that has just run kan_forward on the same layer: forward_ws is the
-   workspace that kan_forward call was given (it holds the scale-folded table, the first
-   kan_workspace_bytes(desc, B, KAN_PASS_FORWARD) bytes), untouched since, with coef, w_s and w_b unchanged;
+   workspace that kan_forward call was given (its first n_in * (G + k + 1) * n_out floats are the scale-folded table),
+   these untouched since, with coef, w_s and w_b unchanged;
    the backward pass then reads the table from there instead of folding it again.  forward_ws must not be
    the same buffer as ws (KAN_ERR_INVALID_ARG); NULL or misaligned gives KAN_ERR_WORKSPACE.  The library
    cannot check that the table is current.  Results are bit-identical to kan_backward. */

@@ -73,10 +73,14 @@ size_t folded_bytes(const kan_layer_desc *d)
     return align_up((size_t)d->n_in * (size_t)(d->G + d->k + 1) * (size_t)d->n_out * sizeof(float));
 }
 
-// the split table of the matrix-core forward kernel, behind the folded one (0: the shape does not qualify)
-size_t matrix_bytes(const kan_layer_desc *d)
+// The split table of the matrix-core forward kernel, behind the folded one; 0: another kernel takes this call.  (Below 2^18 outputs
+// the kernel's fixed costs and steps are hardly ever made up for, and a small call is spared the estimate.)
+size_t matrix_bytes(const kan_layer_desc *d, int64_t B)
 {
-    return matrix_table(d->n_in, d->n_out, d->G + d->k, high_degree(d) ? 6 : kMaxK).bytes;
+    if (B * d->n_out < 1 << 18) return 0;
+    const size_t bytes = matrix_table(d->n_in, d->n_out, d->G + d->k, high_degree(d) ? 6 : kMaxK).bytes;
+    if (!bytes || !(high_degree(d) ? highk_matrix_plan(highk_of(d), B) : forward_matrix_plan(geom_of(d), B))) return 0;
+    return bytes;
 }
 
 size_t edge_bytes(const kan_layer_desc *d)
@@ -163,7 +167,7 @@ extern "C" const char *kan_strerror(int status)
 extern "C" size_t kan_workspace_bytes(const kan_layer_desc *desc, int64_t B, int pass)
 {
     if (check_desc(desc) != KAN_OK || B < 0) return 0;
-    if (pass == KAN_PASS_FORWARD) return folded_bytes(desc) + matrix_bytes(desc);
+    if (pass == KAN_PASS_FORWARD) return folded_bytes(desc) + matrix_bytes(desc, B);
     if (pass != KAN_PASS_BACKWARD) return 0;
     const BackwardPlan bp = backward_plan(desc, B);
     return folded_bytes(desc) + bp.rec_bytes + (size_t)bp.n_slabs * folded_bytes(desc) + bp.tail_bytes +
@@ -172,10 +176,10 @@ extern "C" size_t kan_workspace_bytes(const kan_layer_desc *desc, int64_t B, int
 
 // Forward pass with the scratch space given explicitly; shared by kan_forward and kan_forward_static.
 // keep_table: the caller may hand the workspace to kan_backward_saved, so the folded table must be in it.
-// need: bytes without which the call is refused; the matrix-core kernel runs where its table fits as well.
+// A workspace that holds the folded table is enough; the matrix-core kernel runs where its table fits as well.
 static int forward_impl(const kan_layer_desc *desc, int64_t B, const float *x, const float *coef,
                         const float *w_s, const float *w_b, float *y, void *ws, size_t ws_bytes,
-                        void *stream, bool keep_table, size_t need)
+                        void *stream, bool keep_table)
 {
     int rc = check_desc(desc);
     if (rc != KAN_OK) return rc;
@@ -184,15 +188,13 @@ static int forward_impl(const kan_layer_desc *desc, int64_t B, const float *x, c
     if (!x || !coef || !w_s || !y) return KAN_ERR_INVALID_ARG;
     if (desc->base_act != KAN_BASE_NONE && !w_b) return KAN_ERR_INVALID_ARG;
     if (misaligned(x) || misaligned(coef) || misaligned(w_s) || misaligned(w_b) || misaligned(y)) return KAN_ERR_INVALID_ARG;
-    if (!ws || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < need) return KAN_ERR_WORKSPACE;
+    if (!ws || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < folded_bytes(desc)) return KAN_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     SplineGeom g = geom_of(desc);
     float *cf = (float *)ws;
-    // (fewer edges an input never pay for the matrix-core kernel's steps: a small call is spared the estimate)
-    const size_t split = B * desc->n_out >= 1 << 18 ? matrix_bytes(desc) : 0;
+    const size_t split = matrix_bytes(desc, B);
     void *table = (char *)ws + folded_bytes(desc);
-    if (split && ws_bytes >= folded_bytes(desc) + split &&
-        (high_degree(desc) ? highk_matrix_plan(highk_of(desc), B) : forward_matrix_plan(g, B))) {
+    if (split && ws_bytes >= folded_bytes(desc) + split) {
         const float *wb = g.base_act ? w_b : nullptr;
         const hipError_t e = high_degree(desc) ? highk_matrix_forward(highk_of(desc), x, coef, w_s, wb, cf, table, y, B, st)
                                                : launch_forward_matrix(g, x, coef, w_s, wb, cf, table, y, B, st);
@@ -217,7 +219,7 @@ extern "C" int kan_forward(const kan_layer_desc *desc, int64_t B, const float *x
                            const float *w_s, const float *w_b, float *y, void *ws, size_t ws_bytes,
                            void *stream)
 {
-    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, ws_bytes, stream, true, kan_workspace_bytes(desc, B, KAN_PASS_FORWARD));
+    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, ws_bytes, stream, true);
 }
 
 // ---- forward pass for callers that cannot allocate -------------------------------------------
@@ -259,7 +261,7 @@ extern "C" int kan_forward_static(const kan_layer_desc *desc, int64_t B, const f
     if (folded_bytes(desc) > (size_t)KAN_STATIC_SCRATCH_BYTES) return KAN_ERR_WORKSPACE;
     void *ws = static_scratch();
     if (!ws) return KAN_ERR_HIP;
-    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, KAN_STATIC_SCRATCH_BYTES, stream, false, folded_bytes(desc));
+    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, KAN_STATIC_SCRATCH_BYTES, stream, false);
 }
 
 // Backward pass; `folded` (may be null) is the scale-folded table a forward pass left in its workspace.
