@@ -145,8 +145,8 @@ int kan_backward_saved(const kan_layer_desc *desc, int64_t B, const float *x, co
    no (ws, ws_bytes) to provide and the call allocates nothing.  Each GPU holds its own copy of the array
    from the first call on it until the process ends.  Returns KAN_ERR_WORKSPACE when the scale-folded table
    (n_in * (G + k + 1) * n_out floats) exceeds KAN_STATIC_SCRATCH_BYTES (y is not written), KAN_ERR_HIP when the
-   array's address cannot be obtained.  Where that table fits but kan_workspace_bytes(desc, B, KAN_PASS_FORWARD)
-   does not, another kernel runs than kan_forward's and results agree to rounding instead of bit for bit.  All calls on one GPU share the array: calls that
+   array's address cannot be obtained.  Results are bit-identical to kan_forward's in a workspace of
+   kan_workspace_bytes.  All calls on one GPU share the array: calls that
    may overlap in time on the same GPU (different streams or threads) race on it; calls on one stream do not.
    kan_static_scratch_bytes() returns the limit. */
 #define KAN_STATIC_SCRATCH_BYTES (32u << 20)

@@ -176,7 +176,8 @@ extern "C" size_t kan_workspace_bytes(const kan_layer_desc *desc, int64_t B, int
 
 // Forward pass with the scratch space given explicitly; shared by kan_forward and kan_forward_static.
 // keep_table: the caller may hand the workspace to kan_backward_saved, so the folded table must be in it.
-// A workspace that holds the folded table is enough; the matrix-core kernel runs where its table fits as well.
+// A workspace that holds the folded table is enough; the matrix-core kernel runs where its table fits as well.  With no folded table to
+// keep the whole workspace is that kernel's: it takes every call there that has it in kan_forward, in rounds if need be.
 static int forward_impl(const kan_layer_desc *desc, int64_t B, const float *x, const float *coef,
                         const float *w_s, const float *w_b, float *y, void *ws, size_t ws_bytes,
                         void *stream, bool keep_table)
@@ -193,11 +194,13 @@ static int forward_impl(const kan_layer_desc *desc, int64_t B, const float *x, c
     SplineGeom g = geom_of(desc);
     float *cf = (float *)ws;
     const size_t split = matrix_bytes(desc, B);
-    void *table = (char *)ws + folded_bytes(desc);
-    if (split && ws_bytes >= folded_bytes(desc) + split) {
+    const size_t kept = keep_table ? folded_bytes(desc) : 0;
+    if (split && (!keep_table || ws_bytes >= kept + split)) {
         const float *wb = g.base_act ? w_b : nullptr;
-        const hipError_t e = high_degree(desc) ? highk_matrix_forward(highk_of(desc), x, coef, w_s, wb, cf, table, y, B, st)
-                                               : launch_forward_matrix(g, x, coef, w_s, wb, cf, table, y, B, st);
+        float *folded = keep_table ? cf : nullptr;
+        void *table = (char *)ws + kept;
+        const hipError_t e = high_degree(desc) ? highk_matrix_forward(highk_of(desc), x, coef, w_s, wb, folded, table, ws_bytes - kept, y, B, st)
+                                               : launch_forward_matrix(g, x, coef, w_s, wb, folded, table, ws_bytes - kept, y, B, st);
         return e == hipSuccess ? KAN_OK : KAN_ERR_HIP;
     }
     if (high_degree(desc))
@@ -228,6 +231,7 @@ extern "C" int kan_forward(const kan_layer_desc *desc, int64_t B, const float *x
 // its own, found once per device with hipGetSymbolAddress.  In host code the array's name is only
 // a handle for that query, never a device address.
 static __device__ __align__(256) unsigned char scratch[KAN_STATIC_SCRATCH_BYTES];
+static_assert(kMxScratch <= KAN_STATIC_SCRATCH_BYTES, "kan_forward_static takes the kernels that kan_forward takes");
 
 namespace {
 constexpr int kMaxDevices = 64;

@@ -62,9 +62,9 @@ hipError_t highk_forward(const HighKLayer &l, const float *x, const float *coef,
 int highk_matrix_plan(const HighKLayer &l, int64_t B) { return kan_k5::forward_matrix_plan(geom_of(l), B); }
 
 hipError_t highk_matrix_forward(const HighKLayer &l, const float *x, const float *coef, const float *w_s, const float *w_b,
-                                float *cf, void *table, float *y, int64_t B, hipStream_t st)
+                                float *cf, void *table, size_t table_bytes, float *y, int64_t B, hipStream_t st)
 {
-    return kan_k5::launch_forward_matrix(geom_of(l), x, coef, w_s, w_b, cf, table, y, B, st);
+    return kan_k5::launch_forward_matrix(geom_of(l), x, coef, w_s, w_b, cf, table, table_bytes, y, B, st);
 }
 
 hipError_t highk_backward(const HighKLayer &l, const float *x, const float *coef, const float *w_s, const float *w_b,

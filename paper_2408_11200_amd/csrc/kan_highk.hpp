@@ -20,10 +20,10 @@ int highk_row_blocks(int rows);     // base-term partial slices per chunk
 // y = layer(x); cf: scratch for the scale-folded table ((rows + 1) rows per input); keep_table: it must be filled
 hipError_t highk_forward(const HighKLayer &l, const float *x, const float *coef, const float *w_s, const float *w_b,
                          float *cf, float *y, int64_t B, bool keep_table, hipStream_t st);
-// the matrix-core forward (kan_matrix_k5.hip): 0: another kernel is the better choice; table: the split table's scratch
+// the matrix-core forward (kan_matrix_k5.hip): 0: another kernel is the better choice; cf may be null
 int highk_matrix_plan(const HighKLayer &l, int64_t B);
 hipError_t highk_matrix_forward(const HighKLayer &l, const float *x, const float *coef, const float *w_s, const float *w_b,
-                                float *cf, void *table, float *y, int64_t B, hipStream_t st);
+                                float *cf, void *table, size_t table_bytes, float *y, int64_t B, hipStream_t st);
 // any of gx / (gcoef, gw_s, gw_b) may be null; part_c: n_chunks tables of rows rows, part_b: n_chunks *
 // highk_row_blocks(rows) edge slices
 hipError_t highk_backward(const HighKLayer &l, const float *x, const float *coef, const float *w_s, const float *w_b,

@@ -57,10 +57,10 @@ hipError_t launch_forward_direct(const SplineGeom &g, const float *x, const floa
                                  const float *w_b, float *cf, float *y, int64_t B, hipStream_t st);
 
 // short tables: sparse matrix instructions on floats split in three (kan_matrix.hip).  The plan returns 0 when another kernel is
-// the better choice; table: MatrixTable::bytes of scratch; cf receives the scale-folded table
+// the better choice; table: scratch for the split table, at least a tile's; cf (may be null) receives the scale-folded table
 int forward_matrix_plan(const SplineGeom &g, int64_t B);
 hipError_t launch_forward_matrix(const SplineGeom &g, const float *x, const float *coef, const float *w_s, const float *w_b,
-                                 float *cf, void *table, float *y, int64_t B, hipStream_t st);
+                                 float *cf, void *table, size_t table_bytes, float *y, int64_t B, hipStream_t st);
 
 // generic (any shape) kernels
 hipError_t launch_forward_generic(const SplineGeom &g, const float *x, const float *cf, const float *w_b,

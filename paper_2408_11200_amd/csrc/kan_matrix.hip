@@ -68,15 +68,16 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned (&p)[kMxSp
 // One workgroup per (step of four inputs, tile of 32 outputs), lane l of wave t <-> lane l of instruction t: column l % 32 and four
 // of the instruction's eight groups, whose left operands are spread over both halves of the wave: with h = l / 32 groups
 // 2 h, 2 h + 1, 4 + 2 h, 5 + 2 h, four table rows each.  Writes cf as fold_scale_kernel does and the operands
-// of the forward kernel; rows past the table and columns past the layer are zero.
+// of the forward kernel; rows past the table and columns past the layer are zero.  The first tile begins at output j0; cf: null
+// if no folded table is wanted.
 template <int NG>
 __global__ __launch_bounds__(32 * NG) void matrix_table_kernel(const float *__restrict__ coef, const float *__restrict__ w_s,
                                                                const float *__restrict__ w_b, float *__restrict__ cf,
                                                                U4 *__restrict__ frag, int *__restrict__ odd, int n_in, int rows,
-                                                               int n_out)
+                                                               int n_out, int j0)
 {
     const int lane = threadIdx.x & 63, t = threadIdx.x >> 6, step = blockIdx.x, tile = blockIdx.y;
-    const int j = tile * kMxTile + (lane & 31), half = lane >> 5;
+    const int j = j0 + tile * kMxTile + (lane & 31), half = lane >> 5;
     float v[16];
     bool bad = false;
 #pragma unroll
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(32 * NG) void matrix_table_kernel(const float *__re
             if (ok && (base || row < rows)) {
                 if (!base) c = coef[((int64_t)i * rows + row) * n_out + j] * s;
                 else if (w_b) c = w_b[(int64_t)i * n_out + j];
-                cf[((int64_t)i * (rows + 1) + (base ? rows : row)) * n_out + j] = c;
+                if (cf) cf[((int64_t)i * (rows + 1) + (base ? rows : row)) * n_out + j] = c;
             }
             const bool fits = fabsf(c) < kMxLargest;
             bad |= !fits;
@@ -179,9 +180,10 @@ __device__ __forceinline__ void pair_operands(int row0, const float (&w)[kMaxK],
 
 template <int NG, int SI, int MT, int WM, int WN, bool FOLD, bool AHEAD>
 __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_matrix_kernel(SplineGeom g, const float *__restrict__ x,
-                                                                      const float *__restrict__ cf, const U4 *__restrict__ frag,
+                                                                      const float *__restrict__ coef, const float *__restrict__ w_s,
+                                                                      const float *__restrict__ w_b, const U4 *__restrict__ frag,
                                                                       const int *__restrict__ odd, float *__restrict__ y,
-                                                                      int64_t B, int n_tiles, int fold_mask)
+                                                                      int64_t B, int n_tiles, int j0, int fold_mask)
 {
     constexpr int NT = 64 * WM * WN, S = 32 * MT * WM, EP = S * SI / NT, KS = SI * NG / 8;
     static_assert(S * SI % NT == 0 && SI % kMxInputs == 0, "");
@@ -349,7 +351,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
     }
 
     if (tile >= n_tiles) return;
-    const int j = tile * kMxTile + (lane & 31);
+    const int j = j0 + tile * kMxTile + (lane & 31);
     int flag = 0;
     for (int s = lane; s < n_parts; s += 64) flag |= odd[(int64_t)tile * n_parts + s];
     const bool all_odd = __any(flag != 0);
@@ -386,14 +388,15 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
         int n = 0;
         for (int i = lane >> 5; i < g.n_in; i += 2) {
             const Pair p = pair_basis<false>(x[b * g.n_in + i], g, i);
-            const float *slab = cf + (int64_t)i * g.slab_rows * g.n_out + jc;
+            const float *slab = coef + (int64_t)i * g.rows * g.n_out + jc;
+            const float scale = w_s[(int64_t)i * g.n_out + jc];
 #pragma unroll
             for (int k = 0; k < kMaxK; ++k) {
                 const int m = p.cell + k;                // rows that are not there take no part, whatever stands beside them
-                const float c = slab[(int64_t)clampi(m, 0, g.rows - 1) * g.n_out];
+                const float c = slab[(int64_t)clampi(m, 0, g.rows - 1) * g.n_out] * scale;
                 part = k <= g.k && m >= 0 && m < g.rows ? fmaf(p.w[k], c, part) : part;
             }
-            part = fmaf(p.base, slab[(int64_t)g.rows * g.n_out], part);
+            if (w_b) part = fmaf(p.base, w_b[(int64_t)i * g.n_out + jc], part);
             if (++n == 8) { sum += part; part = 0.0f; n = 0; }
         }
         sum += part;
@@ -403,44 +406,50 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
 }
 
 // ---- host -------------------------------------------------------------------------
+struct MatrixArgs {
+    const float *x, *coef, *w_s, *w_b;
+    float *cf, *y;
+    void *table;
+    int64_t B;
+    int n_tiles, j0;           // tiles of this round, and its first output
+};
+
 template <int NG, int SI, int MT, int WM, int WN, bool FOLD, bool AHEAD>
-static hipError_t matrix_launch(const SplineGeom &g, const MatrixTable &t, const float *x, const float *cf, const void *table,
-                                float *y, int64_t B, hipStream_t st)
+static hipError_t matrix_launch(const SplineGeom &g, const MatrixTable &t, const MatrixArgs &a, hipStream_t st)
 {
     constexpr int S = 32 * MT * WM, bytes = (2 * MxArea<NG, SI>::template words<S>() + S) * 4;
     struct Tag {};
     auto kern = forward_matrix_kernel<NG, SI, MT, WM, WN, FOLD, AHEAD>;
     if (hipError_t e = ensure_dynamic_lds<Tag>((const void *)kern, bytes); e != hipSuccess) return e;
-    const U4 *frag = (const U4 *)table;
-    const int *odd = (const int *)((const char *)table + t.frag_bytes);
-    const unsigned across = (unsigned)((t.n_tiles + WN - 1) / WN);
+    const int *odd = (const int *)((const char *)a.table + a.n_tiles * t.tile_bytes);
+    const unsigned across = (unsigned)((a.n_tiles + WN - 1) / WN);
     const int64_t part = (int64_t)S * ((1 << 22) / across);       // samples of one launch: fewer than 2^32 threads
-    for (int64_t b0 = 0; b0 < B; b0 += part) {
-        const int64_t n = B - b0 < part ? B - b0 : part;
+    for (int64_t b0 = 0; b0 < a.B; b0 += part) {
+        const int64_t n = a.B - b0 < part ? a.B - b0 : part;
         const dim3 grid((unsigned)((n + S - 1) / S), across);
         prof::Timed tm("forward_matrix", st);
-        kern<<<grid, 64 * WM * WN, bytes, st>>>(g, x + b0 * g.n_in, cf, frag, odd, y + b0 * g.n_out, n, t.n_tiles, g.n_in <= 64 ? 0 : 1);
+        kern<<<grid, 64 * WM * WN, bytes, st>>>(g, a.x + b0 * g.n_in, a.coef, a.w_s, a.w_b, (const U4 *)a.table, odd, a.y + b0 * g.n_out,
+                                                n, a.n_tiles, a.j0, g.n_in <= 64 ? 0 : 1);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
 template <int NG>
-static hipError_t matrix_forward(const SplineGeom &g, const MatrixTable &t, int form, const float *x, const float *coef,
-                                 const float *w_s, const float *w_b, float *cf, void *table, float *y, int64_t B, hipStream_t st)
+static hipError_t matrix_forward(const SplineGeom &g, const MatrixTable &t, int form, const MatrixArgs &a, hipStream_t st)
 {
     {
         prof::Timed tm("matrix_table", st);
-        matrix_table_kernel<NG><<<dim3((unsigned)t.n_steps, (unsigned)t.n_tiles), 32 * NG, 0, st>>>(
-            coef, w_s, w_b, cf, (U4 *)table, (int *)((char *)table + t.frag_bytes), g.n_in, g.rows, g.n_out);
+        matrix_table_kernel<NG><<<dim3((unsigned)t.n_steps, (unsigned)a.n_tiles), 32 * NG, 0, st>>>(
+            a.coef, a.w_s, a.w_b, a.cf, (U4 *)a.table, (int *)((char *)a.table + a.n_tiles * t.tile_bytes), g.n_in, g.rows, g.n_out, a.j0);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
     switch (form) {
     case 1:
-        if constexpr (NG < 8) return matrix_launch<NG, 4, 4, 1, 8, false, false>(g, t, x, cf, table, y, B, st);
+        if constexpr (NG < 8) return matrix_launch<NG, 4, 4, 1, 8, false, false>(g, t, a, st);
         return hipErrorInvalidValue;
-    case 2: return matrix_launch<NG, 8, 2, 1, 8, true, true>(g, t, x, cf, table, y, B, st);
-    case 3: return matrix_launch<NG, 8, 1, 2, 4, true, true>(g, t, x, cf, table, y, B, st);
+    case 2: return matrix_launch<NG, 8, 2, 1, 8, true, true>(g, t, a, st);
+    case 3: return matrix_launch<NG, 8, 1, 2, 4, true, true>(g, t, a, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -498,21 +507,34 @@ int forward_matrix_plan(const SplineGeom &g, int64_t B)
     return least < 0.9f * (kMaxK == 6 ? 1.3f : 1.0f) * other ? best : 0;
 }
 
+// A table that does not fit is made and used a range of outputs at a time, the same sums in the same order.
 hipError_t launch_forward_matrix(const SplineGeom &g, const float *x, const float *coef, const float *w_s, const float *w_b,
-                                 float *cf, void *table, float *y, int64_t B, hipStream_t st)
+                                 float *cf, void *table, size_t table_bytes, float *y, int64_t B, hipStream_t st)
 {
     const MatrixTable t = ::kan::matrix_table(g.n_in, g.n_out, g.rows, kMaxK);
-    const int form = forward_matrix_plan(g, B);
-    switch (t.groups) {
-    case 4:
-        if constexpr (kMaxK <= 4) return matrix_forward<4>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
-        return hipErrorInvalidValue;
-    case 6: return matrix_forward<6>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
-    case 10: return matrix_forward<10>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
-    case 12: return matrix_forward<12>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
-    case 8: return matrix_forward<8>(g, t, form, x, coef, w_s, w_b, cf, table, y, B, st);
-    default: return hipErrorInvalidValue;
+    const int form = forward_matrix_plan(g, B), wide = form == 3 ? 4 : 8;
+    const int64_t fit = (int64_t)(table_bytes / (t.tile_bytes + (size_t)t.n_steps * 4));
+    if (form == 0 || fit < 1) return hipErrorInvalidValue;
+    const int rounds = fit >= t.n_tiles ? 1 : (int)((t.n_tiles + fit - 1) / fit);
+    int per = (t.n_tiles + rounds - 1) / rounds;
+    if (rounds > 1 && (per + wide - 1) / wide * wide <= fit) per = (per + wide - 1) / wide * wide;      // whole workgroups
+    for (int tile = 0; tile < t.n_tiles; tile += per) {
+        const MatrixArgs a = {x, coef, w_s, w_b, cf, y, table, B, t.n_tiles - tile < per ? t.n_tiles - tile : per, tile * ::kan::kMxTile};
+        const hipError_t e = [&] {
+            switch (t.groups) {
+            case 4:
+                if constexpr (kMaxK <= 4) return matrix_forward<4>(g, t, form, a, st);
+                return hipErrorInvalidValue;
+            case 6: return matrix_forward<6>(g, t, form, a, st);
+            case 8: return matrix_forward<8>(g, t, form, a, st);
+            case 10: return matrix_forward<10>(g, t, form, a, st);
+            case 12: return matrix_forward<12>(g, t, form, a, st);
+            default: return hipErrorInvalidValue;
+            }
+        }();
+        if (e != hipSuccess) return e;
     }
+    return hipSuccess;
 }
 
 }  // namespace KAN_NS
