@@ -139,6 +139,13 @@ int kan_backward_saved(const kan_layer_desc *desc, int64_t B, const float *x, co
                        float *gx, float *gcoef, float *gw_s, float *gw_b, void *ws, size_t ws_bytes,
                        void *stream);
 
+/* kan_forward with what kan_backward_saved reads in a buffer of its own: table (kan_workspace_bytes(desc, 0, KAN_PASS_FORWARD)
+   bytes) receives the scale-folded table; ws (the rest of kan_workspace_bytes(desc, B, KAN_PASS_FORWARD), which is often
+   nothing; may be NULL) is free again when the call's work is done.  For callers that keep the table over a training step. */
+int kan_forward_kept(const kan_layer_desc *desc, int64_t B, const float *x, const float *coef,
+                     const float *w_s, const float *w_b, float *y, void *table, size_t table_bytes,
+                     void *ws, size_t ws_bytes, void *stream);
+
 /* kan_forward for callers that cannot allocate device memory (code running under HIP graph capture, tight
    serving loops, harnesses that forbid hipMalloc): same arguments and result as kan_forward, but the scratch
    space is a fixed array of KAN_STATIC_SCRATCH_BYTES that is part of the library's device code, so there is

@@ -22,7 +22,7 @@ KAN_ERR_RANGE = -4
 KAN_ERR_HIP = -5
 PASS_FORWARD, PASS_BACKWARD = 0, 1
 
-EXPORTS = ["kan_strerror", "kan_workspace_bytes", "kan_forward", "kan_backward", "kan_backward_saved", "kan_interval_index",
+EXPORTS = ["kan_strerror", "kan_workspace_bytes", "kan_forward", "kan_forward_kept", "kan_backward", "kan_backward_saved", "kan_interval_index",
            "kan_static_scratch_bytes", "kan_forward_static", "kan_set_launch_observer",
            "ukan_workspace_bytes", "ukan_cg_forward", "ukan_cg_backward", "ukan_saved_bytes",
            "ukan_cg_forward_saved", "ukan_cg_forward_saved_async", "ukan_cg_backward_saved", "ukan_materialize_workspace_bytes",

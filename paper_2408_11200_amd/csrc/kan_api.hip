@@ -174,13 +174,13 @@ extern "C" size_t kan_workspace_bytes(const kan_layer_desc *desc, int64_t B, int
            (size_t)bp.cp.n_chunks * bp.b_slices_per_chunk * edge_bytes(desc);
 }
 
-// Forward pass with the scratch space given explicitly; shared by kan_forward and kan_forward_static.
-// keep_table: the caller may hand the workspace to kan_backward_saved, so the folded table must be in it.
-// A workspace that holds the folded table is enough; the matrix-core kernel runs where its table fits as well.  With no folded table to
-// keep the whole workspace is that kernel's: it takes every call there that has it in kan_forward, in rounds if need be.
+// Forward pass with the scratch space given explicitly; shared by the kan_forward calls.  ws: the folded table, needed whatever kernel
+// runs; keep_table: the caller may hand it to kan_backward_saved, so it must be filled.  more: scratch for the matrix-core kernel,
+// which runs where its table fits.  With no folded table to keep, `more` is all the scratch there is and it takes every call
+// that it takes in kan_forward, in rounds if need be.
 static int forward_impl(const kan_layer_desc *desc, int64_t B, const float *x, const float *coef,
                         const float *w_s, const float *w_b, float *y, void *ws, size_t ws_bytes,
-                        void *stream, bool keep_table)
+                        void *more, size_t more_bytes, void *stream, bool keep_table)
 {
     int rc = check_desc(desc);
     if (rc != KAN_OK) return rc;
@@ -194,13 +194,11 @@ static int forward_impl(const kan_layer_desc *desc, int64_t B, const float *x, c
     SplineGeom g = geom_of(desc);
     float *cf = (float *)ws;
     const size_t split = matrix_bytes(desc, B);
-    const size_t kept = keep_table ? folded_bytes(desc) : 0;
-    if (split && (!keep_table || ws_bytes >= kept + split)) {
+    if (split && (!keep_table || more_bytes >= split)) {
         const float *wb = g.base_act ? w_b : nullptr;
         float *folded = keep_table ? cf : nullptr;
-        void *table = (char *)ws + kept;
-        const hipError_t e = high_degree(desc) ? highk_matrix_forward(highk_of(desc), x, coef, w_s, wb, folded, table, ws_bytes - kept, y, B, st)
-                                               : launch_forward_matrix(g, x, coef, w_s, wb, folded, table, ws_bytes - kept, y, B, st);
+        const hipError_t e = high_degree(desc) ? highk_matrix_forward(highk_of(desc), x, coef, w_s, wb, folded, more, more_bytes, y, B, st)
+                                               : launch_forward_matrix(g, x, coef, w_s, wb, folded, more, more_bytes, y, B, st);
         return e == hipSuccess ? KAN_OK : KAN_ERR_HIP;
     }
     if (high_degree(desc))
@@ -222,7 +220,16 @@ extern "C" int kan_forward(const kan_layer_desc *desc, int64_t B, const float *x
                            const float *w_s, const float *w_b, float *y, void *ws, size_t ws_bytes,
                            void *stream)
 {
-    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, ws_bytes, stream, true);
+    const size_t own = check_desc(desc) == KAN_OK ? folded_bytes(desc) : 0, more = ws && ws_bytes > own ? ws_bytes - own : 0;
+    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, ws_bytes, more ? (char *)ws + own : nullptr, more, stream, true);
+}
+
+extern "C" int kan_forward_kept(const kan_layer_desc *desc, int64_t B, const float *x, const float *coef,
+                                const float *w_s, const float *w_b, float *y, void *table, size_t table_bytes,
+                                void *ws, size_t ws_bytes, void *stream)
+{
+    if (((uintptr_t)ws % kAlign) != 0) return KAN_ERR_WORKSPACE;
+    return forward_impl(desc, B, x, coef, w_s, w_b, y, table, table_bytes, ws, ws ? ws_bytes : 0, stream, true);
 }
 
 // ---- forward pass for callers that cannot allocate -------------------------------------------
@@ -265,7 +272,7 @@ extern "C" int kan_forward_static(const kan_layer_desc *desc, int64_t B, const f
     if (folded_bytes(desc) > (size_t)KAN_STATIC_SCRATCH_BYTES) return KAN_ERR_WORKSPACE;
     void *ws = static_scratch();
     if (!ws) return KAN_ERR_HIP;
-    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, KAN_STATIC_SCRATCH_BYTES, stream, false);
+    return forward_impl(desc, B, x, coef, w_s, w_b, y, ws, KAN_STATIC_SCRATCH_BYTES, ws, KAN_STATIC_SCRATCH_BYTES, stream, false);
 }
 
 // Backward pass; `folded` (may be null) is the scale-folded table a forward pass left in its workspace.

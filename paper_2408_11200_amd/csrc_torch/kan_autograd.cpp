@@ -1,6 +1,6 @@
 // Autograd nodes of the KAN and UKAN layers over the C ABI of libkan_hip.so (include/kan.h).
 //
-// Nothing is computed here: forward calls kan_forward / ukan_cg_forward_saved, backward calls kan_backward_saved /
+// Nothing is computed here: forward calls kan_forward_kept / ukan_cg_forward_saved, backward calls kan_backward_saved /
 // ukan_cg_backward_saved with exactly the gradients autograd asks for.  Native, because a step of a small network is bound by
 // the host: with the nodes in Python and the calls through ctypes a step of the [2, 5, 1] network took 230 .. 330 us for 80 us
 // of GPU work, and a layer's backward node needs the interpreter lock here no more.  Tensors of a forward pass are kept
@@ -80,13 +80,16 @@ struct KanLayer : torch::autograd::Function<KanLayer> {
     {
         const Tensor w_b = or_none(base);
         const int64_t B = x.size(0);
-        // the forward pass's workspace (the scale-folded table) is handed to the backward pass
-        const Tensor ws = bytes_like(x, kan_workspace_bytes(&d, B, KAN_PASS_FORWARD));
+        // the scale-folded table is handed to the backward pass, the rest of the workspace is not
+        const size_t kept = kan_workspace_bytes(&d, 0, KAN_PASS_FORWARD), whole_ws = kan_workspace_bytes(&d, B, KAN_PASS_FORWARD);
+        const Tensor table = bytes_like(x, kept), ws = whole_ws > kept ? bytes_like(x, whole_ws - kept) : Tensor();
         ctx->saved_data["desc"] = pack(d);
-        ctx->save_for_backward({x, coef, w_s, w_b, ws});
+        ctx->save_for_backward({x, coef, w_s, w_b, table});
         const Tensor y = at::empty({B, d.n_out}, x.options().dtype(at::kFloat));
         const Tensor xc = whole(x), cc = whole(coef), sc = whole(w_s), bc = whole(w_b);
-        check(kan_forward(&d, B, f32(xc), f32(cc), f32(sc), f32(bc), f32(y), ws.data_ptr(), (size_t)ws.numel(), stream()), "kan_forward");
+        check(kan_forward_kept(&d, B, f32(xc), f32(cc), f32(sc), f32(bc), f32(y), table.data_ptr(), (size_t)table.numel(),
+                               ws.defined() ? ws.data_ptr() : nullptr, ws.defined() ? (size_t)ws.numel() : 0, stream()),
+              "kan_forward");
         return y;
     }
 
@@ -94,7 +97,7 @@ struct KanLayer : torch::autograd::Function<KanLayer> {
     {
         const kan_layer_desc d = unpack<kan_layer_desc>(ctx->saved_data["desc"]);
         const variable_list saved = ctx->get_saved_variables();
-        const Tensor xc = whole(saved[0]), cc = whole(saved[1]), sc = whole(saved[2]), bc = whole(saved[3]), &ws = saved[4];
+        const Tensor xc = whole(saved[0]), cc = whole(saved[1]), sc = whole(saved[2]), bc = whole(saved[3]), &table = saved[4];
         const int64_t B = xc.size(0);
         // edges: x, coef, w_s, and w_b if there is one
         const bool need[4] = {ctx->needs_input_grad(0), ctx->needs_input_grad(1), ctx->needs_input_grad(2),
@@ -108,7 +111,7 @@ struct KanLayer : torch::autograd::Function<KanLayer> {
         if (need[2]) g[2] = at::empty({d.n_in, d.n_out}, f);
         if (need[3]) g[3] = at::empty({d.n_in, d.n_out}, f);
         const Tensor bws = bytes_like(xc, kan_workspace_bytes(&d, B, KAN_PASS_BACKWARD));
-        check(kan_backward_saved(&d, B, f32(xc), f32(cc), f32(sc), f32(bc), f32(gy), kept(ws), f32(g[0]), f32(g[1]), f32(g[2]),
+        check(kan_backward_saved(&d, B, f32(xc), f32(cc), f32(sc), f32(bc), f32(gy), kept(table), f32(g[0]), f32(g[1]), f32(g[2]),
                                  f32(g[3]), bws.data_ptr(), (size_t)bws.numel(), stream()),
               "kan_backward_saved");
         return g;

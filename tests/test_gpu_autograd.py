@@ -188,3 +188,18 @@ def test_traced_module_runs_the_layers(tmp_path):
             assert torch.equal(a, b)
     with pytest.raises(RuntimeError, match="requires grad"):
         torch.jit.trace(lambda a: autograd.kan_layer(s, a, p["coef"], p["w_s"], p["w_b"]), (x.detach(),))
+
+
+def test_kan_node_keeps_the_folded_table_only():
+    """What the forward pass needs besides is given back when it ends: 128 -> 96 on the matrix-core kernel, whose split table is the larger."""
+    s, x, p, gy = kan_tensors(12001, 128, 96)
+    folded = binding.kan_workspace_bytes(s, 0, binding.PASS_FORWARD)
+    assert binding.kan_workspace_bytes(s, 12001, binding.PASS_FORWARD) > 2 * folded
+    held = []
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: held.append((t.dtype, t.untyped_storage().nbytes())) or t, lambda t: t):
+        y = autograd.kan_layer(s, x, p["coef"], p["w_s"], p["w_b"])
+    assert [n for dtype, n in held if dtype == torch.uint8] == [folded]
+    assert torch.equal(y, binding.kan_forward(s, x.detach(), *(p[n].detach() for n in ("coef", "w_s", "w_b"))))
+    g = torch.autograd.grad(y, [x, p["coef"]], gy)
+    want = binding.kan_backward(s, x.detach(), *(p[n].detach() for n in ("coef", "w_s", "w_b")), gy)
+    assert torch.equal(g[0], want["gx"]) and torch.equal(g[1], want["gcoef"])
