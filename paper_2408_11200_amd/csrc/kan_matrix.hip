@@ -448,7 +448,9 @@ static hipError_t matrix_forward(const SplineGeom &g, const MatrixTable &t, int 
     case 1:
         if constexpr (NG < 8) return matrix_launch<NG, 4, 4, 1, 8, false, false>(g, t, a, st);
         return hipErrorInvalidValue;
-    case 2: return matrix_launch<NG, 8, 2, 1, 8, true, true>(g, t, a, st);
+    case 2:
+        if constexpr (NG < 12) return matrix_launch<NG, 8, 2, 1, 8, true, true>(g, t, a, st);
+        return hipErrorInvalidValue;
     case 3: return matrix_launch<NG, 8, 1, 2, 4, true, true>(g, t, a, st);
     default: return hipErrorInvalidValue;
     }
@@ -462,27 +464,30 @@ static hipError_t matrix_forward(const SplineGeom &g, const MatrixTable &t, int 
 // would gain a tenth or more.  Other kernel / this one, us: 512 -> 512, G = 20, B = 16384 914 / 603; 256 -> 256, G = 28, B = 16384
 // 684 / 235; 128 -> 128, G = 10, B = 16384 170 / 54; 75 -> 130, G = 12, B = 6001 58 / 37; not taken: 64 -> 130, G = 28, B = 1024 12 / 48,
 // 32 -> 96, G = 12, B = 32768 39 / 40.  Up to 64 outputs the evaluation of the pairs is not shared by enough of them (64 -> 64,
-// G = 10, B = 65536: 75 / 78 in the best of the forms tried).  Ten and twelve groups (32..47 rows; step costs extrapolated) spill in
-// the form of two tiles a wave and still gain where they are taken, 13 of 110 layers: 233 -> 270, G = 44, B = 5204 605 / 226;
-// 120 -> 138, G = 32, k = 1, B = 41515 706 / 443; not taken: 262 -> 85, G = 40, B = 27764 278 / 416.  More groups do not fit LDS.
+// G = 10, B = 65536: 75 / 78 in the best of the forms tried).  Ten and twelve groups (32..47 rows) spill in the form of two tiles a
+// wave, whose steps then cost 1.3 and 1.7 times what fewer groups suggest (priced as those, it took 138 -> 618, G = 41, B = 20648 from
+// the staged kernel, 846 / 1246; at its price it never is the shortest with twelve); of 230 layers with them or with tables past L2 that the line takes now, 0.49 of the time in the mean,
+// 1.02 at most: 233 -> 270, G = 44, B = 5204 605 / 226.  The direct kernel past L2 at 1.45e6 edges a microsecond is its better half
+// (512 -> 256, G = 16, B = 2182 205 / 232, not taken).  More groups do not fit LDS.
 // Degrees 4 and 5 (kan_matrix_k5.hip): 225 -> 296, G = 4, k = 5, B = 6869 602 / 137; 104 -> 161, G = 14, k = 4, B = 6803 161 / 62; 52 of 110
 // layers, 0.41 of the time in the mean.
 int forward_matrix_plan(const SplineGeom &g, int64_t B)
 {
     const MatrixTable t = ::kan::matrix_table(g.n_in, g.n_out, g.rows, kMaxK);
     if (t.groups == 0) return 0;
-    struct Form { int samples, tiles, inputs; float fixed, round, step[5]; };
-    static const Form forms[] = {{128, 8, 4, 4.0f, 25.0f, {2.96f, 4.12f, 5.67f, 0.0f, 0.0f}},
-                                 {64, 8, 8, 5.0f, 13.0f, {2.74f, 4.01f, 5.64f, 7.2f, 8.8f}},
+    struct Form { int samples, tiles, inputs; float fixed, round, step[5]; };        // step 0: not built, never the shortest
+    static const Form forms[] = {{128, 8, 4, 4.0f, 25.0f, {2.96f, 4.12f, 0.0f, 0.0f, 0.0f}},
+                                 {64, 8, 8, 5.0f, 13.0f, {2.74f, 4.01f, 5.64f, 10.0f, 0.0f}},
                                  {64, 4, 8, 6.3f, 7.5f, {2.32f, 3.19f, 4.48f, 5.7f, 6.9f}}};
     int best = 0;
     float least = 0.0f;
     // The first form has one level of sums: not where another kernel with two would take the layer (403 -> 164, G = 19, k = 1,
-    // B = 16510: error 3.3e-7, the direct kernel's 2.0e-7).  (From eight groups on it is never the shortest.)
+    // B = 16510: error 3.3e-7, the direct kernel's 2.0e-7).
     const bool one_level = forward_lds_plan(g) != 0 && !forward_direct_plan(g, B);
     if (!one_level && g.n_in < 20 && t.groups >= 8) return 0;        // (few inputs of many groups: 16 -> 104, G = 26, k = 5 1.05 of its error)
-    for (int f = t.groups >= 8 || !one_level ? 1 : 0; f < 3; ++f) {
+    for (int f = one_level ? 0 : 1; f < 3; ++f) {
         const Form &o = forms[f];
+        if (o.step[t.groups / 2 - 2] == 0.0f) continue;
         const int64_t groups = ((B + o.samples - 1) / o.samples) * ((t.n_tiles + o.tiles - 1) / o.tiles);
         const float steps = (float)((g.n_in + o.inputs - 1) / o.inputs);
         const float rounds = (float)((groups + 255) / 256);
@@ -492,7 +497,7 @@ int forward_matrix_plan(const SplineGeom &g, int64_t B)
     }
     const int64_t padded = (int64_t)g.n_in * ((g.n_out + 63) / 64 * 64);
     const bool in_l2 = (int64_t)g.n_in * g.slab_rows * g.n_out * 4 < 6ll << 20;
-    const float direct = 5.0f + (float)B * (float)padded / (in_l2 ? 1.75e6f : 1.2e6f);
+    const float direct = 5.0f + (float)B * (float)padded / (in_l2 ? 1.75e6f : 1.45e6f);
     float other = direct;
     if (g.n_out >= 128) {
         const bool wide = g.n_out > 256;
