@@ -243,13 +243,12 @@ static hipError_t direct_latency(const SplineGeom &g, const float *x, const floa
 //             short        32 -> 48, G = 30: 24000 32 / 45; 32 -> 64, G = 30: 17647 29 / 37; 8 -> 40, G = 30: 9448 12.5 / 11.6, 13107
 //                          12.5 / 14.4; 12 -> 40, G = 30: 9649 17 / 13
 // (sums of 4 and 6 products cost in proportion: the line counts them)
-int forward_direct_plan(const SplineGeom &g, int64_t B)
+// lds_rows: whether the staged kernel for long tables would take the layer otherwise.
+static int direct_plan(const SplineGeom &g, int64_t B, bool lds_rows, int lds)
 {
     const int n = g.n_out, ni = g.n_in;
     const int64_t tiles = (n + 63) / 64, w = n <= 16 ? 16 : (n <= 32 ? 32 : tiles * 64), load = B * w * kMaxK / 4;
     const bool in_l2 = (int64_t)ni * g.slab_rows * n * 4 <= 8ll << 20;
-    const int lds = forward_lds_plan(g);
-    const bool lds_rows = forward_lds_rows_plan(g, B) != 0 && (n <= 64 || !lds);
 #if KAN_MAXK == 4
     const bool narrow = narrow_applicable(g) != 0;
 #else
@@ -291,6 +290,14 @@ int forward_direct_plan(const SplineGeom &g, int64_t B)
     if (in_l2 && (n < 256 || n % 4 != 0)) return ni >= 16 || load <= (n >= 128 ? 1 << 20 : (six ? 3 << 20 : 1 << 22)) ? 1 : 0;
     return load <= (in_l2 || six ? 3 << 18 : 1 << 19) ? 1 : 0;
 }
+
+int forward_direct_plan(const SplineGeom &g, int64_t B)
+{
+    const int lds = forward_lds_plan(g);
+    return direct_plan(g, B, forward_lds_rows_plan(g, B) != 0 && (g.n_out <= 64 || !lds), lds);
+}
+
+int forward_direct_beside_gathers(const SplineGeom &g, int64_t B) { return direct_plan(g, B, false, forward_lds_plan(g)); }
 
 hipError_t launch_forward_direct(const SplineGeom &g, const float *x, const float *coef, const float *w_s,
                                  const float *w_b, float *cf, float *y, int64_t B, hipStream_t st)

@@ -53,6 +53,7 @@ hipError_t launch_fold_scale(const float *coef, const float *w_s, const float *w
 // better choice; cf (may be null) receives the scale-folded table in the same launch; w_s may be null when coef is a
 // scaled table (cf null too)
 int forward_direct_plan(const SplineGeom &g, int64_t B);
+int forward_direct_beside_gathers(const SplineGeom &g, int64_t B);        // the same, were there no staged kernel for long tables
 hipError_t launch_forward_direct(const SplineGeom &g, const float *x, const float *coef, const float *w_s,
                                  const float *w_b, float *cf, float *y, int64_t B, hipStream_t st);
 

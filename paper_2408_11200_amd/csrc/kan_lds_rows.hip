@@ -310,10 +310,12 @@ int workgroups_a_cu(int nw, int nq) { return nw == 16 || 2 * lds_bytes(nw, nq) >
 // Other kernel / this one, us: 256 -> 256, G = 200, B = 8192 346 / 279; 400 -> 100, G = 60, B = 20000 1517 / 438; 256 -> 200, G = 80,
 // B = 8192 522 / 212; left: 50 -> 256, G = 230, k = 1, B = 10000 (316 workgroups, one a CU: two rounds) 85 / 129; 32 -> 96, G = 230,
 // B = 20000 62 / 87.  Not below a workgroup a CU: 512 -> 512, B = 2048, G = 200 597 / 617 (on sixteen waves), G = 400 755 / 1004.
-bool eight_waves_pay(int64_t wgs, int a_cu, int64_t quads, int64_t padded_edges)
+// Tiles of 32 in place of the direct kernel, which the others (33..64 outputs) are well behind: 540 a row (96 -> 44, G = 179, k = 1,
+// B = 33091 145 / 158, 71 -> 56, G = 175, B = 40462 117 / 125; taken: 125 -> 50, G = 149, B = 42886 226 / 211).
+bool eight_waves_pay(int64_t wgs, int a_cu, int64_t quads, int64_t padded_edges, bool slow_step)
 {
     const int64_t at_once = 256 * a_cu, full = (wgs - 1) / at_once;
-    const float step = (float)(390 * kMaxK) + (float)quads / 4;
+    const float step = (float)((slow_step ? 540 : 390) * kMaxK) + (float)quads / 4;
     const float clocks = ((float)full * (a_cu == 2 ? 1.4f : 1.0f) + (wgs - full * at_once > 256 ? 1.4f : 1.0f)) * step;
     return clocks < 0.92f * 2200.0f * (kMaxK == 4 ? 1.0f : 1.5f) * (float)padded_edges / 1.5e6f;
 }
@@ -350,12 +352,18 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             if (!nq || !variant_built(lps, 4, nw, nq, g.base_act != 0)) continue;
             // worth it only when a staged row serves many samples (the copy into LDS costs as much LDS
             // time per row as several reads of it): samples * K >= 4 * slab rows
-            if (eight_tiled ? !eight_waves_pay(wgs, workgroups_a_cu(nw, nq), quads, B * ((g.n_out + 63) / 64 * 64))
+            const bool direct = eight_tiled && forward_direct_beside_gathers(g, B) != 0;
+            if (eight_tiled ? !eight_waves_pay(wgs, workgroups_a_cu(nw, nq), quads, B * ((g.n_out + 63) / 64 * 64), direct && lps == 8)
                             : per_wg * kMaxK < 4 * (int64_t)g.slab_rows)
                 continue;
-            // sums as short as those of the direct kernel, whose sixteen lane groups share the inputs and which eight waves mostly
-            // stand in for (25 -> 83, G = 5, B = 19696: its error 0.95e-7, folded every 32 inputs 1.9e-7, this way 0.93e-7)
-            RowsPlan p = {lps, 4, nw, nq, 1, !eight_tiled ? 32 : g.n_in < 16 ? 1 : g.n_in < 40 ? 2 : g.n_in < 160 ? 4 : 8};
+            RowsPlan p = {lps, 4, nw, nq, 1, 32};
+            if (direct) {
+                // In place of the direct kernel, whose sixteen lane groups share the inputs: sums as short as its, chains and number
+                // of partial sums in balance (25 -> 83, G = 5, B = 19696: its error 0.95e-7, folded every 32 inputs 1.9e-7, this
+                // way 0.93e-7).  The generic and the row-stream kernel fold every 32 themselves.
+                const int terms = g.k + 2;
+                p.fold = g.n_in < 2 * terms ? 1 : g.n_in < 8 * terms ? 2 : g.n_in < 32 * terms ? 4 : 8;
+            }
             // Eight samples a group halve the copies a sample (256 -> 256, 180 rows, B = 32768: 608 us, with four 756).  A CU
             // works through its workgroups in rounds of 256; a step of four samples a group takes about 2200 clocks beside
             // the copies, which go at 64 bytes a clock.
