@@ -226,10 +226,9 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN >= 16 ? 4 : 2) void forward_m
             wave_windows<false>(v[c], g, i < g.n_in ? i : g.n_in - 1, row0, w, base, dw, dbase);
             const bool fits = fabsf(base) < kMxLargest;
             if (!fits) special[s] = 1;
-            const float scale = i < g.n_in ? kMxScale : 0.0f;
-            base = fits ? base * scale : 0.0f;
+            base = fits && i < g.n_in ? base * kMxScale : 0.0f;
 #pragma unroll
-            for (int k = 0; k < kMaxK; ++k) w[k] *= scale;
+            for (int k = 0; k < kMaxK; ++k) w[k] = i < g.n_in ? w[k] * kMxScale : 0.0f;
             unsigned out[kMxSplits][NG];
             IndexBits<NG> index;
             pair_operands<NG>(row0, w, base, out, index);

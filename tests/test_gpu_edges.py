@@ -474,7 +474,7 @@ def test_matrix_forward(B, n_in, n_out, G, k):
     ref = oracle.kan_forward(w.x[rows], p["coef"], p["w_s"], p["w_b"], G, k, s.grid_lo, oracle.inv_h_of(s.grid_lo, s.grid_hi, G))
     got = y[0].cpu().numpy()
     assert_close(y[0][torch.from_numpy(rows).cuda()], ref, 1e-5, "y")
-    # in the 2-norm: up to 33 additions of partial sums and 3 products of leading parts an addition, each rounded to about half a
+
     # unit of 2^-24 of a sum that grows to the result: sqrt(4 * 33) / 2 * 0.6 units.  (One part of one factor lost: 4e-7 and more.)
     err = np.linalg.norm(got[rows] - ref) / np.linalg.norm(ref)
     assert err < 3.5 * 2.0 ** -24, err
