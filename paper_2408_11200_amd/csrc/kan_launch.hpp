@@ -92,6 +92,7 @@ hipError_t launch_forward_lds(const SplineGeom &g, const float *x, const float *
 // LDS-staged kernel for long tables (narrow output tile, many samples per workgroup); the plan
 // returns 0 when the shape does not qualify
 int forward_lds_rows_plan(const SplineGeom &g, int64_t B);
+float forward_lds_rows_us(const SplineGeom &g, int64_t B);       // about its time; 0: not applicable
 int forward_lds_rows_rounds(const SplineGeom &g, int64_t B);      // of workgroups on the chip; 0: no plan
 hipError_t launch_forward_lds_rows(const SplineGeom &g, const float *x, const float *cf, float *y, int64_t B,
                                    hipStream_t st);

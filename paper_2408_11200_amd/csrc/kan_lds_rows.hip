@@ -302,8 +302,16 @@ constexpr bool variant_built(int lps, int slots, int nw, int nq, bool base)
 }
 int workgroups_a_cu(int nw, int nq) { return nw == 16 || 2 * lds_bytes(nw, nq) > kLdsBudget ? 1 : 2; }
 
-// Eight waves on several tiles against the kernels that gather (generic and direct), in clocks an input: a step takes 390 a
-// window row beside the copies at 64 bytes a clock, for each round of workgroups, and 1.4 times that where a CU works on two; the
+// Clocks of an input on eight waves and several tiles: a step takes `row` a window row beside the copies at 64 bytes a clock, for
+// each round of workgroups, and 1.4 times that where a CU works on two.
+float eight_waves_clocks(int64_t wgs, int a_cu, int64_t quads, int row)
+{
+    const int64_t at_once = 256 * a_cu, full = (wgs - 1) / at_once;
+    const float step = (float)(row * kMaxK) + (float)quads / 4;
+    return ((float)full * (a_cu == 2 ? 1.4f : 1.0f) + (wgs - full * at_once > 256 ? 1.4f : 1.0f)) * step;
+}
+
+// Eight waves on several tiles against the kernels that gather (generic and direct), at 390 clocks a window row; the
 // others take an edge of the padded width in 1.5e-6 us (windows of six: 2.2e-6), more on ragged rows and past L2.  Over 326
 // layers of 65..512 outputs, 8..400 inputs, 31..251 rows and B = 2048..20000 the line takes 198 to 0.79 of their time in the mean
 // (1.04 at most, where runs of one side differ by as much); of the other 128 those that it would slow reach 1.5 times.
@@ -314,10 +322,8 @@ int workgroups_a_cu(int nw, int nq) { return nw == 16 || 2 * lds_bytes(nw, nq) >
 // B = 33091 145 / 158, 71 -> 56, G = 175, B = 40462 117 / 125; taken: 125 -> 50, G = 149, B = 42886 226 / 211).
 bool eight_waves_pay(int64_t wgs, int a_cu, int64_t quads, int64_t padded_edges, bool slow_step)
 {
-    const int64_t at_once = 256 * a_cu, full = (wgs - 1) / at_once;
-    const float step = (float)((slow_step ? 540 : 390) * kMaxK) + (float)quads / 4;
-    const float clocks = ((float)full * (a_cu == 2 ? 1.4f : 1.0f) + (wgs - full * at_once > 256 ? 1.4f : 1.0f)) * step;
-    return clocks < 0.92f * 2200.0f * (kMaxK == 4 ? 1.0f : 1.5f) * (float)padded_edges / 1.5e6f;
+    return eight_waves_clocks(wgs, a_cu, quads, slow_step ? 540 : 390) <
+           0.92f * 2200.0f * (kMaxK == 4 ? 1.0f : 1.5f) * (float)padded_edges / 1.5e6f;
 }
 
 // tile width, samples a group, workgroup size, copy depth and inputs a step for a layer (lps == 0: not applicable)
@@ -432,6 +438,18 @@ hipError_t launch_by_quads(const RowsPlan &p, const SplineGeom &g, const float *
 }  // namespace
 
 int forward_lds_rows_plan(const SplineGeom &g, int64_t B) { return plan_of(g, B).lps; }
+
+// (sixteen waves at a rate that they reach or pass on tables of up to 47 rows)
+float forward_lds_rows_us(const SplineGeom &g, int64_t B)
+{
+    const RowsPlan p = plan_of(g, B);
+    if (p.lps == 0) return 0.0f;
+    const int64_t tj = p.lps * 4, per_wg = (int64_t)p.nw * (64 / p.lps) * p.slots, tiles = (g.n_out + tj - 1) / tj;
+    if (p.nw == 8 && tiles > 1)
+        return 3.0f + (float)g.n_in * eight_waves_clocks((B + per_wg - 1) / per_wg * tiles, workgroups_a_cu(p.nw, p.nq),
+                                                         (int64_t)g.slab_rows * p.lps, 390) / 2200.0f;
+    return (10.0f + (float)B * (float)g.n_in * (float)((g.n_out + 63) / 64 * 64) / 4.1e6f) * (kMaxK == 4 ? 1.0f : 1.3f);
+}
 
 int forward_lds_rows_rounds(const SplineGeom &g, int64_t B)
 {

@@ -455,60 +455,57 @@ static hipError_t matrix_forward(const SplineGeom &g, const MatrixTable &t, int 
     }
 }
 
-// The form with the shortest estimated time, if that is shorter than the other kernels' by a tenth; 0 otherwise.  Each form
-// costs a fixed time, and per round of 256 workgroups a fixed time and so much a step (us; least squares over 779 layers of
-// 65..512 outputs, 4..512 inputs, G = 5..28, B = 1024..65536: every one within 0.79..1.13 of its time).  The others: the direct
-// kernel by its edges (its table in L2 or past it), the LDS-staged ones by the rounds of their workgroups.  Of the layers with
-// eight inputs and more the line picks 297, at 0.55 of the time in the mean (0.24 at the least, 0.99 at most); 56 that it leaves
-// would gain a tenth or more.  Other kernel / this one, us: 512 -> 512, G = 20, B = 16384 914 / 603; 256 -> 256, G = 28, B = 16384
-// 684 / 235; 128 -> 128, G = 10, B = 16384 170 / 54; 75 -> 130, G = 12, B = 6001 58 / 37; not taken: 64 -> 130, G = 28, B = 1024 12 / 48,
-// 32 -> 96, G = 12, B = 32768 39 / 40.  Up to 64 outputs the evaluation of the pairs is not shared by enough of them (64 -> 64,
-// G = 10, B = 65536: 75 / 78 in the best of the forms tried).  Ten and twelve groups (32..47 rows) spill in the form of two tiles a
-// wave, whose steps then cost 1.3 and 1.7 times what fewer groups suggest (priced as those, it took 138 -> 618, G = 41, B = 20648 from
-// the staged kernel, 846 / 1246; at its price it never is the shortest with twelve); of 230 layers with them or with tables past L2 that the line takes now, 0.49 of the time in the mean,
-// 1.02 at most: 233 -> 270, G = 44, B = 5204 605 / 226.  The direct kernel past L2 at 1.45e6 edges a microsecond is its better half
-// (512 -> 256, G = 16, B = 2182 205 / 232, not taken).  More groups do not fit LDS.
-// Degrees 4 and 5 (kan_matrix_k5.hip): 225 -> 296, G = 4, k = 5, B = 6869 602 / 137; 104 -> 161, G = 14, k = 4, B = 6803 161 / 62; 52 of 110
-// layers, 0.41 of the time in the mean.
+// The form with the shortest estimated time, if that is shorter than the time of the kernel that the layer would have; 0
+// otherwise.  Each form costs a fixed time, and per round of 256 workgroups a fixed time and so much a step (us; least squares over
+// 700 layers of 65..512 outputs, 8..512 inputs, up to 47 rows, B = 1500..65536, all forms of each: 0.82..1.12 of the time, 0.05 in the
+// mean).  Ten and twelve groups (32..47 rows) spill in the form of two tiles a wave, whose steps cost 1.3 and 1.7 times what fewer
+// groups suggest; with twelve it never is the shortest by much and is not built.  More groups do not fit LDS.
+// The other kernel: the direct one by its edges, those of ragged rows dearer, and in L2 or past it (420 layers: 0.73..1.16 of the time);
+// the staged ones for short tables by the rounds of their workgroups, the one for long tables as its own plan counts.  Where the two are
+// even ragged layers come here (137 -> 140, G = 44, B = 12900 240 / 242) and others stay.  Of 1400 layers this takes 0.70 of the time of the
+// other kernels in the mean, 1.07 at most.  Other kernel / this one, us: 512 -> 512, G = 20, B = 16384 914 / 603; 256 -> 256, G = 28,
+// B = 16384 684 / 235; 128 -> 128, G = 10, B = 16384 170 / 54; 75 -> 130, G = 12, B = 6001 58 / 37; 139 -> 139, G = 29, B = 12900 250 / 186;
+// 265 -> 411, G = 41, k = 5, B = 4929 1730 / 593; 231 -> 270, G = 38, k = 1, B = 5201 525 / 181; not taken: 64 -> 130, G = 28, B = 1024
+// 12 / 48, 32 -> 96, G = 12, B = 32768 39 / 40; 37 -> 96, G = 28, B = 22260 43 / 58; 512 -> 256, G = 16, B = 2182 198 / 228.  Up to 64
+// outputs the evaluation of the pairs is not shared by enough of them (64 -> 64, G = 10, B = 65536: 75 / 78 in the best of the forms tried).
 int forward_matrix_plan(const SplineGeom &g, int64_t B)
 {
     const MatrixTable t = ::kan::matrix_table(g.n_in, g.n_out, g.rows, kMaxK);
     if (t.groups == 0) return 0;
-    struct Form { int samples, tiles, inputs; float fixed, round, step[5]; };        // step 0: not built, never the shortest
-    static const Form forms[] = {{128, 8, 4, 4.0f, 25.0f, {2.96f, 4.12f, 0.0f, 0.0f, 0.0f}},
-                                 {64, 8, 8, 5.0f, 13.0f, {2.74f, 4.01f, 5.64f, 10.0f, 0.0f}},
-                                 {64, 4, 8, 6.3f, 7.5f, {2.32f, 3.19f, 4.48f, 5.7f, 6.9f}}};
-    int best = 0;
-    float least = 0.0f;
+    struct Form { int samples, tiles, inputs; float fixed, round, step[5]; };        // step 0: not built
+    static const Form forms[] = {{128, 8, 4, 6.5f, 16.5f, {2.9f, 4.16f, 0.0f, 0.0f, 0.0f}},
+                                 {64, 8, 8, 6.0f, 10.5f, {2.74f, 4.15f, 5.85f, 9.3f, 0.0f}},
+                                 {64, 4, 8, 7.5f, 5.2f, {2.3f, 3.25f, 4.43f, 5.65f, 6.55f}}};
+    const int lds = forward_lds_plan(g);
+    const bool direct = forward_direct_plan(g, B) != 0, staged = !direct && lds != 0;
     // The first form has one level of sums: not where another kernel with two would take the layer (403 -> 164, G = 19, k = 1,
     // B = 16510: error 3.3e-7, the direct kernel's 2.0e-7).
-    const bool one_level = forward_lds_plan(g) != 0 && !forward_direct_plan(g, B);
-    if (!one_level && g.n_in < 20 && t.groups >= 8) return 0;        // (few inputs of many groups: 16 -> 104, G = 26, k = 5 1.05 of its error)
-    for (int f = one_level ? 0 : 1; f < 3; ++f) {
+    if (!staged && g.n_in < 20 && t.groups >= 8) return 0;        // (few inputs of many groups: 16 -> 104, G = 26, k = 5 1.05 of its error)
+    int best = 0;
+    float least = 0.0f;
+    for (int f = staged ? 0 : 1; f < 3; ++f) {
         const Form &o = forms[f];
         if (o.step[t.groups / 2 - 2] == 0.0f) continue;
         const int64_t groups = ((B + o.samples - 1) / o.samples) * ((t.n_tiles + o.tiles - 1) / o.tiles);
         const float steps = (float)((g.n_in + o.inputs - 1) / o.inputs);
-        const float rounds = (float)((groups + 255) / 256);
-        // (the second form's steps take longer behind one another: 512 -> 512, G = 20, B = 16384 603 in the first, 640 in it)
-        const float us = o.fixed + rounds * (o.round + steps * o.step[t.groups / 2 - 2] * (f == 1 && rounds > 1.0f ? 1.08f : 1.0f));
+        const float us = o.fixed + (float)((groups + 255) / 256) * (o.round + steps * o.step[t.groups / 2 - 2]);
         if (best == 0 || us < least) { best = f + 1; least = us; }
     }
-    const int64_t padded = (int64_t)g.n_in * ((g.n_out + 63) / 64 * 64);
-    const bool in_l2 = (int64_t)g.n_in * g.slab_rows * g.n_out * 4 < 6ll << 20;
-    const float direct = 5.0f + (float)B * (float)padded / (in_l2 ? 1.75e6f : 1.45e6f);
-    float other = direct;
-    if (g.n_out >= 128) {
-        const bool wide = g.n_out > 256;
-        const float staged = 8.0f + (float)((g.n_out + 511) / 512 * ((B + (wide ? 16383 : 32767)) / (wide ? 16384 : 32768))) *
-                                        (wide ? 1.78f : 2.62f) * (float)g.n_in;
-        other = staged < direct ? staged : direct;
-    } else if (B >= (t.groups > 8 ? 127 * 128 + 1 : 28000)) {        // (long tables: from a workgroup of eight waves a CU on)
-        const float staged = 10.0f + (float)B * (float)padded / 4.1e6f;
-        other = staged < direct ? staged : direct;
+    const float edges = 1e-6f * (float)B * (float)g.n_in * (float)((g.n_out + 63) / 64 * 64);
+    constexpr float six = kMaxK == 6 ? 1.5f : 1.0f;              // windows of six cost these kernels half as much again
+    float other;
+    if (direct) {
+        const bool in_l2 = (int64_t)g.n_in * g.slab_rows * g.n_out * 4 < 6ll << 20, ragged = g.n_out % 16 != 0;
+        other = 6.0f + six * edges * (in_l2 ? (ragged ? 0.735f : 0.57f) : (ragged ? 0.93f : 0.65f));
+    } else if (staged) {
+        const int64_t samples = lds == 8 ? 64 : 128, width = lds == 8 ? 512 : 256;          // of a workgroup
+        const int64_t groups = (B + samples - 1) / samples * ((g.n_out + width - 1) / width);
+        other = (kMaxK == 6 ? 1.24f : 0.95f) * (8.0f + (float)((groups + 255) / 256) * (lds == 8 ? 1.78f : 2.62f) * (float)g.n_in);
+    } else {
+        other = forward_lds_rows_us(g, B);
+        if (other == 0.0f) other = six * (5.0f + edges / 1.45f);                  // the generic kernel
     }
-    // (windows of six cost the other kernels half as much again, these nothing)
-    return least < 0.9f * (kMaxK == 6 ? 1.3f : 1.0f) * other ? best : 0;
+    return least < other ? best : 0;
 }
 
 // A table that does not fit is made and used a range of outputs at a time, the same sums in the same order.

@@ -457,7 +457,7 @@ MATRIX_SHAPES = [
     (12001, 73, 127, 21, 3), (12031, 66, 130, 28, 3),          # thirty-two: the same
     (16001, 65, 256, 20, 3), (16001, 66, 255, 10, 3), (16001, 63, 193, 28, 2),      # sixty-four samples a workgroup
     (32700, 67, 300, 20, 3), (32641, 42, 512, 10, 3),          # a hundred and twenty-eight
-    (16300, 139, 139, 29, 3), (5201, 231, 270, 38, 1), (5201, 232, 270, 38, 2), (14220, 177, 248, 44, 3),      # up to 47 rows
+    (12900, 139, 139, 29, 3), (5201, 231, 270, 38, 1), (5201, 232, 270, 38, 2), (12900, 137, 140, 44, 3),      # up to 47 rows
     (8096, 163, 230, 3, 4), (13457, 94, 136, 18, 5), (10900, 58, 123, 19, 5), (6801, 105, 161, 26, 5), (5200, 159, 446, 42, 5),      # windows of six
     (30001, 100, 417, 11, 4),
 ]
@@ -474,7 +474,7 @@ def test_matrix_forward(B, n_in, n_out, G, k):
     ref = oracle.kan_forward(w.x[rows], p["coef"], p["w_s"], p["w_b"], G, k, s.grid_lo, oracle.inv_h_of(s.grid_lo, s.grid_hi, G))
     got = y[0].cpu().numpy()
     assert_close(y[0][torch.from_numpy(rows).cuda()], ref, 1e-5, "y")
-
+    # in the 2-norm: up to 33 additions of partial sums and 3 products of leading parts an addition, each rounded to about half a
     # unit of 2^-24 of a sum that grows to the result: sqrt(4 * 33) / 2 * 0.6 units.  (One part of one factor lost: 4e-7 and more.)
     err = np.linalg.norm(got[rows] - ref) / np.linalg.norm(ref)
     assert err < 3.5 * 2.0 ** -24, err

@@ -98,9 +98,9 @@ def test_forward_sums(B, n_in, n_out, G, k, family, chain, parts):
 
 
 @pytest.mark.parametrize("B,n_in,n_out,G,k,family", [
-    (2182, 512, 256, 16, 3, "direct"),                          # its table past L2: 205 us, on the matrix cores 232
-    (16150, 49, 174, 42, 3, "direct"), (18072, 47, 255, 42, 5, "lds"),         # twelve groups: 129 / 138, 188 / 230
-    (40462, 71, 56, 175, 3, "direct"), (33091, 96, 44, 179, 1, "direct"),       # tiles of 32 on eight waves: 117 / 125, 145 / 158
+    (2182, 512, 256, 16, 3, "direct"),                          # its table past L2: 198 us, on the matrix cores 228
+    (22260, 37, 96, 28, 3, "lds_rows"),                         # 43 / 58
+    (33091, 96, 44, 179, 1, "direct"),                          # tiles of 32 on eight waves: 145 / 158
 ])
 def test_layers_left_to_the_other_kernels(B, n_in, n_out, G, k, family):
     got, ref = run_rows(workloads.random_kan_layer(B, B, n_in, n_out, G, k), np.r_[0:50, B - 50:B], family)
