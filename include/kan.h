@@ -97,9 +97,9 @@ const char *kan_strerror(int status);
 
 /* Scratch bytes needed by kan_forward (pass = KAN_PASS_FORWARD) or kan_backward for batch B.
    Returns 0 for an invalid descriptor.  Forward: the scale-folded table (n_in * (G + k + 1) * n_out floats, rounded up to 256
-   bytes; kan_forward takes a workspace of that size for every B) and, for the batches of wide layers on short tables that the
-   matrix-core kernel takes, that table once more in split form (1.5 to 10 times its size): a workspace without room for it
-   gets another kernel and the same result to rounding.  Backward, on top of the folded table:
+   bytes) and, for the batches of wide layers on short tables that the matrix-core kernel takes, that table once more in split
+   form (1.5 to 10 times its size).  kan_forward takes a workspace of the folded table's size for every B, then on another kernel and
+   with the same result to rounding; KAN_ERR_WORKSPACE between the two sizes.  Backward, on top of the folded table:
    - ordinarily the transposed input, two sorted record arrays (44 bytes per (sample, input) pair, 88 for degrees 4 and 5)
      and the per-chunk partial gradient tables: a small multiple of B * n_in * 48 bytes + at most 2 GiB of partial tables
      (more only when a single table exceeds that).  Widths that are no multiple of four need as much as the others
@@ -141,7 +141,7 @@ int kan_backward_saved(const kan_layer_desc *desc, int64_t B, const float *x, co
 
 /* kan_forward with what kan_backward_saved reads in a buffer of its own: table (kan_workspace_bytes(desc, 0, KAN_PASS_FORWARD)
    bytes) receives the scale-folded table; ws (the rest of kan_workspace_bytes(desc, B, KAN_PASS_FORWARD), which is often
-   nothing; may be NULL) is free again when the call's work is done.  For callers that keep the table over a training step. */
+   nothing; NULL: as in a workspace of the folded table's size) is free again when the call's work is done.  For callers that keep the table over a training step. */
 int kan_forward_kept(const kan_layer_desc *desc, int64_t B, const float *x, const float *coef,
                      const float *w_s, const float *w_b, float *y, void *table, size_t table_bytes,
                      void *ws, size_t ws_bytes, void *stream);

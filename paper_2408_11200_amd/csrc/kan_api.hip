@@ -194,6 +194,9 @@ static int forward_impl(const kan_layer_desc *desc, int64_t B, const float *x, c
     SplineGeom g = geom_of(desc);
     float *cf = (float *)ws;
     const size_t split = matrix_bytes(desc, B);
+    // (scratch that is there and too small is of no size that kan_workspace_bytes returns for this layer: refused, where the call would
+    // run on the slower kernel unseen)
+    if (keep_table && more_bytes && more_bytes < split) return KAN_ERR_WORKSPACE;
     if (split && (!keep_table || more_bytes >= split)) {
         const float *wb = g.base_act ? w_b : nullptr;
         float *folded = keep_table ? cf : nullptr;

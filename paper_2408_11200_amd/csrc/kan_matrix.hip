@@ -426,7 +426,7 @@ static hipError_t matrix_launch(const SplineGeom &g, const MatrixTable &t, const
     for (int64_t b0 = 0; b0 < a.B; b0 += part) {
         const int64_t n = a.B - b0 < part ? a.B - b0 : part;
         const dim3 grid((unsigned)((n + S - 1) / S), across);
-        prof::Timed tm("forward_matrix", st);
+        prof::Timed tm(a.n_tiles < t.n_tiles ? "forward_matrix_range" : "forward_matrix", st);      // (a range of the outputs)
         kern<<<grid, 64 * WM * WN, bytes, st>>>(g, a.x + b0 * g.n_in, a.coef, a.w_s, a.w_b, (const U4 *)a.table, odd, a.y + b0 * g.n_out,
                                                 n, a.n_tiles, a.j0, g.n_in <= 64 ? 0 : 1);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;

@@ -105,3 +105,45 @@ def test_forward_sums(B, n_in, n_out, G, k, family, chain, parts):
 def test_layers_left_to_the_other_kernels(B, n_in, n_out, G, k, family):
     got, ref = run_rows(workloads.random_kan_layer(B, B, n_in, n_out, G, k), np.r_[0:50, B - 50:B], family)
     assert rel(got, ref) < 1e-6
+
+
+def layer_tensors(B, s):
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.rand((B, s.n_in), generator=g, device="cuda") * 2 - 1
+    return [x] + [torch.randn(d, generator=g, device="cuda") * 0.04 for d in ((s.n_in, s.M, s.n_out), (s.n_in, s.n_out), (s.n_in, s.n_out))]
+
+
+def test_matrix_forward_in_a_workspace_of_the_folded_table():
+    """The split table is counted only for the batches that the kernel takes, and a workspace without it serves them on another kernel."""
+    s = workloads.KanLayerSpec(512, 512, 20, 3, -1.0, 1.0)
+    folded = s.n_in * (s.M + 1) * s.n_out * 4
+    assert binding.kan_workspace_bytes(s, 64, binding.PASS_FORWARD) == folded
+    assert binding.kan_workspace_bytes(s, 4096, binding.PASS_FORWARD) > 2 * folded
+    x, coef, w_s, w_b = layer_tensors(4096, s)
+    y, ws = [], torch.empty(folded, dtype=torch.uint8, device="cuda")
+    assert "forward_matrix" in families_of(lambda: y.append(binding.kan_forward(s, x, coef, w_s, w_b)))
+    assert "forward_matrix" not in families_of(lambda: y.append(binding.kan_forward(s, x, coef, w_s, w_b, ws=ws)))
+    assert ((y[1] - y[0]).norm() / y[0].norm()).item() < 3e-6
+    assert torch.equal(ws.view(torch.float32), torch.cat([coef * w_s[:, None, :], w_b[:, None, :]], dim=1).flatten())
+    with pytest.raises(binding.KanError):
+        binding.kan_forward(s, x, coef, w_s, w_b, ws=ws[:folded - 256])
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k,family", [
+    (4096, 560, 512, 20, 3, "forward_matrix_range"),        # a split table of 42 MB: rounds of eight tiles
+    (4099, 1100, 225, 20, 3, "forward_matrix_range"),       # of five and three
+    (5003, 2700, 97, 8, 5, "forward_matrix_range"),         # of two, windows of six
+    (12001, 37, 97, 12, 3, "forward_matrix"),               # whole
+])
+def test_matrix_forward_in_the_static_array(B, n_in, n_out, G, k, family):
+    """The same bits as kan_forward, also where the split table does not fit the array, and of values that do not split."""
+    s = workloads.KanLayerSpec(n_in, n_out, G, k, -1.0, 1.0)
+    x, coef, w_s, w_b = layer_tensors(B, s)
+    y, z = torch.empty((B, n_out), device="cuda"), torch.empty((B, n_out), device="cuda")
+    for special in (False, True):
+        if special:
+            x[5, 3], x[B - 1, 2], coef[7, 2, n_out - 1], w_b[4, 40] = float("inf"), 1e30, float("inf"), 1e12
+        z.zero_()
+        assert "forward_matrix" in families_of(lambda: binding.kan_forward(s, x, coef, w_s, w_b, y=y))
+        assert family in families_of(lambda: binding.kan_forward_static(s, x, coef, w_s, w_b, z))
+        assert torch.equal(y.view(torch.int32), z.view(torch.int32))
