@@ -318,12 +318,15 @@ float eight_waves_clocks(int64_t wgs, int a_cu, int64_t quads, int row)
 // Other kernel / this one, us: 256 -> 256, G = 200, B = 8192 346 / 279; 400 -> 100, G = 60, B = 20000 1517 / 438; 256 -> 200, G = 80,
 // B = 8192 522 / 212; left: 50 -> 256, G = 230, k = 1, B = 10000 (316 workgroups, one a CU: two rounds) 85 / 129; 32 -> 96, G = 230,
 // B = 20000 62 / 87.  Not below a workgroup a CU: 512 -> 512, B = 2048, G = 200 597 / 617 (on sixteen waves), G = 400 755 / 1004.
-// Tiles of 32 in place of the direct kernel, which the others (33..64 outputs) are well behind: 540 a row (96 -> 44, G = 179, k = 1,
-// B = 33091 145 / 158, 71 -> 56, G = 175, B = 40462 117 / 125; taken: 125 -> 50, G = 149, B = 42886 226 / 211).
-bool eight_waves_pay(int64_t wgs, int a_cu, int64_t quads, int64_t padded_edges, bool slow_step)
+// Tiles of 32 in place of the direct kernel, which the others (33..64 outputs) are well behind: 540 a row (windows of six: 440), and
+// 1.07 times the direct kernel's time where its rows are not aligned (96 -> 44, G = 179, k = 1, B = 33091 145 / 158, 57 -> 48, G = 285,
+// k = 2, B = 34176 77 / 150; 96 -> 40, G = 243, k = 5, B = 38374 222 / 266; taken: 98 -> 38, G = 202, B = 40000 168 / 156, k = 4,
+// B = 51421 309 / 269; 283 -> 34, G = 165, B = 55796 658 / 441).
+bool eight_waves_pay(int64_t wgs, int a_cu, int64_t quads, int64_t padded_edges, bool tiles_of_32, bool ragged)
 {
-    return eight_waves_clocks(wgs, a_cu, quads, slow_step ? 540 : 390) <
-           0.92f * 2200.0f * (kMaxK == 4 ? 1.0f : 1.5f) * (float)padded_edges / 1.5e6f;
+    const int row = !tiles_of_32 ? 390 : kMaxK == 4 ? 540 : 440;
+    const float edge = (kMaxK == 4 ? 1.0f : 1.5f) * (tiles_of_32 && ragged ? 1.07f : 1.0f) / 1.5e6f;
+    return eight_waves_clocks(wgs, a_cu, quads, row) < 0.92f * 2200.0f * edge * (float)padded_edges;
 }
 
 // tile width, samples a group, workgroup size, copy depth and inputs a step for a layer (lps == 0: not applicable)
@@ -359,7 +362,7 @@ RowsPlan plan_of(const SplineGeom &g, int64_t B)
             // worth it only when a staged row serves many samples (the copy into LDS costs as much LDS
             // time per row as several reads of it): samples * K >= 4 * slab rows
             const bool direct = eight_tiled && forward_direct_beside_gathers(g, B) != 0;
-            if (eight_tiled ? !eight_waves_pay(wgs, workgroups_a_cu(nw, nq), quads, B * ((g.n_out + 63) / 64 * 64), direct && lps == 8)
+            if (eight_tiled ? !eight_waves_pay(wgs, workgroups_a_cu(nw, nq), quads, B * ((g.n_out + 63) / 64 * 64), direct && lps == 8, g.n_out % 4 != 0)
                             : per_wg * kMaxK < 4 * (int64_t)g.slab_rows)
                 continue;
             RowsPlan p = {lps, 4, nw, nq, 1, 32};
