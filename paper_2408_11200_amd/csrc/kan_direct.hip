@@ -152,11 +152,12 @@ __global__ __launch_bounds__(64 * NW) void forward_direct_kernel(SplineGeom g, c
         const int s = e / TJ, jj = tile * TJ + e % TJ;
         if (b0 + s >= B || jj >= g.n_out) continue;
         const float *at = sums + s * TJ + direct_slot(jj, tile * TJ, T, g.n_out);
-        // eight groups in pairs, and the eights one after another: added one by one, groups of a few inputs each round more often than the
-        // kernels of longer sums do (16 -> 16, G = 32, k = 1: error 0.89e-7 with 64 groups in a row, the narrow kernel's 0.76e-7)
-        constexpr int kPairs = NGRP < 8 ? NGRP : 8;
+        // 64 groups of sixteen outputs: eight in pairs, and the eights one after another; added one by one, groups of a few inputs each round
+        // more often than the kernel of longer sums that would have such a layer (16 -> 16, G = 32, k = 1: error 0.89e-7 with 64 in a
+        // row, the narrow kernel's 0.76e-7)
+        constexpr int kPairs = T == 4 && NGRP == 64 ? 8 : 1;
         float v = 0.0f;
-#pragma unroll
+#pragma unroll 8
         for (int q = 0; q < NGRP; q += kPairs) {
             float t[kPairs];
 #pragma unroll
