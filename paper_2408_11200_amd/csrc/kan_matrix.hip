@@ -456,26 +456,27 @@ static hipError_t matrix_forward(const SplineGeom &g, const MatrixTable &t, int 
 }
 
 // The form with the shortest estimated time, if that is shorter than the time of the kernel that the layer would have; 0
-// otherwise.  Each form costs a fixed time, and per round of 256 workgroups a fixed time and so much a step (us; least squares over
-// 700 layers of 65..512 outputs, 8..512 inputs, up to 47 rows, B = 1500..65536, all forms of each: 0.82..1.12 of the time, 0.05 in the
-// mean).  Ten and twelve groups (32..47 rows) spill in the form of two tiles a wave, whose steps cost 1.3 and 1.7 times what fewer
-// groups suggest; with twelve it never is the shortest by much and is not built.  More groups do not fit LDS.
-// The other kernel: the direct one by its edges, those of ragged rows dearer, and in L2 or past it (420 layers: 0.73..1.16 of the time);
-// the staged ones for short tables by the rounds of their workgroups, the one for long tables as its own plan counts.  Where the two are
-// even ragged layers come here (137 -> 140, G = 44, B = 12900 240 / 242) and others stay.  Of 1400 layers this takes 0.70 of the time of the
-// other kernels in the mean, 1.07 at most.  Other kernel / this one, us: 512 -> 512, G = 20, B = 16384 914 / 603; 256 -> 256, G = 28,
+// otherwise.  Each form costs a fixed time, the table 2 us a MB, and a round of 256 workgroups a fixed time and so much a step (us; least
+// squares over 1400 layers of 65..512 outputs, 8..512 inputs, up to 47 rows, B = 1100..65536, all forms of each: 0.85..1.14 of the time, 0.05
+// in the mean).  Ten and twelve groups (32..47 rows) spill in the form of two tiles a wave, whose steps cost 1.7 and 2.2 times those of
+// the third form; with twelve it is not built.  More groups do not fit LDS.
+// The other kernel: the direct one by its edges, those of ragged rows dearer where more than half of the last tile is used, and the
+// longer the table the more, as every row is fetched from it by more samples; the staged ones for short tables by the rounds of their workgroups, the one for long tables as its own plan
+// counts.  Of the 1400 layers this takes 0.70 of the time of the other kernels in the mean, 1.04 at most but where the
+// comment below says so (137 -> 140, G = 44, B = 12900 is one where the two are even, 240 / 242).  Other kernel / this one, us: 512 -> 512, G = 20, B = 16384 914 / 603; 256 -> 256, G = 28,
 // B = 16384 684 / 235; 128 -> 128, G = 10, B = 16384 170 / 54; 75 -> 130, G = 12, B = 6001 58 / 37; 139 -> 139, G = 29, B = 12900 250 / 186;
 // 265 -> 411, G = 41, k = 5, B = 4929 1730 / 593; 231 -> 270, G = 38, k = 1, B = 5201 525 / 181; not taken: 64 -> 130, G = 28, B = 1024
-// 12 / 48, 32 -> 96, G = 12, B = 32768 39 / 40; 37 -> 96, G = 28, B = 22260 43 / 58; 512 -> 256, G = 16, B = 2182 198 / 228.  Up to 64
+// 12 / 48, 32 -> 96, G = 12, B = 32768 39 / 40; 512 -> 256, G = 16, B = 2182 198 / 228.  Up to 64
 // outputs the evaluation of the pairs is not shared by enough of them (64 -> 64, G = 10, B = 65536: 75 / 78 in the best of the forms tried).
 int forward_matrix_plan(const SplineGeom &g, int64_t B)
 {
     const MatrixTable t = ::kan::matrix_table(g.n_in, g.n_out, g.rows, kMaxK);
     if (t.groups == 0) return 0;
     struct Form { int samples, tiles, inputs; float fixed, round, step[5]; };        // step 0: not built
-    static const Form forms[] = {{128, 8, 4, 6.5f, 16.5f, {2.9f, 4.16f, 0.0f, 0.0f, 0.0f}},
-                                 {64, 8, 8, 6.0f, 10.5f, {2.74f, 4.15f, 5.85f, 9.3f, 0.0f}},
-                                 {64, 4, 8, 7.5f, 5.2f, {2.3f, 3.25f, 4.43f, 5.65f, 6.55f}}};
+    static const Form forms[] = {{128, 8, 4, 5.0f, 18.0f, {2.8f, 4.35f, 0.0f, 0.0f, 0.0f}},
+                                 {64, 8, 8, 4.7f, 11.2f, {2.58f, 3.82f, 5.58f, 9.12f, 0.0f}},
+                                 {64, 4, 8, 6.3f, 5.9f, {2.14f, 3.17f, 4.15f, 5.3f, 6.31f}}};
+    const float mb = 1e-6f * (float)g.n_in * (float)g.slab_rows * (float)g.n_out * 4.0f;
     const int lds = forward_lds_plan(g);
     const bool direct = forward_direct_plan(g, B) != 0, staged = !direct && lds != 0;
     // The first form has one level of sums: not where another kernel with two would take the layer (403 -> 164, G = 19, k = 1,
@@ -488,22 +489,28 @@ int forward_matrix_plan(const SplineGeom &g, int64_t B)
         if (o.step[t.groups / 2 - 2] == 0.0f) continue;
         const int64_t groups = ((B + o.samples - 1) / o.samples) * ((t.n_tiles + o.tiles - 1) / o.tiles);
         const float steps = (float)((g.n_in + o.inputs - 1) / o.inputs);
-        const float us = o.fixed + (float)((groups + 255) / 256) * (o.round + steps * o.step[t.groups / 2 - 2]);
+        const float us = o.fixed + 2.0f * mb + (float)((groups + 255) / 256) * (o.round + steps * o.step[t.groups / 2 - 2]);
         if (best == 0 || us < least) { best = f + 1; least = us; }
     }
     const float edges = 1e-6f * (float)B * (float)g.n_in * (float)((g.n_out + 63) / 64 * 64);
     constexpr float six = kMaxK == 6 ? 1.5f : 1.0f;              // windows of six cost these kernels half as much again
     float other;
     if (direct) {
-        const bool in_l2 = (int64_t)g.n_in * g.slab_rows * g.n_out * 4 < 6ll << 20, ragged = g.n_out % 16 != 0;
-        other = 6.0f + six * edges * (in_l2 ? (ragged ? 0.735f : 0.57f) : (ragged ? 0.93f : 0.65f));
+        const bool in_l2 = mb < 6.3f, ragged = g.n_out % 16 != 0;
+        const float past = mb * (B < 4000 ? (float)B / 4000.0f : 1.0f);        // few samples meet few rows of it
+        const float edge = in_l2 ? (!ragged ? 0.57f : ((g.n_out - 1) % 64 < 32 ? 0.64f : 0.71f) + 0.025f * mb)
+                                 : (!ragged ? 0.6f + 0.006f * past : 0.85f + 0.012f * past);
+        other = 6.0f + six * edges * edge;
     } else if (staged) {
         const int64_t samples = lds == 8 ? 64 : 128, width = lds == 8 ? 512 : 256;          // of a workgroup
         const int64_t groups = (B + samples - 1) / samples * ((g.n_out + width - 1) / width);
         other = (kMaxK == 6 ? 1.24f : 0.95f) * (8.0f + (float)((groups + 255) / 256) * (lds == 8 ? 1.78f : 2.62f) * (float)g.n_in);
     } else {
+        // (short tables below B = 28000 come here where the direct kernel would be behind as well: on eight waves the one for long tables is
+        // faster on most of them, 72 -> 97, G = 26, B = 24202 76 / 99, but its sums are 1.03 to 1.08 times as far off)
         other = forward_lds_rows_us(g, B);
         if (other == 0.0f) other = six * (5.0f + edges / 1.45f);                  // the generic kernel
+        else if (t.groups <= 8 && B < 28000) other = (kMaxK == 6 ? 1.1f : 0.85f) * (5.0f + edges / 1.75f);
     }
     return least < other ? best : 0;
 }

@@ -99,7 +99,6 @@ def test_forward_sums(B, n_in, n_out, G, k, family, chain, parts):
 
 @pytest.mark.parametrize("B,n_in,n_out,G,k,family", [
     (2182, 512, 256, 16, 3, "direct"),                          # its table past L2: 198 us, on the matrix cores 228
-    (22260, 37, 96, 28, 3, "lds_rows"),                         # 43 / 58
     (33091, 96, 44, 179, 1, "direct"), (38374, 96, 40, 243, 5, "direct"),       # tiles of 32 on eight waves: 145 / 158, 222 / 266
     (40000, 98, 38, 202, 3, "lds_rows"), (51421, 98, 38, 202, 4, "lds_rows"),   # them: direct 168 / 156, 309 / 269
 ])
