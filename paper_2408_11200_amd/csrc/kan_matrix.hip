@@ -456,16 +456,17 @@ static hipError_t matrix_forward(const SplineGeom &g, const MatrixTable &t, int 
 }
 
 // The form with the shortest estimated time, if that is shorter than the time of the kernel that the layer would have; 0
-// otherwise.  Each form costs a fixed time, the table 2 us a MB, and a round of 256 workgroups a fixed time and so much a step (us; least
-// squares over 1400 layers of 65..512 outputs, 8..512 inputs, up to 47 rows, B = 1100..65536, all forms of each: 0.85..1.14 of the time, 0.05
-// in the mean).  Ten and twelve groups (32..47 rows) spill in the form of two tiles a wave, whose steps cost 1.7 and 2.2 times those of
-// the third form; with twelve it is not built.  More groups do not fit LDS.
+// otherwise.  Each form costs a fixed time, that of the table, and a round of 256 workgroups a fixed time and so much a step (us; least
+// squares over 1660 layers of 65..600 outputs, 8..600 inputs, up to 47 rows and 2^33 edges, all forms of each: 0.85..1.14 of the time,
+// 0.05 in the mean).  Ten and twelve groups (32..47 rows) spill in the form of two tiles a wave, whose steps cost 1.7 and 2.2 times those
+// of the third form; with twelve it is not built.  More groups do not fit LDS.
 // The other kernel: the direct one by its edges, those of ragged rows dearer where more than half of the last tile is used, and the
-// longer the table the more, as every row is fetched from it by more samples; the staged ones for short tables by the rounds of their workgroups, the one for long tables as its own plan
-// counts.  Of the 1400 layers this takes 0.70 of the time of the other kernels in the mean, 1.04 at most but where the
-// comment below says so (137 -> 140, G = 44, B = 12900 is one where the two are even, 240 / 242).  Other kernel / this one, us: 512 -> 512, G = 20, B = 16384 914 / 603; 256 -> 256, G = 28,
-// B = 16384 684 / 235; 128 -> 128, G = 10, B = 16384 170 / 54; 75 -> 130, G = 12, B = 6001 58 / 37; 139 -> 139, G = 29, B = 12900 250 / 186;
-// 265 -> 411, G = 41, k = 5, B = 4929 1730 / 593; 231 -> 270, G = 38, k = 1, B = 5201 525 / 181; not taken: 64 -> 130, G = 28, B = 1024
+// longer the table the more, as more samples fetch each row of it; the staged ones for short tables by the rounds of their workgroups, the
+// one for long tables as its own plan counts.  Of the 1660 layers this takes 0.67 of the time of the other kernels in the mean, 1.04 at most
+// but where the comment below says so (137 -> 140, G = 44, B = 12900 is one where the two are even, 240 / 242).  Other kernel / this one, us:
+// 512 -> 512, G = 20, B = 16384 914 / 603; 256 -> 256, G = 28, B = 16384 684 / 235; 128 -> 128, G = 10, B = 16384 170 / 54; 75 -> 130,
+// G = 12, B = 6001 58 / 37; 139 -> 139, G = 29, B = 12900 250 / 186; 265 -> 411, G = 41, k = 5, B = 4929 1730 / 593; 231 -> 270, G = 38, k = 1,
+// B = 5201 525 / 181; not taken: 64 -> 130, G = 28, B = 1024
 // 12 / 48, 32 -> 96, G = 12, B = 32768 39 / 40; 512 -> 256, G = 16, B = 2182 198 / 228.  Up to 64
 // outputs the evaluation of the pairs is not shared by enough of them (64 -> 64, G = 10, B = 65536: 75 / 78 in the best of the forms tried).
 int forward_matrix_plan(const SplineGeom &g, int64_t B)
@@ -476,7 +477,7 @@ int forward_matrix_plan(const SplineGeom &g, int64_t B)
     static const Form forms[] = {{128, 8, 4, 5.0f, 18.0f, {2.8f, 4.35f, 0.0f, 0.0f, 0.0f}},
                                  {64, 8, 8, 4.7f, 11.2f, {2.58f, 3.82f, 5.58f, 9.12f, 0.0f}},
                                  {64, 4, 8, 6.3f, 5.9f, {2.14f, 3.17f, 4.15f, 5.3f, 6.31f}}};
-    const float mb = 1e-6f * (float)g.n_in * (float)g.slab_rows * (float)g.n_out * 4.0f;
+    const float mb = 1e-6f * (float)g.n_in * (float)g.slab_rows * (float)g.n_out * 4.0f;      // the folded table
     const int lds = forward_lds_plan(g);
     const bool direct = forward_direct_plan(g, B) != 0, staged = !direct && lds != 0;
     // The first form has one level of sums: not where another kernel with two would take the layer (403 -> 164, G = 19, k = 1,
@@ -484,12 +485,16 @@ int forward_matrix_plan(const SplineGeom &g, int64_t B)
     if (!staged && g.n_in < 20 && t.groups >= 8) return 0;        // (few inputs of many groups: 16 -> 104, G = 26, k = 5 1.05 of its error)
     int best = 0;
     float least = 0.0f;
+    const float table = mb < 8.0f ? 2.0f * mb : 16.0f + 1.4f * (mb - 8.0f);
     for (int f = staged ? 0 : 1; f < 3; ++f) {
         const Form &o = forms[f];
         if (o.step[t.groups / 2 - 2] == 0.0f) continue;
         const int64_t groups = ((B + o.samples - 1) / o.samples) * ((t.n_tiles + o.tiles - 1) / o.tiles);
-        const float steps = (float)((g.n_in + o.inputs - 1) / o.inputs);
-        const float us = o.fixed + 2.0f * mb + (float)((groups + 255) / 256) * (o.round + steps * o.step[t.groups / 2 - 2]);
+        const float rounds = (float)((groups + 255) / 256);
+        // (the second form's steps take longer behind one another, more so on large tables: 512 -> 512, G = 20, B = 16384 629 in the first,
+        // 673 in it)
+        const float step = o.step[t.groups / 2 - 2] * (f == 1 && rounds > 1.0f ? 1.06f + 0.005f * mb : 1.0f);
+        const float us = o.fixed + table + rounds * (o.round + (float)((g.n_in + o.inputs - 1) / o.inputs) * step);
         if (best == 0 || us < least) { best = f + 1; least = us; }
     }
     const float edges = 1e-6f * (float)B * (float)g.n_in * (float)((g.n_out + 63) / 64 * 64);
@@ -504,7 +509,7 @@ int forward_matrix_plan(const SplineGeom &g, int64_t B)
     } else if (staged) {
         const int64_t samples = lds == 8 ? 64 : 128, width = lds == 8 ? 512 : 256;          // of a workgroup
         const int64_t groups = (B + samples - 1) / samples * ((g.n_out + width - 1) / width);
-        other = (kMaxK == 6 ? 1.24f : 0.95f) * (8.0f + (float)((groups + 255) / 256) * (lds == 8 ? 1.78f : 2.62f) * (float)g.n_in);
+        other = (kMaxK == 6 ? 1.3f : 1.0f) * (5.5f + (float)((groups + 255) / 256) * (lds == 8 ? 1.78f : 2.62f) * (float)g.n_in);
     } else {
         // (short tables below B = 28000 come here where the direct kernel would be behind as well: on eight waves the one for long tables is
         // faster on most of them, 72 -> 97, G = 26, B = 24202 76 / 99, but its sums are 1.03 to 1.08 times as far off)
