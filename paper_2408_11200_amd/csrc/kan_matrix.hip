@@ -5,8 +5,9 @@
 // of the zeros: table row r of an input goes to group r mod G, position r / G of the G groups of four (mx_groups), so that the
 // rows of a window fall into different groups; w_b, the last position of the last group, meets at most one row there.  Each group
 // then has one row in slot 0 (positions 0..2) or slot 1 (position 3), and every index pair is (position, 3).
-// The precision is that of fp32: every float is split into three bf16 parts (8 bits each, 24 in all), and the six products of
-// the parts that reach 2^-27 of the whole are summed in fp32; the parts have the exponent range of a float, and a common power of
+// The precision is that of fp32: every float is split into three bf16 parts (8 bits each, 24 in all), and six of the nine products of
+// the parts are summed in fp32; the two left out that weigh most reach 2^-24.2 of the product together, and 2^-27.5 in the mean, beside
+// the 2^-24 of a sum's rounding.  The parts have the exponent range of a float, and a common power of
 // two keeps the lowest ones off its end.  Values that do not split (infinite, NaN, or too large for that) are found where they are
 // split; the sums that read them, and those that come out infinite or NaN (two factors that split may have a product of parts
 // that does not fit), are done in plain fp32 at the end.
@@ -14,9 +15,10 @@
 // Error against fp64 (2-norm): 512 -> 512, G = 20 4.9e-7 (the LDS-staged kernel 9.0e-7); 256 -> 256, G = 28 1.3e-7 (6.4e-7);
 // 75 -> 130, G = 12, k = 2 0.96e-7 (direct kernel 1.14e-7); 128 -> 128, G = 10 1.07e-7 (1.38e-7).
 //
-// What bounds it, 512 -> 512, G = 20, B = 16384, 583 us (the staged kernel, bound by its LDS reads: 900): the matrix instructions
-// alone take 360, evaluating the pairs 66 more, fetching the right operands from L2 63, reading the left ones from LDS 31;
-// 47 % of the matrix cores' clocks are used.
+// What bounds it, 512 -> 512, G = 20, B = 16384, 602 us (the staged kernel, bound by its LDS reads: 914): the matrix instructions
+// alone take 360 (by variants that leave a part out), evaluating the pairs 66 more, fetching the right operands from L2 63, reading
+// the left ones from LDS 31; by counters the matrix cores are busy 45 % of the clocks, the rest of the VALU 27 %, LDS 26 %, and waves
+// wait for memory or LDS 40 % of theirs and to issue 34 %.
 #include "kan_device.hpp"
 #include "kan_launch.hpp"
 #include "kan_matrix.hpp"

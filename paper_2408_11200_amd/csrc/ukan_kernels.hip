@@ -233,7 +233,8 @@ __global__ __launch_bounds__(256) void cg_hidden_kernel(const float *__restrict_
 //                  pass, whose long sums cancel heavily; the products are then exact and the
 //                  only rounding is the final conversion to fp32.
 //   BM = 32 : 32x64 tiles, a wave 32x16: twice the workgroups where all of K is one slice and N one tile (the hidden layer's
-//             gradient, 13400 x 64 from 1024: 210 workgroups 75 us, 420 67, beside about 30 for the matrix instructions).
+//             gradient, 13400 x 64 from 1024: 210 workgroups 75 us, 420 67, beside about 30 for the matrix instructions; a backward pass with
+//             128 columns 782 -> 760, 256 268 -> 263, 512, where tiles of 64 fill the chip, 719 -> 720).
 using f32x16 = __attribute__((__vector_size__(16 * sizeof(float)))) float;
 using f64x4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
 
