@@ -25,16 +25,30 @@ __global__ __launch_bounds__(256) void forward_narrow_kernel(SplineGeom g, const
     float acc[NO];
 #pragma unroll
     for (int j = 0; j < NO; ++j) acc[j] = 0.0f;
-    float tot = 0.0f;                            // sixteen lanes: folded every eight inputs, as the direct kernel's sums are short
+    float tot = 0.0f;                            // one output: folded every eight inputs, as the direct kernel's sums are short
     int n = 0;
     for (int i = q; i < g.n_in; i += Q) {
         Pair p = pair_basis<false>(x[bc * g.n_in + i], g, i);
         const float *slab = cf + (int64_t)i * g.slab_rows * g.n_out;
         // one output: a window is four neighbouring floats, one access (the lines looked up in L1 were the bound: 256 -> 1, 244 rows,
-        // B = 32768 64 -> 49 us)
-        if (NO == 1 && __all(p.cell >= 0 && p.cell <= g.rows - kMaxK)) {
-            const float4 r = load4u(slab + p.cell);
-            acc[0] = fmaf(p.w[3], r.w, fmaf(p.w[2], r.z, fmaf(p.w[1], r.y, fmaf(p.w[0], r.x, acc[0]))));
+        // B = 32768 64 -> 49 us).  Where it hangs over an end of the table the access is moved back onto it and what it reads moved along,
+        // so that other rows, whatever stands there, take no part (256 -> 1, G = 40, k = 1, B = 131072 101 us, row by row 145
+        // and with four lanes a sample 121)
+        if (NO == 1 && g.rows >= kMaxK) {
+            const int c = clampi(p.cell, 0, g.rows - kMaxK), d = c - p.cell;
+            const float4 r = load4u(slab + c);
+            float v[kMaxK] = {r.x, r.y, r.z, r.w};
+            if (!__all(d == 0)) {
+                mask_pair<false>(p, g);
+#pragma unroll
+                for (int s = 0; s < kMaxK; ++s) {
+                    float t = 0.0f;
+#pragma unroll
+                    for (int u = 0; u < kMaxK; ++u) t = s - d == u ? (&r.x)[u] : t;
+                    v[s] = t;
+                }
+            }
+            acc[0] = fmaf(p.w[3], v[3], fmaf(p.w[2], v[2], fmaf(p.w[1], v[1], fmaf(p.w[0], v[0], acc[0]))));
         } else {
             mask_pair<false>(p, g);
 #pragma unroll
@@ -51,9 +65,9 @@ __global__ __launch_bounds__(256) void forward_narrow_kernel(SplineGeom g, const
             for (int j = 0; j < NO; ++j)
                 if (j < g.n_out) acc[j] = fmaf(p.base, wb[j], acc[j]);
         }
-        if (Q == 16 && ++n == 8) { tot += acc[0]; acc[0] = 0.0f; n = 0; }
+        if (NO == 1 && ++n == 8) { tot += acc[0]; acc[0] = 0.0f; n = 0; }
     }
-    if (Q == 16) acc[0] += tot;
+    if (NO == 1) acc[0] += tot;
 #pragma unroll
     for (int j = 0; j < NO; ++j) {
         float v = acc[j];
@@ -122,8 +136,11 @@ hipError_t launch_forward_narrow(const SplineGeom &g, const float *x, const floa
     prof::Timed tm("forward_narrow", st);
     // One output from 32 inputs on: sixteen lanes a sample, four times the waves and whole lines of x, until the batch fills the chip
     // either way (four / sixteen, G = 240, us: 256 -> 1, B = 32768 52 / 30; 128 -> 1, B = 5000 26 / 10; 32 -> 1, B = 65536 11.9 / 10.9,
-    // 262144 27 / 30; 16 -> 1, B = 262144 16 / 20; 64 -> 2, B = 65536 41 / 71).
-    if (g.n_out == 1 && g.n_in >= 32 && B <= 1 << 17) {
+    // 262144 27 / 30; 16 -> 1, B = 262144 16 / 20; 64 -> 2, B = 65536 41 / 71).  Degrees 1 and 2, where nearly every wave has a window over
+    // the table's end: 34 -> 1, G = 40, k = 1, B = 65536 13.9 / 13.0, 108173 17.4 / 18.6, its third round of inputs almost empty;
+    // 48 -> 1, B = 131072 25 / 23.
+    const int64_t most = g.k < 3 && g.n_in > 32 && g.n_in < 48 ? 3 << 15 : 1 << 17;
+    if (g.n_out == 1 && g.n_in >= 32 && B <= most) {
         forward_narrow_kernel<1, 16><<<(unsigned)((16 * B + 255) / 256), 256, 0, st>>>(g, x, cf, w_b, y, B);
         return hipGetLastError();
     }

@@ -147,3 +147,24 @@ def test_matrix_forward_in_the_static_array(B, n_in, n_out, G, k, family):
         assert "forward_matrix" in families_of(lambda: binding.kan_forward(s, x, coef, w_s, w_b, y=y))
         assert family in families_of(lambda: binding.kan_forward_static(s, x, coef, w_s, w_b, z))
         assert torch.equal(y.view(torch.int32), z.view(torch.int32))
+
+
+@pytest.mark.parametrize("B,n_in,G,k", [(3000, 64, 5, 1), (2011, 33, 9, 2), (4001, 50, 3, 3), (5000, 20, 3, 1), (140000, 36, 1, 3), (2300, 48, 1, 2)])
+def test_one_output_windows_over_the_ends(B, n_in, G, k):
+    """Windows that hang over an end of the table, samples off the grid, and infinite parameters that only the samples of
+    their windows meet."""
+    w = workloads.random_kan_layer(B + n_in, B, n_in, 1, G, k, outside_frac=0.3)
+    s, p = w.layers[0], w.params[0]
+    rows = np.r_[0:400, B - 400:B]
+    got, ref = run_rows(w, rows, "narrow")
+    assert rel(got, ref) < 4 * 2.0 ** -24
+    p["coef"][3, 0, 0], p["coef"][5, s.M - 1, 0] = np.inf, -np.inf
+    got, ref = run_rows(w, rows, "narrow")
+    near, touched = np.zeros(len(rows), bool), np.zeros(len(rows), bool)        # in the four rows of a window, in its k + 1
+    for i, row in ((3, 0), (5, s.M - 1)):
+        cell = np.floor((w.x[rows, i].astype(np.float64) + 1) * G / 2)
+        near |= (cell <= row) & (row <= cell + 3)
+        touched |= (cell <= row) & (row <= cell + k)
+    assert touched.any() and not np.isfinite(got[touched]).any()
+    assert np.isfinite(got[~near]).all()
+    assert near.all() or rel(got[~near], ref[~near]) < 4 * 2.0 ** -24
