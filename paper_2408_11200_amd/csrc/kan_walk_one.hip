@@ -28,8 +28,9 @@ __global__ __launch_bounds__(64 * kOneWaves) void walk_one_kernel(QuadWalkArgs p
     __shared__ float base_sum[kOneWaves];
     const int in_groups = (p.n_in + kOneInputs - 1) / kOneInputs;
     const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3, unit = k / kOneInputs * 8 + xcd, c = unit / in_groups;
-    // (the groups of a chunk are turned each time they come round to the same XCDs, so that the last one, with fewer inputs, does too)
-    const int even = in_groups & -in_groups, turn = c * (even < 8 ? even : 8) / 8;
+    // (the groups of a chunk, if even in number, are turned each time they come round to the same XCDs, so that the last one, with fewer
+    // inputs, does too)
+    const int even = in_groups & -in_groups, turn = even == 1 ? 0 : c * (even < 8 ? even : 8) / 8;
     const int i = (unit + turn) % in_groups * kOneInputs + k % kOneInputs;
     if (c >= p.n_chunks || i >= p.n_in) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
